@@ -21,7 +21,8 @@ extern "C" {
  * transB == 0: B is [K,N]; 1: B is [N,K].  force_generic: 0 = automatic kernel choice, 1 = the
  * plain tiled kernel, 10..14 = one MFMA tile configuration (10 register-staged 128x128,
  * 11 direct-to-LDS 128x128, 12 direct-to-LDS 128x64, 13 register-prefetch 128x128 with a
- * four-stage ring, 14 direct-to-LDS 256x256; 11..14 fall back to 10 unless K % 64 == 0),
+ * four-stage ring, 14 direct-to-LDS 256x256; 11..14 fall back to 10 unless K % 64 == 0 or both operands have the
+ * contraction as their slow dimension, transA == 1 and transB == 0),
  * for tests and tuning.
  * These are the layer contractions of Eq. 2 / Eq. 6 (forward, input- and weight-gradient). */
 int ouro_op_gemm(void* stream, int dtype, int transA, int transB, int M, int N, int K, float alpha,
@@ -31,7 +32,7 @@ int ouro_op_gemm(void* stream, int dtype, int transA, int transB, int M, int N, 
 /* A grid of by x bz products of one shape in one call (plain epilogue): product (y, z) reads
  * A + y*sAy + z*sAz and B + y*sBy + z*sBz and writes C + y*sCy + z*sCz (strides in elements).
  * With C2 != NULL a second grid of the same shape, strides and leading dimensions runs in the
- * same launch with A2, B2, C2, alpha2.  bf16 products with K % 64 == 0 and 16-byte aligned
+ * same launch with A2, B2, C2, alpha2.  bf16 products that admit the direct-to-LDS MFMA kernel and have 16-byte aligned
  * strides run as one launch of the MFMA kernel, anything else as one launch per product.
  * accumulate: 0 C = alpha A B; 1 fp32 C += alpha A B with the contraction split over workgroups
  * (atomic adds); 2 fp32 C += alpha A B in the epilogue of a single pass (one grid only).
@@ -45,7 +46,7 @@ int ouro_op_gemm_batched(void* stream, int dtype, int transA, int transB, int M,
                          void* C2, float alpha2, int force_generic);
 /* n <= 6 accumulating products C_i (fp32 [M_i, N_i]) += alpha * A_i^T B_i with A_i [K_i, M_i] and
  * B_i [K_i, N_i] (the weight-gradient contractions of a layer, Eq. 6-7: contraction over all
- * tokens onto small outputs).  Products that admit it (bf16, K_i a multiple of 64 and >= 512) share
+ * tokens onto small outputs).  Products that admit it (bf16, aligned operands, any K_i >= 32) share
  * one launch in which every workgroup takes a long K range; the rest run one by one. */
 int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                        const void* const* A, const int* lda, const void* const* B, const int* ldb,

@@ -156,6 +156,8 @@ hipError_t launch_gemm_dlds(hipStream_t s, GemmParams& p, int transA, int transB
 hipError_t launch_gemm_dlds_group(hipStream_t s, GemmParams* ps, int n, int transA, int transB);
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+static inline bool direct_k_ok(int transA, int transB, int K) { return K % 64 == 0 || (transA && !transB); }
+
 bool gemm_uses_mfma(int dtype, const GemmDesc& g) {
   if (dtype != 1) return false;
   if (!aligned16(g.A) || !aligned16(g.B)) return false;
@@ -221,7 +223,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     if (g.bias || g.residual || g.epilogue != EPI_NONE || g.drop.on) return hipErrorInvalidValue;
     if (g.res32 && (!g.out_fp32 || g.ln_mean || g.C2)) return hipErrorInvalidValue;
     const size_t bA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
-    const bool in_grid = force_generic != 1 && gemm_uses_mfma(dtype, g) && (g.K % 64) == 0 && bA < (1ull << 31) && bB < (1ull << 31) &&
+    const bool in_grid = force_generic != 1 && gemm_uses_mfma(dtype, g) && direct_k_ok(g.transA, g.transB, g.K) && bA < (1ull << 31) && bB < (1ull << 31) &&
                          !((p.bAy | p.bAz | p.bBy | p.bBz | p.bCy | p.bCz) & 15) &&
                          (!g.C2 || (aligned16(g.A2) && aligned16(g.B2) && aligned16(g.C2) == aligned16(g.C)));
     if (!in_grid) {
@@ -263,8 +265,9 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       else cfg = GEMM_TILE_128x128;
     }
     const size_t bytesA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
-    // direct global->LDS loads need whole 64-wide K tiles and 32-bit operand offsets
-    const bool direct_ok = (g.K % 64) == 0 && bytesA < (1ull << 31) && bytesB < (1ull << 31);
+    // direct global->LDS loads need 32-bit operand offsets, and whole 64-wide K tiles unless the contraction index is
+    // the slow dimension of both operands (the k-rows past the end of an operand read as zero)
+    const bool direct_ok = direct_k_ok(g.transA, g.transB, g.K) && bytesA < (1ull << 31) && bytesB < (1ull << 31);
     // 256x256 tiles run one workgroup per CU, so a launch takes whole rounds of 256 tiles.  A
     // few tile rows beyond the last full round would cost a whole round more (dV_o of a
     // 50257-word vocabulary: 788 tiles, 3.08 rounds): those rows go out as a second, split-K
@@ -357,7 +360,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     const size_t bA = 2 * (size_t)d.K * d.lda, bB = 2 * (size_t)d.K * d.ldb;
     const bool ok = dtype == 1 && d.transA == 1 && d.transB == 0 && d.accumulate && d.out_fp32 && !d.bias && !d.residual &&
                     !d.res32 && d.epilogue == EPI_NONE && !d.drop.on && d.by <= 1 && d.bz <= 1 && !d.C2 && d.M > 0 && d.N > 0 &&
-                    gemm_uses_mfma(dtype, d) && (d.K % 64) == 0 && d.K >= 512 && bA < (1ull << 31) && bB < (1ull << 31);
+                    gemm_uses_mfma(dtype, d) && bA < (1ull << 31) && bB < (1ull << 31);
     if (ok) { in[ni++] = d; continue; }
     hipError_t e = launch_gemm(s, dtype, d, 0);
     if (e != hipSuccess) return e;
@@ -368,7 +371,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   // One K-range length for all products: whole rounds of workgroups (two per CU) times the K-tiles
   // of a workgroup plus its fixed cost (ring fill, atomic epilogue: 6 K-tiles), as in launch_gemm.
   int kmax = 0;
-  for (int i = 0; i < n; ++i) kmax = std::max(kmax, g[i].K);
+  for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
   double best = 1e30;
   int kchunk = kmax;
   for (int kc = 256; kc <= kmax; kc += 64) {

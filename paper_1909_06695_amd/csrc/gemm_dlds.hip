@@ -28,7 +28,16 @@ __device__ __forceinline__ int colswz(int k) {
   return ROWS >= 128 ? ((k & 3) << 2) : (((k >> 1) & 1) << 2);
 }
 typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_void;
+
+// Direct load of 16 bytes per lane to LDS: lane i's bytes at base + voff (per lane) + soff (uniform) arrive at dst + 16 i.
+// It goes through a buffer descriptor of the operand (`bytes` from its base): the K-tile term of the address, soff, is a
+// scalar operand of the instruction, and what lies past the end reads as zero.  A column-form operand therefore needs no
+// whole K-tiles: rows past the contraction's end contribute zero.
+__device__ __forceinline__ void direct_load(const void* base, int bytes, char* dst, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000), (lds_void*)dst, 16,
+                                           voff, soff, 0, 0);
+}
+__device__ __forceinline__ int operand_bytes(int rows, int ld) { return (int)(2u * (uint32_t)rows * (uint32_t)ld); }
 
 // Wait until at most N vector-memory operations are outstanding and every LDS operation of
 // this wave has completed.
@@ -140,18 +149,16 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
   constexpr int LPT = TileA::PER + TileB::PER;             // loads per thread per K-tile
   static_assert((S - 1) * LPT < 64, "too many loads in flight for vmcnt");
   char* lds = reinterpret_cast<char*>(smem);
-  const bf16_t* A = reinterpret_cast<const bf16_t*>(p.A);
-  const bf16_t* B = reinterpret_cast<const bf16_t*>(p.B);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: kept in a scalar register
   const int wm = wave / WN, wn = wave % WN;
   int m0, n0, kbeg;
   tile_of_block(p, BM, BN, bid, nb, m0, n0, kbeg);
   if (kbeg >= p.K) return;                                  // a work item past the last K range (grouped launches round up)
   const int kend = min(p.K, kbeg + p.kchunk);
-  const int nk = (kend - kbeg) / BK;                        // launcher guarantees exact tiles
+  const int nk = (kend - kbeg + BK - 1) / BK;               // the launcher guarantees whole tiles unless both operands are column-form
 
   // per-load byte offsets from the operand base (32-bit: the launcher keeps operands under
-  // 2 GiB); the K-tile term is a uniform add at issue time
+  // 2 GiB); the K-tile term is a scalar
   uint32_t oa[TileA::PER], ob[TileB::PER];
 #pragma unroll
   for (int i = 0; i < TileA::PER; ++i)
@@ -159,10 +166,9 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
 #pragma unroll
   for (int i = 0; i < TileB::PER; ++i)
     ob[i] = (uint32_t)(2 * (TileB::src_offset(wave + i * NW, lane, n0, p.N, p.ldb) + (TB ? (size_t)kbeg : (size_t)kbeg * p.ldb)));
+  const int bytesA = operand_bytes(TA ? p.K : p.M, p.lda), bytesB = operand_bytes(TB ? p.N : p.K, p.ldb);
   const uint32_t stepA = 2u * (TA ? (uint32_t)BK * p.lda : (uint32_t)BK);
   const uint32_t stepB = 2u * (TB ? (uint32_t)BK : (uint32_t)BK * p.ldb);
-  const char* Ab = reinterpret_cast<const char*>(A);
-  const char* Bb = reinterpret_cast<const char*>(B);
 
   // `slot` (the ring stage) is a compile-time value at every call, so LDS addresses are a lane
   // term plus an immediate offset
@@ -170,11 +176,10 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
     const uint32_t ka = (uint32_t)kt * stepA, kb = (uint32_t)kt * stepB;
 #pragma unroll
     for (int i = 0; i < TileA::PER; ++i)
-      __builtin_amdgcn_global_load_lds((gbl_void*)(Ab + (oa[i] + ka)), (lds_void*)(st + (wave + i * NW) * 1024), 16, 0, 0);
+      direct_load(p.A, bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
 #pragma unroll
     for (int i = 0; i < TileB::PER; ++i)
-      __builtin_amdgcn_global_load_lds((gbl_void*)(Bb + (ob[i] + kb)),
-                                       (lds_void*)(st + TileA::BYTES + (wave + i * NW) * 1024), 16, 0, 0);
+      direct_load(p.B, bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
   };
 
   f32x16 acc[TM][TN];
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
   int m0, n0, kbeg;
   tile_of_block(p, BM, BN, blockIdx.x, gridDim.x, m0, n0, kbeg);
   const int kend = min(p.K, kbeg + p.kchunk);
-  const int nk = (kend - kbeg) / BK;
+  const int nk = (kend - kbeg + BK - 1) / BK;
 
   uint32_t oa[TileA::PER], ob[TileB::PER];
 #pragma unroll
@@ -332,10 +337,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
 #pragma unroll
   for (int i = 0; i < TileB::PER; ++i)
     ob[i] = (uint32_t)(2 * (TileB::src_offset(wave + i * NW, lane, n0, p.N, p.ldb) + (TB ? (size_t)kbeg : (size_t)kbeg * p.ldb)));
+  const int bytesA = operand_bytes(TA ? p.K : p.M, p.lda), bytesB = operand_bytes(TB ? p.N : p.K, p.ldb);
   const uint32_t stepA = 2u * (TA ? (uint32_t)BK * p.lda : (uint32_t)BK);
   const uint32_t stepB = 2u * (TB ? (uint32_t)BK : (uint32_t)BK * p.ldb);
-  const char* Ab = reinterpret_cast<const char*>(p.A);
-  const char* Bb = reinterpret_cast<const char*>(p.B);
 
   // `slot` (the ring stage) is a compile-time value at every call: LDS addresses are a lane term
   // plus an immediate offset
@@ -343,11 +347,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
     const uint32_t ka = (uint32_t)kt * stepA, kb = (uint32_t)kt * stepB;
 #pragma unroll
     for (int i = 0; i < TileA::PER; ++i)
-      __builtin_amdgcn_global_load_lds((gbl_void*)(Ab + (oa[i] + ka)), (lds_void*)(st + (wave + i * NW) * 1024), 16, 0, 0);
+      direct_load(p.A, bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
 #pragma unroll
     for (int i = 0; i < TileB::PER; ++i)
-      __builtin_amdgcn_global_load_lds((gbl_void*)(Bb + (ob[i] + kb)),
-                                       (lds_void*)(st + TileA::BYTES + (wave + i * NW) * 1024), 16, 0, 0);
+      direct_load(p.B, bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
   };
   bf16x8 af[4][TM], bfr[4][TN];
   auto fetch = [&](const char* sa, int ks) __attribute__((always_inline)) {

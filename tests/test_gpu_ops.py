@@ -125,6 +125,26 @@ def test_gemm_batched(dtype, tA, tB, M, N, K, by, bz, second, acc):
             assert rel_err(got[g, i], ref) < 2e-6, (g, i)
 
 
+@pytest.mark.parametrize("force", [0, 11, 12, 13, 14])
+@pytest.mark.parametrize("M,N,K", [(136, 72, 33), (128, 264, 63), (264, 128, 65), (40, 40, 127), (96, 320, 705), (768, 384, 2331)])
+def test_gemm_ragged_contraction(force, M, N, K):
+    """A^T B over a contraction that is no whole number of K-tiles (weight gradients of any token count): the
+    direct-load kernels read k-rows past the end as zero.  What lies behind the operands here is NaN.  Overwriting
+    and accumulating (split-K) forms; bound as in test_gemm_forms."""
+    rng = np.random.default_rng(M + N + K + force)
+    def operand(cols):
+        x = torch.full((K + 64, cols), float("nan"), dtype=torch.bfloat16, device="cuda")
+        x[:K] = torch.from_numpy(rng.standard_normal((K, cols)).astype(np.float32)).cuda()
+        return x
+    dA, dB = operand(M), operand(N)
+    ref = host(dA[:K]).T @ host(dB[:K])
+    for acc in (0, 1):
+        out = torch.ones((M, N), dtype=torch.float32, device="cuda")
+        ok(L().ouro_op_gemm(stream(), 1, 1, 0, M, N, K, 1.0, p(dA), M, p(dB), N, p(out), N, 1, acc, None, None, 0, 0, None, 0, force))
+        torch.cuda.synchronize()
+        assert rel_err(host(out), ref + acc) < 2e-6 + 1e-6 * acc
+
+
 @pytest.mark.parametrize("dtype,shapes", [
     (1, [(256, 128, 2048), (128, 384, 2048), (136, 72, 1024), (128, 128, 512)]),     # all in one launch, ragged tiles
     (1, [(256, 128, 1024), (72, 40, 1000), (128, 256, 4096), (64, 64, 320)]),        # two of them go by themselves
