@@ -1,9 +1,10 @@
-// Dense contractions of the training step: a bf16 MFMA kernel (LDS double-buffered,
-// XOR-swizzled tiles, 32x32x16 matrix instructions, 64-wide wavefronts) and a plain
-// bounds-checked tiled kernel for fp32 operands and shapes the MFMA kernel does not take.
+// Dense contractions of the training step: the choice between the direct-to-LDS MFMA kernels (gemm_pp.hip, gemm_dlds.hip),
+// a register-staged bf16 MFMA kernel (LDS double-buffered, XOR-swizzled tiles, 32x32x16 matrix instructions) and a plain
+// bounds-checked tiled kernel for fp32 operands and shapes the MFMA kernels do not take.
 #include "gemm_common.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -153,6 +154,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
 
 // ----------------------------------------------------------------------------- launch
 hipError_t launch_gemm_dlds(hipStream_t s, GemmParams& p, int transA, int transB, int splits, int cfg);
+hipError_t launch_gemm_pp(hipStream_t s, GemmParams& p, int transA, int transB, int splits);
+hipError_t launch_gemm_pp_group(hipStream_t s, const GemmParams* ps, int n);
 hipError_t launch_gemm_dlds_group(hipStream_t s, GemmParams* ps, int n, int transA, int transB);
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
@@ -201,7 +204,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   GemmParams p;
   p.A = g.A; p.B = g.B; p.C = g.C;
   p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
-  p.out_fp32 = g.out_fp32; p.accumulate = g.accumulate;
+  p.out_fp32 = g.out_fp32; p.accumulate = g.accumulate ? ACC_ATOMIC : 0;
   p.bias = g.bias; p.residual = g.residual; p.ldr = g.ldr;
   p.res32 = g.res32; p.ldr32 = g.ldr32; p.ln_mean = g.ln_mean; p.ln_rstd = g.ln_rstd; p.ln_g = g.ln_g; p.ln_b = g.ln_b;
   if (g.res32 && (g.residual || g.accumulate || (g.ln_mean && !(g.ln_rstd && g.ln_g && g.ln_b)))) return hipErrorInvalidValue;
@@ -257,9 +260,11 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       // put more workgroups on every compute unit
       const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
       const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-      // 256x256 tiles halve the operand bytes per flop; they pay once there are several per CU
-      // (the logits) or one per CU with a long contraction (dV_o)
-      if (!g.accumulate && (t256 >= 1024 || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
+      // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are several per CU (the logits),
+      // one per CU with a long contraction (dV_o: 670 -> 592 us), or whole rounds of them: two rounds of a contraction over
+      // 1024 with the GELU epilogues take 94 us against 101 us of four rounds of 128x128 tiles, one and a half rounds
+      // (8192 x 3072 x 1024) 69 us against 57 us of three
+      if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
       else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
       else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * by * bz * grids <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
       else cfg = GEMM_TILE_128x128;
@@ -302,10 +307,12 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       // chip in whole rounds.  Cost of a candidate in units of (tile area x K-tiles) per CU:
       // rounds x workgroups per CU x tile area x (K-tiles per workgroup + fixed cost) / rate,
       // the fixed cost (ring fill, atomic epilogue) taken as 6 K-tiles, the rate of the 128x64
-      // tiles as 0.8 of the 128x128 ones (more operand bytes per flop).
+      // tiles as 0.8 of the 128x128 ones (more operand bytes per flop), that of the 256x256 ones as 1.65 (1.45 us per K-tile
+      // of a tile against 1.2 us of two 128x128 tiles side by side).
       double best = 1e30;
-      for (int c = 0; c < 2; ++c) {
-        const int bm = 128, bn = c ? 64 : 128, per_cu = c ? 3 : 2;
+      for (int c = 0; c < 3; ++c) {
+        const int bm = c == 2 ? 256 : 128, bn = c == 2 ? 256 : c ? 64 : 128, per_cu = c == 2 ? 1 : c ? 3 : 2;
+        const double rate = c == 2 ? 1.65 : c ? 0.8 : 1.0;
         const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * by * bz * grids;
         const int max_s = std::min(16, g.K / 256);
         for (int sp = 1; sp <= max_s; ++sp) {
@@ -313,8 +320,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
           const int real = (g.K + kc - 1) / kc;
           if (real != sp) continue;
           const long rounds = (tiles * sp + 256L * per_cu - 1) / (256L * per_cu);
-          const double cost = (double)rounds * per_cu * bm * bn * (kc / 64 + 6) / (c ? 0.8 : 1.0);
-          if (cost < best) { best = cost; cfg = c ? GEMM_TILE_128x64 : GEMM_TILE_128x128; splits = sp; }
+          const double cost = (double)rounds * per_cu * bm * bn * (kc / 64 + 6) / rate;
+          if (cost < best) { best = cost; cfg = c == 2 ? GEMM_TILE_256x256 : c ? GEMM_TILE_128x64 : GEMM_TILE_128x128; splits = sp; }
         }
       }
     }
@@ -332,6 +339,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     kchunk = (kchunk + 63) / 64 * 64;
     splits = (g.K + kchunk - 1) / kchunk;
     p.kchunk = kchunk;
+    if (cfg == GEMM_TILE_256x256) return launch_gemm_pp(s, p, g.transA, g.transB, splits);
     if (cfg != GEMM_TILE_STAGED128) return launch_gemm_dlds(s, p, g.transA, g.transB, splits, cfg);
     return launch_mfma_cfg<128, 128, 2, 2>(s, p, g.transA, g.transB, splits);
   }
@@ -368,20 +376,38 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   if (ni == 0) return hipSuccess;
   if (ni == 1) return launch_gemm(s, dtype, in[0], 0);
   g = in; n = ni;
-  // One K-range length for all products: whole rounds of workgroups (two per CU) times the K-tiles
-  // of a workgroup plus its fixed cost (ring fill, atomic epilogue: 6 K-tiles), as in launch_gemm.
+  // One K-range length for all products, and one of two kernels.  128x128 tiles, two workgroups per CU, run in whole rounds
+  // of 512 and take 1.2 us per K-tile (of two side by side) plus 6 K-tiles of fixed cost (ring fill, atomic adds that the
+  // neighbour's matrix work covers).  256x256 tiles, one workgroup per CU, take 1.45 us per K-tile and 6 us besides; nothing
+  // covers their atomic adds, which all workgroups of a round reach together (310 adds per ns over the chip: 70 us for
+  // the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.
+  // The launch runs beside the error-gradient chain, so a compute unit it leaves free is worth as much as time: the mean
+  // of the launch's duration and its share of the chip's is compared.  1024-wide layer, 8192 rows: 264 us on 128x128
+  // tiles, 192 256x256 tiles stored 178 us; 512-wide
+  // layer: 94 -> 69 us.
   int kmax = 0;
   for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
-  double best = 1e30;
-  int kchunk = kmax;
-  for (int kc = 256; kc <= kmax; kc += 64) {
-    long wgs = 0;
-    for (int i = 0; i < n; ++i)
-      wgs += (long)((g[i].M + 127) / 128) * ((g[i].N + 127) / 128) * ((g[i].K + kc - 1) / kc);
-    const long rounds = (wgs + 511) / 512;
-    const double cost = (double)rounds * (kc / 64 + 6);
-    if (cost < best - 1e-9) { best = cost; kchunk = kc; }
+  double best[2] = {1e30, 1e30};
+  int kchunks[2] = {kmax, kmax};
+  for (int kc = std::min(256, kmax); kc <= kmax; kc += 64) {
+    for (int big = 0; big < 2; ++big) {
+      const int bt = big ? 256 : 128;
+      long wgs = 0;
+      double adds = 0;
+      for (int i = 0; i < n; ++i) {
+        const int splits = (g[i].K + kc - 1) / kc;
+        const long tiles = (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt);
+        wgs += tiles * splits;
+        if (splits > 1) adds += (double)tiles * splits * bt * bt;
+      }
+      const double slots = big ? 256 : 512;
+      const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
+      const double cost = 0.5 * one * (std::ceil(wgs / slots) + wgs / slots);
+      if (cost < best[big] - 1e-9) { best[big] = cost; kchunks[big] = kc; }
+    }
   }
+  const bool big = best[1] < best[0];
+  const int kchunk = kchunks[big];
   GemmParams ps[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) {
     const GemmDesc& d = g[i];
@@ -389,13 +415,15 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     memset(&p, 0, sizeof p);
     p.A = d.A; p.B = d.B; p.C = d.C;
     p.M = d.M; p.N = d.N; p.K = d.K; p.lda = d.lda; p.ldb = d.ldb; p.ldc = d.ldc;
-    p.out_fp32 = 1; p.accumulate = 1; p.epilogue = EPI_NONE; p.alpha = d.alpha;
+    p.out_fp32 = 1; p.epilogue = EPI_NONE; p.alpha = d.alpha;
     p.by = p.bz = p.bz1 = 1;
     // every product splits into ranges of the same length, rounded so that the last is not a sliver
     const int splits = (d.K + kchunk - 1) / kchunk;
     p.kchunk = ((d.K + splits - 1) / splits + 63) / 64 * 64;
+    p.accumulate = splits > 1 ? ACC_ATOMIC : d.accumulate == ACC_STORE ? ACC_STORE : ACC_ADD;
   }
   if (grouped) *grouped = true;
+  if (big) return launch_gemm_pp_group(s, ps, n);
   return launch_gemm_dlds_group(s, ps, n, 1, 0);
 }
 

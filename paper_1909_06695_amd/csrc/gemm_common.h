@@ -26,6 +26,47 @@ struct GemmParams {
   DropDesc drop;
 };
 
+// Which output tile and K range a workgroup takes.  Workgroups go to the 8 XCDs round-robin, and
+// each XCD has its own L2: the grid index is turned into (XCD, position in that XCD's share)
+// and the XCD's share is a contiguous run of work items, ordered so that the workgroups in
+// flight together share operand tiles through that L2:
+//  - with split K the K range is the slowest index, so an XCD works inside one K range (or
+//    few) instead of streaming every range at once; tiles are numbered along M first when B
+//    is the larger operand (neighbours then share the B tile), else along N;
+//  - without split K and with tilesM a multiple of 8 an XCD owns a band of tilesM/8 tile rows
+//    and walks it in groups of 8 tile columns (tilesN a multiple of 8), rows fastest: the 32 to 64 tiles in flight
+//    cover (band x 8 columns), so both operands' tiles are re-used from L2 instead of one
+//    operand being re-streamed for every tile row.
+__device__ __forceinline__ void tile_of_block(const GemmParams& p, int BM, int BN, int bid, int nb, int& m0, int& n0, int& kbeg) {
+  {
+    int q = nb >> 3, r = nb & 7, x = bid & 7, idx = bid >> 3;
+    if (p.band) {
+      const int mb = p.tilesM >> 3, per = mb * 8;            // tile rows per XCD, tiles per full group
+      const int g = idx / per, w = idx - g * per;
+      m0 = (x * mb + w % mb) * BM;
+      n0 = (g * 8 + w / mb) * BN;
+      kbeg = 0;
+      return;
+    }
+    bid = x * q + min(x, r) + idx;
+  }
+  const int kz = bid / p.ntiles;
+  const int tile = bid - kz * p.ntiles;
+  m0 = (p.mfast ? tile % p.tilesM : tile / p.tilesN) * BM;
+  n0 = (p.mfast ? tile / p.tilesM : tile % p.tilesN) * BN;
+  kbeg = kz * p.kchunk;
+}
+
+// The product this workgroup belongs to, of a batch laid over blockIdx.y and blockIdx.z.
+__device__ __forceinline__ void batch_offsets(GemmParams& p) {
+  int z = blockIdx.z;
+  if (z >= p.bz1) { z -= p.bz1; p.A = p.A2; p.B = p.B2; p.C = p.C2; p.alpha = p.alpha2; }
+  p.A = reinterpret_cast<const char*>(p.A) + blockIdx.y * p.bAy + z * p.bAz;
+  p.B = reinterpret_cast<const char*>(p.B) + blockIdx.y * p.bBy + z * p.bBz;
+  p.C = reinterpret_cast<char*>(p.C) + blockIdx.y * p.bCy + z * p.bCz;
+  if (p.res32) p.res32 = reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.res32) + blockIdx.y * p.bCy + z * p.bCz);
+}
+
 template <typename T>
 __device__ __forceinline__ void epilogue_store(const GemmParams& p, int m, int n, float acc) {
   float v = acc * p.alpha;
@@ -119,25 +160,44 @@ template <int TN> constexpr int epilogue_stage_floats() { return TN * 32 * 36; }
 // LDS patch (row stride 36 floats) so that a lane leaves with 8 consecutive columns of one
 // output row: 16-byte loads of the residual / pre-activation, 16-byte stores of the result.
 // Only the register dump is unrolled; the arithmetic runs in a rolled loop over the patch.
-template <int TM, int TN>
-__device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)[TM][TN], uint4* smem, int m_w, int n_w,
-                                              int lane, int wave) {
-  if (p.accumulate) {
+// CS: distance in columns between the tiles of a row.
+// p.accumulate: ACC_ATOMIC, several workgroups add to an element of C (split K); ACC_ADD, only this one does; ACC_STORE,
+// likewise, and C is known to be zero.
+template <int TM, int TN, int CS = 32>
+__device__ __forceinline__ void mfma_accumulate(const GemmParams& p, f32x16 (&acc)[TM][TN], int m_w, int n_w, int lane) {
+  const int mode = p.accumulate;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n_w + j * 32 + (lane & 31);
-        const int mb = m_w + i * 32 + 4 * (lane >> 5);
-        float* c = reinterpret_cast<float*>(p.C) + (size_t)mb * p.ldc + n;
+    for (int j = 0; j < TN; ++j) {
+      const int n = n_w + j * CS + (lane & 31);
+      const int mb = m_w + i * 32 + 4 * (lane >> 5);
+      float* c = reinterpret_cast<float*>(p.C) + (size_t)mb * p.ldc + n;
+      if (mode == ACC_ATOMIC) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int dm = 8 * (r >> 2) + (r & 3);
           if (n < p.N && mb + dm < p.M) unsafeAtomicAdd(c + (size_t)dm * p.ldc, acc[i][j][r] * p.alpha);
         }
+      } else {
+        float old[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int dm = 8 * (r >> 2) + (r & 3);
+          old[r] = mode == ACC_ADD && n < p.N && mb + dm < p.M ? c[(size_t)dm * p.ldc] : 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int dm = 8 * (r >> 2) + (r & 3);
+          if (n < p.N && mb + dm < p.M) c[(size_t)dm * p.ldc] = old[r] + acc[i][j][r] * p.alpha;
+        }
       }
-    return;
-  }
+    }
+}
+template <int TM, int TN, int CS = 32>
+__device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)[TM][TN], uint4* smem, int m_w, int n_w,
+                                              int lane, int wave) {
+  if (p.accumulate) { mfma_accumulate<TM, TN, CS>(p, acc, m_w, n_w, lane); return; }
   float* stage = reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<TN>();
   const int h32 = lane >> 5, l32 = lane & 31;
   const int srow = lane >> 2, scol = (lane & 3) * 8;
@@ -155,7 +215,7 @@ __device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)
       const int row = (t & 1) * 16 + srow;
       const float* src = stage + j * (32 * 36) + row * 36 + scol;
       const int m = m_w + i * 32 + row;
-      const int n = n_w + j * 32 + scol;
+      const int n = n_w + j * CS + scol;
       if (m < p.M) {
         if (p.vec_epi && n + 8 <= p.N) {
           float4 lo = *reinterpret_cast<const float4*>(src);

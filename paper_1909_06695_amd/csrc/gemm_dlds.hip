@@ -96,47 +96,6 @@ __device__ __forceinline__ bf16x8 frag_col(const char* tile, int t0, int ks, int
   return u.v;
 }
 
-// Which output tile and K range a workgroup takes.  Workgroups go to the 8 XCDs round-robin, and
-// each XCD has its own L2: the grid index is turned into (XCD, position in that XCD's share)
-// and the XCD's share is a contiguous run of work items, ordered so that the workgroups in
-// flight together share operand tiles through that L2:
-//  - with split K the K range is the slowest index, so an XCD works inside one K range (or
-//    few) instead of streaming every range at once; tiles are numbered along M first when B
-//    is the larger operand (neighbours then share the B tile), else along N;
-//  - without split K and with tilesM a multiple of 8 an XCD owns a band of tilesM/8 tile rows
-//    and walks it in groups of 8 tile columns (tilesN a multiple of 8), rows fastest: the 32 to 64 tiles in flight
-//    cover (band x 8 columns), so both operands' tiles are re-used from L2 instead of one
-//    operand being re-streamed for every tile row.
-__device__ __forceinline__ void tile_of_block(const GemmParams& p, int BM, int BN, int bid, int nb, int& m0, int& n0, int& kbeg) {
-  {
-    int q = nb >> 3, r = nb & 7, x = bid & 7, idx = bid >> 3;
-    if (p.band) {
-      const int mb = p.tilesM >> 3, per = mb * 8;            // tile rows per XCD, tiles per full group
-      const int g = idx / per, w = idx - g * per;
-      m0 = (x * mb + w % mb) * BM;
-      n0 = (g * 8 + w / mb) * BN;
-      kbeg = 0;
-      return;
-    }
-    bid = x * q + min(x, r) + idx;
-  }
-  const int kz = bid / p.ntiles;
-  const int tile = bid - kz * p.ntiles;
-  m0 = (p.mfast ? tile % p.tilesM : tile / p.tilesN) * BM;
-  n0 = (p.mfast ? tile / p.tilesM : tile % p.tilesN) * BN;
-  kbeg = kz * p.kchunk;
-}
-
-// The product this workgroup belongs to, of a batch laid over blockIdx.y and blockIdx.z.
-__device__ __forceinline__ void batch_offsets(GemmParams& p) {
-  int z = blockIdx.z;
-  if (z >= p.bz1) { z -= p.bz1; p.A = p.A2; p.B = p.B2; p.C = p.C2; p.alpha = p.alpha2; }
-  p.A = reinterpret_cast<const char*>(p.A) + blockIdx.y * p.bAy + z * p.bAz;
-  p.B = reinterpret_cast<const char*>(p.B) + blockIdx.y * p.bBy + z * p.bBz;
-  p.C = reinterpret_cast<char*>(p.C) + blockIdx.y * p.bCy + z * p.bCz;
-  if (p.res32) p.res32 = reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.res32) + blockIdx.y * p.bCy + z * p.bCz);
-}
-
 // One workgroup's share of a product: work item `bid` of `nb` (see tile_of_block).
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, int S>
 __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int nb, uint4* smem) {
@@ -509,7 +468,6 @@ hipError_t launch_gemm_dlds(hipStream_t s, GemmParams& p, int transA, int transB
     case GEMM_TILE_128x128: return launch_dlds_cfg<128, 128, 2, 4, 2>(s, p, transA, transB, splits);
     case GEMM_TILE_128x64: return launch_dlds_cfg<128, 64, 4, 1, 2>(s, p, transA, transB, splits);
     case GEMM_TILE_PIPE128: return launch_pipe_cfg<128, 128, 2, 4, 4>(s, p, transA, transB, splits);
-    case GEMM_TILE_256x256: return launch_dlds_cfg<256, 256, 2, 4, 2>(s, p, transA, transB, splits);
     default: return hipErrorInvalidValue;
   }
 }

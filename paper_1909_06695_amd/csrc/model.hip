@@ -1011,7 +1011,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   // FFN2
   {
     GemmDesc g = gd(b.uact, F, 1, ds2m, d, 0, gslot + o.W_2, d, F, d, N);
-    g.out_fp32 = 1; g.accumulate = 1;
+    g.out_fp32 = 1; g.accumulate = ACC_STORE;
     wg[nwg++] = g;
   }
   HIPCHK(launch_colsum(sw, c.dtype, ds2m, d, vc + 2 * d, N, d, m->vec_stride));
@@ -1024,7 +1024,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   // FFN1
   {
     GemmDesc g = gd(b.y, d, 1, dz, F, 0, gslot + o.W_1, F, d, F, N);
-    g.out_fp32 = 1; g.accumulate = 1;
+    g.out_fp32 = 1; g.accumulate = ACC_STORE;
     wg[nwg++] = g;
   }
   HIPCHK(launch_colsum(sw, c.dtype, dz, F, vc + 5 * d, N, F, m->vec_stride));
@@ -1042,7 +1042,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   // output projection
   {
     GemmDesc g = gd(b.a, hd, 1, ds1m, d, 0, gslot + o.W_o, d, hd, d, N);
-    g.out_fp32 = 1; g.accumulate = 1;
+    g.out_fp32 = 1; g.accumulate = ACC_STORE;
     wg[nwg++] = g;
   }
   RUN(run_gemm(m, gd(ds1m, d, 0, m->wT(l, o.W_o), d, 1, m->da, hd, N, hd, d)));
@@ -1063,7 +1063,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
     RUN(ready(3));
     {
       GemmDesc g = gd(b.x, d, 1, dqkv, 3 * hd, 0, gslot + o.W_qkv, 3 * hd, d, 3 * hd, N);
-      g.out_fp32 = 1; g.accumulate = 1;
+      g.out_fp32 = 1; g.accumulate = ACC_STORE;
       wg[nwg++] = g;
     }
     RUN(run_gemm_group_on(m, wg, nwg, sw));
@@ -1098,17 +1098,17 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
     // weight gradients: dW_r = R^T dr, dW_q = x^T dq, dW_kv = [mem ; x]^T dkv
     {
       GemmDesc g = gd(m->rtab, d, 1, drp, hd, 0, gslot + o.W_r, hd, d, hd, S);
-      g.out_fp32 = 1; g.accumulate = 1;
+      g.out_fp32 = 1; g.accumulate = ACC_STORE;
       wg[nwg++] = g;
     }
     {
       GemmDesc g = gd(b.x, d, 1, dq, hd, 0, gslot + o.W_qkv, 3 * hd, d, hd, N);
-      g.out_fp32 = 1; g.accumulate = 1;
+      g.out_fp32 = 1; g.accumulate = ACC_STORE;
       wg[nwg++] = g;
     }
     {
       GemmDesc g = gd(cat, d, 1, dkv, 2 * hd, 0, gslot + o.W_qkv + hd, 3 * hd, d, 2 * hd, B * S);
-      g.out_fp32 = 1; g.accumulate = 1;
+      g.out_fp32 = 1; g.accumulate = ACC_STORE;
       wg[nwg++] = g;
     }
     RUN(run_gemm_group_on(m, wg, nwg, sw));

@@ -168,6 +168,15 @@ def test_gemm_group(dtype, shapes):
         assert rel_err(host(out[i]), ref) < 2e-6, i
 
 
+@pytest.mark.parametrize("shapes", [
+    [(1024, 1024, 2331), (1032, 776, 2331)],                      # K range whole, ragged K-tile and edges of tiles
+    [(264, 520, 8256), (512, 256, 8256)],                         # split over workgroups, atomic adds
+    [(1024, 2048, 1088), (512, 1024, 96), (256, 256, 40)]])       # contractions of one and two K-tiles beside a long one
+def test_gemm_group_large_tiles(shapes):
+    """Sizes at which the grouped launch runs on 256x256 tiles; same bound as the small ones."""
+    test_gemm_group(1, shapes)
+
+
 @pytest.mark.parametrize("dtype,force", [(0, 0), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14)])
 def test_gemm_epilogues_and_strides(dtype, force):
     rng = np.random.default_rng(5)
