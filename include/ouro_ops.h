@@ -23,7 +23,7 @@ extern "C" {
  * 11 direct-to-LDS 128x128, 12 direct-to-LDS 128x64, 13 register-prefetch 128x128 with a
  * four-stage ring, 14 direct-to-LDS 256x256; 11..14 fall back to 10 unless K % 64 == 0 or both operands have the
  * contraction as their slow dimension, transA == 1 and transB == 0),
- * for tests and tuning.
+ * 20..22 = fp32 matrix-core kernel (20 automatic, 21 64x64 tiles, 22 32x32 tiles), for tests and tuning.
  * These are the layer contractions of Eq. 2 / Eq. 6 (forward, input- and weight-gradient). */
 int ouro_op_gemm(void* stream, int dtype, int transA, int transB, int M, int N, int K, float alpha,
                  const void* A, int lda, const void* B, int ldb, void* C, int ldc, int out_fp32,

@@ -1,6 +1,6 @@
-// Dense contractions of the training step: the choice between the direct-to-LDS MFMA kernels (gemm_pp.hip, gemm_dlds.hip),
-// a register-staged bf16 MFMA kernel (LDS double-buffered, XOR-swizzled tiles, 32x32x16 matrix instructions) and a plain
-// bounds-checked tiled kernel for fp32 operands and shapes the MFMA kernels do not take.
+// Dense contractions of the training step: the choice between the direct-to-LDS MFMA kernels (gemm_pp.hip, gemm_dlds.hip;
+// fp32: gemm_f32.hip), a register-staged bf16 MFMA kernel (LDS double-buffered, XOR-swizzled tiles, 32x32x16 matrix
+// instructions) and a plain bounds-checked tiled kernel for what those do not take.
 #include "gemm_common.h"
 
 #include <algorithm>
@@ -156,6 +156,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
 hipError_t launch_gemm_dlds(hipStream_t s, GemmParams& p, int transA, int transB, int splits, int cfg);
 hipError_t launch_gemm_pp(hipStream_t s, GemmParams& p, int transA, int transB, int splits);
 hipError_t launch_gemm_pp_group(hipStream_t s, const GemmParams* ps, int n);
+bool gemm_f32_ok(const GemmDesc& g);
+hipError_t launch_gemm_f32(hipStream_t s, GemmParams& p, int transA, int transB, int form);
 hipError_t launch_gemm_dlds_group(hipStream_t s, GemmParams* ps, int n, int transA, int transB);
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
@@ -343,6 +345,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     if (cfg != GEMM_TILE_STAGED128) return launch_gemm_dlds(s, p, g.transA, g.transB, splits, cfg);
     return launch_mfma_cfg<128, 128, 2, 2>(s, p, g.transA, g.transB, splits);
   }
+
+  if (dtype == 0 && force_generic != 1 && gemm_f32_ok(g)) return launch_gemm_f32(s, p, g.transA, g.transB, force_generic >= 20 ? force_generic - 20 : 0);
 
   dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, 1), block(256);
 #define OURO_PLAIN(T_)                                                                        \

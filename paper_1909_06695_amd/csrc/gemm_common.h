@@ -93,6 +93,78 @@ __device__ __forceinline__ void epilogue_store(const GemmParams& p, int m, int n
 }
 
 
+// The same for R rows of one column: what depends on the column is read once, and the reads of a stage go out together.
+template <typename T, int R>
+__device__ __forceinline__ void epilogue_column(const GemmParams& p, const int (&m)[R], int n, float (&v)[R]) {
+  if (n >= p.N) return;
+  bool on[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) { on[r] = m[r] < p.M; v[r] *= p.alpha; }
+  if (p.accumulate == ACC_ATOMIC) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (on[r]) unsafeAtomicAdd(reinterpret_cast<float*>(p.C) + (size_t)m[r] * p.ldc + n, v[r]);
+    return;
+  }
+  if (p.accumulate) {
+    float old[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) old[r] = on[r] ? reinterpret_cast<const float*>(p.C)[(size_t)m[r] * p.ldc + n] : 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] += old[r];
+  }
+  if (p.bias) {
+    const float b = p.bias[n];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] += b;
+  }
+  if (p.drop.on) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] *= drop_factor(p.drop, (uint64_t)m[r] * p.drop.ld + n);
+  }
+  if (p.epilogue == EPI_GELU) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (on[r]) reinterpret_cast<T*>(p.Z)[(size_t)m[r] * p.ldz + n] = from_f32<T>(v[r]);
+      v[r] = gelu_f(v[r]);
+    }
+  } else if (p.epilogue == EPI_GELUGRAD) {
+    float z[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) z[r] = on[r] ? to_f32(reinterpret_cast<const T*>(p.Z)[(size_t)m[r] * p.ldz + n]) : 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] *= gelu_grad_f(z[r]);
+  }
+  if (p.residual) {
+    float x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = on[r] ? to_f32(reinterpret_cast<const T*>(p.residual)[(size_t)m[r] * p.ldr + n]) : 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] += x[r];
+  }
+  if (p.res32) {
+    float x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = on[r] ? p.res32[(size_t)m[r] * p.ldr32 + n] : 0.f;
+    if (p.ln_mean) {
+      float mu[R], rs[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) { mu[r] = on[r] ? p.ln_mean[m[r]] : 0.f; rs[r] = on[r] ? p.ln_rstd[m[r]] : 0.f; }
+      const float g = p.ln_g[n], b = p.ln_b[n];
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = (x[r] - mu[r]) * rs[r] * g + b;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] += x[r];
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (!on[r]) continue;
+    if (p.out_fp32) reinterpret_cast<float*>(p.C)[(size_t)m[r] * p.ldc + n] = v[r];
+    else reinterpret_cast<T*>(p.C)[(size_t)m[r] * p.ldc + n] = from_f32<T>(v[r]);
+  }
+}
+
 // Eight consecutive columns n..n+7 of row m (bf16 operands), all in range and 16-byte
 // addressable: the same epilogue as epilogue_store with 16-byte accesses.
 __device__ __forceinline__ void epilogue_store8(const GemmParams& p, int m, int n, const float* acc) {

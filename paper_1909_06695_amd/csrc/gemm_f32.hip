@@ -1,0 +1,242 @@
+// fp32 contraction on the matrix cores (32x32x2 instructions: fp32 products, fp32 accumulation), any size and alignment.
+//
+// The fp32 matrix rate is a sixteenth of the bf16 one (157 TFLOP/s), so a wave multiplies one 32x32 tile and even that keeps
+// loads far from limiting: 8 KB of operands per 1024 clocks.  What a launch needs instead is enough workgroups, which the two
+// forms below give over the sizes of a small model:
+//   WIDE    64x64 tiles, waves 2 x 2, a ring of four K-tiles (32) shared by the workgroup;
+//   !WIDE   32x32 tiles, the four waves take K-tiles in turn, each through a ring of its own, and add up through LDS at the
+//           end: sixteen times as many waves on the same product, for products of fewer than 384 64x64 tiles.
+// Operands go global -> LDS by direct loads through a buffer descriptor (what lies past the operand reads as zero): 16 bytes
+// per lane where leading dimensions and bases allow it (VEC = 4), else 4 bytes per lane.
+//   row form (k contiguous in memory): [rows][32 k], 16-byte chunk c of a row at chunk c ^ (row & 7);
+//   column form (k the slow dimension): [32 k][rows].
+// The contraction index may be enumerated in any order as long as both operands agree: step s of group j takes
+// k = 8 j + s from the lower half of the lanes and 8 j + 4 + s from the upper, so a row-form fragment of four steps is
+// one 16-byte read.
+// Against the plain tiled kernel (64x64, vector arithmetic, one synchronous K-tile of 16 at a time): 1024 x 512 x 512 80 ->
+// 9 us, 1024 x 512 x 2048 300 -> 26 us (32x32 tiles); 1024 x 2048 x 512 101 -> 25 us (64x64); the products of a 2-layer
+// 64-wide model on 128 tokens 22 -> 4.4 us each.
+#include "gemm_common.h"
+
+#include <algorithm>
+
+namespace ouro {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((address_space(3))) void lds_void;
+
+constexpr int F32_BK = 32;
+
+// One operand of a tile: ROWS along m (or n), NW waves share its loads.
+template <int ROWS, bool COL, int VEC, int NW>
+struct F32Operand {
+  static constexpr int BYTES = ROWS * F32_BK * 4;
+  static constexpr int EPL = 64 * VEC;                            // elements per wave-load
+  static constexpr int PER = ROWS * F32_BK / EPL / NW;            // wave-loads per wave
+  static_assert(ROWS * F32_BK % (EPL * NW) == 0, "loads divide over the waves");
+  // (row, k) that lane `lane` fetches in wave-load j; with VEC = 4 it also fetches the next three along k (row form) or row
+  __device__ static __forceinline__ void place(int j, int lane, int& row, int& k) {
+    const int e = (j * 64 + lane) * VEC;                          // element index in LDS
+    if (COL) { k = e / ROWS; row = e % ROWS; return; }
+    row = e / F32_BK;
+    const int d = e % F32_BK;
+    k = (((d >> 2) ^ (row & 7)) << 2) + (d & 3);
+  }
+};
+
+__device__ __forceinline__ void f32_load(const void* base, int bytes, char* dst, uint32_t voff, uint32_t soff, int vec) {
+  auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+  if (vec == 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, soff, 0, 0);
+  else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 4, voff, soff, 0, 0);
+}
+
+// The fragment of four steps (group j) of the 32-row tile at LDS address `a` (lane term included).  Inline assembly: the
+// compiler cannot tell an LDS read from the target of the direct loads in flight and would drain those first.
+template <int ROWS, bool COL>
+struct F32Frag {
+  f32x4 v;
+  float c[4];
+  template <int J> __device__ __forceinline__ void read(const uint32_t (&a)[4]) {
+    if constexpr (!COL) {
+      asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(a[J]));
+    } else {
+      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[0]) : "v"(a[0]), "n"((8 * J + 0) * ROWS * 4));
+      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[1]) : "v"(a[0]), "n"((8 * J + 1) * ROWS * 4));
+      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[2]) : "v"(a[0]), "n"((8 * J + 2) * ROWS * 4));
+      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[3]) : "v"(a[0]), "n"((8 * J + 3) * ROWS * 4));
+    }
+  }
+  __device__ __forceinline__ void tie() {
+    if constexpr (!COL) asm volatile("" : "+v"(v));
+    else asm volatile("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+  }
+  __device__ __forceinline__ float get(int s) const { return COL ? c[s] : v[s]; }
+};
+// Address registers of the 32-row tile that starts at row t0: row form one per group, column form one.
+template <int ROWS, bool COL>
+__device__ __forceinline__ void f32_addresses(uint32_t base, int t0, int lane, uint32_t (&a)[4]) {
+  const int row = t0 + (lane & 31), h = lane >> 5;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a[j] = COL ? base + h * 4 * ROWS * 4 + row * 4 : base + row * 128 + (((2 * j + h) ^ (row & 7)) << 4);
+}
+
+template <bool WIDE, bool TA, bool TB, int VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
+  constexpr int T = WIDE ? 64 : 32, S = WIDE ? 4 : 2, NW = WIDE ? 4 : 1;
+  using OA = F32Operand<T, TA, VEC, NW>;
+  using OB = F32Operand<T, !TB, VEC, NW>;
+  constexpr int STAGE = OA::BYTES + OB::BYTES, LPT = OA::PER + OB::PER;
+  static_assert((S - 1) * LPT < 64, "vmcnt range");
+  extern __shared__ __attribute__((aligned(16))) char lds_all[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  char* const lds = WIDE ? lds_all : lds_all + wave * (S * STAGE);
+  const int lw = WIDE ? wave : 0;                                // wave's place among those that share the loads
+  const int m0 = (blockIdx.x / p.tilesN) * T, n0 = (blockIdx.x % p.tilesN) * T;
+  const int kbeg = blockIdx.z * p.kchunk, kend = min(p.K, kbeg + p.kchunk);
+  const int nk_all = (kend - kbeg + F32_BK - 1) / F32_BK;
+  const int k_first = WIDE ? 0 : wave, k_step = WIDE ? 1 : 4;    // K-tiles of this wave
+  const int nk = nk_all > k_first ? (nk_all - k_first + k_step - 1) / k_step : 0;
+  const int bytesA = (int)(4u * (uint32_t)(TA ? p.K : p.M) * (uint32_t)p.lda), bytesB = (int)(4u * (uint32_t)(TB ? p.N : p.K) * (uint32_t)p.ldb);
+
+  uint32_t oa[OA::PER], ob[OB::PER];                             // byte offsets without the K-tile term
+  auto offset = [](bool col, int row, int k, int ld) __attribute__((always_inline)) { return 4u * (col ? (uint32_t)k * (uint32_t)ld + row : (uint32_t)row * (uint32_t)ld + k); };
+#pragma unroll
+  for (int i = 0; i < OA::PER; ++i) { int row, k; OA::place(lw * OA::PER + i, lane, row, k); oa[i] = offset(TA, m0 + row, k, p.lda); }
+#pragma unroll
+  for (int i = 0; i < OB::PER; ++i) { int row, k; OB::place(lw * OB::PER + i, lane, row, k); ob[i] = offset(!TB, n0 + row, k, p.ldb); }
+  auto request = [&](int it, int st) __attribute__((always_inline)) {
+    const int k0 = kbeg + (k_first + it * k_step) * F32_BK;
+    const uint32_t ka = 4u * (TA ? (uint32_t)k0 * (uint32_t)p.lda : (uint32_t)k0), kb = 4u * (TB ? (uint32_t)k0 : (uint32_t)k0 * (uint32_t)p.ldb);
+    char* d = lds + st * STAGE;
+    // a row-form operand's last K-tile may be ragged: what lies past the row's end is sent out of range, which reads as zero
+    const bool ragged = k0 + F32_BK > kend;
+#pragma unroll
+    for (int i = 0; i < OA::PER; ++i) {
+      char* da = d + (lw * OA::PER + i) * (OA::EPL * 4);
+      if (!TA && ragged) { int row, k; OA::place(lw * OA::PER + i, lane, row, k); f32_load(p.A, bytesA, da, k0 + k < kend ? oa[i] + ka : 0x7ffffff0u, 0, VEC); }
+      else f32_load(p.A, bytesA, da, oa[i], ka, VEC);
+    }
+#pragma unroll
+    for (int i = 0; i < OB::PER; ++i) {
+      char* db = d + OA::BYTES + (lw * OB::PER + i) * (OB::EPL * 4);
+      if (TB && ragged) { int row, k; OB::place(lw * OB::PER + i, lane, row, k); f32_load(p.B, bytesB, db, k0 + k < kend ? ob[i] + kb : 0x7ffffff0u, 0, VEC); }
+      else f32_load(p.B, bytesB, db, ob[i], kb, VEC);
+    }
+  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  uint32_t ra[4], rb[4];
+  f32_addresses<T, TA>(lds0, WIDE ? 32 * (wave >> 1) : 0, lane, ra);
+  f32_addresses<T, !TB>(lds0 + OA::BYTES, WIDE ? 32 * (wave & 1) : 0, lane, rb);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s)
+    if (s < nk) request(s, s);
+  int rd = 0, fill = S - 1;
+  for (int it = 0; it < nk; ++it) {
+    // this K-tile has landed once only the younger ones are outstanding; where the stages are shared, for every wave's share
+    if (it + S - 1 <= nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * LPT) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (WIDE) {
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (it + S - 1 < nk) request(it + S - 1, fill);              // the stage read one K-tile ago (its reads were waited for)
+    F32Frag<T, TA> fa[4];
+    F32Frag<T, !TB> fb[4];
+    uint32_t va[4], vb[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { va[j] = ra[j] + rd * STAGE; vb[j] = rb[j] + rd * STAGE; }
+    fa[0].template read<0>(va); fb[0].template read<0>(vb); fa[1].template read<1>(va); fb[1].template read<1>(vb);
+    fa[2].template read<2>(va); fb[2].template read<2>(vb); fa[3].template read<3>(va); fb[3].template read<3>(vb);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { fa[j].tie(); fb[j].tie(); }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j].get(s), fb[j].get(s), acc, 0, 0, 0);
+    fill = rd;
+    rd = rd + 1 == S ? 0 : rd + 1;
+  }
+  const int h = lane >> 5, l32 = lane & 31;
+  if (WIDE) {
+    const int mb = m0 + 32 * (wave >> 1) + 4 * h, n = n0 + 32 * (wave & 1) + l32;
+    float v[16];
+    int m[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { v[r] = acc[r]; m[r] = mb + 8 * (r >> 2) + (r & 3); }
+    epilogue_column<float, 16>(p, m, n, v);
+    return;
+  }
+  // add up the four waves' parts: [wave][row][33]
+  __syncthreads();                                               // every wave is past its last fragment read
+  float* part = reinterpret_cast<float*>(lds_all);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[(wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * 33 + l32] = acc[r];
+  __syncthreads();
+  float v[4];
+  int m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = (tid >> 5) + 8 * i, col = tid & 31;
+    v[i] = part[row * 33 + col] + part[(32 + row) * 33 + col] + part[(64 + row) * 33 + col] + part[(96 + row) * 33 + col];
+    m[i] = m0 + row;
+  }
+  epilogue_column<float, 4>(p, m, n0 + (tid & 31), v);
+}
+
+bool gemm_f32_ok(const GemmDesc& g) {
+  const size_t bytesA = 4 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 4 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
+  return bytesA < (1ull << 31) - 64 && bytesB < (1ull << 31) - 64 && g.K >= 1;
+}
+
+template <bool WIDE, int VEC>
+static hipError_t launch_f32(hipStream_t s, GemmParams& p, int transA, int transB, int splits) {
+  constexpr int T = WIDE ? 64 : 32;
+  constexpr size_t smem = WIDE ? 4 * 2 * 64 * 128 : 4 * 2 * 2 * 32 * 128;
+  static_assert(smem >= 4 * 32 * 33 * 4, "the parts of the four waves fit");
+  p.tilesM = (p.M + T - 1) / T;
+  p.tilesN = (p.N + T - 1) / T;
+  dim3 grid(p.tilesM * p.tilesN, 1, splits), block(256);
+#define OURO_LAUNCH(TA_, TB_)                                                                                 \
+  do {                                                                                                        \
+    static bool attr_done = false;                                                                            \
+    if (!attr_done) {                                                                                         \
+      hipError_t e = hipFuncSetAttribute((const void*)gemm_f32_kernel<WIDE, TA_, TB_, VEC>,                   \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);              \
+      if (e != hipSuccess) return e;                                                                          \
+      attr_done = true;                                                                                       \
+    }                                                                                                         \
+    hipLaunchKernelGGL((gemm_f32_kernel<WIDE, TA_, TB_, VEC>), grid, block, smem, s, p);                      \
+  } while (0)
+  if (!transA && !transB) OURO_LAUNCH(false, false);
+  else if (!transA && transB) OURO_LAUNCH(false, true);
+  else if (transA && !transB) OURO_LAUNCH(true, false);
+  else OURO_LAUNCH(true, true);
+#undef OURO_LAUNCH
+  return hipGetLastError();
+}
+
+// form: 0 automatic, 1 64x64 tiles, 2 32x32 tiles with K-tiles dealt to the waves.
+hipError_t launch_gemm_f32(hipStream_t s, GemmParams& p, int transA, int transB, int form) {
+  const bool vec = !(((uintptr_t)p.A | (uintptr_t)p.B) & 15) && !((p.lda | p.ldb) & 3) && !((transA ? p.M : p.K) & 3) && !((transB ? p.K : p.N) & 3);
+  const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64), t32 = (long)((p.M + 31) / 32) * ((p.N + 31) / 32);
+  // 512 64x64 tiles: 2048 x 1024 x 1024 takes 40 us on them against 47 us in the other form; 128 tiles (1024 x 512 x 2048)
+  // 51 us against 25; in between (1024 x 1536 x 512) 23 us both
+  const bool wide = form == 1 || (form == 0 && t64 >= 384);
+  int splits = 1;
+  // a small output with a long contraction: split it over workgroups too (512 of the small tiles fill the chip), at least
+  // four K-tiles per wave
+  if (p.accumulate && !wide && t32 < 512) splits = (int)std::max<long>(1, std::min<long>(512 / t32, p.K / (16 * F32_BK)));
+  p.kchunk = ((p.K + splits - 1) / splits + F32_BK - 1) / F32_BK * F32_BK;
+  splits = (p.K + p.kchunk - 1) / p.kchunk;
+  if (p.accumulate) p.accumulate = splits > 1 ? ACC_ATOMIC : ACC_ADD;
+  if (wide) return vec ? launch_f32<true, 4>(s, p, transA, transB, splits) : launch_f32<true, 1>(s, p, transA, transB, splits);
+  return vec ? launch_f32<false, 4>(s, p, transA, transB, splits) : launch_f32<false, 1>(s, p, transA, transB, splits);
+}
+
+}  // namespace ouro

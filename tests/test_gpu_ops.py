@@ -218,6 +218,35 @@ def test_gemm_epilogues_and_strides(dtype, force):
     assert rel_err(host(acc), 1.0 + host(dA2).T @ host(dB2)) < 3e-6
 
 
+@pytest.mark.parametrize("force", [21, 22])
+@pytest.mark.parametrize("tA", [0, 1])
+@pytest.mark.parametrize("tB", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 7), (64, 64, 32), (32, 96, 128), (65, 130, 97), (40, 84, 412), (200, 64, 516), (63, 65, 2050)])
+def test_gemm_f32_matrix_core_forms(force, tA, tB, M, N, K):
+    """The two fp32 forms (21: 64x64 tiles, 22: 32x32 tiles with the K-tiles dealt to the waves) at edges of tiles, of
+    K-tiles and of the 16-byte alignment (4-byte loads otherwise); overwriting and accumulating.  fp32 sums of K products:
+    2e-6 in the norm, as test_gemm_forms holds them to."""
+    rng = np.random.default_rng(M + 7 * N + 13 * K + tA * 2 + tB)
+    A = rng.standard_normal((K, M) if tA else (M, K)).astype(np.float32)
+    B = rng.standard_normal((N, K) if tB else (K, N)).astype(np.float32)
+    dA, dB = dev(A, 0), dev(B, 0)
+    ref = (A.T if tA else A).astype(np.float64) @ (B.T if tB else B).astype(np.float64)
+    for acc in (0, 1):
+        out = torch.ones((M, N), dtype=torch.float32, device="cuda")
+        ok(L().ouro_op_gemm(stream(), 0, tA, tB, M, N, K, 1.0, p(dA), dA.shape[1], p(dB), dB.shape[1], p(out), N, 1, acc, None, None, 0, 0, None, 0, force))
+        torch.cuda.synchronize()
+        assert rel_err(host(out), ref + acc) < 2e-6
+
+
+@pytest.mark.parametrize("force", [21, 22])
+def test_gemm_f32_matrix_core_epilogues(force):
+    """Bias, GELU and its gradient, residuals, LayerNorm residual and dropout in the epilogue of both fp32 forms."""
+    test_gemm_epilogues_and_strides(0, force)
+    for ln in (0, 1):
+        test_gemm_with_fp32_layernorm_residual(0, force, 72, 136, 96, ln)
+    test_gemm_with_fused_dropout(0, force, 72, 136, 96)
+
+
 # -------------------------------------------------------------------------- attention
 def _attn_case(dtype, B, H, T, Mv, dh, rel, seed, force=1):
     rng = np.random.default_rng(seed)
