@@ -333,6 +333,14 @@ def test_attention_xl_mfma_kernel(B, H, T, Mv):
     _attn_case(1, B, H, T, Mv, 64, 1, seed=200 + T + Mv, force=0)
 
 
+@pytest.mark.parametrize("B,H,T,Mv,dh", [(1, 1, 1, 0, 64), (2, 2, 33, 0, 32), (1, 3, 70, 5, 41), (2, 2, 128, 0, 64), (1, 2, 150, 40, 48),
+                                         (2, 1, 257, 0, 7), (1, 2, 31, 97, 36)])
+def test_attention_f32_kernel(B, H, T, Mv, dh):
+    """fp32 attention on the matrix cores: one query, ragged tiles on both axes, memory before the segment, head sizes that
+    take the narrow and the wide instance, aligned (16-byte loads) and not; fp32 bound of _attn_case."""
+    _attn_case(0, B, H, T, Mv, dh, 0, seed=300 + T + Mv + dh, force=0)
+
+
 @pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14)])
 @pytest.mark.parametrize("M,N,K,ln", [(200, 136, 328, 1), (384, 520, 192, 1), (130, 88, 128, 0), (260, 256, 64, 1)])
 def test_gemm_with_fp32_layernorm_residual(dtype, force, M, N, K, ln):
