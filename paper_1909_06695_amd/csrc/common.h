@@ -207,6 +207,13 @@ hipError_t launch_embed_bwd(hipStream_t s, int dtype, const int32_t* tok, const 
 // running count of 64x64 tiles before this matrix (the launch covers all matrices of a table).
 struct TransposeEntry { unsigned long long off; int rows, cols, ld_out, tile0; };
 hipError_t launch_transpose_table(hipStream_t s, const void* src, void* dst, const TransposeEntry* dev_tab, int entries, int tiles);
+// One tensor of a parameter group between the caller's dense blob (rows x cols at loff) and the stored one (rows of pcols
+// at poff); a head axis of d_head elements a head is stored in slices of pdh.  tile0 is the running count of REMAP_ROWS-row
+// tiles before this tensor.
+struct RemapEntry { unsigned long long loff, poff; int rows, cols, pcols, row_heads, col_heads, tile0; };
+constexpr int REMAP_ROWS = 16;
+// to_stored != 0: stored <- blob (positions outside the tensors stay as they are); 0: blob <- stored
+hipError_t launch_remap(hipStream_t s, float* stored, float* blob, const RemapEntry* dev_tab, int entries, int tiles, int d_head, int pdh, int to_stored);
 // dst[r, c] = src[r, c] * mask(r*drop.ld + c) over rows x cols elements, both with row stride ld
 hipError_t launch_dropout_apply(hipStream_t s, int dtype, const void* src, void* dst, int rows, int cols, int ld,
                                 const DropDesc& drop);

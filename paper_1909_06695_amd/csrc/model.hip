@@ -29,6 +29,8 @@ static int fail(int code, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(OURO_E_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
+#define RUN(expr) do { int rc_ = (expr); if (rc_) return rc_; } while (0)
+
 extern "C" const char* ouro_last_error(void) { return g_err.c_str(); }
 namespace ouro {
 int set_error(int code, const char* msg) { g_err = msg ? msg : ""; return code; }
@@ -180,6 +182,8 @@ struct ouro_model : BwdCtx {
   bool padded;
   int pd, pdh, phd, pF;           // stored d_model, d_head, n_head * d_head, d_ff
   std::vector<std::vector<TensorMap>> tmap;   // per group 0..K
+  std::vector<std::vector<RemapEntry>> remaps;   // padded: the same for the device (launch_remap)
+  std::vector<RemapEntry*> remaps_dev;
   std::vector<int64_t> pcount;    // stored elements per group
   char* arena;
   size_t bytes;
@@ -511,6 +515,16 @@ static size_t lay_out(ouro_model& m, char* base) {
   m.vec_stride = (vtot + 63) / 64 * 64;
   m.vec_copies = (float*)P(8 * m.vec_stride * 4);
   for (int k = 1; k <= K; ++k) m.segs_dev[k] = (SumSegment*)P(m.segs[k].size() * sizeof(SumSegment));
+  m.remaps.assign(K + 1, {});
+  m.remaps_dev.assign(K + 1, nullptr);
+  for (int k = 0; m.padded && k <= K; ++k) {
+    int tiles = 0;
+    for (const TensorMap& t : m.tmap[k]) {
+      m.remaps[k].push_back({(unsigned long long)t.loff, (unsigned long long)t.poff, t.rows, t.cols, t.pcols, t.row_heads, t.col_heads, tiles});
+      tiles += (t.rows + REMAP_ROWS - 1) / REMAP_ROWS;
+    }
+    m.remaps_dev[k] = (RemapEntry*)P(m.remaps[k].size() * sizeof(RemapEntry));
+  }
   return bp.off;
 }
 
@@ -537,7 +551,7 @@ static void host_sinusoid(std::vector<float>& out, int rows, int d, int ld) {
 }
 
 // Copies a parameter group between the caller's dense blob and the stored layout (host memory
-// both; the stored blob is zero-filled by the caller before to_stored).
+// both, see remap_on_device; the stored blob is zero-filled by the caller before to_stored).
 static void remap_group(const ouro_model* m, int group, float* stored, float* blob, bool to_stored);
 
 extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t bytes, void* hip_stream,
@@ -608,6 +622,9 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
   for (int k = 1; k <= K && e == hipSuccess; ++k)
     if (!m->segs[k].empty())
       e = hipMemcpyAsync(m->segs_dev[k], m->segs[k].data(), m->segs[k].size() * sizeof(SumSegment), hipMemcpyHostToDevice, m->stream);
+  for (int k = 0; k <= K && e == hipSuccess; ++k)
+    if (!m->remaps[k].empty())
+      e = hipMemcpyAsync(m->remaps_dev[k], m->remaps[k].data(), m->remaps[k].size() * sizeof(RemapEntry), hipMemcpyHostToDevice, m->stream);
   if (e != hipSuccess) { ouro_destroy_model(m); return fail(OURO_E_HIP, "table upload: %s", hipGetErrorString(e)); }
   std::vector<float> tab;
   if (!cfg->rel_pos) {
@@ -669,21 +686,29 @@ static int refresh_transposed(ouro_model* m, int group, hipStream_t st) {
   return OURO_OK;
 }
 
+// Padded models, device memory both: the caller's dense blob <-> the stored layout, on the model's stream.
+static int remap_on_device(ouro_model* m, int group, float* blob, bool to_stored) {
+  const std::vector<RemapEntry>& r = m->remaps[group];
+  const int tiles = r.back().tile0 + (r.back().rows + REMAP_ROWS - 1) / REMAP_ROWS;
+  HIPCHK(launch_remap(m->stream, m->master[group], blob, m->remaps_dev[group], (int)r.size(), tiles, m->cfg.d_head, m->pdh, to_stored));
+  return OURO_OK;
+}
+
 extern "C" int ouro_set_params(ouro_model* m, int group, const float* src, int64_t n, int src_is_device) {
   if (!m || !src || group < 0 || group > m->cfg.n_module) return fail(OURO_E_ARG, "set_params: bad argument");
   if (n != m->count[group]) return fail(OURO_E_ARG, "set_params: group %d has %lld elements, got %lld", group, (long long)m->count[group], (long long)n);
   if (m->padded) {
-    std::vector<float> blob, stored((size_t)m->pcount[group], 0.f);
-    const float* hsrc = src;
+    std::vector<float> stored;
     if (src_is_device) {
-      blob.resize((size_t)n);
-      HIPCHK(hipMemcpyAsync(blob.data(), src, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
-      HIPCHK(hipStreamSynchronize(m->stream));
-      hsrc = blob.data();
+      // padding included: it is zero from the arena's clear on, except in a state that was saved with other values there
+      HIPCHK(launch_fill_zero(m->stream, m->master[group], (size_t)m->pcount[group] * 4));
+      RUN(remap_on_device(m, group, const_cast<float*>(src), true));
+    } else {
+      stored.assign((size_t)m->pcount[group], 0.f);
+      remap_group(m, group, stored.data(), const_cast<float*>(src), true);
+      HIPCHK(hipMemcpyAsync(m->master[group], stored.data(), stored.size() * 4, hipMemcpyHostToDevice, m->stream));
     }
-    remap_group(m, group, stored.data(), const_cast<float*>(hsrc), true);
-    HIPCHK(hipMemcpyAsync(m->master[group], stored.data(), stored.size() * 4, hipMemcpyHostToDevice, m->stream));
-    HIPCHK(launch_convert(m->stream, 1, m->shadow[group], m->master[group], stored.size()));
+    HIPCHK(launch_convert(m->stream, 1, m->shadow[group], m->master[group], (size_t)m->pcount[group]));
     if (int rc = refresh_transposed(m, group, m->stream)) return rc;
     HIPCHK(hipStreamSynchronize(m->stream));
     return OURO_OK;
@@ -699,14 +724,15 @@ extern "C" int ouro_get_params(ouro_model* m, int group, float* dst, int64_t n, 
   if (!m || !dst || group < 0 || group > m->cfg.n_module) return fail(OURO_E_ARG, "get_params: bad argument");
   if (n != m->count[group]) return fail(OURO_E_ARG, "get_params: wrong element count");
   if (m->padded) {
-    std::vector<float> stored((size_t)m->pcount[group]), blob;
+    if (dst_is_device) {
+      RUN(remap_on_device(m, group, dst, false));
+      HIPCHK(hipStreamSynchronize(m->stream));
+      return OURO_OK;
+    }
+    std::vector<float> stored((size_t)m->pcount[group]);
     HIPCHK(hipMemcpyAsync(stored.data(), m->master[group], stored.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIPCHK(hipStreamSynchronize(m->stream));
-    if (!dst_is_device) { remap_group(m, group, stored.data(), dst, false); return OURO_OK; }
-    blob.resize((size_t)n);
-    remap_group(m, group, stored.data(), blob.data(), false);
-    HIPCHK(hipMemcpyAsync(dst, blob.data(), (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
-    HIPCHK(hipStreamSynchronize(m->stream));
+    remap_group(m, group, stored.data(), dst, false);
     return OURO_OK;
   }
   HIPCHK(hipMemcpyAsync(dst, m->master[group], (size_t)n * 4, dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, m->stream));
@@ -799,7 +825,6 @@ static GemmDesc gd(const void* A, int lda, int tA, const void* B, int ldb, int t
   g.transA = tA; g.transB = tB; g.alpha = 1.f;
   return g;
 }
-#define RUN(expr) do { int rc_ = (expr); if (rc_) return rc_; } while (0)
 
 // ------------------------------------------------------------------------------ forward
 // Dropout descriptor of a place (0: embedding sum; 2l+1 / 2l+2: attention-projection / feed-forward

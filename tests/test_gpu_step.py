@@ -1,6 +1,7 @@
 """End-to-end parity of the HIP training iteration against the CPU oracle, through the
 C boundary: losses, every gradient store, updated weights, segment memories, and the
 bit-exact staleness bookkeeping (Eq. 8-9)."""
+import ctypes as C
 import json
 import os
 
@@ -812,3 +813,29 @@ def test_full_size_distinct_streams_forward_rows(name, rows):
                             np.concatenate([orc.mems[l], fw["inputs"][l]], axis=1)[:, -c["mem_len"]:].copy() for l in range(L)]
     # Zipf streams at the initial weights: per-stream losses lie close together
     assert abs(np.mean(losses) - np.mean(row_losses)) < 0.05 * np.mean(row_losses)
+
+
+@pytest.mark.parametrize("rel,mem,d,heads,dh,F,vocab", [(0, 0, 82, 2, 41, 100, 203), (1, 5, 82, 2, 41, 100, 73),
+                                                       (1, 0, 96, 3, 32, 200, 17), (0, 0, 64, 1, 64, 68, 1000)])
+def test_padded_params_on_device(rel, mem, d, heads, dh, F, vocab):
+    """Zero-padded storage: device destinations and sources give bit for bit what the host ones give (head axes along rows
+    and along columns, single-row tensors, row counts off the kernel's tile), and setting clears the padding again."""
+    import paper_1909_06695_amd as P
+    c = dict(n_layer=3, d_model=d, n_head=heads, d_head=dh, d_ff=F, vocab=vocab, seq_len=9, mem_len=mem, batch=2, n_module=2,
+             rel_pos=rel, dtype=1, optimizer=1)
+    a, b = P.create_model(device="cuda:0", **c), P.create_model(device="cuda:0", **c)
+    rng = np.random.default_rng(5)
+    for g in range(3):
+        blob = rng.standard_normal(a.param_count(g)).astype(np.float32)
+        a.set_params(g, blob)
+        dblob = torch.from_numpy(blob).cuda()
+        assert b.L.ouro_set_params(b.h, g, C.c_void_p(dblob.data_ptr()), dblob.numel(), 1) == 0
+        for m in (a, b):
+            assert np.array_equal(m.get_params(g), blob)
+            out = torch.full((blob.size + 8,), -3.0, device="cuda")
+            assert m.L.ouro_get_params(m.h, g, C.c_void_p(out.data_ptr()), blob.size, 1) == 0
+            assert np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == -3.0).all())
+    tok = torch.from_numpy(rng.integers(0, vocab, (2, 9)).astype(np.int32)).cuda()
+    losses = [m.eval_step(tok, tok) for m in (a, b)]
+    assert losses[0] == losses[1]
+    a.close(), b.close()
