@@ -266,7 +266,13 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       // one per CU with a long contraction (dV_o: 670 -> 592 us), or whole rounds of them: two rounds of a contraction over
       // 1024 with the GELU epilogues take 94 us against 101 us of four rounds of 128x128 tiles, one and a half rounds
       // (8192 x 3072 x 1024) 69 us against 57 us of three
-      if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
+      // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
+      // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
+      // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
+      // over 256 5.2 -> 4.5; beyond one round 768 x 4096 over 1024 16.7 -> 20.1, 4800 x 640 over 448 9.9 -> 10.4.
+      const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * by * bz * grids;
+      if (!g.accumulate && t64 <= 512) cfg = GEMM_TILE_64x64;
+      else if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
       else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
       else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * by * bz * grids <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
       else cfg = GEMM_TILE_128x128;
@@ -328,8 +334,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       }
     }
     if (!direct_ok) cfg = GEMM_TILE_STAGED128;
-    if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_256x256) return hipErrorInvalidValue;
-    const int BM = cfg == GEMM_TILE_256x256 ? 256 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : BM;
+    if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_64x64) return hipErrorInvalidValue;
+    const int BM = cfg == GEMM_TILE_256x256 ? 256 : cfg == GEMM_TILE_64x64 ? 64 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : BM;
     int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * by * bz * grids;
     if (g.accumulate && !modelled && tiles < 384 && g.K >= 512) {
       splits = (512 + tiles - 1) / tiles;
