@@ -97,6 +97,9 @@ struct GemmDesc {
   // the bf16 rounding of the LayerNorm's stored output (the contraction operand) off the residual path.
   const float* res32; int ldr32;
   const float* ln_mean; const float* ln_rstd; const float* ln_g; const float* ln_b;
+  // not null: colsum[n] += sum over m of what is stored in C, in the first of 8 copies colsum_stride floats apart that the
+  // workgroup's XCD owns (single products without accumulate; copies as in launch_layernorm_bwd)
+  float* colsum; size_t colsum_stride;
   int epilogue;
   void* Z; int ldz;      // EPI_GELU: written (type T); EPI_GELUGRAD: read (type T)
   float alpha;           // scales acc before the epilogue
@@ -183,9 +186,14 @@ hipError_t launch_layernorm_fwd(hipStream_t s, int dtype, const void* x, const f
 // blocks add to the same few addresses, and adds from different XCDs move the line from L2 to L2;
 // the vector kernels therefore add into the copy of the XCD the block runs on (blocks are dealt to
 // the 8 XCDs in launch order), and the caller sums the copies (launch_sum_segments).
+// branch (optional): what else becomes of dx on its way into the branch whose output the normalised sum contains.  With
+// drop.on, dxm = dx (as stored) times the mask; sum != nullptr: sum[c] += sum_r of the branch's gradient (dxm, without
+// dropout dx) as stored, in copies as dg and db.
+struct LnBwdBranch { float* sum; void* dxm; DropDesc drop; };
 hipError_t launch_layernorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const float* g,
                                 const float* mean, const float* rstd, void* dx, float* dg, float* db,
-                                int rows, int d, int dn = 0, bool fuse_params = false, size_t copy_stride = 0);
+                                int rows, int d, int dn = 0, bool fuse_params = false, size_t copy_stride = 0,
+                                const LnBwdBranch* branch = nullptr);
 // dg[c] += sum_r dy*xhat, db[c] += sum_r dy alone (any stream that sees dy, x and the stats)
 hipError_t launch_layernorm_bwd_params(hipStream_t s, int dtype, const void* dy, const void* x, const float* mean,
                                        const float* rstd, float* dg, float* db, int rows, int d);

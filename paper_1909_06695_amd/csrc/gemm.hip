@@ -213,6 +213,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   p.epilogue = g.epilogue; p.Z = g.Z; p.ldz = g.ldz; p.alpha = g.alpha;
   p.drop = g.drop;
   p.kchunk = g.K; p.tilesN = 0; p.vec_epi = 0;
+  p.colsum = g.colsum; p.colsum_stride = g.colsum_stride;
+  if (g.colsum && (g.accumulate || g.by > 1 || g.bz > 1 || g.C2)) return hipErrorInvalidValue;
   if (g.accumulate && (!g.out_fp32 || g.bias || g.residual || g.epilogue != EPI_NONE)) return hipErrorInvalidValue;
   // a batch of products: over the grid's y and z in the direct-to-LDS kernels, else one launch each
   const int by = std::max(1, g.by), bz = std::max(1, g.bz);
@@ -286,7 +288,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     // 50257-word vocabulary: 788 tiles, 3.08 rounds): those rows go out as a second, split-K
     // launch that adds into the zeroed rows of the fp32 result.
     if (cfg == GEMM_TILE_256x256 && force_generic == 0 && direct_ok && g.out_fp32 && !g.accumulate && !g.bias && !g.residual &&
-        !g.res32 && g.epilogue == EPI_NONE && !g.drop.on && by * bz * grids == 1 && g.ldc == g.N && g.K >= 2048) {
+        !g.res32 && !g.colsum && g.epilogue == EPI_NONE && !g.drop.on && by * bz * grids == 1 && g.ldc == g.N && g.K >= 2048) {
       const int tn = (g.N + 255) / 256;
       if (tn <= 256 && 256 % tn == 0) {
         const int rows_round = 256 / tn * 256;
@@ -364,7 +366,9 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   } while (0)
   if (dtype == 1) OURO_PLAIN(bf16_t); else OURO_PLAIN(float);
 #undef OURO_PLAIN
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && g.colsum) e = launch_colsum(s, g.out_fp32 ? 0 : dtype, g.C, g.ldc, g.colsum, g.M, g.N, g.colsum_stride);
+  return e;
 }
 
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, bool* grouped) {
@@ -377,7 +381,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     const GemmDesc& d = g[i];
     const size_t bA = 2 * (size_t)d.K * d.lda, bB = 2 * (size_t)d.K * d.ldb;
     const bool ok = dtype == 1 && d.transA == 1 && d.transB == 0 && d.accumulate && d.out_fp32 && !d.bias && !d.residual &&
-                    !d.res32 && d.epilogue == EPI_NONE && !d.drop.on && d.by <= 1 && d.bz <= 1 && !d.C2 && d.M > 0 && d.N > 0 &&
+                    !d.res32 && !d.colsum && d.epilogue == EPI_NONE && !d.drop.on && d.by <= 1 && d.bz <= 1 && !d.C2 && d.M > 0 && d.N > 0 &&
                     gemm_uses_mfma(dtype, d) && bA < (1ull << 31) && bB < (1ull << 31);
     if (ok) { in[ni++] = d; continue; }
     hipError_t e = launch_gemm(s, dtype, d, 0);

@@ -24,6 +24,7 @@ struct GemmParams {
   const void* A2; const void* B2; void* C2; float alpha2;
   long long bAy, bAz, bBy, bBz, bCy, bCz;   // byte strides of a batch of products over blockIdx.y, blockIdx.z (direct-to-LDS kernels)
   DropDesc drop;
+  float* colsum; size_t colsum_stride;      // see GemmDesc
 };
 
 // Which output tile and K range a workgroup takes.  Workgroups go to the 8 XCDs round-robin, and
@@ -67,12 +68,13 @@ __device__ __forceinline__ void batch_offsets(GemmParams& p) {
   if (p.res32) p.res32 = reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.res32) + blockIdx.y * p.bCy + z * p.bCz);
 }
 
+// Returns the value stored.
 template <typename T>
-__device__ __forceinline__ void epilogue_store(const GemmParams& p, int m, int n, float acc) {
+__device__ __forceinline__ float epilogue_store(const GemmParams& p, int m, int n, float acc) {
   float v = acc * p.alpha;
   if (p.accumulate) {
     unsafeAtomicAdd(reinterpret_cast<float*>(p.C) + (size_t)m * p.ldc + n, v);
-    return;
+    return v;
   }
   if (p.bias) v += p.bias[n];
   if (p.drop.on) v *= drop_factor(p.drop, (uint64_t)m * p.drop.ld + n);
@@ -88,12 +90,19 @@ __device__ __forceinline__ void epilogue_store(const GemmParams& p, int m, int n
     if (p.ln_mean) r = (r - p.ln_mean[m]) * p.ln_rstd[m] * p.ln_g[n] + p.ln_b[n];
     v += r;
   }
-  if (p.out_fp32) reinterpret_cast<float*>(p.C)[(size_t)m * p.ldc + n] = v;
-  else reinterpret_cast<T*>(p.C)[(size_t)m * p.ldc + n] = from_f32<T>(v);
+  if (p.out_fp32) {
+    reinterpret_cast<float*>(p.C)[(size_t)m * p.ldc + n] = v;
+    return v;
+  }
+  const T o = from_f32<T>(v);
+  reinterpret_cast<T*>(p.C)[(size_t)m * p.ldc + n] = o;
+  return to_f32(o);
 }
+// The workgroup's copy of the column sums.
+__device__ __forceinline__ float* epilogue_colsum(const GemmParams& p) { return p.colsum + (blockIdx.x & 7) * p.colsum_stride; }
 
 
-// The same for R rows of one column: what depends on the column is read once, and the reads of a stage go out together.
+// The same for R rows of one column (lanes l and l + 32 of a wave own the same column): what depends on the column is read once, and the reads of a stage go out together.
 template <typename T, int R>
 __device__ __forceinline__ void epilogue_column(const GemmParams& p, const int (&m)[R], int n, float (&v)[R]) {
   if (n >= p.N) return;
@@ -157,20 +166,24 @@ __device__ __forceinline__ void epilogue_column(const GemmParams& p, const int (
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] += x[r];
   }
+  float sum = 0.f;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     if (!on[r]) continue;
-    if (p.out_fp32) reinterpret_cast<float*>(p.C)[(size_t)m[r] * p.ldc + n] = v[r];
-    else reinterpret_cast<T*>(p.C)[(size_t)m[r] * p.ldc + n] = from_f32<T>(v[r]);
+    if (p.out_fp32) { reinterpret_cast<float*>(p.C)[(size_t)m[r] * p.ldc + n] = v[r]; sum += v[r]; }
+    else { const T o = from_f32<T>(v[r]); reinterpret_cast<T*>(p.C)[(size_t)m[r] * p.ldc + n] = o; sum += to_f32(o); }
+  }
+  if (p.colsum) {
+    sum += __shfl_xor(sum, 32, 64);
+    if ((threadIdx.x & 63) < 32) unsafeAtomicAdd(epilogue_colsum(p) + n, sum);
   }
 }
 
 // Eight consecutive columns n..n+7 of row m (bf16 operands), all in range and 16-byte
-// addressable: the same epilogue as epilogue_store with 16-byte accesses.
-__device__ __forceinline__ void epilogue_store8(const GemmParams& p, int m, int n, const float* acc) {
-  float v[8];
+// addressable: the same epilogue as epilogue_store with 16-byte accesses.  v: the accumulator's values, on return those stored.
+__device__ __forceinline__ void epilogue_store8(const GemmParams& p, int m, int n, float (&v)[8]) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = acc[e] * p.alpha;
+  for (int e = 0; e < 8; ++e) v[e] *= p.alpha;
   if (p.bias) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += p.bias[n + e];
@@ -216,7 +229,7 @@ __device__ __forceinline__ void epilogue_store8(const GemmParams& p, int m, int 
   } else {
     union { bf16_t h[8]; uint4 u; } o;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o.h[e] = (bf16_t)v[e];
+    for (int e = 0; e < 8; ++e) { o.h[e] = (bf16_t)v[e]; v[e] = (float)o.h[e]; }
     *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.C) + (size_t)m * p.ldc + n) = o.u;
   }
 }
@@ -273,6 +286,11 @@ __device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)
   float* stage = reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<TN>();
   const int h32 = lane >> 5, l32 = lane & 31;
   const int srow = lane >> 2, scol = (lane & 3) * 8;
+  float cs[TN][8];                                 // the lane's share of the column sums
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[j][e] = 0.f;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -281,10 +299,11 @@ __device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)
       for (int r = 0; r < 16; ++r)
         stage[j * (32 * 36) + (8 * (r >> 2) + 4 * h32 + (r & 3)) * 36 + l32] = acc[i][j][r];
     __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
 #pragma unroll 1
-    for (int t = 0; t < 2 * TN; ++t) {
-      const int j = t >> 1;
-      const int row = (t & 1) * 16 + srow;
+    for (int t = 0; t < 2; ++t) {
+      const int row = t * 16 + srow;
       const float* src = stage + j * (32 * 36) + row * 36 + scol;
       const int m = m_w + i * 32 + row;
       const int n = n_w + j * CS + scol;
@@ -292,16 +311,35 @@ __device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)
         if (p.vec_epi && n + 8 <= p.N) {
           float4 lo = *reinterpret_cast<const float4*>(src);
           float4 hi = *reinterpret_cast<const float4*>(src + 4);
-          const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+          float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
           epilogue_store8(p, m, n, v);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) cs[j][e] += v[e];
         } else {
 #pragma unroll 1
           for (int e = 0; e < 8; ++e)
-            if (n + e < p.N) epilogue_store<bf16_t>(p, m, n + e, src[e]);
+            if (n + e < p.N) {
+              const float v = epilogue_store<bf16_t>(p, m, n + e, src[e]);
+              if (p.colsum) unsafeAtomicAdd(epilogue_colsum(p) + n + e, v);
+            }
         }
       }
     }
     __builtin_amdgcn_wave_barrier();
+  }
+  if (p.colsum) {
+    // lanes of equal lane % 4 hold the same columns
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n_w + j * CS + scol;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float t = cs[j][e];
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+        if (lane < 4 && p.vec_epi && n + 8 <= p.N) unsafeAtomicAdd(epilogue_colsum(p) + n + e, t);
+      }
+    }
   }
 }
 

@@ -146,11 +146,11 @@ struct Bump {
 // backward passes of an iteration are independent and ouro_step runs them side by side.
 struct BwdCtx {
   hipStream_t stream;          // the error-gradient chain (set 0: the caller's stream, which also carries the forward pass)
-  // Weight-gradient GEMMs and bias column sums only feed the gradient ring, so they run on
+  // Weight-gradient GEMMs only feed the gradient ring, so they run on
   // a second stream beside the error-gradient chain (both default priority); events order
   // them against the producers of their operands and against the reuse of those buffers.
   hipStream_t side;
-  hipEvent_t ev_ready[4];      // ds2 / dz / ds1 / dqkv of the current layer written (main)
+  hipEvent_t ev_ready;         // the operands of the next launch on side are written (main)
   hipEvent_t ev_side_done[2];  // side work that reads buffer set p finished
   bool side_busy[2];
   hipEvent_t ev_join;
@@ -589,11 +589,11 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
   for (int i = 0; i < OURO_TIMING_KINDS; ++i) { m->ev_used[i] = 0; m->timed_work[i] = 0; m->timed_launches[i] = 0; }
   m->side = nullptr; m->use_side = false; m->ev_join = nullptr;
   m->aux = nullptr; m->ev_bwd_done = m->ev_upd_done = nullptr; m->upd_pending = false;
-  for (int i = 0; i < 4; ++i) m->ev_ready[i] = nullptr;
+  m->ev_ready = nullptr;
   for (int i = 0; i < 2; ++i) { m->ev_side_done[i] = nullptr; m->side_busy[i] = false; }
   {
     hipError_t es_ = hipStreamCreateWithFlags(&m->side, hipStreamNonBlocking);
-    for (int i = 0; i < 4 && es_ == hipSuccess; ++i) es_ = hipEventCreateWithFlags(&m->ev_ready[i], hipEventDisableTiming);
+    if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&m->ev_ready, hipEventDisableTiming);
     for (int i = 0; i < 2 && es_ == hipSuccess; ++i) es_ = hipEventCreateWithFlags(&m->ev_side_done[i], hipEventDisableTiming);
     if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&m->ev_join, hipEventDisableTiming);
     if (es_ == hipSuccess) es_ = hipStreamCreateWithFlags(&m->aux, hipStreamNonBlocking);
@@ -605,7 +605,7 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
       BwdCtx& x = m->ctxs[i];
       es_ = hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking);
       if (es_ == hipSuccess) es_ = hipStreamCreateWithFlags(&x.side, hipStreamNonBlocking);
-      for (int j = 0; j < 4 && es_ == hipSuccess; ++j) es_ = hipEventCreateWithFlags(&x.ev_ready[j], hipEventDisableTiming);
+      if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&x.ev_ready, hipEventDisableTiming);
       for (int j = 0; j < 2 && es_ == hipSuccess; ++j) es_ = hipEventCreateWithFlags(&x.ev_side_done[j], hipEventDisableTiming);
       if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&x.ev_join, hipEventDisableTiming);
       if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&x.ev_done, hipEventDisableTiming);
@@ -656,13 +656,13 @@ extern "C" int ouro_destroy_model(ouro_model* m) {
     BwdCtx& x = m->ctxs[i];
     if (x.stream) { (void)hipStreamSynchronize(x.stream); (void)hipStreamDestroy(x.stream); }
     if (x.side) { (void)hipStreamSynchronize(x.side); (void)hipStreamDestroy(x.side); }
-    for (hipEvent_t e : {x.ev_ready[0], x.ev_ready[1], x.ev_ready[2], x.ev_ready[3], x.ev_side_done[0], x.ev_side_done[1], x.ev_join, x.ev_done})
+    for (hipEvent_t e : {x.ev_ready, x.ev_side_done[0], x.ev_side_done[1], x.ev_join, x.ev_done})
       if (e) (void)hipEventDestroy(e);
   }
   if (m->ev_fwd) (void)hipEventDestroy(m->ev_fwd);
   (void)hipStreamSynchronize(m->stream);
   if (m->side) { (void)hipStreamSynchronize(m->side); (void)hipStreamDestroy(m->side); }
-  for (int i = 0; i < 4; ++i) if (m->ev_ready[i]) (void)hipEventDestroy(m->ev_ready[i]);
+  if (m->ev_ready) (void)hipEventDestroy(m->ev_ready);
   for (int i = 0; i < 2; ++i) if (m->ev_side_done[i]) (void)hipEventDestroy(m->ev_side_done[i]);
   if (m->ev_join) (void)hipEventDestroy(m->ev_join);
   if (m->aux) { (void)hipStreamSynchronize(m->aux); (void)hipStreamDestroy(m->aux); }
@@ -1002,18 +1002,17 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   hipStream_t st = m->stream;
   const int ps = l & 1;                               // buffer set of this layer
   const bool side = m->use_side;
-  hipStream_t sw = side ? m->side : st;               // stream of the weight-gradient work
+  hipStream_t sw = side ? m->side : st;               // stream of the weight gradients
   char* ds2 = m->ds2[ps]; char* dz = m->dz[ps]; char* ds1 = m->ds1[ps]; char* dqkv = m->dqkv[ps];
   // what flows into the two dropped branches: the LayerNorm input gradients times the masks
   char* ds2m = m->ds2m[ps]; char* ds1m = m->ds1m[ps];
-  const bool dropping = c.dropout > 0;
   char* dy = m->dy[ps];
   // the side stream may still be reading this buffer set (layer l+2 of this module)
   if (side && m->side_busy[ps]) { HIPCHK(hipStreamWaitEvent(st, m->ev_side_done[ps], 0)); m->side_busy[ps] = false; }
-  auto ready = [&](int i) -> int {                    // operand i written on main; side may start
+  auto ready = [&]() -> int {                         // the operands are written on main; side may start
     if (!side) return OURO_OK;
-    HIPCHK(hipEventRecord(m->ev_ready[i], st));
-    HIPCHK(hipStreamWaitEvent(sw, m->ev_ready[i], 0));
+    HIPCHK(hipEventRecord(m->ev_ready, st));
+    HIPCHK(hipStreamWaitEvent(sw, m->ev_ready, 0));
     return OURO_OK;
   };
   // the gradients of this layer's vectors gather in the per-XCD copies; module_backward adds them to gslot
@@ -1028,31 +1027,29 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   // dh, dy (gradients of the normalised rows) and the saved sums s1, s2 are fp32 in every mode
   const int lnk = c.dtype == 1 ? 2 : 0;
   const double ln_bwd_bytes = (double)N * dn * (8 + es) + 8.0 * N;      // fp32 gradient and input rows read, one row written, statistics
+  // ... and so do the masked copy that flows into the dropped branch and the sum of its rows, the gradient of b_2
   RUN(timed_launch(m, OURO_TIMING_LAYERNORM, ln_bwd_bytes, st, [&] {
+    LnBwdBranch br{vc + 2 * d, ds2m, drop_at(m, 2 * l + 2)};
     return launch_layernorm_bwd(st, lnk, dh, b.s2, m->wF(l, o.ln2_g), b.mean2, b.rstd2, ds2,
-                                vc, vc + d, N, d, dn, true, m->vec_stride); }));
-  if (dropping) HIPCHK(launch_dropout_apply(st, c.dtype, ds2, ds2m, N, d, d, drop_at(m, 2 * l + 2)));
-  RUN(ready(0));
+                                vc, vc + d, N, d, dn, true, m->vec_stride, &br); }));
   // FFN2
   {
     GemmDesc g = gd(b.uact, F, 1, ds2m, d, 0, gslot + o.W_2, d, F, d, N);
     g.out_fp32 = 1; g.accumulate = ACC_STORE;
     wg[nwg++] = g;
   }
-  HIPCHK(launch_colsum(sw, c.dtype, ds2m, d, vc + 2 * d, N, d, m->vec_stride));
   {
     GemmDesc g = gd(ds2m, d, 0, m->wT(l, o.W_2), d, 1, dz, F, N, F, d);
     g.epilogue = EPI_GELUGRAD; g.Z = b.z; g.ldz = F;
+    g.colsum = vc + 5 * d; g.colsum_stride = m->vec_stride;      // gradient of b_1
     RUN(run_gemm(m, g));
   }
-  RUN(ready(1));
   // FFN1
   {
     GemmDesc g = gd(b.y, d, 1, dz, F, 0, gslot + o.W_1, F, d, F, N);
     g.out_fp32 = 1; g.accumulate = ACC_STORE;
     wg[nwg++] = g;
   }
-  HIPCHK(launch_colsum(sw, c.dtype, dz, F, vc + 5 * d, N, F, m->vec_stride));
   {
     GemmDesc g = gd(dz, F, 0, m->wT(l, o.W_1), F, 1, dy, d, N, d, F);
     g.residual = ds2; g.ldr = d; g.out_fp32 = 1;
@@ -1060,10 +1057,9 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
   }
   // LN1
   RUN(timed_launch(m, OURO_TIMING_LAYERNORM, ln_bwd_bytes, st, [&] {
+    LnBwdBranch br{nullptr, ds1m, drop_at(m, 2 * l + 1)};
     return launch_layernorm_bwd(st, lnk, dy, b.s1, m->wF(l, o.ln1_g), b.mean1, b.rstd1, ds1,
-                                vc + 3 * d, vc + 4 * d, N, d, dn, true, m->vec_stride); }));
-  if (dropping) HIPCHK(launch_dropout_apply(st, c.dtype, ds1, ds1m, N, d, d, drop_at(m, 2 * l + 1)));
-  RUN(ready(2));
+                                vc + 3 * d, vc + 4 * d, N, d, dn, true, m->vec_stride, &br); }));
   // output projection
   {
     GemmDesc g = gd(b.a, hd, 1, ds1m, d, 0, gslot + o.W_o, d, hd, d, N);
@@ -1085,7 +1081,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
     a.dk = dqkv + (size_t)hd * es; a.lddk = 3 * hd;
     a.dv = dqkv + (size_t)2 * hd * es; a.lddv = 3 * hd;
     RUN(timed_launch(m, OURO_TIMING_ATTENTION, 2.0 * attn_fwd_flops(m, Mv), st, [&] { return launch_attn_bwd(st, c.dtype, a, 0); }));
-    RUN(ready(3));
+    RUN(ready());
     {
       GemmDesc g = gd(b.x, d, 1, dqkv, 3 * hd, 0, gslot + o.W_qkv, 3 * hd, d, 3 * hd, N);
       g.out_fp32 = 1; g.accumulate = ACC_STORE;
@@ -1119,7 +1115,7 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
     RUN(timed_launch(m, OURO_TIMING_ATTENTION, 2.0 * attn_fwd_flops(m, Mv), st, [&] { return launch_attn_bwd(st, c.dtype, a, 0); }));
     const void* drp = drf;
     if (c.dtype == 1) { HIPCHK(launch_convert(st, 1, m->dr_t[ps], drf, (size_t)S * hd)); drp = m->dr_t[ps]; }
-    RUN(ready(3));
+    RUN(ready());
     // weight gradients: dW_r = R^T dr, dW_q = x^T dq, dW_kv = [mem ; x]^T dkv
     {
       GemmDesc g = gd(m->rtab, d, 1, drp, hd, 0, gslot + o.W_r, hd, d, hd, S);
@@ -1220,8 +1216,8 @@ static int module_backward_impl(ouro_model* m, int k, bool defer_join) {
     GemmDesc g = gd(m->G, m->ldv, 1, m->hL, d, 0, dvo, d, Vx, d, N);
     g.out_fp32 = 1;
     if (m->use_side) {        // independent of the error-gradient chain: beside dh_L = G V
-      HIPCHK(hipEventRecord(m->ev_ready[0], m->stream));
-      HIPCHK(hipStreamWaitEvent(m->side, m->ev_ready[0], 0));
+      HIPCHK(hipEventRecord(m->ev_ready, m->stream));
+      HIPCHK(hipStreamWaitEvent(m->side, m->ev_ready, 0));
       RUN(run_gemm_on(m, g, m->side));
     } else {
       RUN(run_gemm(m, g));

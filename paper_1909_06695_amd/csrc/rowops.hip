@@ -212,17 +212,24 @@ __global__ __launch_bounds__(256) void colsum_kernel(const T* __restrict__ x, in
 // Vector path of the LayerNorm backward: one wavefront per row, rows strided over the grid;
 // the row's packs stay in registers, dg / db partial sums are kept per lane over all the
 // wave's rows, reduced over the block's four waves through LDS and added atomically once.
-template <typename TI, typename TO, int MAXI, bool PARAMS>
+// SUM: also the sum of the branch's gradient over the rows (see LnBwdBranch).
+template <typename TI, typename TO, int MAXI, bool PARAMS, bool SUM>
 __global__ __launch_bounds__(256) void ln_bwd_fused_kernel(const TI* __restrict__ dy, const TI* __restrict__ x,
                                                            const float* __restrict__ g, const float* __restrict__ mean,
                                                            const float* __restrict__ rstd, TO* __restrict__ dx,
                                                            float* __restrict__ dg, float* __restrict__ db, int rows, int d,
-                                                           int dn, size_t copy_stride) {
+                                                           int dn, size_t copy_stride, LnBwdBranch br) {
   constexpr int N = Group<TI, TO>::N;
   extern __shared__ float red[];                 // [4][d]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nvec = d / N;
-  float gl[MAXI][N], ag[MAXI][N], ab[MAXI][N];
+  float gl[MAXI][N], ag[MAXI][N], ab[MAXI][N], as[SUM ? MAXI : 1][N];
+  if (SUM) {
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i)
+#pragma unroll
+      for (int e = 0; e < N; ++e) as[i][e] = 0.f;
+  }
 #pragma unroll
   for (int i = 0; i < MAXI; ++i) {
     int vi = lane + 64 * i;
@@ -284,6 +291,15 @@ __global__ __launch_bounds__(256) void ln_bwd_fused_kernel(const TI* __restrict_
 #pragma unroll
           for (int e = 0; e < N; ++e) out[e] = vi * N + e < dn ? rs[u] * (t[u][i][e] - s1 - xh[u][i][e] * s2) : 0.f;
           store_n<TO, N>(dx + (size_t)row * d + vi * N, out);
+          if (br.drop.on) {
+#pragma unroll
+            for (int e = 0; e < N; ++e) out[e] = to_f32(from_f32<TO>(out[e])) * drop_factor(br.drop, (uint64_t)row * br.drop.ld + vi * N + e);
+            store_n<TO, N>(reinterpret_cast<TO*>(br.dxm) + (size_t)row * d + vi * N, out);
+          }
+          if (SUM) {
+#pragma unroll
+            for (int e = 0; e < N; ++e) as[i][e] += to_f32(from_f32<TO>(out[e]));
+          }
         }
       }
     }
@@ -293,19 +309,20 @@ __global__ __launch_bounds__(256) void ln_bwd_fused_kernel(const TI* __restrict_
   // one XCD (blocks are dealt to the 8 XCDs in launch order) go to that XCD's own copy
   dg += (blockIdx.x & 7) * copy_stride;
   db += (blockIdx.x & 7) * copy_stride;
+  float* ds = SUM ? br.sum + (blockIdx.x & 7) * copy_stride : nullptr;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < (SUM ? 3 : 2); ++pass) {
 #pragma unroll
     for (int i = 0; i < MAXI; ++i) {
       int vi = lane + 64 * i;
       if (vi < nvec) {
 #pragma unroll
-        for (int e = 0; e < N; ++e) red[wave * d + vi * N + e] = pass ? ab[i][e] : ag[i][e];
+        for (int e = 0; e < N; ++e) red[wave * d + vi * N + e] = pass == 0 ? ag[i][e] : pass == 1 ? ab[i][e] : as[SUM ? i : 0][e];
       }
     }
     __syncthreads();
     for (int c = threadIdx.x; c < d; c += 256)
-      unsafeAtomicAdd((pass ? db : dg) + c, red[c] + red[d + c] + red[2 * d + c] + red[3 * d + c]);
+      unsafeAtomicAdd((pass == 0 ? dg : pass == 1 ? db : ds) + c, red[c] + red[d + c] + red[2 * d + c] + red[3 * d + c]);
     __syncthreads();
   }
 }
@@ -402,18 +419,25 @@ static bool ln_vec_ok(int dtype, const void* dy, const void* x, int d) {
 // from many blocks spreads its adds over them by XCD and the caller sums the copies (0: one copy).
 hipError_t launch_layernorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const float* g,
                                 const float* mean, const float* rstd, void* dx, float* dg, float* db,
-                                int rows, int d, int dn, bool fuse_params, size_t copy_stride) {
+                                int rows, int d, int dn, bool fuse_params, size_t copy_stride, const LnBwdBranch* branch) {
   if (rows <= 0) return hipSuccess;
   if (dn <= 0 || dn > d) dn = d;
   dim3 grid((rows + 3) / 4), block(256);
   bool fused = false;
-  if (ln_vec_ok(dtype, dy, x, d) && ptr16(dx)) {
+  LnBwdBranch br;
+  memset(&br, 0, sizeof br);
+  if (branch) br = *branch;
+  if (ln_vec_ok(dtype, dy, x, d) && ptr16(dx) && (!br.drop.on || ptr16(br.dxm)) && (!br.sum || (fuse_params && dg && db))) {
     const int grp = dtype == 0 ? 4 : 8;
     dim3 gf(std::min((rows + 3) / 4, 384));   // every block ends with 2 d atomic adds: 384 blocks measured best in the step (256, 512: +0.5 %)
     const int npl = (d / grp + 63) / 64;      // groups per lane
     fused = fuse_params && dg && db;
     const size_t smem = fused ? (size_t)4 * d * sizeof(float) : 0;
-#define OURO_LNB2(TI_, TO_, MI_, PAR_) hipLaunchKernelGGL((ln_bwd_fused_kernel<TI_, TO_, MI_, PAR_>), gf, block, smem, s, (const TI_*)dy, (const TI_*)x, g, mean, rstd, (TO_*)dx, dg, db, rows, d, dn, copy_stride)
+#define OURO_LNB2(TI_, TO_, MI_, PAR_) \
+  do { \
+    if (PAR_ && br.sum) hipLaunchKernelGGL((ln_bwd_fused_kernel<TI_, TO_, MI_, PAR_, PAR_>), gf, block, smem, s, (const TI_*)dy, (const TI_*)x, g, mean, rstd, (TO_*)dx, dg, db, rows, d, dn, copy_stride, br); \
+    else hipLaunchKernelGGL((ln_bwd_fused_kernel<TI_, TO_, MI_, PAR_, false>), gf, block, smem, s, (const TI_*)dy, (const TI_*)x, g, mean, rstd, (TO_*)dx, dg, db, rows, d, dn, copy_stride, br); \
+  } while (0)
 #define OURO_LNB(TI_, TO_)                                                                  \
   do {                                                                                      \
     if (fused) { if (npl <= 1) OURO_LNB2(TI_, TO_, 1, true); else if (npl <= 2) OURO_LNB2(TI_, TO_, 2, true); else OURO_LNB2(TI_, TO_, 4, true); } \
@@ -422,6 +446,7 @@ hipError_t launch_layernorm_bwd(hipStream_t s, int dtype, const void* dy, const 
     if (dtype == 1) OURO_LNB(bf16_t, bf16_t);
     else if (dtype == 2) OURO_LNB(float, bf16_t);
     else OURO_LNB(float, float);
+    if (branch) { br.drop.on = 0; br.sum = nullptr; }           // done
 #undef OURO_LNB
 #undef OURO_LNB2
   } else if (dtype == 1) {
@@ -432,6 +457,9 @@ hipError_t launch_layernorm_bwd(hipStream_t s, int dtype, const void* dy, const 
     hipLaunchKernelGGL((ln_bwd_dx_kernel<float, float>), grid, block, 0, s, (const float*)dy, (const float*)x, g, mean, rstd, (float*)dx, rows, d, dn);
   }
   hipError_t e = hipGetLastError();
+  const int dt = dtype == 0 ? 0 : 1;
+  if (e == hipSuccess && br.drop.on) e = launch_dropout_apply(s, dt, dx, br.dxm, rows, d, d, br.drop);
+  if (e == hipSuccess && br.sum) e = launch_colsum(s, dt, br.drop.on ? br.dxm : dx, d, br.sum, rows, d, copy_stride);
   if (e != hipSuccess || !dg || fused) return e;
   return launch_layernorm_bwd_params(s, dtype, dy, x, mean, rstd, dg, db, rows, d);
 }

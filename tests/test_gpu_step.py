@@ -839,3 +839,15 @@ def test_padded_params_on_device(rel, mem, d, heads, dh, F, vocab):
     losses = [m.eval_step(tok, tok) for m in (a, b)]
     assert losses[0] == losses[1]
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("d,heads,dh,F,N,dtype,drop", [
+    (128, 2, 64, 192, 70, 1, 0.0), (576, 9, 64, 128, 33, 1, 0.125), (1088, 17, 64, 1088, 40, 1, 0.125),   # 1, 2 and 4 groups per lane
+    (82, 2, 41, 100, 70, 1, 0.125), (320, 4, 80, 100, 70, 1, 0.0),                                         # padded; unpadded, ragged columns
+    (20, 2, 10, 30, 33, 0, 0.125), (260, 4, 65, 100, 70, 0, 0.0)])
+def test_branch_sums(d, heads, dh, F, N, dtype, drop):
+    """The gradients of b_1 and b_2 leave from the kernels that produce their summands (the GELU-gradient contraction's
+    epilogue, the LayerNorm backward with the dropout masks): every gradient of a one-layer model against the oracle."""
+    c = dict(n_layer=1, d_model=d, n_head=heads, d_head=dh, d_ff=F, vocab=97, seq_len=N, mem_len=0, batch=3, n_module=1,
+             rel_pos=0, dtype=dtype, optimizer=0, dropout=drop)
+    run_both(c, steps=2, lr=0.05, seed=91, std=0.05, perturb=0.05, **({"tol": 2e-2} if dtype else {}))
