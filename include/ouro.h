@@ -240,7 +240,7 @@ int ouro_debug_get_hidden(ouro_model* m, int layer, float* host_dst, int64_t n);
 enum { OURO_TIMING_CONTRACTION = 0, OURO_TIMING_UPDATE = 1, OURO_TIMING_ATTENTION = 2, OURO_TIMING_LAYERNORM = 3,
        OURO_TIMING_CE_ROWS = 4, OURO_TIMING_KINDS = 5 };
 int ouro_debug_timing_enable(ouro_model* m, int on);
-/* Stream overlap switch on = 1 (default): weight-gradient contractions run on a second
+/* Stream overlap switch (default: chosen by the size of a layer's work). on = 1: weight-gradient contractions run on a second
  * stream beside the error-gradient chain and ouro_step enqueues each module's update behind
  * its backward pass on a third. on = 0: every kernel runs on the model's stream in program
  * order, so a HIP-event bracket or a profiler's kernel duration measures that kernel alone.

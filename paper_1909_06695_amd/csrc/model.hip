@@ -554,6 +554,23 @@ static void host_sinusoid(std::vector<float>& out, int rows, int d, int ld) {
 // both, see remap_on_device; the stored blob is zero-filled by the caller before to_stored).
 static void remap_group(const ouro_model* m, int group, float* stored, float* blob, bool to_stored);
 
+// Whether the weight gradients and updates run on streams of their own (ouro_debug_set_overlap overrides).  A launch that
+// waits for another stream starts later, and every layer and module has such waits.  Against that stand a layer's
+// weight-gradient work (GFLOP), which fills the chip while the error-gradient chain leaves it idle, and the updates, which run
+// beside that chain (long where the parameters are many for the tokens).  Time of the steps on one stream over that on several, bf16:
+// 128-wide on 512 tokens (0.2) 0.91, 256-wide on 1024 (1.6) 0.91, on 2048 (3.2) 0.94, 512-wide on 1024 (6.4) 0.97, on 2048 (13)
+// 1.01, on 8192 1.03, 1024-wide on 8192 1.04; fewer tokens than the model is wide: 256 1.03, 512 1.05, 1024 1.04.  fp32:
+// 64 to 256-wide (0.01 to 0.8) 0.72 to 0.91, 512-wide on 1024 (6.4) 1.03.  Relative-position layers, whose attention backward
+// fills the chip by itself: 128 to 512-wide 0.89 to 0.97, 16 x 410-wide and 18 x 1024-wide 0.99.  Under the stored-input
+// schedule the modules' backward passes run side by side as well: 1.03 at 0.2, 1.05 to 1.17 from there on.
+static bool overlap_pays(const ouro_model& m) {
+  const double wgrad = 2.0 * m.N * (4.0 * m.pd * m.phd + 2.0 * m.pd * m.pF);
+  if (m.cfg.schedule == 1 && m.cfg.n_module > 1) return wgrad >= 0.1e9;
+  if (m.cfg.rel_pos) return false;
+  if (m.cfg.dtype == 0) return wgrad >= 3e9;
+  return wgrad >= 8e9 || (m.N <= m.pd && wgrad >= 0.3e9);
+}
+
 extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t bytes, void* hip_stream,
                                  ouro_model** out) {
   if (!out) return fail(OURO_E_ARG, "out is null");
@@ -611,7 +628,7 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
       if (es_ == hipSuccess) es_ = hipEventCreateWithFlags(&x.ev_done, hipEventDisableTiming);
     }
     if (es_ != hipSuccess) { ouro_destroy_model(m); return fail(OURO_E_HIP, "streams / events: %s", hipGetErrorString(es_)); }
-    m->use_side = true;
+    m->use_side = overlap_pays(*m);
   }
   // zero optimizer state, rings, everything else too (one fill over the arena)
   hipError_t e = launch_fill_zero(m->stream, m->arena, need);
