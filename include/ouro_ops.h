@@ -19,10 +19,11 @@ extern "C" {
  *   (no bias / residual / epilogue then).
  * transA == 0: A is [M,K] row-major with leading dimension lda; 1: A is [K,M].
  * transB == 0: B is [K,N]; 1: B is [N,K].  force_generic: 0 = automatic kernel choice, 1 = the
- * plain tiled kernel, 10..15 = one MFMA tile configuration (10 register-staged 128x128,
+ * plain tiled kernel, 10..16 = one MFMA tile configuration (10 register-staged 128x128,
  * 11 direct-to-LDS 128x128, 12 direct-to-LDS 128x64, 13 register-prefetch 128x128 with a
  * four-stage ring, 14 direct-to-LDS 256x256,
- * 15 direct-to-LDS 64x64; 11..15 fall back to 10 unless K % 64 == 0 or both operands have the
+ * 15 direct-to-LDS 64x64,
+ * 16 direct-to-LDS 128x256; 11..16 fall back to 10 unless K % 64 == 0 or both operands have the
  * contraction as their slow dimension, transA == 1 and transB == 0),
  * 20..22 = fp32 matrix-core kernel (20 automatic, 21 64x64 tiles, 22 32x32 tiles), for tests and tuning.
  * These are the layer contractions of Eq. 2 / Eq. 6 (forward, input- and weight-gradient). */

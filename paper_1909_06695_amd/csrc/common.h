@@ -117,10 +117,10 @@ struct GemmDesc {
 };
 // Most products one grouped launch takes (launch_gemm_group).
 constexpr int GEMM_GROUP_MAX = 6;
-// MFMA tile configurations (bf16): register-staged 128x128 (any K multiple of 8), and five
+// MFMA tile configurations (bf16): register-staged 128x128 (any K multiple of 8), and six
 // direct-to-LDS kernels that need operands under 2 GiB and K % 64 == 0 (any K where transA = 1 and transB = 0).
 enum { GEMM_TILE_STAGED128 = 10, GEMM_TILE_128x128 = 11, GEMM_TILE_128x64 = 12, GEMM_TILE_PIPE128 = 13, GEMM_TILE_256x256 = 14,
-       GEMM_TILE_64x64 = 15 };
+       GEMM_TILE_64x64 = 15, GEMM_TILE_128x256 = 16 };
 // dtype 0: fp32 operands, 1: bf16 operands.  force_generic: 0 = automatic choice, 1 = the
 // plain tiled kernel, GEMM_TILE_* = that MFMA configuration where the problem admits MFMA
 // (a direct-to-LDS configuration falls back to the staged one when its conditions fail).

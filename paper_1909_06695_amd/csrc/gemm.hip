@@ -273,7 +273,12 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
       // over 256 5.2 -> 4.5; beyond one round 768 x 4096 over 1024 16.7 -> 20.1, 4800 x 640 over 448 9.9 -> 10.4.
       const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * by * bz * grids;
+      const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * by * bz * grids;
       if (!g.accumulate && t64 <= 512) cfg = GEMM_TILE_64x64;
+      // One round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles, three
+      // stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue: 8192 x 1024 over
+      // 4096 81 -> 68 us, 6144 x 1024 over 4096 69 -> 60, over 2048 34.7 -> 32.5; over 1024 24.1 -> 24.4.
+      else if (!g.accumulate && g.K >= 2048 && t128x256 >= 160 && t128x256 <= 256) cfg = GEMM_TILE_128x256;
       else if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
       else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
       else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * by * bz * grids <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
@@ -336,8 +341,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
       }
     }
     if (!direct_ok) cfg = GEMM_TILE_STAGED128;
-    if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_64x64) return hipErrorInvalidValue;
-    const int BM = cfg == GEMM_TILE_256x256 ? 256 : cfg == GEMM_TILE_64x64 ? 64 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : BM;
+    if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_128x256) return hipErrorInvalidValue;
+    const int BM = cfg == GEMM_TILE_256x256 ? 256 : cfg == GEMM_TILE_64x64 ? 64 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : cfg == GEMM_TILE_128x256 ? 256 : BM;
     int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * by * bz * grids;
     if (g.accumulate && !modelled && tiles < 384 && g.K >= 512) {
       splits = (512 + tiles - 1) / tiles;

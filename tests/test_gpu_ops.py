@@ -50,8 +50,8 @@ TOL = {0: 2e-5, 1: 1e-2}
 
 
 # ------------------------------------------------------------------------------- GEMM
-# force: 0 automatic, 1 plain kernel, 10..15 one MFMA tile configuration each
-@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15)])
+# force: 0 automatic, 1 plain kernel, 10..16 one MFMA tile configuration each
+@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(200, 136, 328), (128, 256, 64), (72, 40, 1000), (384, 520, 96), (136, 264, 512),
                                    (392, 136, 192), (520, 392, 1024)])
@@ -125,7 +125,7 @@ def test_gemm_batched(dtype, tA, tB, M, N, K, by, bz, second, acc):
             assert rel_err(got[g, i], ref) < 2e-6, (g, i)
 
 
-@pytest.mark.parametrize("force", [0, 11, 12, 13, 14])
+@pytest.mark.parametrize("force", [0, 11, 12, 13, 14, 15, 16])
 @pytest.mark.parametrize("M,N,K", [(136, 72, 33), (128, 264, 63), (264, 128, 65), (40, 40, 127), (96, 320, 705), (768, 384, 2331)])
 def test_gemm_ragged_contraction(force, M, N, K):
     """A^T B over a contraction that is no whole number of K-tiles (weight gradients of any token count): the
@@ -177,7 +177,7 @@ def test_gemm_group_large_tiles(shapes):
     test_gemm_group(1, shapes)
 
 
-@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15)])
+@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
 def test_gemm_epilogues_and_strides(dtype, force):
     rng = np.random.default_rng(5)
     M, N, K = 264, 200, 136
@@ -341,7 +341,7 @@ def test_attention_f32_kernel(B, H, T, Mv, dh):
     _attn_case(0, B, H, T, Mv, dh, 0, seed=300 + T + Mv + dh, force=0)
 
 
-@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15)])
+@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
 @pytest.mark.parametrize("M,N,K,ln", [(200, 136, 328, 1), (384, 520, 192, 1), (130, 88, 128, 0), (260, 256, 64, 1)])
 def test_gemm_with_fp32_layernorm_residual(dtype, force, M, N, K, ln):
     """C = A B + bias + R with R the LayerNorm of an fp32 matrix recomputed in the epilogue (ln = 1) or
@@ -450,7 +450,7 @@ def test_dropout_mask_bit_exact(dtype, rows, cols, ld, drop_ld):
     assert 0.58 < (mask != 0).mean() < 0.8 or mask.size < 100
 
 
-@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15)])
+@pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
 @pytest.mark.parametrize("M,N,K", [(200, 136, 328), (384, 520, 192), (130, 82, 128)])
 def test_gemm_with_fused_dropout(dtype, force, M, N, K):
     """C = dropout(A B + bias) + residual in every contraction kernel's epilogue (16-byte and
