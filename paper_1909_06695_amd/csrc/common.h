@@ -235,9 +235,13 @@ hipError_t launch_sum_rows(hipStream_t s, const float* rowloss, int N, float* lo
 hipError_t launch_convert(hipStream_t s, int dtype_dst, void* dst, const float* src, size_t n);      // fp32 -> T
 hipError_t launch_to_f32(hipStream_t s, int dtype_src, float* dst, const void* src, size_t n);       // T -> fp32
 hipError_t launch_fill_zero(hipStream_t s, void* p, size_t bytes);                                   // bytes % 4 == 0
-// strided row copy: dst[b, r, :] = src[b, r0 + r, :]; rows of d elements of type T
+// strided row copy: dst[b, r, :] = src[b, r0 + r, :]; rows of d elements of type T; the same for `layers` buffers that lie
+// dst_lstride / src_lstride elements apart
 hipError_t launch_copy_rows(hipStream_t s, int dtype, void* dst, size_t dst_bstride, size_t dst_off,
-                            const void* src, size_t src_bstride, size_t src_off, int B, int rows, int d);
+                            const void* src, size_t src_bstride, size_t src_off, int B, int rows, int d,
+                            int layers = 1, size_t dst_lstride = 0, size_t src_lstride = 0);
+// dst [B, rows_a + rows_b, d] = per batch element the rows of a [B, rows_a, d], then those of b [B, rows_b, d]
+hipError_t launch_concat_rows(hipStream_t s, int dtype, void* dst, const void* a, int rows_a, const void* b, int rows_b, int B, int d);
 
 // ------------------------------------------------------------------------------ update
 // Algorithm 1 / Algorithm 2 on n elements.  g = gscale0*g0 + gscale1*g1 (null pointers

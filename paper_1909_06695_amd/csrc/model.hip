@@ -887,8 +887,7 @@ static int layer_forward(ouro_model* m, int l, char* out_override = nullptr, boo
   } else {
     const char* cat = b.x;
     if (Mv > 0) {
-      HIPCHK(launch_copy_rows(m->stream, c.dtype, b.cat, (size_t)S * d, 0, b.mem, (size_t)Mv * d, 0, B, Mv, d));
-      HIPCHK(launch_copy_rows(m->stream, c.dtype, b.cat, (size_t)S * d, (size_t)Mv * d, b.x, (size_t)T * d, 0, B, T, d));
+      HIPCHK(launch_concat_rows(m->stream, c.dtype, b.cat, b.mem, Mv, b.x, T, B, d));
       cat = b.cat;
     }
     char* q = b.qkv;
@@ -1310,11 +1309,18 @@ static int close_iteration(ouro_model* m) {
     // memory for t+1 = last M rows of [memory ; layer input] (constants, no gradient)
     const int T = c.seq_len, d = m->pd, Mv = m->mem_valid, S = Mv + T;
     const int Mn = std::min(c.mem_len, S);
+    // every layer's buffers have the same sizes and so lie equally far apart in the arena: one launch (16 to 18 launches
+    // of 5 us per step before)
+    const LayerBuf& b0 = m->L[0];
+    const char* src0 = Mv > 0 ? b0.cat : b0.x;
+    size_t step = 0;
+    if (c.n_layer > 1) step = (size_t)(m->L[1].mem - b0.mem);
     for (int l = 0; l < c.n_layer; ++l) {
-      LayerBuf& b = m->L[l];
-      const char* cat = Mv > 0 ? b.cat : b.x;
-      HIPCHK(launch_copy_rows(m->stream, c.dtype, b.mem, (size_t)Mn * d, 0, cat, (size_t)S * d, (size_t)(S - Mn) * d, c.batch, Mn, d));
+      const LayerBuf& b = m->L[l];
+      if (b.mem != b0.mem + l * step || (Mv > 0 ? b.cat : b.x) != src0 + l * step) return fail(OURO_E_CONFIG, "layer buffers are not equally spaced");
     }
+    HIPCHK(launch_copy_rows(m->stream, c.dtype, b0.mem, (size_t)Mn * d, 0, src0, (size_t)S * d, (size_t)(S - Mn) * d, c.batch, Mn, d, c.n_layer,
+                            step / m->esz, step / m->esz));
     m->mem_valid = Mn;
   }
   m->t += 1;

@@ -939,26 +939,54 @@ __global__ void copy_rows_kernel(T* dst, size_t dst_bstride, size_t dst_off, con
 }
 // The same copy in 16-byte pieces (all strides, offsets and the row block a multiple of 16 bytes).
 __global__ void copy_rows_vec_kernel(uint4* dst, size_t dst_bstride, size_t dst_off, const uint4* src, size_t src_bstride,
-                                     size_t src_off, size_t n) {
+                                     size_t src_off, size_t n, size_t dst_lstride, size_t src_lstride) {
   const int b = blockIdx.y;
+  dst += blockIdx.z * dst_lstride;
+  src += blockIdx.z * src_lstride;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) dst[b * dst_bstride + dst_off + i] = src[b * src_bstride + src_off + i];
 }
 hipError_t launch_copy_rows(hipStream_t s, int dtype, void* dst, size_t dst_bstride, size_t dst_off,
-                            const void* src, size_t src_bstride, size_t src_off, int B, int rows, int d) {
-  if (B <= 0 || rows <= 0) return hipSuccess;
+                            const void* src, size_t src_bstride, size_t src_off, int B, int rows, int d,
+                            int layers, size_t dst_lstride, size_t src_lstride) {
+  if (B <= 0 || rows <= 0 || layers <= 0) return hipSuccess;
   const size_t esz = dtype == 1 ? 2 : 4, per = 16 / esz, n = (size_t)rows * d;
-  if (!((dst_bstride | dst_off | src_bstride | src_off | n) % per) && !((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15)) {
-    dim3 grid(grid_for(n / per, 256, 1024), B), block(256);
+  if (!((dst_bstride | dst_off | src_bstride | src_off | n | dst_lstride | src_lstride) % per) && !((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15)) {
+    dim3 grid(grid_for(n / per, 256, 1024), B, layers), block(256);
     hipLaunchKernelGGL(copy_rows_vec_kernel, grid, block, 0, s, (uint4*)dst, dst_bstride / per, dst_off / per, (const uint4*)src,
-                       src_bstride / per, src_off / per, n / per);
+                       src_bstride / per, src_off / per, n / per, dst_lstride / per, src_lstride / per);
     return hipGetLastError();
+  }
+  for (int l = 1; l < layers; ++l) {
+    hipError_t e = launch_copy_rows(s, dtype, (char*)dst + l * dst_lstride * esz, dst_bstride, dst_off, (const char*)src + l * src_lstride * esz,
+                                    src_bstride, src_off, B, rows, d);
+    if (e != hipSuccess) return e;
   }
   dim3 grid(grid_for((size_t)rows * d, 256, 1024), B), block(256);
   if (dtype == 1) hipLaunchKernelGGL(copy_rows_kernel<bf16_t>, grid, block, 0, s, (bf16_t*)dst, dst_bstride, dst_off, (const bf16_t*)src, src_bstride, src_off, rows, d);
   else hipLaunchKernelGGL(copy_rows_kernel<float>, grid, block, 0, s, (float*)dst, dst_bstride, dst_off, (const float*)src, src_bstride, src_off, rows, d);
   return hipGetLastError();
+}
+
+// dst [B, na + nb] <- a [B, na] ; b [B, nb], in 16-byte pieces.
+__global__ __launch_bounds__(256) void concat_rows_kernel(uint4* __restrict__ dst, const uint4* __restrict__ a, size_t na,
+                                                          const uint4* __restrict__ b, size_t nb) {
+  dst += blockIdx.y * (na + nb);
+  a += blockIdx.y * na;
+  b += blockIdx.y * nb;
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += stride) dst[i] = i < na ? a[i] : b[i - na];
+}
+hipError_t launch_concat_rows(hipStream_t s, int dtype, void* dst, const void* a, int rows_a, const void* b, int rows_b, int B, int d) {
+  const size_t na = (size_t)rows_a * d, nb = (size_t)rows_b * d, per = dtype == 1 ? 8 : 4;
+  if (B > 0 && rows_a > 0 && rows_b > 0 && !((na | nb) % per) && ptr16(dst) && ptr16(a) && ptr16(b)) {
+    hipLaunchKernelGGL(concat_rows_kernel, dim3(grid_for((na + nb) / per, 256, 1024), B), dim3(256), 0, s, (uint4*)dst, (const uint4*)a, na / per,
+                       (const uint4*)b, nb / per);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_copy_rows(s, dtype, dst, na + nb, 0, a, na, 0, B, rows_a, d);
+  return e != hipSuccess ? e : launch_copy_rows(s, dtype, dst, na + nb, na, b, nb, 0, B, rows_b, d);
 }
 
 // ------------------------------------------------------------------------------- update
