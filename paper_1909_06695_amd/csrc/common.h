@@ -220,7 +220,7 @@ hipError_t launch_transpose_table(hipStream_t s, const void* src, void* dst, con
 // at poff); a head axis of d_head elements a head is stored in slices of pdh.  tile0 is the running count of REMAP_ROWS-row
 // tiles before this tensor.
 struct RemapEntry { unsigned long long loff, poff; int rows, cols, pcols, row_heads, col_heads, tile0; };
-constexpr int REMAP_ROWS = 16;
+constexpr int REMAP_ROWS = 4;
 // to_stored != 0: stored <- blob (positions outside the tensors stay as they are); 0: blob <- stored
 hipError_t launch_remap(hipStream_t s, float* stored, float* blob, const RemapEntry* dev_tab, int entries, int tiles, int d_head, int pdh, int to_stored);
 // dst[r, c] = src[r, c] * mask(r*drop.ld + c) over rows x cols elements, both with row stride ld
