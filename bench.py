@@ -192,7 +192,7 @@ def main():
     ap.add_argument("--no-kernel-timing", action="store_true")
     ap.add_argument("--serial", action="store_true",
                     help="run every kernel on one stream in the timed steps too (the mode the per-launch pass and "
-                         "the committed kernel traces use; the default overlaps independent kernels on extra streams)")
+                         "the committed kernel traces use; the default overlaps independent kernels on extra streams where that pays)")
     ap.add_argument("--schedule", type=int, default=0, choices=[0, 1],
                     help="0: gradient rings, Eq. 8 to the letter (the headline workload); 1: stored module inputs "
                          "and recomputation (the paper's memory-saving schedule; one more forward pass per module below K)")
