@@ -53,6 +53,9 @@ int ouro_op_gemm_batched(void* stream, int dtype, int transA, int transB, int M,
 int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                        const void* const* A, const int* lda, const void* const* B, const int* ldb,
                        float* const* C, const int* ldc, float alpha);
+/* Bytes from the base of an operand (rows along its slow dimension, cols contiguous) to the end of its last element: what
+ * the contraction kernels may read of it (host only). */
+size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld);
 /* 1 if ouro_op_gemm would run the MFMA kernel for these arguments (host only). */
 int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A,
                            int lda, const void* B, int ldb);

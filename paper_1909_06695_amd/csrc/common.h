@@ -121,6 +121,11 @@ constexpr int GEMM_GROUP_MAX = 6;
 // direct-to-LDS kernels that need operands under 2 GiB and K % 64 == 0 (any K where transA = 1 and transB = 0).
 enum { GEMM_TILE_STAGED128 = 10, GEMM_TILE_128x128 = 11, GEMM_TILE_128x64 = 12, GEMM_TILE_PIPE128 = 13, GEMM_TILE_256x256 = 14,
        GEMM_TILE_64x64 = 15, GEMM_TILE_128x256 = 16 };
+// Bytes from an operand's base to the end of its last element: `rows` along the slow dimension, `cols` contiguous.  An
+// operand may be a column block of a wider matrix (ld > cols, base inside a row), so rows * ld would reach past that matrix.
+inline size_t operand_extent(size_t esz, int rows, int cols, int ld) {
+  return rows > 0 && cols > 0 ? esz * ((size_t)(rows - 1) * ld + cols) : 0;
+}
 // dtype 0: fp32 operands, 1: bf16 operands.  force_generic: 0 = automatic choice, 1 = the
 // plain tiled kernel, GEMM_TILE_* = that MFMA configuration where the problem admits MFMA
 // (a direct-to-LDS configuration falls back to the staged one when its conditions fail).

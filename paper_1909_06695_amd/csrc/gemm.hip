@@ -213,6 +213,9 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   p.epilogue = g.epilogue; p.Z = g.Z; p.ldz = g.ldz; p.alpha = g.alpha;
   p.drop = g.drop;
   p.kchunk = g.K; p.tilesN = 0; p.vec_epi = 0;
+  // taken by the direct-load kernels only, which are not chosen for operands of 2 GiB and more
+  p.bytesA = (int)operand_extent(dtype == 1 ? 2 : 4, g.transA ? g.K : g.M, g.transA ? g.M : g.K, g.lda);
+  p.bytesB = (int)operand_extent(dtype == 1 ? 2 : 4, g.transB ? g.N : g.K, g.transB ? g.K : g.N, g.ldb);
   p.colsum = g.colsum; p.colsum_stride = g.colsum_stride;
   if (g.colsum && (g.accumulate || g.by > 1 || g.bz > 1 || g.C2)) return hipErrorInvalidValue;
   if (g.accumulate && (!g.out_fp32 || g.bias || g.residual || g.epilogue != EPI_NONE)) return hipErrorInvalidValue;
@@ -434,6 +437,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     memset(&p, 0, sizeof p);
     p.A = d.A; p.B = d.B; p.C = d.C;
     p.M = d.M; p.N = d.N; p.K = d.K; p.lda = d.lda; p.ldb = d.ldb; p.ldc = d.ldc;
+    p.bytesA = (int)operand_extent(2, d.K, d.M, d.lda); p.bytesB = (int)operand_extent(2, d.K, d.N, d.ldb);
     p.out_fp32 = 1; p.epilogue = EPI_NONE; p.alpha = d.alpha;
     p.by = p.bz = p.bz1 = 1;
     // every product splits into ranges of the same length, rounded so that the last is not a sliver

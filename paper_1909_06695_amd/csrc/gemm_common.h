@@ -16,6 +16,7 @@ struct GemmParams {
   int epilogue;
   void* Z; int ldz;
   float alpha;
+  int bytesA, bytesB;   // operand extents, for the buffer descriptors of the direct loads (each operand is under 2 GiB)
   int kchunk;      // K range per blockIdx.z
   int tilesN;      // tiles along N (MFMA kernel)
   int tilesM, ntiles, mfast, band;   // direct-to-LDS kernels: see tile_of_block

@@ -37,7 +37,6 @@ __device__ __forceinline__ void direct_load(const void* base, int bytes, char* d
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000), (lds_void*)dst, 16,
                                            voff, soff, 0, 0);
 }
-__device__ __forceinline__ int operand_bytes(int rows, int ld) { return (int)(2u * (uint32_t)rows * (uint32_t)ld); }
 
 // Wait until at most N vector-memory operations are outstanding and every LDS operation of
 // this wave has completed.
@@ -125,7 +124,6 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
 #pragma unroll
   for (int i = 0; i < TileB::PER; ++i)
     ob[i] = (uint32_t)(2 * (TileB::src_offset(wave + i * NW, lane, n0, p.N, p.ldb) + (TB ? (size_t)kbeg : (size_t)kbeg * p.ldb)));
-  const int bytesA = operand_bytes(TA ? p.K : p.M, p.lda), bytesB = operand_bytes(TB ? p.N : p.K, p.ldb);
   const uint32_t stepA = 2u * (TA ? (uint32_t)BK * p.lda : (uint32_t)BK);
   const uint32_t stepB = 2u * (TB ? (uint32_t)BK : (uint32_t)BK * p.ldb);
 
@@ -135,10 +133,10 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
     const uint32_t ka = (uint32_t)kt * stepA, kb = (uint32_t)kt * stepB;
 #pragma unroll
     for (int i = 0; i < TileA::PER; ++i)
-      direct_load(p.A, bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
+      direct_load(p.A, p.bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
 #pragma unroll
     for (int i = 0; i < TileB::PER; ++i)
-      direct_load(p.B, bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
+      direct_load(p.B, p.bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
   };
 
   f32x16 acc[TM][TN];
@@ -296,7 +294,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
 #pragma unroll
   for (int i = 0; i < TileB::PER; ++i)
     ob[i] = (uint32_t)(2 * (TileB::src_offset(wave + i * NW, lane, n0, p.N, p.ldb) + (TB ? (size_t)kbeg : (size_t)kbeg * p.ldb)));
-  const int bytesA = operand_bytes(TA ? p.K : p.M, p.lda), bytesB = operand_bytes(TB ? p.N : p.K, p.ldb);
   const uint32_t stepA = 2u * (TA ? (uint32_t)BK * p.lda : (uint32_t)BK);
   const uint32_t stepB = 2u * (TB ? (uint32_t)BK : (uint32_t)BK * p.ldb);
 
@@ -306,10 +303,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
     const uint32_t ka = (uint32_t)kt * stepA, kb = (uint32_t)kt * stepB;
 #pragma unroll
     for (int i = 0; i < TileA::PER; ++i)
-      direct_load(p.A, bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
+      direct_load(p.A, p.bytesA, st + (wave + i * NW) * 1024, oa[i], ka);
 #pragma unroll
     for (int i = 0; i < TileB::PER; ++i)
-      direct_load(p.B, bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
+      direct_load(p.B, p.bytesB, st + TileA::BYTES + (wave + i * NW) * 1024, ob[i], kb);
   };
   bf16x8 af[4][TM], bfr[4][TN];
   auto fetch = [&](const char* sa, int ks) __attribute__((always_inline)) {

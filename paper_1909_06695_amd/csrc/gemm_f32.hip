@@ -96,7 +96,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
   const int nk_all = (kend - kbeg + F32_BK - 1) / F32_BK;
   const int k_first = WIDE ? 0 : wave, k_step = WIDE ? 1 : 4;    // K-tiles of this wave
   const int nk = nk_all > k_first ? (nk_all - k_first + k_step - 1) / k_step : 0;
-  const int bytesA = (int)(4u * (uint32_t)(TA ? p.K : p.M) * (uint32_t)p.lda), bytesB = (int)(4u * (uint32_t)(TB ? p.N : p.K) * (uint32_t)p.ldb);
 
   uint32_t oa[OA::PER], ob[OB::PER];                             // byte offsets without the K-tile term
   auto offset = [](bool col, int row, int k, int ld) __attribute__((always_inline)) { return 4u * (col ? (uint32_t)k * (uint32_t)ld + row : (uint32_t)row * (uint32_t)ld + k); };
@@ -113,14 +112,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
 #pragma unroll
     for (int i = 0; i < OA::PER; ++i) {
       char* da = d + (lw * OA::PER + i) * (OA::EPL * 4);
-      if (!TA && ragged) { int row, k; OA::place(lw * OA::PER + i, lane, row, k); f32_load(p.A, bytesA, da, k0 + k < kend ? oa[i] + ka : 0x7ffffff0u, 0, VEC); }
-      else f32_load(p.A, bytesA, da, oa[i], ka, VEC);
+      if (!TA && ragged) { int row, k; OA::place(lw * OA::PER + i, lane, row, k); f32_load(p.A, p.bytesA, da, k0 + k < kend ? oa[i] + ka : 0x7ffffff0u, 0, VEC); }
+      else f32_load(p.A, p.bytesA, da, oa[i], ka, VEC);
     }
 #pragma unroll
     for (int i = 0; i < OB::PER; ++i) {
       char* db = d + OA::BYTES + (lw * OB::PER + i) * (OB::EPL * 4);
-      if (TB && ragged) { int row, k; OB::place(lw * OB::PER + i, lane, row, k); f32_load(p.B, bytesB, db, k0 + k < kend ? ob[i] + kb : 0x7ffffff0u, 0, VEC); }
-      else f32_load(p.B, bytesB, db, ob[i], kb, VEC);
+      if (TB && ragged) { int row, k; OB::place(lw * OB::PER + i, lane, row, k); f32_load(p.B, p.bytesB, db, k0 + k < kend ? ob[i] + kb : 0x7ffffff0u, 0, VEC); }
+      else f32_load(p.B, p.bytesB, db, ob[i], kb, VEC);
     }
   };
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;

@@ -133,7 +133,6 @@ __device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0,
   using OB = PpOperand<!TB>;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  const int bytesA = (int)(2u * (uint32_t)(TA ? p.K : p.M) * (uint32_t)p.lda), bytesB = (int)(2u * (uint32_t)(TB ? p.N : p.K) * (uint32_t)p.ldb);
   const uint32_t oa = OA::src(wave, lane, m0, p.lda), ob = OB::src(wave, lane, n0, p.ldb);
   const uint32_t jumpA = OA::jump(p.lda), jumpB = OB::jump(p.ldb), halfA = OA::half(p.lda), halfB = OB::half(p.ldb);
   const uint32_t stepA = 2u * (TA ? (uint32_t)PP_BK * p.lda : (uint32_t)PP_BK), stepB = 2u * (TB ? (uint32_t)PP_BK : (uint32_t)PP_BK * p.ldb);
@@ -143,8 +142,8 @@ __device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0,
   OA::template addresses<2>(lds0, wm * 64, lane, ra);
   OB::template addresses<1>(lds0 + 4 * PP_HALF, wn * 32, lane, rb);
   char* const dst = lds + wave * 1024;
-  auto reqA = [&](int st, int h, uint32_t k) __attribute__((always_inline)) { pp_request(p.A, bytesA, dst + (2 * st + h) * PP_HALF, oa, k + h * halfA, jumpA); };
-  auto reqB = [&](int st, int h, uint32_t k) __attribute__((always_inline)) { pp_request(p.B, bytesB, dst + (4 + 2 * st + h) * PP_HALF, ob, k + h * halfB, jumpB); };
+  auto reqA = [&](int st, int h, uint32_t k) __attribute__((always_inline)) { pp_request(p.A, p.bytesA, dst + (2 * st + h) * PP_HALF, oa, k + h * halfA, jumpA); };
+  auto reqB = [&](int st, int h, uint32_t k) __attribute__((always_inline)) { pp_request(p.B, p.bytesB, dst + (4 + 2 * st + h) * PP_HALF, ob, k + h * halfB, jumpB); };
   PpFrag<TA> fa[4][2];
   PpFrag<!TB> fb0[2][4][1], fb1[4][1];             // B0 is read one K-tile ahead, into the set of that K-tile's parity
   auto mul = [&](int h, int j, PpFrag<!TB> (&b)[4][1]) __attribute__((always_inline)) {

@@ -90,6 +90,10 @@ extern "C" int ouro_op_dropout(void* stream, int dtype, const void* src, void* d
   return rc_of(launch_dropout_apply((hipStream_t)stream, dtype, src, dst, rows, cols, ld, make_drop(p, seed, stream_id, drop_ld)));
 }
 
+extern "C" size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld) {
+  return operand_extent(dtype == 1 ? 2 : 4, rows, cols, ld);
+}
+
 extern "C" int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A, int lda,
                                       const void* B, int ldb) {
   GemmDesc g = make_gemm(transA, transB, M, N, K, 1.f, A, lda, B, ldb, nullptr, N, 0, 0, nullptr, nullptr, 0, 0, nullptr, 0);

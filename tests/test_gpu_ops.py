@@ -145,6 +145,26 @@ def test_gemm_ragged_contraction(force, M, N, K):
         assert rel_err(host(out), ref + acc) < 2e-6 + 1e-6 * acc
 
 
+@pytest.mark.parametrize("dtype,force", [(0, 21), (0, 22), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(200, 72, 64), (136, 264, 128)])
+def test_gemm_column_blocks(dtype, force, tA, tB, M, N, K):
+    """Operands that are the last columns of a matrix twice as wide, the other half NaN: tiles reach past the operand on
+    every side; bound as in test_gemm_forms."""
+    rng = np.random.default_rng(M + N + K + force)
+    def operand(rows, cols):
+        x = torch.full((rows, 2 * cols), float("nan"), dtype=torch.bfloat16 if dtype else torch.float32, device="cuda")
+        x[:, cols:] = torch.from_numpy(rng.standard_normal((rows, cols)).astype(np.float32)).cuda()
+        return x, x[:, cols:]
+    wA, A = operand(*((K, M) if tA else (M, K)))
+    wB, B = operand(*((N, K) if tB else (K, N)))
+    out = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    ok(L().ouro_op_gemm(stream(), dtype, tA, tB, M, N, K, 1.0, p(A), wA.shape[1], p(B), wB.shape[1], p(out), N, 1, 0, None, None, 0, 0, None, 0, force))
+    torch.cuda.synchronize()
+    ref = (host(A).T if tA else host(A)) @ (host(B).T if tB else host(B))
+    assert rel_err(host(out), ref) < 2e-6
+
+
 @pytest.mark.parametrize("dtype,shapes", [
     (1, [(256, 128, 2048), (128, 384, 2048), (136, 72, 1024), (128, 128, 512)]),     # all in one launch, ragged tiles
     (1, [(256, 128, 1024), (72, 40, 1000), (128, 256, 4096), (64, 64, 320)]),        # two of them go by themselves

@@ -91,6 +91,20 @@ def test_create_model_rejects_bad_arena_without_touching_it():
     assert rc == binding.E_ARENA and not h.value
 
 
+@pytest.mark.parametrize("dtype,esz", [(0, 4), (1, 2)])
+def test_contraction_operands_end_at_their_last_element(dtype, esz):
+    """What the buffer descriptors of the contraction kernels let through ends with the operand's last element, also where
+    the operand is the last column block of a wider matrix: rows * ld from the block's base would run past that matrix."""
+    f = P.lib().ouro_op_gemm_operand_bytes
+    for rows, ld in [(1, 1600), (33, 1600), (2331, 2304), (7, 41)]:
+        for cols in {1, 8, ld // 2, ld}:
+            off = ld - cols
+            assert f(dtype, rows, cols, ld) + off * esz == rows * ld * esz
+    assert f(dtype, 0, 8, 8) == 0
+    # sizes beyond 32 bits do not wrap
+    assert f(dtype, 1 << 20, 8, 1 << 14) == esz * (((1 << 20) - 1) * (1 << 14) + 8)
+
+
 def test_lr_schedule_matches_the_oracle():
     """The library's host-side step-size function against the oracle's, over both phases and
     the boundaries (both fp64: agreement to rounding); bad arguments are refused."""
