@@ -190,7 +190,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
 
 bool gemm_f32_ok(const GemmDesc& g) {
   const size_t bytesA = 4 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 4 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
-  return bytesA < (1ull << 31) - 64 && bytesB < (1ull << 31) - 64 && g.K >= 1;
+  // offsets are 32-bit, also those of the up to 63 rows that a tile has past the operand's end: none may wrap back into it
+  const size_t pastA = bytesA + 256 * (size_t)g.lda, pastB = bytesB + 256 * (size_t)g.ldb;
+  return bytesA < (1ull << 31) - 64 && bytesB < (1ull << 31) - 64 && pastA < (1ull << 32) && pastB < (1ull << 32) && g.K >= 1;
 }
 
 template <bool WIDE, int VEC>

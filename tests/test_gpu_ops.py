@@ -258,6 +258,21 @@ def test_gemm_f32_matrix_core_forms(force, tA, tB, M, N, K):
         assert rel_err(host(out), ref + acc) < 2e-6
 
 
+@pytest.mark.parametrize("force", [0, 21, 22])
+def test_gemm_f32_rows_far_apart(force):
+    """Rows 2^26 floats apart: the 32-bit offset of the tile's row 16 would come round to row 0.  Such an operand takes the
+    plain kernel whatever is asked for."""
+    K, M, N, ld = 2, 40, 36, 1 << 26
+    rng = np.random.default_rng(3)
+    wide = torch.empty((K, ld), dtype=torch.float32, device="cuda")
+    wide[:, :M + N] = torch.from_numpy(rng.standard_normal((K, M + N)).astype(np.float32))
+    A, B = wide[:, :M], wide[:, M:M + N]
+    out = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    ok(L().ouro_op_gemm(stream(), 0, 1, 0, M, N, K, 1.0, p(A), ld, p(B), ld, p(out), N, 1, 0, None, None, 0, 0, None, 0, force))
+    torch.cuda.synchronize()
+    assert rel_err(host(out), host(A).T @ host(B)) < 2e-6
+
+
 @pytest.mark.parametrize("force", [21, 22])
 def test_gemm_f32_matrix_core_epilogues(force):
     """Bias, GELU and its gradient, residuals, LayerNorm residual and dropout in the epilogue of both fp32 forms."""
