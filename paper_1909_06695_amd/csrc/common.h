@@ -52,7 +52,7 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
 //   (+ residual[m,n]); store as T or fp32, or atomically add to fp32 C (split-K).
 // transA == 0: A stored [M,K] (lda >= K); transA == 1: A stored [K,M] (lda >= M).
 // transB == 0: B stored [K,N] (ldb >= N); transB == 1: B stored [N,K] (ldb >= K).
-enum { ACC_ATOMIC = 1, ACC_ADD = 2, ACC_STORE = 3 };
+enum { ACC_ATOMIC = 1, ACC_STORE = 2 };
 enum { EPI_NONE = 0, EPI_GELU = 1, EPI_GELUGRAD = 2 };
 // Repeatable dropout (Section 5.2): element i of a tensor is kept iff the high 32 bits of output
 // number i + stream*2^40 + 1 of the SplitMix64 sequence started at the seed are >= thresh; kept
@@ -86,8 +86,9 @@ struct GemmDesc {
   int M, N, K, lda, ldb, ldc;
   int transA, transB;
   int out_fp32;          // C element type: 1 fp32, 0 same as inputs
-  int accumulate;        // ACC_ATOMIC: C (fp32) += result (allows split-K); ACC_STORE (launch_gemm_group only): the same
-                         // onto a C that the caller has cleared, so a part that is the only one may be stored; 0: overwrite
+  int accumulate;        // ACC_ATOMIC: C (fp32) += result, atomically: other products, in this launch or on another stream,
+                         // may add to the same C; ACC_STORE: the caller has cleared C and nothing else adds to it, so a
+                         // part that is the only one may be stored; 0: overwrite
   const float* bias;     // [N] or null
   const void* residual;  // [M, ldr] element type T, or null
   int ldr;

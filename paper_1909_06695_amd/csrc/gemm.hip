@@ -362,6 +362,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     return launch_mfma_cfg<128, 128, 2, 2>(s, p, g.transA, g.transB, splits);
   }
 
+  p.accumulate = g.accumulate;
   if (dtype == 0 && force_generic != 1 && gemm_f32_ok(g)) return launch_gemm_f32(s, p, g.transA, g.transB, force_generic >= 20 ? force_generic - 20 : 0);
 
   dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, 1), block(256);
@@ -420,7 +421,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
         const int splits = (g[i].K + kc - 1) / kc;
         const long tiles = (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt);
         wgs += tiles * splits;
-        if (splits > 1) adds += (double)tiles * splits * bt * bt;
+        if (splits > 1 || g[i].accumulate != ACC_STORE) adds += (double)tiles * splits * bt * bt;
       }
       const double slots = big ? 256 : 512;
       const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
@@ -443,7 +444,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     // every product splits into ranges of the same length, rounded so that the last is not a sliver
     const int splits = (d.K + kchunk - 1) / kchunk;
     p.kchunk = ((d.K + splits - 1) / splits + 63) / 64 * 64;
-    p.accumulate = splits > 1 ? ACC_ATOMIC : d.accumulate == ACC_STORE ? ACC_STORE : ACC_ADD;
+    p.accumulate = splits > 1 ? ACC_ATOMIC : d.accumulate;
   }
   if (grouped) *grouped = true;
   if (big) return launch_gemm_pp_group(s, ps, n);

@@ -116,13 +116,6 @@ __device__ __forceinline__ void epilogue_column(const GemmParams& p, const int (
       if (on[r]) unsafeAtomicAdd(reinterpret_cast<float*>(p.C) + (size_t)m[r] * p.ldc + n, v[r]);
     return;
   }
-  if (p.accumulate) {
-    float old[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) old[r] = on[r] ? reinterpret_cast<const float*>(p.C)[(size_t)m[r] * p.ldc + n] : 0.f;
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] += old[r];
-  }
   if (p.bias) {
     const float b = p.bias[n];
 #pragma unroll
@@ -247,8 +240,7 @@ template <int TN> constexpr int epilogue_stage_floats() { return TN * 32 * 36; }
 // output row: 16-byte loads of the residual / pre-activation, 16-byte stores of the result.
 // Only the register dump is unrolled; the arithmetic runs in a rolled loop over the patch.
 // CS: distance in columns between the tiles of a row.
-// p.accumulate: ACC_ATOMIC, several workgroups add to an element of C (split K); ACC_ADD, only this one does; ACC_STORE,
-// likewise, and C is known to be zero.
+// p.accumulate: ACC_ATOMIC, others may add to the same elements of C; ACC_STORE, nothing else does and C is known to be zero.
 template <int TM, int TN, int CS = 32>
 __device__ __forceinline__ void mfma_accumulate(const GemmParams& p, f32x16 (&acc)[TM][TN], int m_w, int n_w, int lane) {
   const int mode = p.accumulate;
@@ -266,16 +258,10 @@ __device__ __forceinline__ void mfma_accumulate(const GemmParams& p, f32x16 (&ac
           if (n < p.N && mb + dm < p.M) unsafeAtomicAdd(c + (size_t)dm * p.ldc, acc[i][j][r] * p.alpha);
         }
       } else {
-        float old[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int dm = 8 * (r >> 2) + (r & 3);
-          old[r] = mode == ACC_ADD && n < p.N && mb + dm < p.M ? c[(size_t)dm * p.ldc] : 0.f;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int dm = 8 * (r >> 2) + (r & 3);
-          if (n < p.N && mb + dm < p.M) c[(size_t)dm * p.ldc] = old[r] + acc[i][j][r] * p.alpha;
+          if (n < p.N && mb + dm < p.M) c[(size_t)dm * p.ldc] = acc[i][j][r] * p.alpha;
         }
       }
     }

@@ -235,7 +235,7 @@ hipError_t launch_gemm_f32(hipStream_t s, GemmParams& p, int transA, int transB,
   if (p.accumulate && !wide && t32 < 512) splits = (int)std::max<long>(1, std::min<long>(512 / t32, p.K / (16 * F32_BK)));
   p.kchunk = ((p.K + splits - 1) / splits + F32_BK - 1) / F32_BK * F32_BK;
   splits = (p.K + p.kchunk - 1) / p.kchunk;
-  if (p.accumulate) p.accumulate = splits > 1 ? ACC_ATOMIC : ACC_ADD;
+  if (splits > 1) p.accumulate = ACC_ATOMIC;
   if (wide) return vec ? launch_f32<true, 4>(s, p, transA, transB, splits) : launch_f32<true, 1>(s, p, transA, transB, splits);
   return vec ? launch_f32<false, 4>(s, p, transA, transB, splits) : launch_f32<false, 1>(s, p, transA, transB, splits);
 }

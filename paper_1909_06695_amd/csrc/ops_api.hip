@@ -17,7 +17,7 @@ static GemmDesc make_gemm(int transA, int transB, int M, int N, int K, float alp
   GemmDesc g;
   memset(&g, 0, sizeof g);
   g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
-  g.transA = transA; g.transB = transB; g.out_fp32 = out_fp32; g.accumulate = accumulate;
+  g.transA = transA; g.transB = transB; g.out_fp32 = out_fp32; g.accumulate = accumulate ? ACC_ATOMIC : 0;
   g.bias = bias; g.residual = residual; g.ldr = ldr; g.epilogue = epilogue; g.Z = Z; g.ldz = ldz; g.alpha = alpha;
   return g;
 }

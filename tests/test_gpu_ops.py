@@ -188,6 +188,29 @@ def test_gemm_group(dtype, shapes):
         assert rel_err(host(out[i]), ref) < 2e-6, i
 
 
+@pytest.mark.parametrize("dtype,M,N,K", [(1, 256, 128, 512), (1, 1024, 512, 256), (1, 136, 72, 40), (0, 64, 64, 128), (0, 640, 1024, 32)])
+def test_products_onto_one_output(dtype, M, N, K):
+    """Accumulating products that share their output: six of them in one grouped call, then six calls on three streams.
+    Integer operands, so that every order of additions gives the same sum and a lost one shows."""
+    rng = np.random.default_rng(M + N + K)
+    A = [dev(rng.integers(-2, 3, (K, M)), dtype) for _ in range(6)]
+    B = [dev(rng.integers(-2, 3, (K, N)), dtype) for _ in range(6)]
+    ref = 1.0 + sum(host(a).T @ host(b) for a, b in zip(A, B))
+    ia = lambda v: (C.c_int * 6)(*[v] * 6)
+    pa = lambda ts: (C.c_void_p * 6)(*[t.data_ptr() for t in ts])
+    out = torch.ones((M, N), dtype=torch.float32, device="cuda")
+    ok(L().ouro_op_gemm_group(stream(), dtype, 6, ia(M), ia(N), ia(K), pa(A), ia(M), pa(B), ia(N), pa([out] * 6), ia(N), 1.0))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out), ref)
+    out = torch.ones((M, N), dtype=torch.float32, device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for i in range(6):
+        ok(L().ouro_op_gemm(C.c_void_p(streams[i % 3].cuda_stream), dtype, 1, 0, M, N, K, 1.0, p(A[i]), M, p(B[i]), N, p(out), N, 1, 1, None, None, 0, 0, None, 0, 0))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out), ref)
+
+
 @pytest.mark.parametrize("shapes", [
     [(1024, 1024, 2331), (1032, 776, 2331)],                      # K range whole, ragged K-tile and edges of tiles
     [(264, 520, 8256), (512, 256, 8256)],                         # split over workgroups, atomic adds
