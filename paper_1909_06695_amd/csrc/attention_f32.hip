@@ -45,7 +45,7 @@ __device__ __forceinline__ void af_load_row(const float* src, int dh, int h32, b
   }
 }
 // Column fragment: register r of tile dt holds feature 32 dt + l32 of row row0 + af_row(r, h32) (rows clamped to rmax - 1:
-// what they meet in the other operand is zero).
+// what they meet in the other operand is zero, see af_check).
 template <int DH>
 __device__ __forceinline__ void af_load_cols(const float* base, int ld, int row0, int rmax, int dh, int h32, int l32, float (&f)[DH / 32][16]) {
 #pragma unroll
@@ -78,6 +78,20 @@ __device__ __forceinline__ void af_cols_product(f32x16 (&acc)[DH / 32], const fl
 #pragma unroll
     for (int dt = 0; dt < DH / 32; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(cols[dt][r], x[r], acc[dt], 0, 0, 0);
 }
+// The products over a tile's rows give those that a lane does not see a weight of zero, which does not keep an infinity or
+// NaN out of the sum.  `bad` becomes NaN when a tile that not every lane sees whole (`part`) holds one; the workgroup then
+// computes its rows once more, one at a time over the visible rows alone (af_*_rows).  The check is one instruction per
+// element in the tiles on the diagonal and at the end.
+template <int DH>
+__device__ __forceinline__ void af_check(bool part, const float (&cols)[DH / 32][16], float& bad) {
+  if (!part) return;
+#pragma unroll
+  for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) bad = fmaf(cols[dt][r], 0.f, bad);
+}
+// a . b over the features, in every lane
+__device__ __forceinline__ float af_dot(const float* a, const float* b, int dh, int lane) { return wave_sum(lane < dh ? a[lane] * b[lane] : 0.f); }
 // Four registers of one group g of a transposed tile (features 32 dt + 8 g + 4 h32 + (0..3) of the lane's row) to memory.
 template <bool VEC>
 __device__ __forceinline__ void af_store4(float* row, int c, int dh, f32x4 v) {
@@ -91,8 +105,26 @@ __device__ __forceinline__ void af_store4(float* row, int c, int dh, f32x4 v) {
 }
 
 // ------------------------------------------------------------------------------ forward
+__device__ __forceinline__ void af_fwd_rows(const AfParams& p, int q0, int head, int b, int wave, int lane) {
+  const float* kb = p.k + (size_t)b * p.S * p.ldk + head * p.dh;
+  const float* vb = p.v + (size_t)b * p.S * p.ldv + head * p.dh;
+  for (int i = q0 + wave; i < min(p.T, q0 + 32); i += 4) {
+    const float* q = p.q + ((size_t)b * p.T + i) * p.ldq + head * p.dh;
+    const int nvis = p.Mv + i + 1;
+    float mx = -INFINITY, sum = 0.f, acc = 0.f;
+    for (int j = 0; j < nvis; ++j) mx = fmaxf(mx, af_dot(q, kb + (size_t)j * p.ldk, p.dh, lane) * p.scale);
+    for (int j = 0; j < nvis; ++j) {
+      const float e = expf(af_dot(q, kb + (size_t)j * p.ldk, p.dh, lane) * p.scale - mx);
+      sum += e;
+      if (lane < p.dh) acc = fmaf(e, vb[(size_t)j * p.ldv + lane], acc);
+    }
+    if (lane < p.dh) p.out[((size_t)b * p.T + i) * p.ldo + head * p.dh + lane] = acc / sum;
+    if (lane == 0) p.lse[((size_t)b * p.H + head) * p.T + i] = mx + logf(sum);
+  }
+}
+// (the bound on registers keeps the occupancy that the kernel has without af_check)
 template <int DH, bool VEC>
-__global__ __launch_bounds__(256) void af_fwd_kernel(AfParams p) {
+__global__ __launch_bounds__(256, DH == 64 ? 2 : 3) void af_fwd_kernel(AfParams p) {
   constexpr int ND = DH / 32;
   __shared__ float so[4][ND * 16][64];
   __shared__ float sm[4][32], sl[4][32];
@@ -109,7 +141,7 @@ __global__ __launch_bounds__(256) void af_fwd_kernel(AfParams p) {
   for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f, bad = 0.f;
   for (int kt = wave; kt < nkt; kt += 4) {
     const int k0 = kt * 32;
     f32x4 kf[DH / 8];
@@ -136,8 +168,10 @@ __global__ __launch_bounds__(256) void af_fwd_kernel(AfParams p) {
     for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+    af_check<DH>(k0 + 31 > p.Mv + q0, vf, bad);
     af_cols_product<DH>(oacc, vf, s);
   }
+  if (__syncthreads_or(bad != bad)) { af_fwd_rows(p, q0, head, b, wave, lane); return; }
 #pragma unroll
   for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
@@ -192,6 +226,23 @@ __device__ __forceinline__ void af_reduce_store(float (&so)[4][DH / 2][64], cons
 }
 
 // ------------------------------------------------------------------------------ dQ, and D = rowsum(dO * O)
+__device__ __forceinline__ void af_dq_rows(const AfParams& p, int q0, int head, int b, int wave, int lane) {
+  const float* kb = p.k + (size_t)b * p.S * p.ldk + head * p.dh;
+  const float* vb = p.v + (size_t)b * p.S * p.ldv + head * p.dh;
+  for (int i = q0 + wave; i < min(p.T, q0 + 32); i += 4) {
+    const size_t row = (size_t)b * p.T + i, stat = ((size_t)b * p.H + head) * p.T + i;
+    const float *q = p.q + row * p.ldq + head * p.dh, *dov = p.d_o + row * p.lddo + head * p.dh;
+    const float D = af_dot(p.o + row * p.ldo + head * p.dh, dov, p.dh, lane), lse = p.lse[stat];
+    float acc = 0.f;
+    for (int j = 0; j <= p.Mv + i; ++j) {
+      const float* kj = kb + (size_t)j * p.ldk;
+      const float e = expf(af_dot(q, kj, p.dh, lane) * p.scale - lse);
+      const float ds = e * (af_dot(dov, vb + (size_t)j * p.ldv, p.dh, lane) - D) * p.scale;
+      if (lane < p.dh) acc = fmaf(ds, kj[lane], acc);
+    }
+    if (lane < p.dh) p.dq[row * p.lddq + head * p.dh + lane] = acc;
+  }
+}
 template <int DH, bool VEC>
 __global__ __launch_bounds__(256) void af_bwd_dq_kernel(AfParams p) {
   constexpr int ND = DH / 32;
@@ -218,6 +269,7 @@ __global__ __launch_bounds__(256) void af_bwd_dq_kernel(AfParams p) {
     if (wave == 0 && h32 == 0 && qi < p.T) p.D[stat] = D;
   }
   const int nkt = (min(p.S, p.Mv + min(p.T, q0 + 32)) + 31) / 32;
+  float bad = 0.f;
   f32x16 acc[ND];
 #pragma unroll
   for (int dt = 0; dt < ND; ++dt)
@@ -238,12 +290,33 @@ __global__ __launch_bounds__(256) void af_bwd_dq_kernel(AfParams p) {
       const bool vis = key <= p.Mv + qi && key < p.S && qi < p.T;
       dp[r] = vis ? __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -lse2)) * (dp[r] - D) : 0.f;
     }
+    af_check<DH>(k0 + 31 > p.Mv + q0, kcol, bad);
     af_cols_product<DH>(acc, kcol, dp);
   }
+  if (__syncthreads_or(bad != bad)) { af_dq_rows(p, q0, head, b, wave, lane); return; }
   af_reduce_store<DH, VEC>(so, acc, p.dq + ((size_t)b * p.T + qc) * p.lddq + head * p.dh, p.dh, p.scale, qi < p.T, wave, lane);
 }
 
 // ------------------------------------------------------------------------------ dK, dV
+__device__ __forceinline__ void af_dkv_rows(const AfParams& p, int k0, int head, int b, int wave, int lane) {
+  const float* qb = p.q + (size_t)b * p.T * p.ldq + head * p.dh;
+  const float* dob = p.d_o + (size_t)b * p.T * p.lddo + head * p.dh;
+  const size_t stat = ((size_t)b * p.H + head) * p.T;
+  for (int j = k0 + wave; j < min(p.S, k0 + 32); j += 4) {
+    const float *kj = p.k + ((size_t)b * p.S + j) * p.ldk + head * p.dh, *vj = p.v + ((size_t)b * p.S + j) * p.ldv + head * p.dh;
+    float dk = 0.f, dv = 0.f;
+    for (int i = max(0, j - p.Mv); i < p.T; ++i) {
+      const float *q = qb + (size_t)i * p.ldq, *dov = dob + (size_t)i * p.lddo;
+      const float e = expf(af_dot(q, kj, p.dh, lane) * p.scale - p.lse[stat + i]);
+      const float ds = e * (af_dot(dov, vj, p.dh, lane) - p.D[stat + i]) * p.scale;
+      if (lane < p.dh) { dv = fmaf(e, dov[lane], dv); dk = fmaf(ds, q[lane], dk); }
+    }
+    if (lane < p.dh) {
+      p.dk[((size_t)b * p.S + j) * p.lddk + head * p.dh + lane] = dk;
+      p.dv[((size_t)b * p.S + j) * p.lddv + head * p.dh + lane] = dv;
+    }
+  }
+}
 template <int DH, bool VEC>
 __global__ __launch_bounds__(256) void af_bwd_dkv_kernel(AfParams p) {
   constexpr int ND = DH / 32;
@@ -264,6 +337,7 @@ __global__ __launch_bounds__(256) void af_bwd_dkv_kernel(AfParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dk[dt][r] = 0.f; dv[dt][r] = 0.f; }
   const int nqt = (p.T + 31) / 32;
+  float bad = 0.f;
   for (int qt = max(0, k0 - p.Mv) / 32 + wave; qt < nqt; qt += 4) {
     const int q0 = qt * 32, qc = min(q0 + l32, p.T - 1);
     f32x16 s, dp;
@@ -283,14 +357,18 @@ __global__ __launch_bounds__(256) void af_bwd_dkv_kernel(AfParams p) {
       const bool vis = key <= p.Mv + i && i < p.T && key < p.S;
       const float pv = vis ? __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -lse[ic] * 1.4426950408889634f)) : 0.f;
       s[r] = pv;
-      dp[r] = pv * (dp[r] - Db[ic]);
+      dp[r] = vis ? pv * (dp[r] - Db[ic]) : 0.f;
     }
+    const bool part = k0 + 31 > p.Mv + q0 || q0 + 32 > p.T;
     float col[ND][16];
     af_load_cols<DH>(dob, p.lddo, q0, p.T, p.dh, h32, l32, col);
+    af_check<DH>(part, col, bad);
     af_cols_product<DH>(dv, col, s);
     af_load_cols<DH>(qb, p.ldq, q0, p.T, p.dh, h32, l32, col);
+    af_check<DH>(part, col, bad);
     af_cols_product<DH>(dk, col, dp);
   }
+  if (__syncthreads_or(bad != bad)) { af_dkv_rows(p, k0, head, b, wave, lane); return; }
   af_reduce_store<DH, VEC>(so, dk, p.dk + ((size_t)b * p.S + kc) * p.lddk + head * p.dh, p.dh, p.scale, key < p.S, wave, lane);
   af_reduce_store<DH, VEC>(so, dv, p.dv + ((size_t)b * p.S + kc) * p.lddv + head * p.dh, p.dh, 1.f, key < p.S, wave, lane);
 }

@@ -399,6 +399,42 @@ def test_attention_f32_kernel(B, H, T, Mv, dh):
     _attn_case(0, B, H, T, Mv, dh, 0, seed=300 + T + Mv + dh, force=0)
 
 
+def _attn_f32(q, kv, do, B, H, T, Mv, dh, force):
+    """o, lse, dq, and dk | dv of the fp32 kernels."""
+    S, d = Mv + T, H * dh
+    q, kv, do = (torch.from_numpy(x).cuda() for x in (q, kv, do))
+    o, gq, gkv = torch.zeros_like(q), torch.zeros_like(q), torch.zeros_like(kv)
+    lse = torch.zeros((B, H, T), device="cuda")
+    scr = torch.zeros(max(L().ouro_op_attention_bwd_scratch(B, H, T, S, dh), 1), device="cuda")
+    half = lambda t: C.c_void_p(t.data_ptr() + 4 * d)
+    sc = 1.0 / math.sqrt(dh)
+    ok(L().ouro_op_attention_fwd(stream(), 0, B, H, T, S, dh, Mv, sc, p(q), d, p(kv), 2 * d, half(kv), 2 * d, p(o), d, p(lse), 0, None, None, None, 0, force))
+    ok(L().ouro_op_attention_bwd(stream(), 0, B, H, T, S, dh, Mv, sc, p(q), d, p(kv), 2 * d, half(kv), 2 * d, p(o), d, p(lse), p(do), d, p(gq), d,
+                                 p(gkv), 2 * d, half(gkv), 2 * d, 0, None, None, None, 0, None, None, None, p(scr), force))
+    torch.cuda.synchronize()
+    return host(o), host(lse), host(gq), host(gkv)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("what", ["k", "v", "q", "d"])
+@pytest.mark.parametrize("B,H,T,Mv,dh,pos", [(1, 2, 96, 0, 64, 40), (2, 1, 70, 5, 41, 69), (1, 1, 33, 20, 32, 0), (1, 2, 20, 0, 7, 13), (2, 1, 64, 0, 64, 31)])
+def test_attention_f32_non_finite_rows(B, H, T, Mv, dh, pos, what, value):
+    """An infinity or NaN at one position reaches what depends on it and nothing else (keys and values the queries that
+    see them, queries and output gradients the keys they see): the matrix-core kernels against the per-row ones, which
+    never touch what is not visible.  Finite values to the fp32 bound of _attn_case."""
+    rng = np.random.default_rng(T + pos)
+    S, d = Mv + T, H * dh
+    q, kv, do = (rng.standard_normal((B, n, m)).astype(np.float32) for n, m in ((T, d), (S, 2 * d), (T, d)))
+    at = {"k": kv[B - 1, :, :d], "v": kv[B - 1, :, d:], "q": q[B - 1], "d": do[B - 1]}[what]
+    at[Mv + pos if what in "kv" else pos] = value
+    got, ref = (_attn_f32(q, kv, do, B, H, T, Mv, dh, force) for force in (0, 1))
+    assert any(not np.isfinite(r).all() for r in ref)
+    for name, x, y in zip(("o", "lse", "dq", "dkv"), got, ref):
+        fin = np.isfinite(y)
+        assert np.array_equal(np.isfinite(x), fin), name
+        assert not fin.any() or rel_err(x[fin], y[fin]) < 2 * TOL[0], name
+
+
 @pytest.mark.parametrize("dtype,force", [(0, 0), (1, 1), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
 @pytest.mark.parametrize("M,N,K,ln", [(200, 136, 328, 1), (384, 520, 192, 1), (130, 88, 128, 0), (260, 256, 64, 1)])
 def test_gemm_with_fp32_layernorm_residual(dtype, force, M, N, K, ln):
