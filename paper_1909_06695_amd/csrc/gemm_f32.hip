@@ -50,28 +50,93 @@ __device__ __forceinline__ void f32_load(const void* base, int bytes, char* dst,
   else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 4, voff, soff, 0, 0);
 }
 
-// The fragment of four steps (group j) of the 32-row tile at LDS address `a` (lane term included).  Inline assembly: the
-// compiler cannot tell an LDS read from the target of the direct loads in flight and would drain those first.
-template <int ROWS, bool COL>
+// The fragment of four steps (group j) of a 32-row tile.
+template <bool COL>
 struct F32Frag {
   f32x4 v;
   float c[4];
-  template <int J> __device__ __forceinline__ void read(const uint32_t (&a)[4]) {
-    if constexpr (!COL) {
-      asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(a[J]));
-    } else {
-      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[0]) : "v"(a[0]), "n"((8 * J + 0) * ROWS * 4));
-      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[1]) : "v"(a[0]), "n"((8 * J + 1) * ROWS * 4));
-      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[2]) : "v"(a[0]), "n"((8 * J + 2) * ROWS * 4));
-      asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(c[3]) : "v"(a[0]), "n"((8 * J + 3) * ROWS * 4));
-    }
-  }
-  __device__ __forceinline__ void tie() {
-    if constexpr (!COL) asm volatile("" : "+v"(v));
-    else asm volatile("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
-  }
   __device__ __forceinline__ float get(int s) const { return COL ? c[s] : v[s]; }
 };
+// The fragments of a K-tile of both operands, ra and rb their address registers (column form: one, k-rows ROWS floats
+// apart).  Inline assembly, because the compiler cannot tell an LDS read from the target of the direct loads in flight and
+// would drain those first; the reads and the wait for them are one block, so that no register of a read under way is the
+// compiler's to move or use.
+#define OURO_F32_A_ROW_TEXT                                                                          \
+  "ds_read_b128 %[a0], %[ra0]\n\t" "ds_read_b128 %[a1], %[ra1]\n\t" "ds_read_b128 %[a2], %[ra2]\n\t" \
+  "ds_read_b128 %[a3], %[ra3]\n\t"
+#define OURO_F32_A_ROW_OUT                                                       \
+  [a0] "=&v"(a[0].v), [a1] "=&v"(a[1].v), [a2] "=&v"(a[2].v), [a3] "=&v"(a[3].v)
+#define OURO_F32_A_ROW_IN                                                \
+  [ra0] "v"(ra[0]), [ra1] "v"(ra[1]), [ra2] "v"(ra[2]), [ra3] "v"(ra[3])
+#define OURO_F32_A_COL_TEXT                                                                     \
+  "ds_read_b32 %[a0], %[ra0] offset:%[k0]\n\t" "ds_read_b32 %[a1], %[ra0] offset:%[k1]\n\t"     \
+  "ds_read_b32 %[a2], %[ra0] offset:%[k2]\n\t" "ds_read_b32 %[a3], %[ra0] offset:%[k3]\n\t"     \
+  "ds_read_b32 %[a4], %[ra0] offset:%[k4]\n\t" "ds_read_b32 %[a5], %[ra0] offset:%[k5]\n\t"     \
+  "ds_read_b32 %[a6], %[ra0] offset:%[k6]\n\t" "ds_read_b32 %[a7], %[ra0] offset:%[k7]\n\t"     \
+  "ds_read_b32 %[a8], %[ra0] offset:%[k8]\n\t" "ds_read_b32 %[a9], %[ra0] offset:%[k9]\n\t"     \
+  "ds_read_b32 %[a10], %[ra0] offset:%[k10]\n\t" "ds_read_b32 %[a11], %[ra0] offset:%[k11]\n\t" \
+  "ds_read_b32 %[a12], %[ra0] offset:%[k12]\n\t" "ds_read_b32 %[a13], %[ra0] offset:%[k13]\n\t" \
+  "ds_read_b32 %[a14], %[ra0] offset:%[k14]\n\t" "ds_read_b32 %[a15], %[ra0] offset:%[k15]\n\t"
+#define OURO_F32_A_COL_OUT                                                                                           \
+  [a0] "=&v"(a[0].c[0]), [a1] "=&v"(a[0].c[1]), [a2] "=&v"(a[0].c[2]), [a3] "=&v"(a[0].c[3]), [a4] "=&v"(a[1].c[0]), \
+  [a5] "=&v"(a[1].c[1]), [a6] "=&v"(a[1].c[2]), [a7] "=&v"(a[1].c[3]), [a8] "=&v"(a[2].c[0]), [a9] "=&v"(a[2].c[1]), \
+  [a10] "=&v"(a[2].c[2]), [a11] "=&v"(a[2].c[3]), [a12] "=&v"(a[3].c[0]), [a13] "=&v"(a[3].c[1]),                    \
+  [a14] "=&v"(a[3].c[2]), [a15] "=&v"(a[3].c[3])
+#define OURO_F32_A_COL_IN \
+  [ra0] "v"(ra[0])
+#define OURO_F32_B_ROW_TEXT                                                                          \
+  "ds_read_b128 %[b0], %[rb0]\n\t" "ds_read_b128 %[b1], %[rb1]\n\t" "ds_read_b128 %[b2], %[rb2]\n\t" \
+  "ds_read_b128 %[b3], %[rb3]\n\t"
+#define OURO_F32_B_ROW_OUT                                                       \
+  [b0] "=&v"(b[0].v), [b1] "=&v"(b[1].v), [b2] "=&v"(b[2].v), [b3] "=&v"(b[3].v)
+#define OURO_F32_B_ROW_IN                                                \
+  [rb0] "v"(rb[0]), [rb1] "v"(rb[1]), [rb2] "v"(rb[2]), [rb3] "v"(rb[3])
+#define OURO_F32_B_COL_TEXT                                                                     \
+  "ds_read_b32 %[b0], %[rb0] offset:%[k0]\n\t" "ds_read_b32 %[b1], %[rb0] offset:%[k1]\n\t"     \
+  "ds_read_b32 %[b2], %[rb0] offset:%[k2]\n\t" "ds_read_b32 %[b3], %[rb0] offset:%[k3]\n\t"     \
+  "ds_read_b32 %[b4], %[rb0] offset:%[k4]\n\t" "ds_read_b32 %[b5], %[rb0] offset:%[k5]\n\t"     \
+  "ds_read_b32 %[b6], %[rb0] offset:%[k6]\n\t" "ds_read_b32 %[b7], %[rb0] offset:%[k7]\n\t"     \
+  "ds_read_b32 %[b8], %[rb0] offset:%[k8]\n\t" "ds_read_b32 %[b9], %[rb0] offset:%[k9]\n\t"     \
+  "ds_read_b32 %[b10], %[rb0] offset:%[k10]\n\t" "ds_read_b32 %[b11], %[rb0] offset:%[k11]\n\t" \
+  "ds_read_b32 %[b12], %[rb0] offset:%[k12]\n\t" "ds_read_b32 %[b13], %[rb0] offset:%[k13]\n\t" \
+  "ds_read_b32 %[b14], %[rb0] offset:%[k14]\n\t" "ds_read_b32 %[b15], %[rb0] offset:%[k15]\n\t"
+#define OURO_F32_B_COL_OUT                                                                                           \
+  [b0] "=&v"(b[0].c[0]), [b1] "=&v"(b[0].c[1]), [b2] "=&v"(b[0].c[2]), [b3] "=&v"(b[0].c[3]), [b4] "=&v"(b[1].c[0]), \
+  [b5] "=&v"(b[1].c[1]), [b6] "=&v"(b[1].c[2]), [b7] "=&v"(b[1].c[3]), [b8] "=&v"(b[2].c[0]), [b9] "=&v"(b[2].c[1]), \
+  [b10] "=&v"(b[2].c[2]), [b11] "=&v"(b[2].c[3]), [b12] "=&v"(b[3].c[0]), [b13] "=&v"(b[3].c[1]),                    \
+  [b14] "=&v"(b[3].c[2]), [b15] "=&v"(b[3].c[3])
+#define OURO_F32_B_COL_IN \
+  [rb0] "v"(rb[0])
+#define OURO_F32_KROWS                                                                                            \
+  [k0] "n"(0 * ROWS), [k1] "n"(4 * ROWS), [k2] "n"(8 * ROWS), [k3] "n"(12 * ROWS), [k4] "n"(32 * ROWS),           \
+  [k5] "n"(36 * ROWS), [k6] "n"(40 * ROWS), [k7] "n"(44 * ROWS), [k8] "n"(64 * ROWS), [k9] "n"(68 * ROWS),        \
+  [k10] "n"(72 * ROWS), [k11] "n"(76 * ROWS), [k12] "n"(96 * ROWS), [k13] "n"(100 * ROWS), [k14] "n"(104 * ROWS), \
+  [k15] "n"(108 * ROWS)
+#define OURO_F32_READ(FA, FB, ...) \
+  asm volatile(OURO_F32_A_##FA##_TEXT OURO_F32_B_##FB##_TEXT "s_waitcnt lgkmcnt(0)" \
+               : OURO_F32_A_##FA##_OUT, OURO_F32_B_##FB##_OUT : OURO_F32_A_##FA##_IN, OURO_F32_B_##FB##_IN __VA_ARGS__ : "memory")
+template <int ROWS>
+__device__ __forceinline__ void f32_read(F32Frag<false> (&a)[4], const uint32_t (&ra)[4], F32Frag<false> (&b)[4], const uint32_t (&rb)[4]) { OURO_F32_READ(ROW, ROW); }
+template <int ROWS>
+__device__ __forceinline__ void f32_read(F32Frag<false> (&a)[4], const uint32_t (&ra)[4], F32Frag<true> (&b)[4], const uint32_t (&rb)[4]) { OURO_F32_READ(ROW, COL, , OURO_F32_KROWS); }
+template <int ROWS>
+__device__ __forceinline__ void f32_read(F32Frag<true> (&a)[4], const uint32_t (&ra)[4], F32Frag<false> (&b)[4], const uint32_t (&rb)[4]) { OURO_F32_READ(COL, ROW, , OURO_F32_KROWS); }
+template <int ROWS>
+__device__ __forceinline__ void f32_read(F32Frag<true> (&a)[4], const uint32_t (&ra)[4], F32Frag<true> (&b)[4], const uint32_t (&rb)[4]) { OURO_F32_READ(COL, COL, , OURO_F32_KROWS); }
+#undef OURO_F32_READ
+#undef OURO_F32_KROWS
+#undef OURO_F32_A_ROW_TEXT
+#undef OURO_F32_A_ROW_OUT
+#undef OURO_F32_A_ROW_IN
+#undef OURO_F32_A_COL_TEXT
+#undef OURO_F32_A_COL_OUT
+#undef OURO_F32_A_COL_IN
+#undef OURO_F32_B_ROW_TEXT
+#undef OURO_F32_B_ROW_OUT
+#undef OURO_F32_B_ROW_IN
+#undef OURO_F32_B_COL_TEXT
+#undef OURO_F32_B_COL_OUT
+#undef OURO_F32_B_COL_IN
 // Address registers of the 32-row tile that starts at row t0: row form one per group, column form one.
 template <int ROWS, bool COL>
 __device__ __forceinline__ void f32_addresses(uint32_t base, int t0, int lane, uint32_t (&a)[4]) {
@@ -144,16 +209,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
       __builtin_amdgcn_sched_barrier(0);
     }
     if (it + S - 1 < nk) request(it + S - 1, fill);              // the stage read one K-tile ago (its reads were waited for)
-    F32Frag<T, TA> fa[4];
-    F32Frag<T, !TB> fb[4];
+    F32Frag<TA> fa[4];
+    F32Frag<!TB> fb[4];
     uint32_t va[4], vb[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) { va[j] = ra[j] + rd * STAGE; vb[j] = rb[j] + rd * STAGE; }
-    fa[0].template read<0>(va); fb[0].template read<0>(vb); fa[1].template read<1>(va); fb[1].template read<1>(vb);
-    fa[2].template read<2>(va); fb[2].template read<2>(vb); fa[3].template read<3>(va); fb[3].template read<3>(vb);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { fa[j].tie(); fb[j].tie(); }
+    f32_read<T>(fa, va, fb, vb);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll

@@ -18,8 +18,8 @@
 //     1    A0, B1                A0 x B0, A0 x B1      A1 of K-tile kt+1, B0 of kt+2     (both halves were last read in the phase before)
 //     2    A1, B0 of kt+1        A1 x B1, A1 x B0      A0 and B1 of kt+2                 (likewise)
 //
-// and a phase is: read; request; wait for the fragments and for the halves that the next phase reads; barrier; multiply;
-// barrier.  Waves 4-7 run one barrier behind waves 0-3, so one group's multiplications coincide with the other group's
+// and a phase is: read the fragments and wait for them; request; wait for the halves that the next phase reads; barrier;
+// multiply; barrier (requests ahead of the reads delay them: 3 % on dV_o).  Waves 4-7 run one barrier behind waves 0-3, so one group's multiplications coincide with the other group's
 // reads.  Every wave waits for its fragments before the barrier inside the phase: a wave that has begun the next phase
 // knows that all eight have read what this phase reads, which is what the refill needs.  A request has two phases of both
 // groups' matrix work to arrive in.
@@ -76,42 +76,100 @@ struct PpOperand {
   }
 };
 
-// A fragment as it leaves LDS (two transposing reads in column form).  Reads are inline assembly: the compiler cannot
-// tell an LDS read from the target of the direct loads in flight and would drain those first.  A fragment may only be
-// used after pp_wait_lds() and tie().
+// A fragment as it leaves LDS (two transposing reads in column form).
 template <bool COL> struct PpFrag;
 template <> struct PpFrag<false> {
   u32x4 v;
-  template <int OFF> __device__ __forceinline__ void read(uint32_t a) { asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a), "n"(OFF)); }
-  __device__ __forceinline__ void tie() { asm volatile("" : "+v"(v)); }
   __device__ __forceinline__ bf16x8 get() const { return __builtin_bit_cast(bf16x8, v); }
 };
 template <> struct PpFrag<true> {
   u32x2 lo, hi;
-  template <int OFF> __device__ __forceinline__ void read(uint32_t a) {
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(a), "n"(OFF));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a), "n"(OFF + 1024));
-  }
-  __device__ __forceinline__ void tie() { asm volatile("" : "+v"(lo), "+v"(hi)); }
   __device__ __forceinline__ bf16x8 get() const { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3)); }
 };
-__device__ __forceinline__ void pp_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 template <int N> __device__ __forceinline__ void pp_wait_mem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-// f[ks][t]: the fragments of the wave's T tiles of the half at LDS offset BASE, for the four k steps.
-template <int BASE, int T, int I = 0>
-__device__ __forceinline__ void pp_fetch(PpFrag<false> (&f)[4][T], const uint32_t* a) {
-  if constexpr (I < 4 * T) { f[I / T][I % T].template read<BASE + (I % T) * 4096>(a[I / T]); pp_fetch<BASE, T, I + 1>(f, a); }
+// The fragments of a phase: a[ks][t], the wave's two tiles of the half of A at LDS offset BA, and b[ks][0], its tile of the
+// half of B at BB, for the four k steps.  Inline assembly, because the compiler cannot tell an LDS read from the target of
+// the direct loads in flight and would drain those first; the reads and the wait for them are one block, so that no
+// register of a read under way is the compiler's to move or use.
+#define OURO_PP_A_ROW_TEXT                                                                      \
+  "ds_read_b128 %[a0], %[ra0] offset:%[oa0]\n\t" "ds_read_b128 %[a1], %[ra0] offset:%[oa1]\n\t" \
+  "ds_read_b128 %[a2], %[ra1] offset:%[oa0]\n\t" "ds_read_b128 %[a3], %[ra1] offset:%[oa1]\n\t" \
+  "ds_read_b128 %[a4], %[ra2] offset:%[oa0]\n\t" "ds_read_b128 %[a5], %[ra2] offset:%[oa1]\n\t" \
+  "ds_read_b128 %[a6], %[ra3] offset:%[oa0]\n\t" "ds_read_b128 %[a7], %[ra3] offset:%[oa1]\n\t"
+#define OURO_PP_A_ROW_OUT                                                                                            \
+  [a0] "=&v"(a[0][0].v), [a1] "=&v"(a[0][1].v), [a2] "=&v"(a[1][0].v), [a3] "=&v"(a[1][1].v), [a4] "=&v"(a[2][0].v), \
+  [a5] "=&v"(a[2][1].v), [a6] "=&v"(a[3][0].v), [a7] "=&v"(a[3][1].v)
+#define OURO_PP_A_ROW_IN                                                                                      \
+  [ra0] "v"(ra[0]), [ra1] "v"(ra[1]), [ra2] "v"(ra[2]), [ra3] "v"(ra[3]), [oa0] "n"(BA), [oa1] "n"(BA + 4096)
+#define OURO_PP_A_COL_TEXT                                                                                    \
+  "ds_read_b64_tr_b16 %[a0], %[ra0] offset:%[oa0]\n\t" "ds_read_b64_tr_b16 %[a1], %[ra0] offset:%[oa1]\n\t"   \
+  "ds_read_b64_tr_b16 %[a2], %[ra1] offset:%[oa0]\n\t" "ds_read_b64_tr_b16 %[a3], %[ra1] offset:%[oa1]\n\t"   \
+  "ds_read_b64_tr_b16 %[a4], %[ra0] offset:%[oa2]\n\t" "ds_read_b64_tr_b16 %[a5], %[ra0] offset:%[oa3]\n\t"   \
+  "ds_read_b64_tr_b16 %[a6], %[ra1] offset:%[oa2]\n\t" "ds_read_b64_tr_b16 %[a7], %[ra1] offset:%[oa3]\n\t"   \
+  "ds_read_b64_tr_b16 %[a8], %[ra0] offset:%[oa4]\n\t" "ds_read_b64_tr_b16 %[a9], %[ra0] offset:%[oa5]\n\t"   \
+  "ds_read_b64_tr_b16 %[a10], %[ra1] offset:%[oa4]\n\t" "ds_read_b64_tr_b16 %[a11], %[ra1] offset:%[oa5]\n\t" \
+  "ds_read_b64_tr_b16 %[a12], %[ra0] offset:%[oa6]\n\t" "ds_read_b64_tr_b16 %[a13], %[ra0] offset:%[oa7]\n\t" \
+  "ds_read_b64_tr_b16 %[a14], %[ra1] offset:%[oa6]\n\t" "ds_read_b64_tr_b16 %[a15], %[ra1] offset:%[oa7]\n\t"
+#define OURO_PP_A_COL_OUT                                                                            \
+  [a0] "=&v"(a[0][0].lo), [a1] "=&v"(a[0][0].hi), [a2] "=&v"(a[0][1].lo), [a3] "=&v"(a[0][1].hi),    \
+  [a4] "=&v"(a[1][0].lo), [a5] "=&v"(a[1][0].hi), [a6] "=&v"(a[1][1].lo), [a7] "=&v"(a[1][1].hi),    \
+  [a8] "=&v"(a[2][0].lo), [a9] "=&v"(a[2][0].hi), [a10] "=&v"(a[2][1].lo), [a11] "=&v"(a[2][1].hi),  \
+  [a12] "=&v"(a[3][0].lo), [a13] "=&v"(a[3][0].hi), [a14] "=&v"(a[3][1].lo), [a15] "=&v"(a[3][1].hi)
+#define OURO_PP_A_COL_IN                                                                                         \
+  [ra0] "v"(ra[0]), [ra1] "v"(ra[1]), [oa0] "n"(BA + 0), [oa1] "n"(BA + 1024), [oa2] "n"(BA + 4096),             \
+  [oa3] "n"(BA + 5120), [oa4] "n"(BA + 8192), [oa5] "n"(BA + 9216), [oa6] "n"(BA + 12288), [oa7] "n"(BA + 13312)
+#define OURO_PP_B_ROW_TEXT                                                                      \
+  "ds_read_b128 %[b0], %[rb0] offset:%[ob0]\n\t" "ds_read_b128 %[b1], %[rb1] offset:%[ob0]\n\t" \
+  "ds_read_b128 %[b2], %[rb2] offset:%[ob0]\n\t" "ds_read_b128 %[b3], %[rb3] offset:%[ob0]\n\t"
+#define OURO_PP_B_ROW_OUT                                                                    \
+  [b0] "=&v"(b[0][0].v), [b1] "=&v"(b[1][0].v), [b2] "=&v"(b[2][0].v), [b3] "=&v"(b[3][0].v)
+#define OURO_PP_B_ROW_IN                                                                \
+  [rb0] "v"(rb[0]), [rb1] "v"(rb[1]), [rb2] "v"(rb[2]), [rb3] "v"(rb[3]), [ob0] "n"(BB)
+#define OURO_PP_B_COL_TEXT                                                                                  \
+  "ds_read_b64_tr_b16 %[b0], %[rb0] offset:%[ob0]\n\t" "ds_read_b64_tr_b16 %[b1], %[rb0] offset:%[ob1]\n\t" \
+  "ds_read_b64_tr_b16 %[b2], %[rb0] offset:%[ob2]\n\t" "ds_read_b64_tr_b16 %[b3], %[rb0] offset:%[ob3]\n\t" \
+  "ds_read_b64_tr_b16 %[b4], %[rb0] offset:%[ob4]\n\t" "ds_read_b64_tr_b16 %[b5], %[rb0] offset:%[ob5]\n\t" \
+  "ds_read_b64_tr_b16 %[b6], %[rb0] offset:%[ob6]\n\t" "ds_read_b64_tr_b16 %[b7], %[rb0] offset:%[ob7]\n\t"
+#define OURO_PP_B_COL_OUT                                                                         \
+  [b0] "=&v"(b[0][0].lo), [b1] "=&v"(b[0][0].hi), [b2] "=&v"(b[1][0].lo), [b3] "=&v"(b[1][0].hi), \
+  [b4] "=&v"(b[2][0].lo), [b5] "=&v"(b[2][0].hi), [b6] "=&v"(b[3][0].lo), [b7] "=&v"(b[3][0].hi)
+#define OURO_PP_B_COL_IN                                                                                 \
+  [rb0] "v"(rb[0]), [ob0] "n"(BB + 0), [ob1] "n"(BB + 1024), [ob2] "n"(BB + 4096), [ob3] "n"(BB + 5120), \
+  [ob4] "n"(BB + 8192), [ob5] "n"(BB + 9216), [ob6] "n"(BB + 12288), [ob7] "n"(BB + 13312)
+#define OURO_PP_READ(FA, FB) \
+  asm volatile(OURO_PP_A_##FA##_TEXT OURO_PP_B_##FB##_TEXT "s_waitcnt lgkmcnt(0)" \
+               : OURO_PP_A_##FA##_OUT, OURO_PP_B_##FB##_OUT : OURO_PP_A_##FA##_IN, OURO_PP_B_##FB##_IN : "memory")
+template <int BA, int BB>
+__device__ __forceinline__ void pp_read(PpFrag<false> (&a)[4][2], const uint32_t* ra, PpFrag<false> (&b)[4][1], const uint32_t* rb) { OURO_PP_READ(ROW, ROW); }
+template <int BA, int BB>
+__device__ __forceinline__ void pp_read(PpFrag<false> (&a)[4][2], const uint32_t* ra, PpFrag<true> (&b)[4][1], const uint32_t* rb) { OURO_PP_READ(ROW, COL); }
+template <int BA, int BB>
+__device__ __forceinline__ void pp_read(PpFrag<true> (&a)[4][2], const uint32_t* ra, PpFrag<false> (&b)[4][1], const uint32_t* rb) { OURO_PP_READ(COL, ROW); }
+template <int BA, int BB>
+__device__ __forceinline__ void pp_read(PpFrag<true> (&a)[4][2], const uint32_t* ra, PpFrag<true> (&b)[4][1], const uint32_t* rb) { OURO_PP_READ(COL, COL); }
+// B alone
+template <int BB>
+__device__ __forceinline__ void pp_read(PpFrag<false> (&b)[4][1], const uint32_t* rb) {
+  asm volatile(OURO_PP_B_ROW_TEXT "s_waitcnt lgkmcnt(0)" : OURO_PP_B_ROW_OUT : OURO_PP_B_ROW_IN : "memory");
 }
-template <int BASE, int T, int I = 0>
-__device__ __forceinline__ void pp_fetch(PpFrag<true> (&f)[4][T], const uint32_t* a) {
-  if constexpr (I < 4 * T) { f[I / T][I % T].template read<BASE + (I / T) * 4096>(a[I % T]); pp_fetch<BASE, T, I + 1>(f, a); }
+template <int BB>
+__device__ __forceinline__ void pp_read(PpFrag<true> (&b)[4][1], const uint32_t* rb) {
+  asm volatile(OURO_PP_B_COL_TEXT "s_waitcnt lgkmcnt(0)" : OURO_PP_B_COL_OUT : OURO_PP_B_COL_IN : "memory");
 }
-template <bool COL, int T>
-__device__ __forceinline__ void pp_tie(PpFrag<COL> (&f)[4][T]) {
-#pragma unroll
-  for (int i = 0; i < 4 * T; ++i) f[i / T][i % T].tie();
-}
+#undef OURO_PP_READ
+#undef OURO_PP_A_ROW_TEXT
+#undef OURO_PP_A_ROW_OUT
+#undef OURO_PP_A_ROW_IN
+#undef OURO_PP_A_COL_TEXT
+#undef OURO_PP_A_COL_OUT
+#undef OURO_PP_A_COL_IN
+#undef OURO_PP_B_ROW_TEXT
+#undef OURO_PP_B_ROW_OUT
+#undef OURO_PP_B_ROW_IN
+#undef OURO_PP_B_COL_TEXT
+#undef OURO_PP_B_COL_OUT
+#undef OURO_PP_B_COL_IN
 // plain hardware barrier: a fenced one would drain the loads in flight
 __device__ __forceinline__ void pp_barrier() {
   __builtin_amdgcn_sched_barrier(0);
@@ -161,18 +219,14 @@ __device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0,
   if (nk > 1) { reqB(1, 0, kb + stepB); reqA(1, 0, ka + stepA); reqB(1, 1, kb + stepB); pp_wait_mem<8>(); }
   else pp_wait_mem<2>();                           // all but A1 (and K-tile 1)
   pp_barrier();
-  pp_fetch<0, 1>(fb0[0], rb);
-  pp_wait_lds();
-  pp_tie(fb0[0]);
+  pp_read<0>(fb0[0], rb);
   pp_barrier();                                    // B0 of stage 0 may be refilled
   if (wm == 1) pp_barrier();                       // the second group stays one barrier behind
 #define OURO_PP_TILE(ST)                                                                                     \
   do {                                                                                                       \
-    pp_fetch<2 * (ST) * PP_HALF, 2>(fa, ra);                                                                 \
-    pp_fetch<(2 * (ST) + 1) * PP_HALF, 1>(fb1, rb);                                                          \
+    pp_read<2 * (ST) * PP_HALF, (2 * (ST) + 1) * PP_HALF>(fa, ra, fb1, rb);                                  \
     if (kt + 1 < nk) reqA(1 - (ST), 1, ka + stepA);                                                          \
     if (kt + 2 < nk) reqB(ST, 0, kb + 2 * stepB);                                                            \
-    pp_wait_lds(); pp_tie(fa); pp_tie(fb1);                                                                  \
     if (kt + 2 < nk) pp_wait_mem<8>();                                                                       \
     else if (kt + 1 < nk) pp_wait_mem<2>();         /* A1 of kt+1 may be under way */                        \
     else pp_wait_mem<0>();                                                                                   \
@@ -181,10 +235,9 @@ __device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0,
     mul(0, 0, fb0[ST]); mul(0, 1, fb1);                                                                      \
     __builtin_amdgcn_s_setprio(0);                                                                           \
     pp_barrier();                                                                                            \
-    pp_fetch<(2 * (ST) + 1) * PP_HALF, 2>(fa, ra);                                                           \
-    pp_fetch<2 * (1 - (ST)) * PP_HALF, 1>(fb0[1 - (ST)], rb);   /* past the last K-tile: never used */       \
+    /* past the last K-tile: B0 is never used */                                                             \
+    pp_read<(2 * (ST) + 1) * PP_HALF, 2 * (1 - (ST)) * PP_HALF>(fa, ra, fb0[1 - (ST)], rb);                  \
     if (kt + 2 < nk) { reqA(ST, 0, ka + 2 * stepA); reqB(ST, 1, kb + 2 * stepB); }                           \
-    pp_wait_lds(); pp_tie(fa); pp_tie(fb0[1 - (ST)]);                                                        \
     if (kt + 2 < nk) pp_wait_mem<8>();                                                                       \
     else pp_wait_mem<0>();                                                                                   \
     pp_barrier();                                                                                            \

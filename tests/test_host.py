@@ -105,6 +105,21 @@ def test_contraction_operands_end_at_their_last_element(dtype, esz):
     assert f(dtype, 1 << 20, 8, 1 << 14) == esz * (((1 << 20) - 1) * (1 << 14) + 8)
 
 
+def test_reads_in_inline_assembly_wait_in_their_own_block():
+    """The compiler takes the output registers of an asm block as written when the block ends: a load that is still under
+    way then could be overtaken by whatever the compiler puts into them."""
+    csrc = os.path.join(ROOT, "paper_1909_06695_amd", "csrc")
+    reads = r"\b(ds_read|ds_load|global_load|buffer_load|flat_load|s_load)|_TEXT\b"      # ..._TEXT: lists of reads
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        text = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, name)).read())
+        for block in re.findall(r"asm volatile\((.*?)\)\s*(?:;|\n)", text, flags=re.S):
+            if re.search(reads, block):
+                found += 1
+                assert "s_waitcnt" in block, (name, block[:80])
+    assert found >= 4
+
+
 def test_lr_schedule_matches_the_oracle():
     """The library's host-side step-size function against the oracle's, over both phases and
     the boundaries (both fp64: agreement to rounding); bad arguments are refused."""
