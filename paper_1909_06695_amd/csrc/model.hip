@@ -703,6 +703,17 @@ static int refresh_transposed(ouro_model* m, int group, hipStream_t st) {
   return OURO_OK;
 }
 
+// Whether a kernel on the model's GPU may work on the caller's memory: device memory of that GPU, on a float's boundary.  A
+// pointer to anything else that counts as device memory to a copy (another GPU's, pinned or managed memory) is only ever copied.
+static bool on_model_device(const ouro_model* m, const void* p) {
+  hipPointerAttribute_t a, mine;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipPointerGetAttributes(&mine, m->arena) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && !a.isManaged && a.device == mine.device && !((uintptr_t)p & 3);
+}
+
 // Padded models, device memory both: the caller's dense blob <-> the stored layout, on the model's stream.
 static int remap_on_device(ouro_model* m, int group, float* blob, bool to_stored) {
   const std::vector<RemapEntry>& r = m->remaps[group];
@@ -715,14 +726,21 @@ extern "C" int ouro_set_params(ouro_model* m, int group, const float* src, int64
   if (!m || !src || group < 0 || group > m->cfg.n_module) return fail(OURO_E_ARG, "set_params: bad argument");
   if (n != m->count[group]) return fail(OURO_E_ARG, "set_params: group %d has %lld elements, got %lld", group, (long long)m->count[group], (long long)n);
   if (m->padded) {
-    std::vector<float> stored;
-    if (src_is_device) {
+    std::vector<float> blob, stored;
+    if (src_is_device && on_model_device(m, src)) {
       // padding included: it is zero from the arena's clear on, except in a state that was saved with other values there
       HIPCHK(launch_fill_zero(m->stream, m->master[group], (size_t)m->pcount[group] * 4));
       RUN(remap_on_device(m, group, const_cast<float*>(src), true));
     } else {
+      const float* hsrc = src;
+      if (src_is_device) {
+        blob.resize((size_t)n);
+        HIPCHK(hipMemcpyAsync(blob.data(), src, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
+        HIPCHK(hipStreamSynchronize(m->stream));
+        hsrc = blob.data();
+      }
       stored.assign((size_t)m->pcount[group], 0.f);
-      remap_group(m, group, stored.data(), const_cast<float*>(src), true);
+      remap_group(m, group, stored.data(), const_cast<float*>(hsrc), true);
       HIPCHK(hipMemcpyAsync(m->master[group], stored.data(), stored.size() * 4, hipMemcpyHostToDevice, m->stream));
     }
     HIPCHK(launch_convert(m->stream, 1, m->shadow[group], m->master[group], (size_t)m->pcount[group]));
@@ -741,15 +759,19 @@ extern "C" int ouro_get_params(ouro_model* m, int group, float* dst, int64_t n, 
   if (!m || !dst || group < 0 || group > m->cfg.n_module) return fail(OURO_E_ARG, "get_params: bad argument");
   if (n != m->count[group]) return fail(OURO_E_ARG, "get_params: wrong element count");
   if (m->padded) {
-    if (dst_is_device) {
+    if (dst_is_device && on_model_device(m, dst)) {
       RUN(remap_on_device(m, group, dst, false));
       HIPCHK(hipStreamSynchronize(m->stream));
       return OURO_OK;
     }
-    std::vector<float> stored((size_t)m->pcount[group]);
+    std::vector<float> stored((size_t)m->pcount[group]), blob;
     HIPCHK(hipMemcpyAsync(stored.data(), m->master[group], stored.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIPCHK(hipStreamSynchronize(m->stream));
-    remap_group(m, group, stored.data(), dst, false);
+    if (!dst_is_device) { remap_group(m, group, stored.data(), dst, false); return OURO_OK; }
+    blob.resize((size_t)n);
+    remap_group(m, group, stored.data(), blob.data(), false);
+    HIPCHK(hipMemcpyAsync(dst, blob.data(), (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+    HIPCHK(hipStreamSynchronize(m->stream));
     return OURO_OK;
   }
   HIPCHK(hipMemcpyAsync(dst, m->master[group], (size_t)n * 4, dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, m->stream));

@@ -841,6 +841,28 @@ def test_padded_params_on_device(rel, mem, d, heads, dh, F, vocab):
     a.close(), b.close()
 
 
+def test_padded_params_in_other_memory():
+    """Sources and destinations that no kernel of the model should touch (pinned host memory given as device memory, an
+    address off a float's boundary) are copied: the same values as by the host route."""
+    c = dict(n_layer=2, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=73, seq_len=9, mem_len=0, batch=2, n_module=2, rel_pos=0, dtype=1, optimizer=1)
+    m = P().create_model(device="cuda:0", **c)
+    rng = np.random.default_rng(6)
+    for g in range(3):
+        n = m.param_count(g)
+        for make in (lambda: torch.empty(4 * n + 2, dtype=torch.uint8, pin_memory=True), lambda: torch.empty(4 * n + 2, dtype=torch.uint8, device="cuda")):
+            for off in (0, 2):
+                blob = rng.standard_normal(n).astype(np.float32)
+                src, dst = make(), make()
+                src[off:off + 4 * n] = torch.from_numpy(blob.view(np.uint8))
+                torch.cuda.synchronize()
+                assert m.L.ouro_set_params(m.h, g, C.c_void_p(src.data_ptr() + off), n, 1) == 0
+                assert np.array_equal(m.get_params(g), blob)
+                assert m.L.ouro_get_params(m.h, g, C.c_void_p(dst.data_ptr() + off), n, 1) == 0
+                torch.cuda.synchronize()
+                assert dst[off:off + 4 * n].cpu().numpy().tobytes() == blob.tobytes()
+    m.close()
+
+
 @pytest.mark.parametrize("d,heads,dh,F,N,dtype,drop", [
     (128, 2, 64, 192, 70, 1, 0.0), (576, 9, 64, 128, 33, 1, 0.125), (1088, 17, 64, 1088, 40, 1, 0.125),   # 1, 2 and 4 groups per lane
     (82, 2, 41, 100, 70, 1, 0.125), (320, 4, 80, 100, 70, 1, 0.0),                                         # padded; unpadded, ragged columns
