@@ -266,16 +266,16 @@ __device__ __forceinline__ void mfma_accumulate(const GemmParams& p, f32x16 (&ac
       }
     }
 }
-template <int TM, int TN, int CS = 32>
-__device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)[TM][TN], uint4* smem, int m_w, int n_w,
-                                              int lane, int wave) {
-  if (p.accumulate) { mfma_accumulate<TM, TN, CS>(p, acc, m_w, n_w, lane); return; }
+// SUM: with column sums (p.colsum).
+template <int TM, int TN, int CS, bool SUM>
+__device__ __forceinline__ void mfma_epilogue_rows(const GemmParams& p, f32x16 (&acc)[TM][TN], uint4* smem, int m_w, int n_w,
+                                                   int lane, int wave) {
   float* stage = reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<TN>();
   const int h32 = lane >> 5, l32 = lane & 31;
   const int srow = lane >> 2, scol = (lane & 3) * 8;
-  float cs[TN][8];                                 // the lane's share of the column sums
+  float cs[SUM ? TN : 1][8];                       // the lane's share of the column sums
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
+  for (int j = 0; j < (SUM ? TN : 1); ++j)
 #pragma unroll
     for (int e = 0; e < 8; ++e) cs[j][e] = 0.f;
 #pragma unroll
@@ -300,34 +300,44 @@ __device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)
           float4 hi = *reinterpret_cast<const float4*>(src + 4);
           float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
           epilogue_store8(p, m, n, v);
+          if (SUM) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) cs[j][e] += v[e];
+            for (int e = 0; e < 8; ++e) cs[SUM ? j : 0][e] += v[e];
+          }
         } else {
 #pragma unroll 1
           for (int e = 0; e < 8; ++e)
             if (n + e < p.N) {
               const float v = epilogue_store<bf16_t>(p, m, n + e, src[e]);
-              if (p.colsum) unsafeAtomicAdd(epilogue_colsum(p) + n + e, v);
+              if (SUM) unsafeAtomicAdd(epilogue_colsum(p) + n + e, v);
             }
         }
       }
     }
     __builtin_amdgcn_wave_barrier();
   }
-  if (p.colsum) {
+  if (SUM) {
     // lanes of equal lane % 4 hold the same columns
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n_w + j * CS + scol;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        float t = cs[j][e];
+        float t = cs[SUM ? j : 0][e];
 #pragma unroll
         for (int o = 4; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
         if (lane < 4 && p.vec_epi && n + 8 <= p.N) unsafeAtomicAdd(epilogue_colsum(p) + n + e, t);
       }
     }
   }
+}
+
+template <int TM, int TN, int CS = 32>
+__device__ __forceinline__ void mfma_epilogue(const GemmParams& p, f32x16 (&acc)[TM][TN], uint4* smem, int m_w, int n_w,
+                                              int lane, int wave) {
+  if (p.accumulate) mfma_accumulate<TM, TN, CS>(p, acc, m_w, n_w, lane);
+  else if (p.colsum) mfma_epilogue_rows<TM, TN, CS, true>(p, acc, smem, m_w, n_w, lane, wave);
+  else mfma_epilogue_rows<TM, TN, CS, false>(p, acc, smem, m_w, n_w, lane, wave);
 }
 
 }  // namespace ouro

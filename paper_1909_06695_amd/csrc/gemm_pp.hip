@@ -265,9 +265,9 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(GemmParams p) {
   const int nk = (min(p.K, kbeg + p.kchunk) - kbeg + PP_BK - 1) / PP_BK;
   f32x16 acc[2][2][2];
   pp_mainloop<TA, TB>(p, m0, n0, kbeg, nk, reinterpret_cast<char*>(smem), acc);
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-    mfma_epilogue<2, 2, 128>(p, acc[h], smem, m0 + 128 * h + 64 * (wave >> 2), n0 + 32 * (wave & 3), lane, wave);
+  const int m_w = m0 + 64 * (wave >> 2), n_w = n0 + 32 * (wave & 3);
+  mfma_epilogue<2, 2, 128>(p, acc[0], smem, m_w, n_w, lane, wave);
+  mfma_epilogue<2, 2, 128>(p, acc[1], smem, m_w + 128, n_w, lane, wave);
 }
 
 // Several accumulating products in one launch (weight gradients of a layer).  Product i owns the work items
