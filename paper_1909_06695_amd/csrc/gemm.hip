@@ -201,6 +201,93 @@ static hipError_t launch_mfma_cfg(hipStream_t s, GemmParams& p, int transA, int 
   return hipGetLastError();
 }
 
+// Tile configuration and contraction ranges of a product (of each of `products` in a launch) on the MFMA kernels.
+struct GemmPlan { int cfg, splits, kchunk; bool direct_ok; };
+static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& plan) {
+  int cfg = force >= 2 ? force : -1;
+  if (cfg < 0) {
+    // 128x128 tiles (8 waves, two workgroups per CU) when they fill the chip at least twice
+    // over; with one tile per CU and a long contraction the register-prefetch kernel with its
+    // four-stage ring; otherwise, and for the split-K weight gradients, 128x64 tiles, which
+    // put more workgroups on every compute unit
+    const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+    // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are several per CU (the logits),
+    // one per CU with a long contraction (dV_o: 670 -> 592 us), or whole rounds of them: two rounds of a contraction over
+    // 1024 with the GELU epilogues take 94 us against 101 us of four rounds of 128x128 tiles, one and a half rounds
+    // (8192 x 3072 x 1024) 69 us against 57 us of three
+    // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
+    // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
+    // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
+    // over 256 5.2 -> 4.5; beyond one round 768 x 4096 over 1024 16.7 -> 20.1, 4800 x 640 over 448 9.9 -> 10.4.
+    const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
+    const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
+    if (!g.accumulate && t64 <= 512) cfg = GEMM_TILE_64x64;
+    // One round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles, three
+    // stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue: 8192 x 1024 over
+    // 4096 81 -> 68 us, 6144 x 1024 over 4096 69 -> 60, over 2048 34.7 -> 32.5; over 1024 24.1 -> 24.4.
+    else if (!g.accumulate && g.K >= 2048 && t128x256 >= 160 && t128x256 <= 256) cfg = GEMM_TILE_128x256;
+    else if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
+    else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
+    else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * products <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
+    else cfg = GEMM_TILE_128x128;
+  }
+  const size_t bytesA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
+  // direct global->LDS loads need 32-bit operand offsets, and whole 64-wide K tiles unless the contraction index is
+  // the slow dimension of both operands (the k-rows past the end of an operand read as zero)
+  const bool direct_ok = direct_k_ok(g.transA, g.transB, g.K) && bytesA < (1ull << 31) && bytesB < (1ull << 31);
+  int splits = 1;
+  bool modelled = false;
+  if (g.accumulate && force < 2 && direct_ok && g.K >= 512) {
+    modelled = true;
+    // Split-K launch: tile shape and number of K ranges together, so that the grid fills the
+    // chip in whole rounds.  Cost of a candidate in us, as in launch_gemm_group: a round of 128x128
+    // tiles, two workgroups per CU, takes 1.2 per K-tile and 6 K-tiles besides (ring fill, atomic
+    // adds); 128x64 tiles, three per CU, do the same work at 0.8 of that rate (more operand bytes
+    // per flop).  256x256 tiles take 1.45 per K-tile, 6 for the launch, and their atomic adds in full (310 per ns):
+    // nothing else runs on the CU meanwhile.  256 x 4232 over 7488 47 us on 128x128 tiles against 82, 4472 x 5312 over 3200
+    // 205 against 246; 8192 x 1024 over 50304 578 on 256x256 ones against 874.
+    double best = 1e30;
+    for (int c = 0; c < 3; ++c) {
+      const int bm = c == 2 ? 256 : 128, bn = c == 2 ? 256 : c ? 64 : 128, per_cu = c == 2 ? 1 : c ? 3 : 2;
+      const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * products;
+      const int max_s = std::min(16, g.K / 256);
+      for (int sp = 1; sp <= max_s; ++sp) {
+        const int kc = ((g.K + sp - 1) / sp + 63) / 64 * 64;
+        const int real = (g.K + kc - 1) / kc;
+        if (real != sp) continue;
+        const long rounds = (tiles * sp + 256L * per_cu - 1) / (256L * per_cu);
+        const double adds = (double)g.M * g.N * products * sp;
+        const double cost = c == 2 ? rounds * 1.45 * (kc / 64) + 6 + adds / 310e3 : rounds * (c ? 1.125 : 1.2) * (kc / 64 + 6);
+        if (cost < best) { best = cost; cfg = c == 2 ? GEMM_TILE_256x256 : c ? GEMM_TILE_128x64 : GEMM_TILE_128x128; splits = sp; }
+      }
+    }
+  }
+  if (!direct_ok) cfg = GEMM_TILE_STAGED128;
+  if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_128x256) return false;
+  const int BM = cfg == GEMM_TILE_256x256 ? 256 : cfg == GEMM_TILE_64x64 ? 64 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : cfg == GEMM_TILE_128x256 ? 256 : BM;
+  long tiles = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * products;
+  if (g.accumulate && !modelled && tiles < 384 && g.K >= 512) {
+    splits = (int)((512 + tiles - 1) / tiles);
+    int maxs = g.K / 256;
+    if (splits > maxs) splits = maxs;
+    if (splits < 1) splits = 1;
+  }
+  int kchunk = (g.K + splits - 1) / splits;
+  kchunk = (kchunk + 63) / 64 * 64;
+  splits = (g.K + kchunk - 1) / kchunk;
+  plan = {cfg, splits, kchunk, direct_ok};
+  return true;
+}
+int gemm_plan(int dtype, const GemmDesc& g, int* splits) {
+  GemmPlan plan;
+  *splits = 1;
+  if (!gemm_uses_mfma(dtype, g)) return 1;
+  if (!plan_mfma(g, 0, 1, plan)) return -1;
+  *splits = plan.splits;
+  return plan.cfg;
+}
+
 hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_generic) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   GemmParams p;
@@ -259,43 +346,13 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     p.vec_epi = aligned16(g.C) && !(g.ldc & oe) && (!g.residual || (aligned16(g.residual) && !(g.ldr & 7))) &&
                 (!g.res32 || (aligned16(g.res32) && !(g.ldr32 & 3))) &&
                 (g.epilogue == EPI_NONE || (aligned16(g.Z) && !(g.ldz & 7)));
-    int cfg = force_generic >= 2 ? force_generic : -1;
-    if (cfg < 0) {
-      // 128x128 tiles (8 waves, two workgroups per CU) when they fill the chip at least twice
-      // over; with one tile per CU and a long contraction the register-prefetch kernel with its
-      // four-stage ring; otherwise, and for the split-K weight gradients, 128x64 tiles, which
-      // put more workgroups on every compute unit
-      const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-      const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-      // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are several per CU (the logits),
-      // one per CU with a long contraction (dV_o: 670 -> 592 us), or whole rounds of them: two rounds of a contraction over
-      // 1024 with the GELU epilogues take 94 us against 101 us of four rounds of 128x128 tiles, one and a half rounds
-      // (8192 x 3072 x 1024) 69 us against 57 us of three
-      // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
-      // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
-      // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
-      // over 256 5.2 -> 4.5; beyond one round 768 x 4096 over 1024 16.7 -> 20.1, 4800 x 640 over 448 9.9 -> 10.4.
-      const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * by * bz * grids;
-      const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * by * bz * grids;
-      if (!g.accumulate && t64 <= 512) cfg = GEMM_TILE_64x64;
-      // One round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles, three
-      // stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue: 8192 x 1024 over
-      // 4096 81 -> 68 us, 6144 x 1024 over 4096 69 -> 60, over 2048 34.7 -> 32.5; over 1024 24.1 -> 24.4.
-      else if (!g.accumulate && g.K >= 2048 && t128x256 >= 160 && t128x256 <= 256) cfg = GEMM_TILE_128x256;
-      else if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
-      else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
-      else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * by * bz * grids <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
-      else cfg = GEMM_TILE_128x128;
-    }
-    const size_t bytesA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
-    // direct global->LDS loads need 32-bit operand offsets, and whole 64-wide K tiles unless the contraction index is
-    // the slow dimension of both operands (the k-rows past the end of an operand read as zero)
-    const bool direct_ok = direct_k_ok(g.transA, g.transB, g.K) && bytesA < (1ull << 31) && bytesB < (1ull << 31);
+    GemmPlan plan;
+    if (!plan_mfma(g, force_generic, (long)by * bz * grids, plan)) return hipErrorInvalidValue;
     // 256x256 tiles run one workgroup per CU, so a launch takes whole rounds of 256 tiles.  A
     // few tile rows beyond the last full round would cost a whole round more (dV_o of a
     // 50257-word vocabulary: 788 tiles, 3.08 rounds): those rows go out as a second, split-K
     // launch that adds into the zeroed rows of the fp32 result.
-    if (cfg == GEMM_TILE_256x256 && force_generic == 0 && direct_ok && g.out_fp32 && !g.accumulate && !g.bias && !g.residual &&
+    if (plan.cfg == GEMM_TILE_256x256 && force_generic == 0 && plan.direct_ok && g.out_fp32 && !g.accumulate && !g.bias && !g.residual &&
         !g.res32 && !g.colsum && g.epilogue == EPI_NONE && !g.drop.on && by * bz * grids == 1 && g.ldc == g.N && g.K >= 2048) {
       const int tn = (g.N + 255) / 256;
       if (tn <= 256 && 256 % tn == 0) {
@@ -317,46 +374,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
         }
       }
     }
-    int splits = 1;
-    bool modelled = false;
-    if (g.accumulate && force_generic < 2 && direct_ok && g.K >= 512) {
-      modelled = true;
-      // Split-K launch: tile shape and number of K ranges together, so that the grid fills the
-      // chip in whole rounds.  Cost of a candidate in units of (tile area x K-tiles) per CU:
-      // rounds x workgroups per CU x tile area x (K-tiles per workgroup + fixed cost) / rate,
-      // the fixed cost (ring fill, atomic epilogue) taken as 6 K-tiles, the rate of the 128x64
-      // tiles as 0.8 of the 128x128 ones (more operand bytes per flop), that of the 256x256 ones as 1.65 (1.45 us per K-tile
-      // of a tile against 1.2 us of two 128x128 tiles side by side).
-      double best = 1e30;
-      for (int c = 0; c < 3; ++c) {
-        const int bm = c == 2 ? 256 : 128, bn = c == 2 ? 256 : c ? 64 : 128, per_cu = c == 2 ? 1 : c ? 3 : 2;
-        const double rate = c == 2 ? 1.65 : c ? 0.8 : 1.0;
-        const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * by * bz * grids;
-        const int max_s = std::min(16, g.K / 256);
-        for (int sp = 1; sp <= max_s; ++sp) {
-          const int kc = ((g.K + sp - 1) / sp + 63) / 64 * 64;
-          const int real = (g.K + kc - 1) / kc;
-          if (real != sp) continue;
-          const long rounds = (tiles * sp + 256L * per_cu - 1) / (256L * per_cu);
-          const double cost = (double)rounds * per_cu * bm * bn * (kc / 64 + 6) / rate;
-          if (cost < best) { best = cost; cfg = c == 2 ? GEMM_TILE_256x256 : c ? GEMM_TILE_128x64 : GEMM_TILE_128x128; splits = sp; }
-        }
-      }
-    }
-    if (!direct_ok) cfg = GEMM_TILE_STAGED128;
-    if (cfg < GEMM_TILE_STAGED128 || cfg > GEMM_TILE_128x256) return hipErrorInvalidValue;
-    const int BM = cfg == GEMM_TILE_256x256 ? 256 : cfg == GEMM_TILE_64x64 ? 64 : 128, BN = cfg == GEMM_TILE_128x64 ? 64 : cfg == GEMM_TILE_128x256 ? 256 : BM;
-    int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * by * bz * grids;
-    if (g.accumulate && !modelled && tiles < 384 && g.K >= 512) {
-      splits = (512 + tiles - 1) / tiles;
-      int maxs = g.K / 256;
-      if (splits > maxs) splits = maxs;
-      if (splits < 1) splits = 1;
-    }
-    int kchunk = (g.K + splits - 1) / splits;
-    kchunk = (kchunk + 63) / 64 * 64;
-    splits = (g.K + kchunk - 1) / kchunk;
-    p.kchunk = kchunk;
+    p.kchunk = plan.kchunk;
+    const int cfg = plan.cfg, splits = plan.splits;
     if (cfg == GEMM_TILE_256x256) return launch_gemm_pp(s, p, g.transA, g.transB, splits);
     if (cfg != GEMM_TILE_STAGED128) return launch_gemm_dlds(s, p, g.transA, g.transB, splits, cfg);
     return launch_mfma_cfg<128, 128, 2, 2>(s, p, g.transA, g.transB, splits);

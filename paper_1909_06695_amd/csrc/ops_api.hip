@@ -94,6 +94,13 @@ extern "C" size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int 
   return operand_extent(dtype == 1 ? 2 : 4, rows, cols, ld);
 }
 
+extern "C" int ouro_op_gemm_plan(int dtype, int transA, int transB, int M, int N, int K, int accumulate, int* tile, int* splits) {
+  if (!tile || !splits || M < 1 || N < 1 || K < 0) return OURO_E_ARG;
+  GemmDesc g = make_gemm(transA, transB, M, N, K, 1.f, nullptr, transA ? M : K, nullptr, transB ? K : N, nullptr, N, 1, accumulate, nullptr, nullptr, 0, 0, nullptr, 0);
+  *tile = gemm_plan(dtype, g, splits);
+  return OURO_OK;
+}
+
 extern "C" int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A, int lda,
                                       const void* B, int ldb) {
   GemmDesc g = make_gemm(transA, transB, M, N, K, 1.f, A, lda, B, ldb, nullptr, N, 0, 0, nullptr, nullptr, 0, 0, nullptr, 0);

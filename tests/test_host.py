@@ -105,6 +105,21 @@ def test_contraction_operands_end_at_their_last_element(dtype, esz):
     assert f(dtype, 1 << 20, 8, 1 << 14) == esz * (((1 << 20) - 1) * (1 << 14) + 8)
 
 
+def plan(dtype, tA, tB, M, N, K, acc=0):
+    tile, splits = ctypes.c_int(), ctypes.c_int()
+    assert P.lib().ouro_op_gemm_plan(dtype, tA, tB, M, N, K, acc, ctypes.byref(tile), ctypes.byref(splits)) == 0
+    return tile.value, splits.value
+
+
+@pytest.mark.parametrize("M,N,K,big", [(256, 4232, 7488, False), (616, 1720, 4544, False), (4472, 5312, 3200, False), (12048, 824, 4096, False), (8192, 1024, 50304, True)])
+def test_split_contractions_price_their_atomic_adds(M, N, K, big):
+    """256x256 tiles (14) pay for an accumulating product only where the contraction is long against the output's adds; the
+    others took 1.2 to 1.8 times as long on them as on 128-wide tiles (11, 12)."""
+    for tA, tB in ((1, 0), (0, 1)):
+        tile, splits = plan(1, tA, tB, M, N, K, 1)
+        assert tile in ((14,) if big else (11, 12)) and 1 <= splits <= max(1, K // 256)
+
+
 def test_reads_in_inline_assembly_wait_in_their_own_block():
     """The compiler takes the output registers of an asm block as written when the block ends: a load that is still under
     way then could be overtaken by whatever the compiler puts into them."""
