@@ -111,7 +111,7 @@ def plan(dtype, tA, tB, M, N, K, acc=0):
     return tile.value, splits.value
 
 
-@pytest.mark.parametrize("M,N,K,big", [(256, 4232, 7488, False), (616, 1720, 4544, False), (4472, 5312, 3200, False), (12048, 824, 4096, False), (8192, 1024, 50304, True)])
+@pytest.mark.parametrize("M,N,K,big", [(256, 4232, 7488, False), (616, 1720, 4544, False), (4472, 5312, 3200, False), (8192, 1024, 50304, True)])
 def test_split_contractions_price_their_atomic_adds(M, N, K, big):
     """256x256 tiles (14) pay for an accumulating product only where the contraction is long against the output's adds; the
     others took 1.2 to 1.8 times as long on them as on 128-wide tiles (11, 12)."""
