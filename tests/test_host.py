@@ -120,6 +120,14 @@ def test_split_contractions_price_their_atomic_adds(M, N, K, big):
         assert tile in ((14,) if big else (11, 12)) and 1 <= splits <= max(1, K // 256)
 
 
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0)])
+def test_tiles_of_few_tile_products(tA, tB):
+    """Up to one round of 64x64 tiles (15), but the register-prefetch kernel (13) for long contractions of a column-form
+    operand with both sides long, which the 64x64 tiles made slower."""
+    assert plan(1, tA, tB, 768, 1024, 1024)[0] == 15 and plan(1, tA, tB, 448, 4096, 8192)[0] == 15
+    assert plan(1, tA, tB, 1088, 1496, 8192)[0] == plan(1, tA, tB, 1600, 1024, 4096)[0] == (15 if (tA, tB) == (0, 1) else 13)
+
+
 def test_reads_in_inline_assembly_wait_in_their_own_block():
     """The compiler takes the output registers of an asm block as written when the block ends: a load that is still under
     way then could be overtaken by whatever the compiler puts into them."""
