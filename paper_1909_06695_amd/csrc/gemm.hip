@@ -220,13 +220,13 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
     // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
     // over 256 5.2 -> 4.5; beyond one round 768 x 4096 over 1024 16.7 -> 20.1, 4800 x 640 over 448 9.9 -> 10.4.
-    // Not where both sides are long and an operand is column-form: its 128-byte rows then cross lines, and L2 is the limit
-    // (A B, 1088 x 1496 over 4096 32.8 us on the register-prefetch kernel, 35.9 on 64x64 tiles, over 8192 58 and 70; A B^T 57.9
-    // and 57.1; narrower, 448 x 4096 over 8192, 60 and 50).
+    // Not where they nearly fill the round, both sides are long and an operand is column-form: L2 is the limit then (A B, 1088 x
+    // 1496 over 4096 32.8 us on the register-prefetch kernel, 35.9 on 64x64 tiles, over 8192 58 and 70; A B^T 57.9 and 57.1;
+    // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
-    if (!g.accumulate && t64 <= 512 && !(column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
+    if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
     // One round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles, three
     // stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue: 8192 x 1024 over
     // 4096 81 -> 68 us, 6144 x 1024 over 4096 69 -> 60, over 2048 34.7 -> 32.5; over 1024 24.1 -> 24.4.

@@ -29,7 +29,7 @@ struct GemmParams {
   uint8_t vec_epi;      // C, Z, residual allow 16-byte row-chunk accesses (MFMA kernel)
 };
 // The grid's size follows the struct in a launch's arguments.  The GPU fetches those from host memory: with all of them in five
-// 64-byte lines a launch of 5 us takes 0.4 us less than with the sixth line begun.
+// 64-byte lines a launch of 5 us takes 0.2 to 0.5 us less than with the sixth line begun.
 static_assert(sizeof(GemmParams) <= 304, "kernel arguments of a single product");
 
 // Which output tile and K range a workgroup takes.  Workgroups go to the 8 XCDs round-robin, and

@@ -125,6 +125,7 @@ def test_tiles_of_few_tile_products(tA, tB):
     """Up to one round of 64x64 tiles (15), but the register-prefetch kernel (13) for long contractions of a column-form
     operand with both sides long, which the 64x64 tiles made slower."""
     assert plan(1, tA, tB, 768, 1024, 1024)[0] == 15 and plan(1, tA, tB, 448, 4096, 8192)[0] == 15
+    assert plan(1, tA, tB, 1344, 528, 7552)[0] == 15
     assert plan(1, tA, tB, 1088, 1496, 8192)[0] == plan(1, tA, tB, 1600, 1024, 4096)[0] == (15 if (tA, tB) == (0, 1) else 13)
 
 
