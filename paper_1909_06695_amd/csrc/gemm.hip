@@ -212,10 +212,12 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // put more workgroups on every compute unit
     const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-    // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are several per CU (the logits),
-    // one per CU with a long contraction (dV_o: 670 -> 592 us), or whole rounds of them: two rounds of a contraction over
-    // 1024 with the GELU epilogues take 94 us against 101 us of four rounds of 128x128 tiles, one and a half rounds
-    // (8192 x 3072 x 1024) 69 us against 57 us of three
+    // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are four per CU (the logits: 8192 x
+    // 32768 over 512 404 us against 460 on 128x128 tiles, 4800 x 32768 over 448 212 against 241).  From one per CU on the two are
+    // compared: us per round 13 + 1.43 per K-tile for 256 of them, 4.5 + 0.925 for 512 128x128 ones, a round that is not full
+    // halfway between its share and a whole one.  Measured alone on the chip, against 128x128 tiles: 512 tiles over 512 45.7
+    // and 47.5 (4096 x 8192), over 1024 69.9 and 76.5, 496 over 1024 71 and 80, 448 over 512 47 and 45, over 1024 68 and 74,
+    // 384 over 1024 62 and 55, over 4096 172 and 190, 528 over 1024 95 and 89.  The worst choice of 40 costs 4 %.
     // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
     // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
@@ -224,16 +226,22 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // 1496 over 4096 32.8 us on the register-prefetch kernel, 35.9 on 64x64 tiles, over 8192 58 and 70; A B^T 57.9 and 57.1;
     // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
+    const double kt = g.K / 64.0;
+    auto rounds = [](double tiles, double slots) { return 0.5 * (std::ceil(tiles / slots) + tiles / slots); };
+    const bool big = t256 >= 1024 || (t256 >= 256 && rounds(t256, 256) * (13 + 1.43 * kt) < rounds(t128, 512) * (4.5 + 0.925 * kt));
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
     if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
-    // One round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles, three
-    // stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue: 8192 x 1024 over
-    // 4096 81 -> 68 us, 6144 x 1024 over 4096 69 -> 60, over 2048 34.7 -> 32.5; over 1024 24.1 -> 24.4.
-    else if (!g.accumulate && g.K >= 2048 && t128x256 >= 160 && t128x256 <= 256) cfg = GEMM_TILE_128x256;
-    else if (!g.accumulate && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0) || (t256 >= 256 && g.K >= 4096))) cfg = GEMM_TILE_256x256;
+    // One nearly full round of 128x256 tiles (64x64 a wave: a third less LDS traffic per matrix instruction than 128x128 tiles,
+    // three stages) pays over a long contraction, as there is one workgroup per CU and nothing beside its epilogue.  Against
+    // 128x128 tiles: 256 of them (8192 x 1024) over 4096 64.8 and 66.5 us, over 2048 35.7 and 36.2, over 1024 22.1 and 21.6; 192 over
+    // 4096 54.9 and 54.1; 160 52.5 and 48.7.
+    else if (!g.accumulate && g.K >= 2048 && t128x256 >= 224 && t128x256 <= 256) cfg = GEMM_TILE_128x256;
+    else if (!g.accumulate && big) cfg = GEMM_TILE_256x256;
     else if (g.accumulate && t128 >= 192) cfg = GEMM_TILE_128x128;   // split-K with two workgroups per CU
-    else if (g.accumulate || t128 <= 384) cfg = (!g.accumulate && (long)t128 * products <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
+    // 128x64 tiles up to three per CU, over a long contraction only up to two (320 128x128 tiles: over 4096 48.7 us, on 128x64
+    // ones 55.7; over 1024 18.1 and 18.2)
+    else if (g.accumulate || t128 <= (g.K >= 2048 ? 256 : 384)) cfg = (!g.accumulate && (long)t128 * products <= 256 && g.K >= 1024 && g.K <= 8192) ? GEMM_TILE_PIPE128 : GEMM_TILE_128x64;
     else cfg = GEMM_TILE_128x128;
   }
   const size_t bytesA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bytesB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;

@@ -129,6 +129,14 @@ def test_tiles_of_few_tile_products(tA, tB):
     assert plan(1, tA, tB, 1088, 1496, 8192)[0] == plan(1, tA, tB, 1600, 1024, 4096)[0] == (15 if (tA, tB) == (0, 1) else 13)
 
 
+@pytest.mark.parametrize("M,N,K,tile", [
+    (8192, 4096, 1024, 14), (7936, 4096, 1024, 14), (8192, 3584, 1024, 14), (8192, 3072, 1024, 11), (12288, 2816, 1024, 11), (4096, 8192, 512, 11),
+    (8192, 32768, 512, 14), (6144, 4096, 4096, 14), (8192, 1024, 4096, 16), (6144, 1024, 4096, 11), (5120, 1024, 2048, 11), (5120, 1024, 1024, 12)])
+def test_tiles_of_large_products(M, N, K, tile):
+    """256x256 tiles (14) by how full their rounds are, not by whole rounds; 128x256 ones (16) for a nearly full round."""
+    assert plan(1, 0, 1, M, N, K) == (tile, 1)
+
+
 def test_reads_in_inline_assembly_wait_in_their_own_block():
     """The compiler takes the output registers of an asm block as written when the block ends: a load that is still under
     way then could be overtaken by whatever the compiler puts into them."""
