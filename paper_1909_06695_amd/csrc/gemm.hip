@@ -213,11 +213,11 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
     // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are four per CU (the logits: 8192 x
-    // 32768 over 512 404 us against 460 on 128x128 tiles, 4800 x 32768 over 448 212 against 241).  From one per CU on the two are
-    // compared: us per round 13 + 1.43 per K-tile for 256 of them, 4.5 + 0.925 for 512 128x128 ones, a round that is not full
-    // halfway between its share and a whole one.  Measured alone on the chip, against 128x128 tiles: 512 tiles over 512 45.7
-    // and 47.5 (4096 x 8192), over 1024 69.9 and 76.5, 496 over 1024 71 and 80, 448 over 512 47 and 45, over 1024 68 and 74,
-    // 384 over 1024 62 and 55, over 4096 172 and 190, 528 over 1024 95 and 89.  The worst choice of 40 costs 4 %.
+    // 32768 over 512 404 us against 460 on 128x128 tiles, 4800 x 32768 over 448 212 against 241), one per CU with a long
+    // contraction (dV_o: 670 -> 592 us), or where their last round is at least three quarters full.  Alone on the chip, against
+    // 128x128 tiles, plain and with the GELU-gradient epilogue: 512 tiles over 1024 70 and 77 us, 87 and 91; 464 over 768 57
+    // and 75, 83 and 84; 496 over 1024 69 and 84, 95 and 103; 448 over 1024 68 and 74, over 512 47 and 45; 416 over 1024 63
+    // and 69 but 91 and 82; 528 over 1024 95 and 89.
     // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
     // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
@@ -226,9 +226,7 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // 1496 over 4096 32.8 us on the register-prefetch kernel, 35.9 on 64x64 tiles, over 8192 58 and 70; A B^T 57.9 and 57.1;
     // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
-    const double kt = g.K / 64.0;
-    auto rounds = [](double tiles, double slots) { return 0.5 * (std::ceil(tiles / slots) + tiles / slots); };
-    const bool big = t256 >= 1024 || (t256 >= 256 && rounds(t256, 256) * (13 + 1.43 * kt) < rounds(t128, 512) * (4.5 + 0.925 * kt));
+    const bool big = t256 >= 1024 || (t256 >= 256 && g.K >= 4096) || (t256 >= 448 && (t256 % 256 == 0 || t256 % 256 >= 192) && g.K >= 768);
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
     if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;

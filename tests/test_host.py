@@ -130,7 +130,8 @@ def test_tiles_of_few_tile_products(tA, tB):
 
 
 @pytest.mark.parametrize("M,N,K,tile", [
-    (8192, 4096, 1024, 14), (7936, 4096, 1024, 14), (8192, 3584, 1024, 14), (8192, 3072, 1024, 11), (12288, 2816, 1024, 11), (4096, 8192, 512, 11),
+    (8192, 4096, 1024, 14), (7936, 4096, 768, 14), (8192, 3584, 1024, 14), (8192, 3072, 1024, 11), (12288, 2816, 1024, 11), (4096, 8192, 512, 11),
+    (13312, 2048, 1024, 11), (9472, 2048, 2816, 11),
     (8192, 32768, 512, 14), (6144, 4096, 4096, 14), (8192, 1024, 4096, 16), (6144, 1024, 4096, 11), (5120, 1024, 2048, 11), (5120, 1024, 1024, 12)])
 def test_tiles_of_large_products(M, N, K, tile):
     """256x256 tiles (14) by how full their rounds are, not by whole rounds; 128x256 ones (16) for a nearly full round."""
