@@ -321,7 +321,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   const size_t esz = dtype == 1 ? 2 : 4, csz = g.out_fp32 ? 4 : esz;
   const int grids = g.C2 ? 2 : 1;
   if (g.C2 && (!g.A2 || !g.B2)) return hipErrorInvalidValue;
-  p.by = (uint16_t)by; p.bz = (uint16_t)(bz * grids); p.bz1 = (uint16_t)bz;
+  p.by = by; p.bz = bz * grids; p.bz1 = bz;
   p.A2 = g.A2; p.B2 = g.B2; p.C2 = g.C2; p.alpha2 = g.alpha2;
   p.bAy = g.sAy * (long long)esz; p.bAz = g.sAz * (long long)esz;
   p.bBy = g.sBy * (long long)esz; p.bBz = g.sBz * (long long)esz;
@@ -330,7 +330,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     if (g.bias || g.residual || g.epilogue != EPI_NONE || g.drop.on) return hipErrorInvalidValue;
     if (g.res32 && (!g.out_fp32 || g.ln_mean || g.C2)) return hipErrorInvalidValue;
     const size_t bA = 2 * (size_t)(g.transA ? g.K : g.M) * g.lda, bB = 2 * (size_t)(g.transB ? g.N : g.K) * g.ldb;
-    const bool in_grid = force_generic != 1 && by <= 65535 && bz * grids <= 65535 && gemm_uses_mfma(dtype, g) && direct_k_ok(g.transA, g.transB, g.K) && bA < (1ull << 31) && bB < (1ull << 31) &&
+    const bool in_grid = force_generic != 1 && gemm_uses_mfma(dtype, g) && direct_k_ok(g.transA, g.transB, g.K) && bA < (1ull << 31) && bB < (1ull << 31) &&
                          !((p.bAy | p.bAz | p.bBy | p.bBz | p.bCy | p.bCz) & 15) &&
                          (!g.C2 || (aligned16(g.A2) && aligned16(g.B2) && aligned16(g.C2) == aligned16(g.C)));
     if (!in_grid) {

@@ -7,30 +7,26 @@ namespace ouro {
 
 struct GemmParams {
   const void* A; const void* B; void* C;
-  const float* bias;
-  const void* residual;
-  const float* res32;
-  const float* ln_mean; const float* ln_rstd; const float* ln_g; const float* ln_b;
-  void* Z;
-  float* colsum; size_t colsum_stride;      // see GemmDesc
-  const void* A2; const void* B2; void* C2;
-  long long bAy, bAz, bBy, bBz, bCy, bCz;   // byte strides of a batch of products over blockIdx.y, blockIdx.z (direct-to-LDS kernels)
-  DropDesc drop;
   int M, N, K, lda, ldb, ldc;
-  int ldr, ldr32, ldz;
+  int out_fp32, accumulate;
+  const float* bias;
+  const void* residual; int ldr;
+  const float* res32; int ldr32;
+  const float* ln_mean; const float* ln_rstd; const float* ln_g; const float* ln_b;
+  int epilogue;
+  void* Z; int ldz;
+  float alpha;
   int bytesA, bytesB;   // operand extents, for the buffer descriptors of the direct loads (each operand is under 2 GiB)
   int kchunk;      // K range per blockIdx.z
   int tilesN;      // tiles along N (MFMA kernel)
-  int tilesM, ntiles;   // direct-to-LDS kernels: see tile_of_block
-  float alpha, alpha2;
-  uint16_t by, bz, bz1;                     // bz1: blockIdx.z from here on belongs to the second grid of products
-  uint8_t mfast, band;  // see tile_of_block
-  uint8_t out_fp32, accumulate, epilogue;
-  uint8_t vec_epi;      // C, Z, residual allow 16-byte row-chunk accesses (MFMA kernel)
+  int tilesM, ntiles, mfast, band;   // direct-to-LDS kernels: see tile_of_block
+  int vec_epi;     // 1: C, Z, residual allow 16-byte row-chunk accesses (MFMA kernel)
+  int by, bz, bz1;                          // bz1: blockIdx.z from here on belongs to the second grid of products
+  const void* A2; const void* B2; void* C2; float alpha2;
+  long long bAy, bAz, bBy, bBz, bCy, bCz;   // byte strides of a batch of products over blockIdx.y, blockIdx.z (direct-to-LDS kernels)
+  DropDesc drop;
+  float* colsum; size_t colsum_stride;      // see GemmDesc
 };
-// The grid's size follows the struct in a launch's arguments.  The GPU fetches those from host memory: with all of them in five
-// 64-byte lines a launch of 5 us takes 0.2 to 0.5 us less than with the sixth line begun.
-static_assert(sizeof(GemmParams) <= 304, "kernel arguments of a single product");
 
 // Which output tile and K range a workgroup takes.  Workgroups go to the 8 XCDs round-robin, and
 // each XCD has its own L2: the grid index is turned into (XCD, position in that XCD's share)
