@@ -58,7 +58,7 @@ int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* 
  * the contraction kernels may read of it (host only). */
 size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld);
 /* What ouro_op_gemm chooses (force_generic 0) for dense, aligned operands: *tile as force_generic names it, *splits the
- * number of contraction ranges (host only). */
+ * number of contraction ranges (bf16; host only). */
 int ouro_op_gemm_plan(int dtype, int transA, int transB, int M, int N, int K, int accumulate, int* tile, int* splits);
 /* 1 if ouro_op_gemm would run the MFMA kernel for these arguments (host only). */
 int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A,

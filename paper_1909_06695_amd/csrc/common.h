@@ -136,7 +136,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
 // kernel; otherwise one launch_gemm each.  *grouped (optional) tells which it was.
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, bool* grouped = nullptr);
 // true if launch_gemm would take the MFMA path for this problem
-// What launch_gemm chooses for one product (host only): 1 the plain kernel, GEMM_TILE_*, and the contraction ranges.
+// What launch_gemm chooses for one product (host only): 1 the plain kernel, 20 the fp32 matrix-core
+// kernel, GEMM_TILE_*, and (bf16) the contraction ranges.
 int gemm_plan(int dtype, const GemmDesc& g, int* splits);
 bool gemm_uses_mfma(int dtype, const GemmDesc& g);
 

@@ -289,9 +289,19 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
   plan = {cfg, splits, kchunk, direct_ok};
   return true;
 }
+// fp32 products go to the matrix cores except contractions of one K-tile of the plain kernel (16) where that has more than two
+// workgroups of the small matrix-core tiles per CU to save on: 2053 x 570 over 8 6.8 us, on the matrix cores 8.6; 564 x 1197
+// over 6 6.2 and 9.0; 888 x 590 over 5 6.1 and 8.9; but 1024 x 512 (512 tiles) over 16 5.6 and 4.8, 31 x 2000 5.6 and 3.7, and
+// 2053 x 570 over 32 7.8 and 8.3, 564 x 1197 7.1 and 6.3.
+static bool f32_on_matrix_cores(const GemmDesc& g) {
+  if (!gemm_f32_ok(g)) return false;
+  const long t32 = (long)((g.M + 31) / 32) * ((g.N + 31) / 32);
+  return g.K > 16 || t32 <= 512;
+}
 int gemm_plan(int dtype, const GemmDesc& g, int* splits) {
   GemmPlan plan;
   *splits = 1;
+  if (dtype == 0) return f32_on_matrix_cores(g) ? 20 : 1;
   if (!gemm_uses_mfma(dtype, g)) return 1;
   if (!plan_mfma(g, 0, 1, plan)) return -1;
   *splits = plan.splits;
@@ -392,7 +402,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   }
 
   p.accumulate = g.accumulate;
-  if (dtype == 0 && force_generic != 1 && gemm_f32_ok(g)) return launch_gemm_f32(s, p, g.transA, g.transB, force_generic >= 20 ? force_generic - 20 : 0);
+  if (dtype == 0 && force_generic != 1 && (force_generic >= 20 ? gemm_f32_ok(g) : f32_on_matrix_cores(g))) return launch_gemm_f32(s, p, g.transA, g.transB, force_generic >= 20 ? force_generic - 20 : 0);
 
   dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, 1), block(256);
 #define OURO_PLAIN(T_)                                                                        \

@@ -138,6 +138,12 @@ def test_tiles_of_large_products(M, N, K, tile):
     assert plan(1, 0, 1, M, N, K) == (tile, 1)
 
 
+@pytest.mark.parametrize("M,N,K,tile", [(2053, 570, 16, 1), (2053, 570, 17, 20), (1024, 512, 8, 20), (1056, 512, 8, 1), (1, 2082, 4, 20), (1, 1, 1, 20)])
+def test_short_fp32_contractions(M, N, K, tile):
+    for tA, tB in ((0, 0), (0, 1), (1, 0)):
+        assert plan(0, tA, tB, M, N, K) == (tile, 1)
+
+
 def test_reads_in_inline_assembly_wait_in_their_own_block():
     """The compiler takes the output registers of an asm block as written when the block ends: a load that is still under
     way then could be overtaken by whatever the compiler puts into them."""
