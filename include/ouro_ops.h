@@ -54,6 +54,12 @@ int ouro_op_gemm_batched(void* stream, int dtype, int transA, int transB, int M,
 int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                        const void* const* A, const int* lda, const void* const* B, const int* ldb,
                        float* const* C, const int* ldc, float alpha);
+/* The same with cleared != 0 where the caller has zeroed every C and no two of them overlap (a part that is the only one is
+ * stored), and, for tests and tuning, on the kernel with tile 128 or 256 wide tiles and K ranges of kchunk (a multiple of
+ * 64; 0 automatic). */
+int ouro_op_gemm_group_as(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
+                          const void* const* A, const int* lda, const void* const* B, const int* ldb,
+                          float* const* C, const int* ldc, float alpha, int cleared, int tile, int kchunk);
 /* Bytes from the base of an operand (rows along its slow dimension, cols contiguous) to the end of its last element: what
  * the contraction kernels may read of it (host only). */
 size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld);

@@ -419,9 +419,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   return e;
 }
 
-hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, bool* grouped) {
-  if (grouped) *grouped = false;
-  if (n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
+hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile, int kchunk) {
+  if (n < 1 || n > GEMM_GROUP_MAX || (tile != 0 && tile != 128 && tile != 256) || kchunk < 0 || kchunk % 64) return hipErrorInvalidValue;
   // products that do not admit the grouped kernel go by themselves
   GemmDesc in[GEMM_GROUP_MAX];
   int ni = 0;
@@ -436,7 +435,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     if (e != hipSuccess) return e;
   }
   if (ni == 0) return hipSuccess;
-  if (ni == 1) return launch_gemm(s, dtype, in[0], 0);
+  if (ni == 1 && !tile) return launch_gemm(s, dtype, in[0], 0);
   g = in; n = ni;
   // One K-range length for all products, and one of two kernels.  128x128 tiles, two workgroups per CU, run in whole rounds
   // of 512 and take 1.2 us per K-tile (of two side by side) plus 6 K-tiles of fixed cost (ring fill, atomic adds that the
@@ -468,8 +467,8 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
       if (cost < best[big] - 1e-9) { best[big] = cost; kchunks[big] = kc; }
     }
   }
-  const bool big = best[1] < best[0];
-  const int kchunk = kchunks[big];
+  const bool big = tile ? tile == 256 : best[1] < best[0];
+  if (!tile || !kchunk) kchunk = kchunks[big];
   GemmParams ps[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) {
     const GemmDesc& d = g[i];
@@ -485,7 +484,6 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
     p.kchunk = ((d.K + splits - 1) / splits + 63) / 64 * 64;
     p.accumulate = splits > 1 ? ACC_ATOMIC : d.accumulate;
   }
-  if (grouped) *grouped = true;
   if (big) return launch_gemm_pp_group(s, ps, n);
   return launch_gemm_dlds_group(s, ps, n, 1, 0);
 }

@@ -49,16 +49,23 @@ extern "C" int ouro_op_gemm_batched(void* stream, int dtype, int transA, int tra
   return rc_of(launch_gemm((hipStream_t)stream, dtype, g, force_generic));
 }
 
-extern "C" int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
-                                  const void* const* A, const int* lda, const void* const* B, const int* ldb,
-                                  float* const* C, const int* ldc, float alpha) {
+extern "C" int ouro_op_gemm_group_as(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
+                                     const void* const* A, const int* lda, const void* const* B, const int* ldb,
+                                     float* const* C, const int* ldc, float alpha, int cleared, int tile, int kchunk) {
+  if ((tile != 0 && tile != 128 && tile != 256) || kchunk < 0 || kchunk % 64) return OURO_E_ARG;
   if (n < 1 || n > GEMM_GROUP_MAX || !M || !N || !K || !A || !lda || !B || !ldb || !C || !ldc) return OURO_E_ARG;
   GemmDesc g[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) {
     if (!A[i] || !B[i] || !C[i] || M[i] < 0 || N[i] < 0 || K[i] < 0 || lda[i] < M[i] || ldb[i] < N[i] || ldc[i] < N[i]) return OURO_E_ARG;
     g[i] = make_gemm(1, 0, M[i], N[i], K[i], alpha, A[i], lda[i], B[i], ldb[i], C[i], ldc[i], 1, 1, nullptr, nullptr, 0, EPI_NONE, nullptr, 0);
+    if (cleared) g[i].accumulate = ACC_STORE;
   }
-  return rc_of(launch_gemm_group((hipStream_t)stream, dtype, g, n));
+  return rc_of(launch_gemm_group((hipStream_t)stream, dtype, g, n, tile, kchunk));
+}
+extern "C" int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
+                                  const void* const* A, const int* lda, const void* const* B, const int* ldb,
+                                  float* const* C, const int* ldc, float alpha) {
+  return ouro_op_gemm_group_as(stream, dtype, n, M, N, K, A, lda, B, ldb, C, ldc, alpha, 0, 0, 0);
 }
 
 extern "C" int ouro_op_gemm_dropout(void* stream, int dtype, int transA, int transB, int M, int N, int K,

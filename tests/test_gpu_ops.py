@@ -211,13 +211,40 @@ def test_products_onto_one_output(dtype, M, N, K):
     assert np.array_equal(host(out), ref)
 
 
+@pytest.mark.parametrize("tile,kchunk", [(128, 0), (256, 0), (128, 512), (256, 512)])
+@pytest.mark.parametrize("cleared", [0, 1])
 @pytest.mark.parametrize("shapes", [
-    [(1024, 1024, 2331), (1032, 776, 2331)],                      # K range whole, ragged K-tile and edges of tiles
-    [(264, 520, 8256), (512, 256, 8256)],                         # split over workgroups, atomic adds
-    [(1024, 2048, 1088), (512, 1024, 96), (256, 256, 40)]])       # contractions of one and two K-tiles beside a long one
-def test_gemm_group_large_tiles(shapes):
-    """Sizes at which the grouped launch runs on 256x256 tiles; same bound as the small ones."""
-    test_gemm_group(1, shapes)
+    [(1024, 1024, 2331), (1032, 776, 2331)],                      # K range whole or split, ragged K-tile and edges of tiles
+    [(264, 520, 8256), (512, 256, 8256)],
+    [(1024, 2048, 1088), (512, 1024, 96), (256, 256, 40)],        # contractions of one and two K-tiles beside a long one
+    [(72, 40, 33), (136, 264, 705)]])
+def test_gemm_group_large_tiles(shapes, cleared, tile, kchunk):
+    """Both kernels of the grouped launch by name, whatever the rule would choose: K ranges whole (stored where the caller
+    cleared the output, added atomically otherwise) and split; outputs off the tiles; NaN behind the operands; same bound as
+    test_gemm_group, plus the rounding of the atomic adds."""
+    rng = np.random.default_rng(sum(m + n + k for m, n, k in shapes))
+    n = len(shapes)
+    def operand(k, cols):
+        x = torch.full((k + 64, cols), float("nan"), dtype=torch.bfloat16, device="cuda")
+        x[:k] = torch.from_numpy(rng.standard_normal((k, cols)).astype(np.float32)).cuda()
+        return x
+    dA = [operand(k, m) for m, nn, k in shapes]
+    dB = [operand(k, nn) for m, nn, k in shapes]
+    init = [np.zeros((m, nn), np.float32) if cleared else rng.standard_normal((m, nn)).astype(np.float32) for m, nn, k in shapes]
+    out = [torch.full((m + 1, nn + 8), -7.0, device="cuda") for m, nn, k in shapes]
+    for o, x in zip(out, init):
+        o[:-1, :-8] = torch.from_numpy(x)
+    ia = lambda v: (C.c_int * n)(*v)
+    pa = lambda ts: (C.c_void_p * n)(*[t.data_ptr() for t in ts])
+    ok(L().ouro_op_gemm_group_as(stream(), 1, n, ia([s[0] for s in shapes]), ia([s[1] for s in shapes]), ia([s[2] for s in shapes]), pa(dA),
+                                 ia([s[0] for s in shapes]), pa(dB), ia([s[1] for s in shapes]), pa(out), ia([s[1] + 8 for s in shapes]), 0.25,
+                                 cleared, tile, kchunk))
+    torch.cuda.synchronize()
+    for i, (m, nn, k) in enumerate(shapes):
+        got = host(out[i])
+        ref = init[i] + 0.25 * (host(dA[i][:k]).T @ host(dB[i][:k]))
+        assert rel_err(got[:-1, :-8], ref) < 3e-6, i
+        assert np.all(got[-1] == -7.0) and np.all(got[:, -8:] == -7.0)
 
 
 @pytest.mark.parametrize("dtype,force", [(0, 0), (1, 0), (1, 10), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15), (1, 16)])
