@@ -5,7 +5,7 @@
 // forms below give over the sizes of a small model:
 //   WIDE    64x64 tiles, waves 2 x 2, a ring of four K-tiles (32) shared by the workgroup;
 //   !WIDE   32x32 tiles, the four waves take K-tiles in turn, each through a ring of its own, and add up through LDS at the
-//           end: sixteen times as many waves on the same product, for products of fewer than 384 64x64 tiles.
+//           end: four times as many waves on the same product (16 against 4 per 64x64 outputs), for products of fewer than 384 64x64 tiles.
 // Operands go global -> LDS by direct loads through a buffer descriptor (what lies past the operand reads as zero): 16 bytes
 // per lane where leading dimensions and bases allow it (VEC = 4), else 4 bytes per lane.
 //   row form (k contiguous in memory): [rows][32 k], 16-byte chunk c of a row at chunk c ^ (row & 7);
