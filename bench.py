@@ -93,6 +93,7 @@ def run_config(name, steps, warmup, windows, args, kernel_timing=True):
     lr = c["lr"]
     if args.serial:
         m.set_overlap(False)
+    streams = "overlapped" if m.overlap() else "serial"      # of the timed windows
     it = 0
 
     def run(n, want_last=False):
@@ -122,7 +123,7 @@ def run_config(name, steps, warmup, windows, args, kernel_timing=True):
            "ms_per_step": round(ms, 3), "ms_per_step_windows": [round(x, 3) for x in win_ms],
            "ms_per_step_min": round(min(win_ms), 3), "ms_per_step_max": round(max(win_ms), 3),
            "mfu_bf16": round(F / (ms * 1e-3) / (PEAK_BF16_TFLOPS * 1e12), 4), "step_tflop": round(F / 1e12, 3),
-           "prime_steps": prime, "loss_first_timed": loss, "loss_last": loss_end, "kernels": None}
+           "streams": streams, "prime_steps": prime, "loss_first_timed": loss, "loss_last": loss_end, "kernels": None}
     if kernel_timing:
         # one more pass of `steps` steps with per-launch HIP events on the library's stream; one
         # stream, so that each bracket (like a profiler's kernel duration) holds that launch alone
@@ -262,7 +263,7 @@ def main():
         "ms_per_step_spread": [head["ms_per_step_min"], head["ms_per_step_max"]],
         "prime_steps": head["prime_steps"],
         "mfu_bf16": head["mfu_bf16"], "step_tflop": head["step_tflop"],
-        "streams": "serial" if args.serial else "overlapped",
+        "streams": head["streams"],
         "schedule": "stored inputs + recompute" if args.schedule else "gradient rings (Eq. 8)",
         "dropout": args.dropout,
         "loss_first_timed": head["loss_first_timed"], "loss_last": head["loss_last"],

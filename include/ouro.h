@@ -247,6 +247,8 @@ int ouro_debug_timing_enable(ouro_model* m, int on);
  * The results are the same in both modes up to the order of atomic float additions. Call it
  * between iterations; it drains the extra streams. */
 int ouro_debug_set_overlap(ouro_model* m, int on);
+/* *on = 1 if the model's steps use the extra streams (unless launches are being timed), else 0. */
+int ouro_debug_get_overlap(const ouro_model* m, int* on);
 int ouro_debug_timing_read(ouro_model* m, int kind, double* ms, int64_t* launches, double* work);
 /* Cost of one timing bracket by itself: enqueues `reps` (at most 4096) empty brackets (two
  * event records with nothing between them) back to back on the model's stream and returns their

@@ -79,6 +79,7 @@ def lib():
         "ouro_debug_get_hidden": (i32, [vp, i32, vp, i64]),
         "ouro_debug_timing_enable": (i32, [vp, i32]),
         "ouro_debug_set_overlap": (i32, [vp, i32]),
+        "ouro_debug_get_overlap": (i32, [vp, P(i32)]),
         "ouro_debug_timing_overhead": (i32, [vp, i32, P(C.c_double)]),
         "ouro_debug_timing_read": (i32, [vp, i32, P(C.c_double), P(i64), P(C.c_double)]),
         # single-kernel entry points
@@ -338,6 +339,12 @@ class Model:
 
     def set_overlap(self, on):
         check(self.L.ouro_debug_set_overlap(self.h, int(on)))
+
+    def overlap(self):
+        """Whether the steps use the extra streams."""
+        on = C.c_int()
+        check(self.L.ouro_debug_get_overlap(self.h, C.byref(on)))
+        return bool(on.value)
 
     def timing_read(self, kind):
         """(ms, launches, work) since the last read: kind 0 = MFMA contraction kernel (flops), 1 = update

@@ -1770,6 +1770,12 @@ extern "C" int ouro_debug_set_overlap(ouro_model* m, int on) {
   return OURO_OK;
 }
 
+extern "C" int ouro_debug_get_overlap(const ouro_model* m, int* on) {
+  if (!m || !on) return fail(OURO_E_ARG, "get_overlap: null argument");
+  *on = m->use_side ? 1 : 0;
+  return OURO_OK;
+}
+
 extern "C" int ouro_debug_timing_read(ouro_model* m, int kind, double* ms, int64_t* launches, double* work) {
   if (!m || kind < 0 || kind >= OURO_TIMING_KINDS) return fail(OURO_E_ARG, "timing_read: bad argument");
   HIPCHK(hipStreamSynchronize(m->stream));

@@ -155,14 +155,16 @@ def param_shapes_of_groups(cfg, orc):
     return out
 
 
-def run_both(c, steps, lr, seed=0, std=0.02, perturb=0.0, check_grads=True, tol=1e-4, module_api=False, rep=1):
+def run_both(c, steps, lr, seed=0, std=0.02, perturb=0.0, check_grads=True, tol=1e-4, module_api=False, rep=1, overlap=None):
     """Runs `steps` iterations on both sides; returns nothing, asserts parity.
 
     rep > 1: the HIP model runs with batch * rep streams, each of the oracle's streams
     replicated rep times.  Streams do not interact and the loss is a mean over all targets, so
     the loss, every gradient and every weight equal those of the oracle's batch exactly (up to
     summation order): the full-size launch configuration is checked element by element at
-    the oracle cost of the small batch."""
+    the oracle cost of the small batch.
+
+    overlap: on one stream (False) or on several (True); None leaves it to the model, which takes one for small layers."""
     pkg = P()
     blobs = S.init_params(c, seed=seed, std=std, perturb=perturb)
     tok, tgt = S.token_batches(c["vocab"], c["batch"], c["seq_len"], steps, c.get("zipf_s", 1.1), seed + 1,
@@ -171,6 +173,8 @@ def run_both(c, steps, lr, seed=0, std=0.02, perturb=0.0, check_grads=True, tol=
     stored = c.get("schedule", 0) == 1                    # stored-input / recompute schedule
     orc = (O.RecomputeOracle if stored else O.Oracle)(cfg, blobs, keep_history=False)
     m = pkg.create_model(**dict(c, batch=c["batch"] * rep))
+    if overlap is not None:
+        m.set_overlap(overlap)
     K = c["n_module"]
     for g in range(K + 1):
         assert m.param_count(g) == blobs[g].size
@@ -280,17 +284,19 @@ def test_config1_fp32_sgd_three_steps():
     run_both(c, steps=3, lr=c["lr"], seed=c["seed"])
 
 
-def test_config1_perturbed_params_module_api():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_config1_perturbed_params_module_api(overlap):
     """Same shape with non-trivial biases / gains, Adam, more steps than K, driven through
     module_forward / module_backward / delayed_update with shuffled update order."""
     c = dict(S.CONFIGS["cfg1"], optimizer=1)
-    run_both(c, steps=5, lr=1e-3, seed=3, std=0.08, perturb=0.1, module_api=True)
+    run_both(c, steps=5, lr=1e-3, seed=3, std=0.08, perturb=0.1, module_api=True, overlap=overlap)
 
 
-def test_ragged_shapes_K3_fp32():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_ragged_shapes_K3_fp32(overlap):
     c = dict(n_layer=4, d_model=40, n_head=5, d_head=8, d_ff=72, vocab=131, seq_len=19, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=0, optimizer=0)
-    run_both(c, steps=5, lr=0.05, seed=5, std=0.1, perturb=0.1)
+    run_both(c, steps=5, lr=0.05, seed=5, std=0.1, perturb=0.1, overlap=overlap)
 
 
 def test_K1_fp32_adam():
@@ -299,93 +305,103 @@ def test_K1_fp32_adam():
     run_both(c, steps=3, lr=1e-3, seed=6, std=0.1, perturb=0.1)
 
 
-def test_xl_fp32_memory_carry():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_xl_fp32_memory_carry(overlap):
     """Relative attention with a segment memory that is empty, then partial, then rolling."""
     c = dict(n_layer=3, d_model=32, n_head=2, d_head=16, d_ff=48, vocab=61, seq_len=6, mem_len=10, batch=2,
              n_module=3, rel_pos=1, dtype=0, optimizer=0)
-    run_both(c, steps=5, lr=0.05, seed=7, std=0.15, perturb=0.1)
+    run_both(c, steps=5, lr=0.05, seed=7, std=0.15, perturb=0.1, overlap=overlap)
 
 
-def test_xl_fp32_odd_dims_adam():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_xl_fp32_odd_dims_adam(overlap):
     c = dict(n_layer=2, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=73, seq_len=9, mem_len=9, batch=2,
              n_module=2, rel_pos=1, dtype=0, optimizer=1, embed_warm_mode=1)
-    run_both(c, steps=4, lr=1e-3, seed=8, std=0.1, perturb=0.1)
+    run_both(c, steps=4, lr=1e-3, seed=8, std=0.1, perturb=0.1, overlap=overlap)
 
 
+@pytest.mark.parametrize("overlap", [False, True])
 @pytest.mark.parametrize("K,opt,api", [(2, 0, False), (3, 0, True), (4, 1, False), (1, 1, False)])
-def test_stored_input_schedule_fp32(K, opt, api):
+def test_stored_input_schedule_fp32(K, opt, api, overlap):
     """The memory-saving schedule (stored module inputs, recomputation with the current weights,
     error gradients handed down one iteration late) against its oracle in fp32: losses, every
     gradient with the mini-batch and ring slot it was recomputed from, and the weights, over more
     iterations than the pipeline is deep."""
     c = dict(n_layer=max(K, 4), d_model=40, n_head=5, d_head=8, d_ff=72, vocab=131, seq_len=19, mem_len=0, batch=3,
              n_module=K, rel_pos=0, dtype=0, optimizer=opt, schedule=1)
-    run_both(c, steps=K + 4, lr=0.05 if opt == 0 else 1e-3, seed=50 + K, std=0.1, perturb=0.1, module_api=api)
+    run_both(c, steps=K + 4, lr=0.05 if opt == 0 else 1e-3, seed=50 + K, std=0.1, perturb=0.1, module_api=api, overlap=overlap)
 
 
-def test_stored_input_schedule_xl_blocks_fp32():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_stored_input_schedule_xl_blocks_fp32(overlap):
     c = dict(n_layer=3, d_model=32, n_head=2, d_head=16, d_ff=48, vocab=61, seq_len=12, mem_len=0, batch=2,
              n_module=3, rel_pos=1, dtype=0, optimizer=0, schedule=1, embed_warm_mode=1)
-    run_both(c, steps=6, lr=0.05, seed=57, std=0.15, perturb=0.1)
+    run_both(c, steps=6, lr=0.05, seed=57, std=0.15, perturb=0.1, overlap=overlap)
 
 
-def test_stored_input_schedule_with_segment_memory():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_stored_input_schedule_with_segment_memory(overlap):
     """Transformer-XL memories under the stored-input schedule: a module recomputes mini-batch
     t-K+k against the memories its layers held at that iteration, while the forward pass rolls
     them on.  fp32 (general kernels), then bf16 at head size 64 (fused kernels)."""
     c = dict(n_layer=4, d_model=32, n_head=2, d_head=16, d_ff=48, vocab=61, seq_len=6, mem_len=10, batch=2,
              n_module=3, rel_pos=1, dtype=0, optimizer=0, schedule=1)
-    run_both(c, steps=7, lr=0.05, seed=71, std=0.15, perturb=0.1)
+    run_both(c, steps=7, lr=0.05, seed=71, std=0.15, perturb=0.1, overlap=overlap)
     c = dict(n_layer=3, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=512, seq_len=80, mem_len=112, batch=2,
              n_module=3, rel_pos=1, dtype=1, optimizer=0, embed_warm_mode=1, schedule=1)
-    run_both(c, steps=6, lr=0.05, seed=73, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=6, lr=0.05, seed=73, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
-def test_stored_input_schedule_bf16():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_stored_input_schedule_bf16(overlap):
     """bf16 mode, K = 4, shapes that span several MFMA tiles; then K = 3 with Adam through the
     zero-padded storage."""
     c = dict(n_layer=4, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=1001, seq_len=96, mem_len=0, batch=3,
              n_module=4, rel_pos=0, dtype=1, optimizer=0, schedule=1)
-    run_both(c, steps=7, lr=0.05, seed=61, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=7, lr=0.05, seed=61, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
     c = dict(n_layer=3, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=203, seq_len=70, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=1, optimizer=1, schedule=1)
-    run_both(c, steps=5, lr=1e-3, seed=63, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=5, lr=1e-3, seed=63, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
+@pytest.mark.parametrize("overlap", [False, True])
 @pytest.mark.parametrize("schedule", [0, 1])
-def test_dropout_fp32(schedule):
+def test_dropout_fp32(schedule, overlap):
     """Repeatable dropout (embedding sum, attention-projection and feed-forward outputs) in both
     schedules against the oracle, fp32: the masks are bit-identical on both sides, so the usual
     tolerance holds.  Under schedule 1 the recomputation of mini-batch t-K+k must regenerate that
     mini-batch's masks from the stored seed (a recomputation under the running seed fails this)."""
     c = dict(n_layer=4, d_model=40, n_head=5, d_head=8, d_ff=72, vocab=131, seq_len=19, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=0, optimizer=0, schedule=schedule, dropout=0.1875, seed=2 ** 40 + 17)
-    run_both(c, steps=6, lr=0.05, seed=81, std=0.1, perturb=0.1)
+    run_both(c, steps=6, lr=0.05, seed=81, std=0.1, perturb=0.1, overlap=overlap)
 
 
-def test_dropout_xl_memory_adam_fp32():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_dropout_xl_memory_adam_fp32(overlap):
     c = dict(n_layer=3, d_model=32, n_head=2, d_head=16, d_ff=48, vocab=61, seq_len=6, mem_len=10, batch=2,
              n_module=3, rel_pos=1, dtype=0, optimizer=1, schedule=1, dropout=0.125, seed=5)
-    run_both(c, steps=6, lr=1e-3, seed=83, std=0.15, perturb=0.1)
+    run_both(c, steps=6, lr=1e-3, seed=83, std=0.15, perturb=0.1, overlap=overlap)
 
 
+@pytest.mark.parametrize("overlap", [False, True])
 @pytest.mark.parametrize("schedule", [0, 1])
-def test_dropout_bf16(schedule):
+def test_dropout_bf16(schedule, overlap):
     """bf16: fused masks in the MFMA epilogues (16-byte store path) and through zero-padded storage."""
     c = dict(n_layer=3, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=512, seq_len=96, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=1, optimizer=0, schedule=schedule, dropout=0.15625, seed=99)
-    run_both(c, steps=5, lr=0.05, seed=85, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=5, lr=0.05, seed=85, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
     c = dict(n_layer=2, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=203, seq_len=70, mem_len=0, batch=3,
              n_module=2, rel_pos=0, dtype=1, optimizer=0, schedule=schedule, dropout=0.15625, seed=7)
-    run_both(c, steps=4, lr=0.05, seed=87, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=4, lr=0.05, seed=87, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
+@pytest.mark.parametrize("overlap", [False, True])
 @pytest.mark.parametrize("dtype,tol", [(0, 1e-4), (1, 2e-2)])
 @pytest.mark.parametrize("kw", [dict(seq_len=1, batch=5), dict(seq_len=2, batch=1, n_layer=1, n_module=1),
                                 dict(seq_len=3, batch=2, rel_pos=1, mem_len=7, embed_warm_mode=1),
                                 dict(seq_len=5, batch=1, n_layer=4, n_module=4, schedule=1, rel_pos=1, mem_len=1),
                                 dict(seq_len=4, batch=2, vocab=2, d_ff=1)])
-def test_degenerate_shapes(dtype, tol, kw):
+def test_degenerate_shapes(dtype, tol, kw, overlap):
     """Single-token segments (each query sees only itself), one layer in one module, a memory
     longer than the segment or of one row, as many modules as layers, a two-word vocabulary and a
     one-unit feed-forward layer: both modes, every gradient and the weights against the oracle."""
@@ -394,48 +410,53 @@ def test_degenerate_shapes(dtype, tol, kw):
     c.update(kw)
     if dtype == 1 and c["d_ff"] == 1:
         pytest.skip("8 tokens through one bf16 hidden unit: rounding noise is averaged over nothing, the 2e-2 bar does not apply")
-    run_both(c, steps=c["n_module"] + 3, lr=0.05, seed=91, std=0.2, perturb=0.1, tol=tol)
+    run_both(c, steps=c["n_module"] + 3, lr=0.05, seed=91, std=0.2, perturb=0.1, tol=tol, overlap=overlap)
 
 
-def test_bf16_small_sgd():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_bf16_small_sgd(overlap):
     """bf16 mode against the fp64 oracle within 2e-2 (several tiles of the MFMA kernels)."""
     c = dict(n_layer=2, d_model=128, n_head=2, d_head=64, d_ff=512, vocab=512, seq_len=128, mem_len=0, batch=2,
              n_module=2, rel_pos=0, dtype=1, optimizer=0)
-    run_both(c, steps=3, lr=0.05, seed=9, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=3, lr=0.05, seed=9, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
-def test_bf16_odd_vocab_adam():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_bf16_odd_vocab_adam(overlap):
     """bf16 mode with a vocabulary that is no multiple of 8 (the zero-padded vocabulary keeps the
     dh = G V and dV_o = G^T h contractions on the MFMA kernels) and K = 3 with Adam."""
     c = dict(n_layer=3, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=1001, seq_len=96, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=1, optimizer=1, embed_warm_mode=0)
-    run_both(c, steps=5, lr=1e-3, seed=21, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=5, lr=1e-3, seed=21, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
-def test_xl_bf16_mfma_path_memory_carry():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_xl_bf16_mfma_path_memory_carry(overlap):
     """Transformer-XL blocks in bf16 with head size 64 (the fused relative-position kernels),
     memory shorter than, equal to and rolling past the segment over four steps."""
     c = dict(n_layer=2, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=512, seq_len=80, mem_len=112, batch=2,
              n_module=2, rel_pos=1, dtype=1, optimizer=0, embed_warm_mode=1)
-    run_both(c, steps=4, lr=0.05, seed=31, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=4, lr=0.05, seed=31, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
-def test_bf16_widths_off_the_tile_grid_adam():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_bf16_widths_off_the_tile_grid_adam(overlap):
     """bf16 mode with d_head = 41, d_model = 82, d_ff = 100: stored zero-padded to 64 / 128 / 128 so
     that the MFMA kernels run; every result the caller sees (loss, gradients, weights) is that of
     the unpadded model.  Adam over more steps than K: padding that picked up a value would leak
     into the visible weights."""
     c = dict(n_layer=3, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=203, seq_len=70, mem_len=0, batch=3,
              n_module=3, rel_pos=0, dtype=1, optimizer=1, embed_warm_mode=0)
-    run_both(c, steps=6, lr=1e-3, seed=41, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=6, lr=1e-3, seed=41, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
-def test_xl_bf16_widths_off_the_tile_grid_memory_carry():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_xl_bf16_widths_off_the_tile_grid_memory_carry(overlap):
     """The same zero-padded storage with Transformer-XL blocks (W_r, u, v per head) and a rolling
     memory; head size 32 here."""
     c = dict(n_layer=2, d_model=96, n_head=3, d_head=32, d_ff=200, vocab=301, seq_len=40, mem_len=56, batch=2,
              n_module=2, rel_pos=1, dtype=1, optimizer=0, embed_warm_mode=1)
-    run_both(c, steps=4, lr=0.05, seed=43, std=0.05, perturb=0.05, tol=2e-2)
+    run_both(c, steps=4, lr=0.05, seed=43, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
 @pytest.mark.parametrize("rel_pos,mem_len,schedule", [(0, 0, 0), (1, 96, 0), (0, 0, 1), (1, 96, 1)])
@@ -465,6 +486,18 @@ def test_stream_overlap_matches_one_stream(rel_pos, mem_len, schedule):
         # SGD: a last-bit difference of an fp32 sum can flip the bf16 rounding of a weight's
         # copy now and then, nothing more
         assert rel_err(a, b) < 1e-3
+
+
+def test_overlap_switch_is_what_the_model_reports():
+    """Small and relative-position models start on one stream, larger plain ones and the stored-input schedule on several."""
+    small = dict(n_layer=2, d_model=128, n_head=2, d_head=64, d_ff=256, vocab=512, seq_len=96, mem_len=0, batch=2, n_module=2, rel_pos=0, dtype=1, optimizer=0)
+    for c, want in ((small, False), (dict(small, rel_pos=1, mem_len=96, seq_len=512, batch=8, schedule=0), False),
+                    (dict(small, seq_len=512, batch=32, d_model=512, n_head=8, d_ff=2048), True), (dict(small, seq_len=512, batch=4, schedule=1), True)):
+        m = P().create_model(**c)
+        assert m.overlap() == want
+        m.set_overlap(not want)
+        assert m.overlap() == (not want)
+        m.close()
 
 
 def test_long_run_with_warmup_and_cosine_schedule():
@@ -747,12 +780,13 @@ def test_bench_config_full_size_steady_state():
     run_both(c, steps=c["n_module"] + 2, lr=c["lr"], seed=0, tol=2e-2, rep=4)
 
 
-def test_xl_config_full_size_first_steps():
+@pytest.mark.parametrize("overlap", [False, True])
+def test_xl_config_full_size_first_steps(overlap):
     """cfg3: Transformer-XL with widths off the tile grid (16 layers, d=410, 10 heads of 41,
     d_ff=2100, segment and memory 150) at full size, stored zero-padded: empty memory, full
     memory, rolled memory against the oracle."""
     c = dict(S.CONFIGS["cfg3"], batch=8)                 # 8 oracle streams, each 4 times on the HIP side: 32 streams
-    run_both(c, steps=3, lr=c["lr"], seed=0, tol=2e-2, rep=4)
+    run_both(c, steps=3, lr=c["lr"], seed=0, tol=2e-2, rep=4, overlap=overlap)
 
 
 def test_cfg4_shapes_full_size_launch():
