@@ -853,7 +853,7 @@ def test_full_size_distinct_streams_forward_rows(name, rows):
                                                        (1, 0, 96, 3, 32, 200, 17), (0, 0, 64, 1, 64, 68, 1000)])
 def test_padded_params_on_device(rel, mem, d, heads, dh, F, vocab):
     """Zero-padded storage: device destinations and sources give bit for bit what the host ones give (head axes along rows
-    and along columns, single-row tensors, row counts off the kernel's tile), and setting clears the padding again."""
+    and along columns, single-row tensors, row counts off the kernel's tile)."""
     import paper_1909_06695_amd as P
     c = dict(n_layer=3, d_model=d, n_head=heads, d_head=dh, d_ff=F, vocab=vocab, seq_len=9, mem_len=mem, batch=2, n_module=2,
              rel_pos=rel, dtype=1, optimizer=1)
@@ -872,6 +872,36 @@ def test_padded_params_on_device(rel, mem, d, heads, dh, F, vocab):
     tok = torch.from_numpy(rng.integers(0, vocab, (2, 9)).astype(np.int32)).cuda()
     losses = [m.eval_step(tok, tok) for m in (a, b)]
     assert losses[0] == losses[1]
+    a.close(), b.close()
+
+
+@pytest.mark.parametrize("on_device", [False, True])
+def test_setting_params_clears_the_padding(on_device):
+    """A state whose padding holds other values (saved, altered between the weights, loaded again): handing the weights over,
+    from host or device memory, leaves the whole state as that of a model whose padding was never touched."""
+    c = dict(n_layer=2, d_model=82, n_head=2, d_head=41, d_ff=100, vocab=73, seq_len=9, mem_len=0, batch=2, n_module=2, rel_pos=1, dtype=1, optimizer=1)
+    a, b = P().create_model(device="cuda:0", **c), P().create_model(device="cuda:0", **c)
+    blobs = [np.full(a.param_count(g), 3.25 + g, np.float32) for g in range(3)]
+    for g in range(3):
+        a.set_params(g, blobs[g])
+    want = a.save_state()
+    dirty = want.copy()
+    words = dirty[len(dirty) % 4:].view(np.float32)
+    for g in range(3):
+        at = np.flatnonzero(words == blobs[g][0])
+        hole = at[0] + np.flatnonzero(words[at[0]:at[-1]] == 0.0)
+        assert at.size == blobs[g].size and hole.size > 100
+        words[hole] = 7.0
+    b.load_state(dirty)
+    assert np.array_equal(b.save_state(), dirty)
+    for g in range(3):
+        if on_device:
+            d = torch.from_numpy(blobs[g]).cuda()
+            torch.cuda.synchronize()
+            assert b.L.ouro_set_params(b.h, g, C.c_void_p(d.data_ptr()), d.numel(), 1) == 0
+        else:
+            b.set_params(g, blobs[g])
+    assert np.array_equal(b.save_state(), want)
     a.close(), b.close()
 
 
