@@ -443,9 +443,10 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   // covers their atomic adds, which all workgroups of a round reach together (310 adds per ns over the chip: 70 us for
   // the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.
   // The launch runs beside the error-gradient chain, so a compute unit it leaves free is worth as much as time: the mean
-  // of the launch's duration and its share of the chip's is compared.  1024-wide layer, 8192 rows: 264 us on 128x128
-  // tiles, 192 256x256 tiles stored 178 us; 512-wide
-  // layer: 94 -> 69 us.
+  // of the launch's duration and its share of the chip's is compared.  Alone on the chip, 128x128 and
+  // 256x256 tiles: 1024-wide layer, 8192 rows 255 and 185 us, 6144 rows 182 and 131 (256x256 taken); 512-wide, 8192 rows 73 and
+  // 80, 448-wide, 4800 rows 47 and 58 (128x128 taken); 768-wide, 2331 rows 42 and 52 (256x256 taken: 108 compute units instead
+  // of all).
   int kmax = 0;
   for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
   double best[2] = {1e30, 1e30};

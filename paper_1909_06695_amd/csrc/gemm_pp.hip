@@ -1,10 +1,11 @@
 // bf16 MFMA contraction on 256x256 tiles in which the two waves of a SIMD take turns: while one runs its
 // matrix instructions the other reads fragments from LDS and requests tiles from memory.
 //
-// What bounds it: nothing in the loop any more but power.  With random operands the chip runs these loops at 1.5-1.65 GHz
-// (2.4 GHz without matrix instructions), and at that clock the matrix pipe is busy 89 % of the time: 8192^3 in 802 us
-// (A B^T) and 772 us (A^T B), 1.37 and 1.42 PFLOP/s; in the 24-layer 1024-wide step dh_L = G V goes 874 -> 578 us, dV_o
-// 670 -> 592 us, a layer's weight gradients 255 -> 178 us.  The same tile with one barrier per K-tile, all eight waves in step
+// What bounds it: the clock first.  With random operands the chip runs these loops at 1.54 (A B^T) and 1.69 GHz (A^T B) against
+// 2.4 GHz nominal, and at that clock the matrix pipe is busy 82 and 77 % of the cycles (LDS conflicts 1 %): the rest are the
+// barriers between the phases and the epilogue.  8192^3 takes 780-830 us in either form, 1.33-1.41 PFLOP/s; in the 24-layer
+// 1024-wide step dh_L = G V goes 874 -> 589 us, dV_o
+// 670 -> 592 us, a layer's weight gradients 255 -> 170-178 us.  The same tile with one barrier per K-tile, all eight waves in step
 // (the form this one replaced), needs 895 and 912 us: fragment reads and requests then stand between the matrix
 // instructions instead of beside them.  Tried on the way, same products: BK = 32 with a four-stage ring 883 / 829 us (a
 // row-form request then fetches half cache lines), five stages the same (latency is not the limit), requests between the
