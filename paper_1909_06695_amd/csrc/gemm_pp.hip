@@ -178,6 +178,8 @@ __device__ __forceinline__ void pp_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 // The wave's two requests for a half: 16 bytes per lane, the K-tile's offset `k` a scalar.
+// `k` and `jump` may by themselves lie past the operand's end (a ragged last K-tile, a second half past a narrow operand): the
+// range check counts the scalar offset in, and such a request reads zeros (a contraction over 65 with NaN behind it).
 __device__ __forceinline__ void pp_request(const void* base, int bytes, char* dst, uint32_t voff, uint32_t k, uint32_t jump) {
   auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, k, 0, 0);
