@@ -149,7 +149,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
     __syncthreads();
   }
 
-  mfma_epilogue<TM, TN>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
+  mfma_epilogue<TM, TN, false>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
 }
 
 // ----------------------------------------------------------------------------- launch
@@ -319,7 +319,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   if (g.res32 && (g.residual || g.accumulate || (g.ln_mean && !(g.ln_rstd && g.ln_g && g.ln_b)))) return hipErrorInvalidValue;
   p.epilogue = g.epilogue; p.Z = g.Z; p.ldz = g.ldz; p.alpha = g.alpha;
   p.drop = g.drop;
-  p.kchunk = g.K; p.tilesN = 0; p.vec_epi = 0;
+  p.kchunk = g.K; p.tilesN = 0; p.vec_epi = 0; p.kind = EPIK_GENERAL;
   // taken by the direct-load kernels only, which are not chosen for operands of 2 GiB and more
   p.bytesA = (int)operand_extent(dtype == 1 ? 2 : 4, g.transA ? g.K : g.M, g.transA ? g.M : g.K, g.lda);
   p.bytesB = (int)operand_extent(dtype == 1 ? 2 : 4, g.transB ? g.N : g.K, g.transB ? g.K : g.N, g.ldb);
@@ -366,6 +366,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
     p.vec_epi = aligned16(g.C) && !(g.ldc & oe) && (!g.residual || (aligned16(g.residual) && !(g.ldr & 7))) &&
                 (!g.res32 || (aligned16(g.res32) && !(g.ldr32 & 3))) &&
                 (g.epilogue == EPI_NONE || (aligned16(g.Z) && !(g.ldz & 7)));
+    p.kind = epilogue_kind(p);
     GemmPlan plan;
     if (!plan_mfma(g, force_generic, (long)by * bz * grids, plan)) return hipErrorInvalidValue;
     // 256x256 tiles run one workgroup per CU, so a launch takes whole rounds of 256 tiles.  A

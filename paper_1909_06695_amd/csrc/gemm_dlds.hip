@@ -233,11 +233,13 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmParams& p, int bid, int
       if (kt + slot < nk) step(kt + slot, lds + ((slot + S - 1) % S) * STAGE, lds + slot * STAGE);
   }
   __syncthreads();                                          // operand reads done: LDS reusable
-  mfma_epilogue<TM, TN>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
+  mfma_epilogue<TM, TN, !TA && TB>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
 }
 
+// Waves per SIMD that a kernel's LDS leaves room for: two workgroups of eight waves, three or two of four, one of eight.
+template <int BM, int BN> constexpr int dlds_waves() { return BM == 128 && BN == 128 ? 4 : BN == 256 ? 2 : BM == 64 ? 2 : 3; }
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, int S>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_dlds_kernel(GemmParams p) {
+__global__ __launch_bounds__(WM * WN * 64, (dlds_waves<BM, BN>())) void gemm_dlds_kernel(GemmParams p) {
   extern __shared__ uint4 smem[];
   batch_offsets(p);
   gemm_dlds_body<BM, BN, WM, WN, TA, TB, S>(p, blockIdx.x, gridDim.x, smem);
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dlds_group_kernel(GemmGroup
 // used them, so an LDS read has a full K-tile of matrix work to hide behind.  Stage kt+1 is
 // being read while kt computes, so S >= 3 and S-2 stages are in flight from memory.
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, int S>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_pipe_kernel(GemmParams p) {
   constexpr int BK = 64;
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmParams p) {
       if (kt + slot < nk) step(kt + slot, lds + ((slot + S - 1) % S) * STAGE, lds + ((slot + 1) % S) * STAGE);
   }
   __syncthreads();                                          // operand reads done: LDS reusable
-  mfma_epilogue<TM, TN>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
+  mfma_epilogue<TM, TN, !TA && TB>(p, acc, smem, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane, wave);
 }
 
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, int S, bool PIPE>

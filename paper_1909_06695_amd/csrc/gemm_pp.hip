@@ -186,10 +186,10 @@ __device__ __forceinline__ void pp_request(const void* base, int bytes, char* ds
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + PP_HALF / 2), 16, voff, k + jump, 0, 0);
 }
 
-// acc[row half][32-row tile][column half] = the tile at (m0, n0) over nk K-tiles from contraction index kbeg on (nk >= 1;
+// acc[2 * row half + 32-row tile][column half] = the tile at (m0, n0) over nk K-tiles from contraction index kbeg on (nk >= 1;
 // where both operands are column-form the last may be ragged).  LDS is free for reuse when the call returns.
 template <bool TA, bool TB>
-__device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0, int kbeg, int nk, char* lds, f32x16 (&acc)[2][2][2]) {
+__device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0, int kbeg, int nk, char* lds, f32x16 (&acc)[4][2]) {
   using OA = PpOperand<TA>;
   using OB = PpOperand<!TB>;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -211,12 +211,12 @@ __device__ __forceinline__ void pp_mainloop(const GemmParams& p, int m0, int n0,
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) acc[h][t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][t].get(), b[ks][0].get(), acc[h][t][j], 0, 0, 0);
+      for (int t = 0; t < 2; ++t) acc[2 * h + t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][t].get(), b[ks][0].get(), acc[2 * h + t][j], 0, 0, 0);
   };
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[i >> 1][i & 1][r] = 0.f;
 
   reqB(0, 0, kb); reqA(0, 0, ka); reqB(0, 1, kb); reqA(0, 1, ka);
   if (nk > 1) { reqB(1, 0, kb + stepB); reqA(1, 0, ka + stepA); reqB(1, 1, kb + stepB); pp_wait_mem<8>(); }
@@ -266,11 +266,10 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(GemmParams p) {
   int m0, n0, kbeg;
   tile_of_block(p, 256, 256, blockIdx.x, gridDim.x, m0, n0, kbeg);
   const int nk = (min(p.K, kbeg + p.kchunk) - kbeg + PP_BK - 1) / PP_BK;
-  f32x16 acc[2][2][2];
+  f32x16 acc[4][2];
   pp_mainloop<TA, TB>(p, m0, n0, kbeg, nk, reinterpret_cast<char*>(smem), acc);
   const int m_w = m0 + 64 * (wave >> 2), n_w = n0 + 32 * (wave & 3);
-  mfma_epilogue<2, 2, 128>(p, acc[0], smem, m_w, n_w, lane, wave);
-  mfma_epilogue<2, 2, 128>(p, acc[1], smem, m_w + 128, n_w, lane, wave);
+  mfma_epilogue<4, 2, !TA && TB, 128, 128>(p, acc, smem, m_w, n_w, lane, wave);
 }
 
 // Several accumulating products in one launch (weight gradients of a layer).  Product i owns the work items
@@ -291,10 +290,9 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_group_kernel(PpGroupParams g) 
   int m0, n0, kbeg;
   tile_of_block(p, 256, 256, bid - g.first[i], g.first[i + 1] - g.first[i], m0, n0, kbeg);
   if (kbeg >= p.K) return;                         // a work item past the last K range (the item count is rounded up)
-  f32x16 acc[2][2][2];
+  f32x16 acc[4][2];
   pp_mainloop<true, false>(p, m0, n0, kbeg, (min(p.K, kbeg + p.kchunk) - kbeg + PP_BK - 1) / PP_BK, reinterpret_cast<char*>(smem), acc);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) mfma_accumulate<2, 2, 128>(p, acc[h], m0 + 128 * h + 64 * (wave >> 2), n0 + 32 * (wave & 3), lane);
+  mfma_accumulate<4, 2, 128, 128>(p, acc, m0 + 64 * (wave >> 2), n0 + 32 * (wave & 3), lane);
 }
 
 static hipError_t pp_allow_lds(const void* kern, size_t smem, bool& done) {

@@ -487,6 +487,47 @@ def test_gemm_with_fp32_layernorm_residual(dtype, force, M, N, K, ln):
     assert np.abs(host(Cc) - ref).max() < (1e-4 if dtype == 0 else 0.1) * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("force", [11, 12, 13, 14, 15, 16])
+@pytest.mark.parametrize("M,N", [(32, 40), (130, 88), (200, 100), (264, 200), (300, 530), (520, 392)])
+@pytest.mark.parametrize("kind", ["bias", "fp32", "gelu", "gelu_grad", "residual", "fp32_residual", "layernorm"])
+def test_gemm_fused_epilogues(kind, M, N, force):
+    """Two row-form operands with each epilogue a layer uses: whole tiles, tiles over the edge, columns that do and do not
+    end at a multiple of 8, results with a row pitch; nothing outside the result is written."""
+    rng = np.random.default_rng(M + N + force)
+    K, pitch = 128, (N + 7) // 8 * 8 + 8
+    A = dev(rng.standard_normal((M, K)), 1); B = dev(rng.standard_normal((N, K)) / math.sqrt(K), 1)
+    fp32 = kind in ("fp32", "residual", "fp32_residual", "layernorm")
+    full = torch.full((M + 2, pitch), 7.0, dtype=torch.float32 if fp32 else torch.bfloat16, device="cuda")
+    side = dev(rng.standard_normal((M, pitch)), 0 if kind in ("fp32_residual", "layernorm") else 1)      # what the epilogue reads, or Z
+    bias, g, b = (dev(rng.standard_normal(N), 0) for _ in range(3))
+    mean, rstd = dev(rng.standard_normal(M), 0), dev(rng.random(M) + 0.5, 0)
+    C_, ref, R = full[1:], host(A) @ host(B).T, host(side)[:, :N]
+    if kind in ("fp32_residual", "layernorm"):
+        ln = kind == "layernorm"
+        ok(L().ouro_op_gemm_ln_residual(stream(), 1, 0, 1, M, N, K, p(A), K, p(B), K, p(C_), pitch, 1, p(bias) if ln else None, p(side), pitch,
+                                        p(mean) if ln else None, p(rstd) if ln else None, p(g) if ln else None, p(b) if ln else None, force))
+        ref = ref + (host(bias) + (R - host(mean)[:, None]) * host(rstd)[:, None] * host(g) + host(b) if ln else R)
+    else:
+        epi = {"gelu": 1, "gelu_grad": 2}.get(kind, 0)
+        use_bias = kind in ("bias", "gelu")
+        ok(L().ouro_op_gemm(stream(), 1, 0, 1, M, N, K, 1.0, p(A), K, p(B), K, p(C_), pitch, int(fp32), 0, p(bias) if use_bias else None,
+                            p(side) if kind == "residual" else None, pitch, epi, p(side) if epi else None, pitch, force))
+        if use_bias: ref = ref + host(bias)
+        if kind == "residual": ref = ref + R
+        if kind == "gelu_grad": ref = ref * O.gelu_grad(R)
+        if kind == "gelu":
+            torch.cuda.synchronize()
+            assert rel_err(host(side)[:, :N], ref) < TOL[1]
+            ref = O.gelu(ref)
+    torch.cuda.synchronize()
+    out = host(full)
+    # fp32 results: sums of 128 exact products, a few operations behind them (2^-24 each); bf16: one rounding
+    got, tol = out[1:M + 1, :N], 1e-5 if fp32 else TOL[1]
+    assert rel_err(got, ref) < tol
+    assert np.abs(got - ref).max() < tol * np.abs(ref).max()
+    assert np.all(out[0] == 7) and np.all(out[M + 1] == 7) and np.all(out[1:, N:] == 7)
+
+
 # ------------------------------------------------------------------ row-wise kernels
 @pytest.mark.parametrize("dtype", [0, 1, 2])
 @pytest.mark.parametrize("rows,d", [(37, 64), (130, 512), (9, 410), (5, 1024), (3, 4100), (517, 1024), (66, 2048)])
