@@ -354,7 +354,7 @@ inline int epilogue_kind(const GemmParams& p) {
   if (p.epilogue != EPI_NONE) {
     if (p.drop.on || p.out_fp32 || p.residual || p.res32 || p.ldz >= LIM) return EPIK_GENERAL;
     if (p.epilogue == EPI_GELU) return p.colsum ? EPIK_GENERAL : EPIK_GELU;
-    return p.colsum && !p.bias ? EPIK_GELUGRAD : EPIK_GENERAL;
+    return p.bias ? EPIK_GENERAL : EPIK_GELUGRAD;
   }
   if (p.colsum) return EPIK_GENERAL;
   if (p.res32) return !p.out_fp32 || p.ldr32 >= LIM || ((p.bias || p.drop.on) && !p.ln_mean) ? EPIK_GENERAL : !p.ln_mean ? EPIK_RES_F32 : p.drop.on ? EPIK_RES_LN_DROP : EPIK_RES_LN;
@@ -522,7 +522,7 @@ __device__ __forceinline__ void epilogue_tiles(const GemmParams& p, f32x16 (&acc
     if (READS && s + AHEAD < NT) request(s + AHEAD);
     if (NT > 4) __builtin_amdgcn_sched_barrier(0);            // else the requests of all tiles are moved up, beyond the registers there are
   }
-  if (SUM) {
+  if (SUM && p.colsum) {
     // lanes of equal lane % 4 hold the same columns
 #pragma unroll
     for (int j = 0; j < (SUM ? TN : 1); ++j)
