@@ -21,51 +21,100 @@
 
 namespace ouro {
 
-constexpr int XL_RWIN = 192;                         // rows of r a workgroup needs per block
-constexpr int XL_STAGE = 2 * TILE_BYTES + XL_RWIN * 128;   // K, V, r window
+// LDS of a workgroup: two stages of K and V, the rows of r, a patch per wave.  A block needs the 192 distances
+// Mv + Q0 - 64 jb + 128 - [0, 192), largest first: three groups of 64; the next block needs two of them and the 64 below.  Group t
+// of block jb is at place (2 - t - jb) mod 4, so that a block fetches one group (8 KB instead of 24) into the place that no one
+// reads.
 constexpr int XL_NSTAGE = 2;
-constexpr int XL8_LD = 34;                           // floats per patch row (33: 218 us in the dQ kernel, 32: 227, 34: 214)
-constexpr int XL8_PATCH = 64 * XL8_LD * 4;           // bytes per wave
+constexpr int XL_STAGE = 2 * TILE_BYTES;             // K, V
+constexpr int XL_R = XL_NSTAGE * XL_STAGE;           // where the rows of r start
+constexpr int XL_PATCHES = XL_R + 4 * TILE_BYTES;
+// A wave's patch: what its 32 queries have with the 64 distances of a 32 x 32 sub-tile, a query's cells next to each other.
+// fp32 position terms, then in the same memory bf16 dS.  With both pitches (68 floats, 68 halves: 34 dwords) the lanes' rows
+// start at different banks, also along the diagonals.
+constexpr int XL8_LD = 68;
+constexpr int XL8_PATCH = 32 * XL8_LD * 4;           // bytes per wave
+constexpr int XL_DS_LD = 68;
+constexpr int XL_LDS_Q8 = XL_PATCHES + 8 * XL8_PATCH;
+static_assert(XL8_PATCH >= 5 * 1024 && 5 * 1024 >= 32 * XL_DS_LD * 2, "clearing the dS cells takes five writes");
 static_assert(XL8_PATCH >= (32 * 64 + 2 * 64) * 4, "the sums of the bias gradients use the whole patch");
-constexpr int XL_LDS_Q8 = XL_NSTAGE * XL_STAGE + 8 * XL8_PATCH;
+// the patch holds floats and halves in turn
+typedef float xl_f32 __attribute__((may_alias));
+typedef float xl_f32x4 __attribute__((ext_vector_type(4), may_alias));
+typedef uint32_t xl_u32x4 __attribute__((ext_vector_type(4), may_alias));
+typedef uint64_t xl_u64_at2 __attribute__((may_alias, aligned(2)));
+typedef uint32_t xl_u32x2 __attribute__((ext_vector_type(2), may_alias));
 
 // One wave's share (8 rows) of a direct load of 64 rows x 64 features into an LDS tile; the row
-// index is clamped to [0 or -inf, rmax-1].
-__device__ __forceinline__ void dma_tile8(const bf16_t* src, int ld, int row0, int rmax, char* tile, int wave, int lane, bool clamp_low) {
+// index is clamped to rmax-1.
+__device__ __forceinline__ void dma_tile8(const bf16_t* src, int ld, int row0, int rmax, char* tile, int wave, int lane) {
   const int row = 8 * wave + (lane >> 3);
   const int c = (lane & 7) ^ swza(row);
-  int gr = min(row0 + row, rmax - 1);
-  if (clamp_low) gr = max(0, gr);
+  const int gr = min(row0 + row, rmax - 1);
+  __builtin_amdgcn_global_load_lds((gbl_void*)(src + (size_t)gr * ld + 8 * c), (lds_void*)(tile + wave * 1024), 16, 0, 0);
+}
+// The same for the rows row0 down to row0 - 63 of r, clamped to [0, rmax-1].
+__device__ __forceinline__ void dma_tile8_down(const bf16_t* src, int ld, int row0, int rmax, char* tile, int wave, int lane) {
+  const int row = 8 * wave + (lane >> 3);
+  const int c = (lane & 7) ^ swza(row);
+  const int gr = max(0, min(row0 - row, rmax - 1));
   __builtin_amdgcn_global_load_lds((gbl_void*)(src + (size_t)gr * ld + 8 * c), (lds_void*)(tile + wave * 1024), 16, 0, 0);
 }
 
 // q + bias for the lane's fragment features (fp32 add, rounded to bf16 once)
-__device__ __forceinline__ bf16x8 add_bias(bf16x8 q, const bf16_t* bias8) {
-  bf16x8 b = as_bf16x8(*reinterpret_cast<const uint4*>(bias8)), r;
+__device__ __forceinline__ bf16x8 add_bias(bf16x8 q, bf16x8 b) {
+  bf16x8 r;
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16_t)((float)q[e] + (float)b[e]);
   return r;
 }
 
+// The lane's share of 64 features of a row in operand order, zero where row >= rows; the loads are not conditional, so that
+// those of several rows are under way together (row by row under a condition a workgroup began with eight round trips to memory).
+__device__ __forceinline__ void xl_load_row(const bf16_t* src, int ld, int row, int rows, int h32, uint4 (&t)[4]) {
+  const bf16_t* at = src + (size_t)min(row, rows - 1) * ld + 8 * h32;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) t[ks] = *reinterpret_cast<const uint4*>(at + 16 * ks);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    if (row >= rows) t[ks] = make_uint4(0, 0, 0, 0);
+}
+
 // row of the accumulator element r of the lane's half: 8*(r/4) + 4*half + r%4
 __device__ __forceinline__ constexpr int acc_row(int r, int h32) { return 8 * (r >> 2) + 4 * h32 + (r & 3); }
 
-// Position term of a 32-key sub-tile for a wave whose lanes own queries: rows [rrow0, +64) of
-// the r window times (q + v), written to the wave's patch as patch[rho][query].  Key kk of the
-// sub-tile and the lane's query meet at patch row 31 + lane%32 - kk.
-__device__ __forceinline__ void xl_position_product(const char* sR, int rrow0, const bf16x8 (&qvf)[4], float* patch, int lane) {
+// 32 rows of the r window from row w0 (a multiple of 32) on, at block jb
+__device__ __forceinline__ const char* xl_r_rows(const char* lds, int w0, int jb) { return lds + XL_R + ((2 - (w0 >> 6) - jb) & 3) * TILE_BYTES + (w0 & 32) * 128; }
+
+// Position term of a 32-key sub-tile for a wave whose lanes own queries: rows [rrow0, +64) of the r window times (q + v), as
+// patch[query][cell].  Key kk of the sub-tile and the lane's query meet at cell 32 - lane%32 + kk (ascending with the key: four
+// keys of a lane are next to each other): added to s.
+__device__ __forceinline__ void xl_position_product(const char* lds, int rrow0, int jb, const bf16x8 (&qvf)[4], char* patch, int lane) {
   const int h32 = lane >> 5, l32 = lane & 31;
+  f32x16 acc[2];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    f32x16 acc;
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows(sR, rrow0 + 32 * t, ks, lane), qvf[ks], acc, 0, 0, 0);
+  for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) patch[(32 * t + acc_row(r, h32)) * XL8_LD + l32] = acc[r];
-  }
+    for (int t = 0; t < 2; ++t)
+      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows(xl_r_rows(lds, rrow0 + 32 * t, jb), 0, ks, lane), qvf[ks], acc[t], 0, 0, 0);
+  xl_f32* row = reinterpret_cast<xl_f32*>(patch) + l32 * XL8_LD + 4 * h32;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      xl_f32x4 x = {acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+      *reinterpret_cast<xl_f32x4*>(row + 32 * t + 8 * g) = x;
+    }
+}
+__device__ __forceinline__ void xl_add_position(f32x16& s, const char* patch, int lane) {
+  const int h32 = lane >> 5, l32 = lane & 31;
+  const xl_f32* cell = reinterpret_cast<const xl_f32*>(patch) + l32 * XL8_LD + 32 - l32 + 4 * h32;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] += cell[8 * (r >> 2) + (r & 3)];
 }
 
 // Forward kernel: workgroup -> (query block, head, batch), longest rows first over the whole launch: the
@@ -82,11 +131,12 @@ __device__ __forceinline__ void xl_decode_block(int& qblk, int& head, int& b) {
 
 // Both kernels below: grid (ceil(T/128), H, B); 8 waves = (4 groups of 32 queries) x (the two
 // 32-key halves of a 64-key block), waves w and w + 4 (one query group) on one SIMD; one
-// workgroup per CU, so two waves per SIMD (with four waves owning whole 64-key blocks, one per
-// SIMD, the forward pass took 93 us and the dQ kernel 266 us per layer at 16 x 16 heads,
-// T = M = 384; in this form 89 and 214).  A wave's patch holds the 63 distances of its 32 x 32
-// sub-tile (64 rows).  Stages hold K, V and the r window of the 128 queries; every wave issues
-// one 1 KiB load per tile.
+// workgroup per CU, so two waves per SIMD (four waves owning whole 64-key blocks, one per
+// SIMD, were 4 and 20 % slower).  What bounds them is the chain of a block in each wave: position
+// product -> patch -> scores -> exponentials -> patch -> gradient product.  16 x 16 heads, T = M = 384: forward 72 -> 69 us, dQ 209 ->
+// 156; 32 x 10 heads, T = M = 150: 38 -> 37 and 138 -> 75, by the patches in query rows (16-byte writes, dS in place as bf16 without masks
+// and conversions), one r group a block, the loads of the prologue together, the sums of the bias gradients through LDS.
+// Without the position path the dQ kernel takes 35 us less, without its stores 30 (both at 16 x 16 heads, before those changes).
 
 // ------------------------------------------------------------------------------ forward
 // The two key halves of a query group keep their own running maximum, sum and output; the
@@ -102,21 +152,14 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
   const bf16_t* kb = p.k + (size_t)b * p.S * p.ldk + head * 64;
   const bf16_t* vb = p.v + (size_t)b * p.S * p.ldv + head * 64;
   const bf16_t* rb = p.r + head * 64;
-  float* patch = reinterpret_cast<float*>(lds + XL_NSTAGE * XL_STAGE + wave * XL8_PATCH);
+  char* const patch = lds + XL_PATCHES + wave * XL8_PATCH;
   bf16x8 quf[4], qvf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    uint4 t = make_uint4(0, 0, 0, 0);
-    if (qi < p.T) t = *reinterpret_cast<const uint4*>(qb + (size_t)qi * p.ldq + 16 * ks + 8 * h32);
-    quf[ks] = add_bias(as_bf16x8(t), p.u + head * 64 + 16 * ks + 8 * h32);
-    qvf[ks] = add_bias(as_bf16x8(t), p.vb + head * 64 + 16 * ks + 8 * h32);
-  }
   const int wg_last_q = min(p.T, Q0 + 128) - 1;
   const int kend = min(p.S, p.Mv + wg_last_q + 1);
   const int nkb = (kend + 63) / 64;
   const bool wave_on = q0 < p.T;
   const int wave_kmax = p.Mv + min(p.T - 1, q0 + 31);
-  const int rrow0 = 32 * qg + 32 * (1 - kh);                // window row of the wave's patch row 0
+  const int rrow0 = 96 - 32 * qg + 32 * kh;                 // window row of the wave's patch cell 0
   f32x16 oacc[2];
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
@@ -125,24 +168,35 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
   float m = -INFINITY, l = 0.f;
   auto issue = [&](int jb) __attribute__((always_inline)) {
     char* st = lds + (jb % XL_NSTAGE) * XL_STAGE;
-    dma_tile8(kb, p.ldk, jb * 64, p.S, st, wave, lane, false);
-    dma_tile8(vb, p.ldv, jb * 64, p.S, st + TILE_BYTES, wave, lane, false);
-    const int d0 = p.Mv + Q0 - jb * 64 - 63;              // distance of window row 0
+    dma_tile8(kb, p.ldk, jb * 64, p.S, st, wave, lane);
+    dma_tile8(vb, p.ldv, jb * 64, p.S, st + TILE_BYTES, wave, lane);
+    const int d0 = p.Mv + Q0 - jb * 64 + 128;             // distance of window row 0
 #pragma unroll
-    for (int t = 0; t < 3; ++t) dma_tile8(rb, p.ldr, d0 + 64 * t, p.S, st + 2 * TILE_BYTES + t * TILE_BYTES, wave, lane, true);
+    for (int t = 0; t < 3; ++t)
+      if (t == 2 || jb == 0) dma_tile8_down(rb, p.ldr, d0 - 64 * t, p.S, lds + XL_R + ((2 - t - jb) & 3) * TILE_BYTES, wave, lane);
   };
   issue(0);
+  {
+    uint4 q[4], ub[4], vb8[4];
+    xl_load_row(qb, p.ldq, qi, p.T, h32, q);
+    xl_load_row(p.u + head * 64, 0, 0, 1, h32, ub);
+    xl_load_row(p.vb + head * 64, 0, 0, 1, h32, vb8);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      quf[ks] = add_bias(as_bf16x8(q[ks]), as_bf16x8(ub[ks]));
+      qvf[ks] = add_bias(as_bf16x8(q[ks]), as_bf16x8(vb8[ks]));
+    }
+  }
   for (int jb = 0; jb < nkb; ++jb) {
     fa_wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     if (jb + 1 < nkb) issue(jb + 1);
     const char* sK = lds + (jb % XL_NSTAGE) * XL_STAGE;
     const char* sV = sK + TILE_BYTES;
-    const char* sR = sK + 2 * TILE_BYTES;
     const int key0 = jb * 64 + 32 * kh;                     // first key of the wave's sub-tile
     if (wave_on && key0 <= wave_kmax) {
       const bool edge = key0 + 31 > p.Mv + q0 || key0 + 31 >= p.S || q0 + 31 >= p.T;
-      xl_position_product(sR, rrow0, qvf, patch, lane);
+      xl_position_product(lds, rrow0, jb, qvf, patch, lane);
       f32x16 s;
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -150,9 +204,7 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
       for (int ks = 0; ks < 4; ++ks)
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows(sK, 32 * kh, ks, lane), quf[ks], s, 0, 0, 0);
       __builtin_amdgcn_wave_barrier();
-      const float* cell0 = patch + (31 + l32 - 4 * h32) * XL8_LD + l32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] += cell0[-(8 * (r >> 2) + (r & 3)) * XL8_LD];
+      xl_add_position(s, patch, lane);
       __builtin_amdgcn_wave_barrier();
       float mloc = -INFINITY;
       if (edge) {
@@ -197,16 +249,17 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
   }
   // merge the two key halves: state of the second through its patch (34 floats per lane)
   if (kh == 1) {
+    xl_f32* mine = reinterpret_cast<xl_f32*>(patch);
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) patch[(16 * dt + r) * 64 + lane] = oacc[dt][r];
-    patch[32 * 64 + lane] = m;
-    patch[33 * 64 + lane] = l;
+      for (int r = 0; r < 16; ++r) mine[(16 * dt + r) * 64 + lane] = oacc[dt][r];
+    mine[32 * 64 + lane] = m;
+    mine[33 * 64 + lane] = l;
   }
   __syncthreads();
   if (kh == 0 && qi < p.T) {
-    const float* other = reinterpret_cast<const float*>(lds + XL_NSTAGE * XL_STAGE + (wave + 4) * XL8_PATCH);
+    const xl_f32* other = reinterpret_cast<const xl_f32*>(lds + XL_PATCHES + (wave + 4) * XL8_PATCH);
     const float m1 = other[32 * 64 + lane], l1 = other[33 * 64 + lane];
     const float mm = fmaxf(m, m1);
     const float a0 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mm);
@@ -251,33 +304,8 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
   const bf16_t* kb = p.k + (size_t)b * p.S * p.ldk + head * 64;
   const bf16_t* vb = p.v + (size_t)b * p.S * p.ldv + head * 64;
   const bf16_t* rb = p.r + head * 64;
-  float* patch = reinterpret_cast<float*>(lds + XL_NSTAGE * XL_STAGE + wave * XL8_PATCH);
+  char* const patch = lds + XL_PATCHES + wave * XL8_PATCH;
   bf16x8 quf[4], qvf[4], dof[4];
-  float part = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    uint4 t0 = make_uint4(0, 0, 0, 0), t1 = t0, t2 = t0;
-    if (qi < p.T) {
-      t0 = *reinterpret_cast<const uint4*>(qb + (size_t)qi * p.ldq + 16 * ks + 8 * h32);
-      t1 = *reinterpret_cast<const uint4*>(dob + (size_t)qi * p.lddo + 16 * ks + 8 * h32);
-      t2 = *reinterpret_cast<const uint4*>(ob + (size_t)qi * p.ldo + 16 * ks + 8 * h32);
-    }
-    quf[ks] = add_bias(as_bf16x8(t0), p.u + head * 64 + 16 * ks + 8 * h32);
-    qvf[ks] = add_bias(as_bf16x8(t0), p.vb + head * 64 + 16 * ks + 8 * h32);
-    dof[ks] = as_bf16x8(t1);
-    if (qi < p.T && kh == 0) {
-      const size_t at = ((size_t)b * p.t_ld + qi) * (p.H * 64) + head * 64 + 16 * ks + 8 * h32;
-      *reinterpret_cast<bf16x8*>(p.qu + at) = quf[ks];
-      *reinterpret_cast<bf16x8*>(p.qv + at) = qvf[ks];
-      *reinterpret_cast<bf16x8*>(p.dop + at) = dof[ks];
-    }
-    const bf16x8 of = as_bf16x8(t2);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) part += (float)of[e] * (float)dof[ks][e];
-  }
-  const float D_q = part + __shfl_xor(part, 32, 64);
-  float lse_q = 0.f;
-  if (qi < p.T) lse_q = p.lse[((size_t)b * p.H + head) * p.T + qi] * 1.4426950408889634f;
   // this (batch, head)'s P^T and dS^T (uniform bases; a cell's offset fits 32 bits)
   bf16_t* ptb = p.pt + ((size_t)b * p.H + head) * p.S * p.t_ld;
   bf16_t* dstb = p.dst + ((size_t)b * p.H + head) * p.S * p.t_ld;
@@ -286,7 +314,7 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
   const int nkb = (kend + 63) / 64;
   const bool wave_on = q0 < p.T;
   const int wave_kmax = p.Mv + min(p.T - 1, q0 + 31);
-  const int rrow0 = 32 * qg + 32 * (1 - kh);                // window row of the wave's patch row 0
+  const int rrow0 = 96 - 32 * qg + 32 * kh;                 // window row of the wave's patch cell 0
   f32x16 dqa[2], dqb[2];
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
@@ -294,24 +322,57 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
     for (int r = 0; r < 16; ++r) { dqa[dt][r] = 0.f; dqb[dt][r] = 0.f; }
   auto issue = [&](int jb) __attribute__((always_inline)) {
     char* st = lds + (jb % XL_NSTAGE) * XL_STAGE;
-    dma_tile8(kb, p.ldk, jb * 64, p.S, st, wave, lane, false);
-    dma_tile8(vb, p.ldv, jb * 64, p.S, st + TILE_BYTES, wave, lane, false);
-    const int d0 = p.Mv + Q0 - jb * 64 - 63;
+    dma_tile8(kb, p.ldk, jb * 64, p.S, st, wave, lane);
+    dma_tile8(vb, p.ldv, jb * 64, p.S, st + TILE_BYTES, wave, lane);
+    const int d0 = p.Mv + Q0 - jb * 64 + 128;             // distance of window row 0
 #pragma unroll
-    for (int t = 0; t < 3; ++t) dma_tile8(rb, p.ldr, d0 + 64 * t, p.S, st + 2 * TILE_BYTES + t * TILE_BYTES, wave, lane, true);
+    for (int t = 0; t < 3; ++t)
+      if (t == 2 || jb == 0) dma_tile8_down(rb, p.ldr, d0 - 64 * t, p.S, lds + XL_R + ((2 - t - jb) & 3) * TILE_BYTES, wave, lane);
   };
   issue(0);
+  float D_q = 0.f, lse_q = 0.f;
+  {
+    uint4 q[4], dO[4], o[4], ub[4], vb8[4];
+    xl_load_row(qb, p.ldq, qi, p.T, h32, q);
+    xl_load_row(dob, p.lddo, qi, p.T, h32, dO);
+    xl_load_row(ob, p.ldo, qi, p.T, h32, o);
+    xl_load_row(p.u + head * 64, 0, 0, 1, h32, ub);
+    xl_load_row(p.vb + head * 64, 0, 0, 1, h32, vb8);
+    lse_q = p.lse[((size_t)b * p.H + head) * p.T + min(qi, p.T - 1)] * 1.4426950408889634f;
+    if (qi >= p.T) lse_q = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      quf[ks] = add_bias(as_bf16x8(q[ks]), as_bf16x8(ub[ks]));
+      qvf[ks] = add_bias(as_bf16x8(q[ks]), as_bf16x8(vb8[ks]));
+      dof[ks] = as_bf16x8(dO[ks]);
+      const bf16x8 of = as_bf16x8(o[ks]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) D_q += (float)of[e] * (float)dof[ks][e];
+    }
+    D_q += __shfl_xor(D_q, 32, 64);
+    if (qi < p.T && kh == 0) {
+      const size_t at = ((size_t)b * p.t_ld + qi) * (p.H * 64) + head * 64 + 8 * h32;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        *reinterpret_cast<bf16x8*>(p.qu + at + 16 * ks) = quf[ks];
+        *reinterpret_cast<bf16x8*>(p.qv + at + 16 * ks) = qvf[ks];
+        *reinterpret_cast<bf16x8*>(p.dop + at + 16 * ks) = dof[ks];
+      }
+    }
+  }
+  bool stores = false;                                      // the wave's last block left exactly 32 stores behind its loads
   for (int jb = 0; jb < nkb; ++jb) {
-    fa_wait_vmcnt<0>();
+    if (stores) fa_wait_vmcnt<32>();                        // the loads have landed; the stores may be under way
+    else fa_wait_vmcnt<0>();
+    stores = false;
     __builtin_amdgcn_s_barrier();
     if (jb + 1 < nkb) issue(jb + 1);
     const char* sK = lds + (jb % XL_NSTAGE) * XL_STAGE;
     const char* sV = sK + TILE_BYTES;
-    const char* sR = sK + 2 * TILE_BYTES;
     const int key0 = jb * 64 + 32 * kh;                     // first key of the wave's sub-tile
     if (wave_on && key0 <= wave_kmax) {
       const bool edge = key0 + 31 > p.Mv + q0 || key0 + 31 >= p.S || q0 + 31 >= p.T;
-      xl_position_product(sR, rrow0, qvf, patch, lane);
+      xl_position_product(lds, rrow0, jb, qvf, patch, lane);
       f32x16 s, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
@@ -321,12 +382,13 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows(sV, 32 * kh, ks, lane), dof[ks], dp, 0, 0, 0);
       }
       __builtin_amdgcn_wave_barrier();
-      // key kk of the sub-tile and the lane's query meet at patch row 31 + l32 - kk: the lane
-      // takes its position terms from there, forms P and dS, and puts dS (without its factor
-      // `scale`: the finished gradients take it once) back in the same cells
-      float* cell0 = patch + (31 + l32 - 4 * h32) * XL8_LD + l32;
+      // key kk of the sub-tile and the lane's query meet at cell 32 - l32 + kk: the lane takes its position terms from there,
+      // forms P and dS, and puts dS (without its factor `scale`: the finished gradients take it once) into the same cells of
+      // the cleared patch, as bf16
+      xl_add_position(s, patch, lane);
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] += cell0[-(8 * (r >> 2) + (r & 3)) * XL8_LD];
+      for (int i = 0; i < 5; ++i) reinterpret_cast<xl_u32x4*>(patch)[64 * i + lane] = xl_u32x4{0, 0, 0, 0};
       if (edge) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -342,28 +404,32 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
           dp[r] = s[r] * (dp[r] - D_q);
         }
       }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) cell0[-(8 * (r >> 2) + (r & 3)) * XL8_LD] = dp[r];
       // bf16 once: the rounded dS feeds dQ below and, with P, goes to the workspace
       bf16x8 pb[2], dsb[2];
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) { pb[sub] = pack_acc(s, sub); dsb[sub] = pack_acc(dp, sub); }
-      const unsigned at0 = ((unsigned)(key0 + 4 * h32) * (unsigned)p.t_ld + (unsigned)qi) * 2u;   // byte offset
-      if (edge) {
+      union { bf16x8 v; uint64_t q[2]; uint32_t w[4]; } pw[2], dw[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (key0 + acc_row(r, h32) < p.S && qi < p.T) {
-            const unsigned at = at0 + (unsigned)(8 * (r >> 2) + (r & 3)) * (unsigned)p.t_ld * 2u;
-            *reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(ptb) + at) = pb[r >> 3][r & 7];
-            *reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(dstb) + at) = dsb[r >> 3][r & 7];
-          }
+      for (int sub = 0; sub < 2; ++sub) { pw[sub].v = pb[sub]; dw[sub].v = dsb[sub]; }
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<xl_u64_at2*>(patch + 2 * (l32 * XL_DS_LD + 32 - l32 + 4 * h32 + 8 * g)) = dw[g >> 1].q[g & 1];
+      const unsigned at0 = ((unsigned)(key0 + 4 * h32) * (unsigned)p.t_ld + (unsigned)qi) * 2u;   // byte offset
+      auto put = [&](int r) __attribute__((always_inline)) {
+        const unsigned at = at0 + (unsigned)(8 * (r >> 2) + (r & 3)) * (unsigned)p.t_ld * 2u;
+        *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ptb) + at) = (uint16_t)(pw[r >> 3].w[(r & 7) >> 1] >> (16 * (r & 1)));
+        *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(dstb) + at) = (uint16_t)(dw[r >> 3].w[(r & 7) >> 1] >> (16 * (r & 1)));
+      };
+      if (key0 + 31 < p.S) {                                // some lane's query is in range: 32 stores
+        if (qi < p.T) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) put(r);
+        }
+        stores = true;
       } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const unsigned at = at0 + (unsigned)(8 * (r >> 2) + (r & 3)) * (unsigned)p.t_ld * 2u;
-          *reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(ptb) + at) = pb[r >> 3][r & 7];
-          *reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(dstb) + at) = dsb[r >> 3][r & 7];
-        }
+        for (int r = 0; r < 16; ++r)
+          if (key0 + acc_row(r, h32) < p.S && qi < p.T) put(r);
       }
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
@@ -371,25 +437,19 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
         for (int dt = 0; dt < 2; ++dt)
           dqa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows_t(sK, 32 * dt, 32 * kh + 16 * sub, lane), dsb[sub], dqa[dt], 0, 0, 0);
       __builtin_amdgcn_wave_barrier();
-      // rows of the patch that hold a gradient: 0 <= 31 + l32 - rho < 32
+      // position half of dQ: the cells off the lane's diagonal band are zero
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        f32x16 g;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rho = 32 * t + acc_row(r, h32);
-          const int kk = 31 + l32 - rho;
-          const float v = patch[rho * XL8_LD + l32];
-          g[r] = (kk >= 0 && kk < 32) ? v : 0.f;
-        }
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
-          bf16x8 gb = pack_acc(g, sub);
+          const char* at = patch + l32 * (2 * XL_DS_LD) + 2 * (32 * t + 16 * sub + 4 * h32);
+          union { xl_u32x2 h[2]; bf16x8 v; } g;
+          g.h[0] = *reinterpret_cast<const xl_u32x2*>(at);
+          g.h[1] = *reinterpret_cast<const xl_u32x2*>(at + 16);
 #pragma unroll
           for (int dt = 0; dt < 2; ++dt)
-            dqb[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows_t(sR, 32 * dt, rrow0 + 32 * t + 16 * sub, lane), gb, dqb[dt], 0, 0, 0);
+            dqb[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows_t(xl_r_rows(lds, rrow0 + 32 * t, jb), 32 * dt, 16 * sub, lane), g.v, dqb[dt], 0, 0, 0);
         }
-      }
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -400,19 +460,20 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
   // the kernel: backward pass of 32 x 10 heads, T = M = 150, 200 -> 155 us, 16 x 16 heads, T = M = 384, 400 -> 373.
   {
     const f32x16* both[2] = {dqa, dqb};
+    xl_f32* mine = reinterpret_cast<xl_f32*>(patch);
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
 #pragma unroll
-      for (int i = 0; i < 32; ++i) patch[i * 64 + lane] = both[w][i >> 4][i & 15];
+      for (int i = 0; i < 32; ++i) mine[i * 64 + lane] = both[w][i >> 4][i & 15];
       __builtin_amdgcn_wave_barrier();
       float sum = 0.f;
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
-        const float4 x = *reinterpret_cast<const float4*>(patch + 32 * lane + 4 * ((c + (lane >> 1)) & 7));
+        const xl_f32x4 x = *reinterpret_cast<const xl_f32x4*>(mine + 32 * lane + 4 * ((c + (lane >> 1)) & 7));
         sum += (x.x + x.y) + (x.z + x.w);
       }
       __builtin_amdgcn_wave_barrier();
-      patch[2048 + 64 * w + lane] = sum;
+      mine[2048 + 64 * w + lane] = sum;
     }
   }
   // dQ: the second key half hands its sum to the first through its (own) patch
@@ -420,18 +481,18 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) patch[(16 * dt + r) * 64 + lane] = dqa[dt][r] + dqb[dt][r];
+      for (int r = 0; r < 16; ++r) reinterpret_cast<xl_f32*>(patch)[(16 * dt + r) * 64 + lane] = dqa[dt][r] + dqb[dt][r];
   }
   __syncthreads();
   if (wave < 2) {
     float sum = 0.f;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) sum += reinterpret_cast<const float*>(lds + XL_NSTAGE * XL_STAGE + w * XL8_PATCH)[2048 + 64 * wave + lane];
+    for (int w = 0; w < 8; ++w) sum += reinterpret_cast<const xl_f32*>(lds + XL_PATCHES + w * XL8_PATCH)[2048 + 64 * wave + lane];
     const int reg = lane >> 1;
     unsafeAtomicAdd((wave ? p.dvb : p.du) + head * 64 + 32 * (reg >> 4) + acc_row(reg & 15, lane & 1), sum * p.scale);
   }
   if (kh == 0 && qi < p.T) {
-    const float* other = reinterpret_cast<const float*>(lds + XL_NSTAGE * XL_STAGE + (wave + 4) * XL8_PATCH);
+    const xl_f32* other = reinterpret_cast<const xl_f32*>(lds + XL_PATCHES + (wave + 4) * XL8_PATCH);
     f32x16 sum[2];
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
