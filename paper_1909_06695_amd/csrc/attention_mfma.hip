@@ -161,19 +161,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // read Q / dO rows, dV^T += dO^T P and dK^T += Q^T dS read the same tiles transposed.
 constexpr int DKV_STAGE = 2 * TILE_BYTES + 1024;   // Q, dO, lse[64], D[64], two spare lines
 // two workgroups per compute unit (256 registers per lane)
-template <bool PAIR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fa_bwd_dkv_kernel(FaParams p) {
-  __shared__ __attribute__((aligned(16))) char lds[NSTAGE * DKV_STAGE];
+// OWN_D: the row sums D and the base-2 log-sum-exp of a query block are formed here, four lanes a query, one block ahead (the
+// launch does not wait for the dQ kernel, which otherwise leaves them in the scratch arrays).
+template <bool PAIR, bool OWN_D>
+__device__ __forceinline__ void fa_bwd_dkv_body(const FaParams& p, char* lds, int first, int head, int b) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h32 = lane >> 5, l32 = lane & 31;
-  int first, head, b;                                     // key block 0 sees every query: the heaviest
-  if (PAIR) { first = blockIdx.x; head = blockIdx.y; b = blockIdx.z; }
-  else fa_decode_block(first, head, b);
   const bf16_t* qb = p.q + (size_t)b * p.T * p.ldq + head * 64;
   const bf16_t* dob = p.d_o + (size_t)b * p.T * p.lddo + head * 64;
   const bf16_t* kbp = p.k + (size_t)b * p.S * p.ldk + head * 64;
   const bf16_t* vbp = p.v + (size_t)b * p.S * p.ldv + head * 64;
-  const float* lseb = p.lse2 + ((size_t)b * p.H + head) * p.T;
-  const float* Db = p.D + ((size_t)b * p.H + head) * p.T;
+  const float* lseb = (OWN_D ? p.lse : p.lse2) + ((size_t)b * p.H + head) * p.T;
+  const float* Db = OWN_D ? nullptr : p.D + ((size_t)b * p.H + head) * p.T;
+  const bf16_t* ob = p.o + (size_t)b * p.T * p.ldo + head * 64;
   // Key block k sees the queries from 128 k - Mv on, so its work falls linearly with k.  Where
   // the launch still fills the chip that way (PAIR), a workgroup takes block k and then block
   // (last - k), and every workgroup has the same amount of work: with one block each the resident
@@ -216,16 +215,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     dma_tile(dob, p.lddo, i0, p.T, st + TILE_BYTES, wave, lane);
     // waves 0/1 fetch lse / D; waves 2/3 repeat them into spare lines so that every wave
     // has the same number of loads in flight
-    dma_floats((wave & 1) ? Db : lseb, i0, p.T, st + 2 * TILE_BYTES + wave * 256, lane);
+    if (!OWN_D) dma_floats((wave & 1) ? Db : lseb, i0, p.T, st + 2 * TILE_BYTES + wave * 256, lane);
   };
-  constexpr int LPT = 5;
+  constexpr int LPT = OWN_D ? 4 : 5;
+  uint4 own_o[2], own_do[2];
+  float own_lse = 0.f;
+  auto request_D = [&](int it) __attribute__((always_inline)) {                 // row 16 wave + lane / 4 of the block, 16 features
+    const size_t row = min((ib0 + it) * 64 + 16 * wave + (lane >> 2), p.T - 1);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      own_o[c] = *reinterpret_cast<const uint4*>(ob + row * p.ldo + 16 * (lane & 3) + 8 * c);
+      own_do[c] = *reinterpret_cast<const uint4*>(dob + row * p.lddo + 16 * (lane & 3) + 8 * c);
+    }
+    own_lse = lseb[row];
+  };
+  auto put_D = [&](int it) __attribute__((always_inline)) {
+    float d = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const bf16x8 x = as_bf16x8(own_o[c]), y = as_bf16x8(own_do[c]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d += (float)x[e] * (float)y[e];
+    }
+    d += __shfl_xor(d, 1, 64);
+    d += __shfl_xor(d, 2, 64);
+    float* line = reinterpret_cast<float*>(lds + (it % NSTAGE) * DKV_STAGE + 2 * TILE_BYTES) + 16 * wave + (lane >> 2);
+    if ((lane & 3) == 0) { line[0] = own_lse * 1.4426950408889634f; line[64] = d; }
+  };
+  if (OWN_D && nit > 0) request_D(0);
 #pragma unroll
   for (int s = 0; s < NSTAGE - 1; ++s)
     if (s < nit) issue(s);
+  if (OWN_D && nit > 0) put_D(0);
   for (int it = 0; it < nit; ++it) {
     if (it + NSTAGE - 1 <= nit) fa_wait_vmcnt<(NSTAGE - 2) * LPT>();
     else fa_wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();   // unfenced: younger tiles' loads stay in flight
+    if (OWN_D && it + 1 < nit) request_D(it + 1);           // ahead of the tiles, so that waiting for these does not wait for those
     if (it + NSTAGE - 1 < nit) issue(it + NSTAGE - 1);
     const int ib = ib0 + it;
     const char* sQ = lds + (it % NSTAGE) * DKV_STAGE;
@@ -298,6 +324,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
       }
     }
+    if (OWN_D && it + 1 < nit) put_D(it + 1);               // into the stage read two blocks ago
   }
   if (key < p.S) {
     store_acc_row(p.dk + ((size_t)b * p.S + key) * p.lddk + head * 64, dkT, p.scale, h32);
@@ -309,13 +336,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // ---------------------------------------------------------------------------- dQ kernel
 // grid (ceil(ceil(T/128) / 2), H, B); 4 waves x 32 queries; key blocks of 64: S^T = K Q^T and
 // dP^T = V dO^T read K / V rows, dQ^T += K^T dS^T reads the K tile transposed.
-template <bool PAIR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fa_bwd_dq_kernel(FaParams p) {
-  __shared__ __attribute__((aligned(16))) char lds[NSTAGE * 2 * TILE_BYTES];
+// LEAVE: D and the base-2 log-sum-exp are left in the scratch arrays for the dK/dV kernel, which runs after this one.
+template <bool PAIR, bool LEAVE>
+__device__ __forceinline__ void fa_bwd_dq_body(const FaParams& p, char* lds, int rank, int head, int b) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h32 = lane >> 5, l32 = lane & 31;
-  int rank, head, b;                                      // rank 0: the last query block, the heaviest
-  if (PAIR) { rank = blockIdx.x; head = blockIdx.y; b = blockIdx.z; }
-  else fa_decode_block(rank, head, b);
   const bf16_t* qb = p.q + (size_t)b * p.T * p.ldq + head * 64;
   const bf16_t* dob = p.d_o + (size_t)b * p.T * p.lddo + head * 64;
   const bf16_t* kb = p.k + (size_t)b * p.S * p.ldk + head * 64;
@@ -343,8 +367,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     qf[ks] = as_bf16x8(t0);
     dof[ks] = as_bf16x8(t1);
   }
-  // D = sum_c dO[i,c] O[i,c] and the base-2 log-sum-exp of the lane's query; both are also
-  // left in the scratch arrays for the dK/dV kernel, which runs after this one
+  // D = sum_c dO[i,c] O[i,c] and the base-2 log-sum-exp of the lane's query
   float lse_q = 0.f, D_q = 0.f;
   {
     const bf16_t* ob = p.o + (size_t)b * p.T * p.ldo + head * 64;
@@ -361,7 +384,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (qi < p.T) {
       const size_t r = ((size_t)b * p.H + head) * p.T + qi;
       lse_q = p.lse[r] * 1.4426950408889634f;
-      if (h32 == 0) { p.D[r] = D_q; p.lse2[r] = lse_q; }
+      if (LEAVE && h32 == 0) { p.D[r] = D_q; p.lse2[r] = lse_q; }
     }
   }
   const int wg_last_q = min(p.T, qblk * 128 + 128) - 1;
@@ -438,6 +461,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 }
 
+// ----------------------------------------------------------------------------- kernels
+constexpr int DQ_LDS = NSTAGE * 2 * TILE_BYTES, DKV_LDS = NSTAGE * DKV_STAGE;
+// two workgroups per compute unit (256 registers per lane)
+template <bool PAIR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fa_bwd_dkv_kernel(FaParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[DKV_LDS];
+  int first, head, b;                                     // key block 0 sees every query: the heaviest
+  if (PAIR) { first = blockIdx.x; head = blockIdx.y; b = blockIdx.z; }
+  else fa_decode_block(first, head, b);
+  fa_bwd_dkv_body<PAIR, false>(p, lds, first, head, b);
+}
+template <bool PAIR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fa_bwd_dq_kernel(FaParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[DQ_LDS];
+  int rank, head, b;                                      // rank 0: the last query block, the heaviest
+  if (PAIR) { rank = blockIdx.x; head = blockIdx.y; b = blockIdx.z; }
+  else fa_decode_block(rank, head, b);
+  fa_bwd_dq_body<PAIR, true>(p, lds, rank, head, b);
+}
+// Both in one launch, where all their workgroups fit the chip side by side (two per compute unit): nq blocks of queries and nk of
+// keys for each of `groups` = heads x batches.  Work items are numbered heaviest first, and the second half of the
+// workgroups takes them from the light end, so that the two workgroups of a compute unit carry complementary loads.
+// 3 x 12 heads, T = 777 (504 workgroups): 58 -> 44 us; 3 x 2 heads, T = 96 (12): 15.4 -> 9.6.  Beyond that it gives nothing: 16 x 8 heads,
+// T = 512, two blocks a workgroup: 46.7 and 44.9 beside other work, the pass of the model the same.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fa_bwd_both_kernel(FaParams p, int nq, int nk) {
+  __shared__ __attribute__((aligned(16))) char lds[DKV_LDS];
+  const int groups = p.H * p.B, n = gridDim.x, nmin = min(nq, nk);
+  int i = blockIdx.x;
+  if (i >= (n + 1) / 2) i = n - 1 - (i - (n + 1) / 2);
+  // ranks both axes have: a row of dK/dV items, then a row of dQ items; the longer axis' surplus is at the light end
+  int rank = i / (2 * groups), r = i - rank * 2 * groups;
+  bool keys = r < groups;
+  if (rank >= nmin) {
+    r = i - nmin * 2 * groups;
+    rank = nmin + r / groups;
+    keys = nk > nq;
+  }
+  const int g = r % groups, head = g % p.H, b = g / p.H;
+  if (keys) fa_bwd_dkv_body<false, true>(p, lds, rank, head, b);
+  else fa_bwd_dq_body<false, false>(p, lds, rank, head, b);
+}
+
 // ----------------------------------------------------------------------------- dispatch
 static inline bool al16(const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
 
@@ -464,6 +529,11 @@ hipError_t launch_attn_bwd_mfma(hipStream_t s, const AttnDesc& a) {
   // two blocks of the causal axis per workgroup where that still leaves two workgroups per compute unit
   const int nq = (a.T + 127) / 128, nk = (a.S + 127) / 128;
   const bool pair = (long)((std::min(nq, nk) + 1) / 2) * a.H * a.B >= 512;
+  const long both = (long)(nq + nk) * a.H * a.B;
+  if (both <= 512) {
+    hipLaunchKernelGGL(fa_bwd_both_kernel, dim3((unsigned)both), dim3(256), 0, s, p, nq, nk);
+    return hipGetLastError();
+  }
   // the dQ kernel also produces the row sums D and the base-2 log-sum-exp the dK/dV kernel reads
   if (pair) hipLaunchKernelGGL(fa_bwd_dq_kernel<true>, dim3((nq + 1) / 2, a.H, a.B), dim3(256), 0, s, p);
   else hipLaunchKernelGGL(fa_bwd_dq_kernel<false>, dim3(nq, a.H, a.B), dim3(256), 0, s, p);

@@ -400,10 +400,12 @@ def test_attention_general_kernel(dtype, B, H, T, Mv, dh, rel):
 
 
 @pytest.mark.parametrize("B,H,T,Mv", [(2, 2, 128, 0), (1, 3, 200, 0), (2, 1, 96, 40), (1, 2, 512, 0), (1, 1, 33, 0),
-                                      (1, 2, 300, 77), (32, 16, 256, 0), (16, 16, 384, 0), (16, 16, 300, 90)])
+                                      (1, 2, 300, 77), (1, 2, 100, 300), (4, 16, 512, 0), (8, 16, 300, 0), (32, 16, 256, 0), (16, 16, 384, 0),
+                                      (16, 16, 300, 90)])
 def test_attention_mfma_kernel(B, H, T, Mv):
     """Fused matrix-core kernels (bf16, head size 64): several query/key blocks, ragged
-    tails, and a key prefix (Mv) that every query sees.  The last three cases have enough
+    tails, and a key prefix (Mv) that every query sees.  Up to 512 workgroups the backward pass is one launch (unequal block
+    counts; the largest one), beyond it two.  The last three cases have enough
     (batch, head) pairs for the backward kernels to take two blocks per workgroup (an even
     count, an odd one whose middle block goes alone, and unequal query / key block counts)."""
     _attn_case(1, B, H, T, Mv, 64, 0, seed=100 + T + Mv, force=0)
@@ -418,7 +420,7 @@ def test_attention_xl_mfma_kernel(B, H, T, Mv):
     _attn_case(1, B, H, T, Mv, 64, 1, seed=200 + T + Mv, force=0)
 
 
-@pytest.mark.parametrize("B,H,T,Mv,dh", [(1, 1, 1, 0, 64), (2, 2, 33, 0, 32), (1, 3, 70, 5, 41), (2, 2, 128, 0, 64), (1, 2, 150, 40, 48),
+@pytest.mark.parametrize("B,H,T,Mv,dh", [(1, 1, 1, 0, 64), (2, 1, 10, 200, 32), (2, 2, 33, 0, 32), (1, 3, 70, 5, 41), (2, 2, 128, 0, 64), (1, 2, 150, 40, 48),
                                          (2, 1, 257, 0, 7), (1, 2, 31, 97, 36)])
 def test_attention_f32_kernel(B, H, T, Mv, dh):
     """fp32 attention on the matrix cores: one query, ragged tiles on both axes, memory before the segment, head sizes that
