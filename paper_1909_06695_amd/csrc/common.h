@@ -217,8 +217,10 @@ hipError_t launch_layernorm_bwd_params(hipStream_t s, int dtype, const void* dy,
 hipError_t launch_colsum(hipStream_t s, int dtype, const void* x, int ldx, float* out, int rows, int cols, size_t copy_stride = 0);
 // One piece of a gathered sum: dst[dst_off + i] += sum over 8 copies of src[c * stride + src_off + i], i < len <= 256
 struct SumSegment { unsigned src_off, dst_off, len; };
-// All pieces of a device table in one launch; the copies are left zero.
-hipError_t launch_sum_segments(hipStream_t s, const SumSegment* table, int count, float* src, size_t stride, float* dst);
+struct SumSegmentsOf { const SumSegment* table; int count; float* dst; };      // a device table and where its sums go
+constexpr int SUM_SEGMENTS_MAX = 16;
+// All pieces of n tables, SUM_SEGMENTS_MAX tables a launch; the copies are left zero.
+hipError_t launch_sum_segments(hipStream_t s, const SumSegmentsOf* of, int n, float* src, size_t stride);
 // h[n,:] = scale * V[tok[n],:] (+ pe[n % T,:]); ids outside [0,vocab) set *flag and give a zero row
 // drop (optional): dropout on the sum, element index n*drop->ld + c
 hipError_t launch_embed_fwd(hipStream_t s, int dtype, const int32_t* tok, const void* V, const float* pe,
@@ -249,8 +251,12 @@ hipError_t launch_ce_rows(hipStream_t s, int dtype, const void* logits, int ld, 
 // loss = sum(rowloss) (fixed order, one block)
 hipError_t launch_sum_rows(hipStream_t s, const float* rowloss, int N, float* loss);
 hipError_t launch_convert(hipStream_t s, int dtype_dst, void* dst, const float* src, size_t n);      // fp32 -> T
+hipError_t launch_convert_clear(hipStream_t s, bf16_t* dst, float* src, size_t n);                // fp32 -> bf16, src left zero; both 16-byte aligned
 hipError_t launch_to_f32(hipStream_t s, int dtype_src, float* dst, const void* src, size_t n);       // T -> fp32
 hipError_t launch_fill_zero(hipStream_t s, void* p, size_t bytes);                                   // bytes % 4 == 0
+struct FillRange { void* p; size_t bytes; };                                                        // 16-byte aligned, bytes % 4 == 0
+constexpr int FILL_MAX = 16;
+hipError_t launch_fill_zero_ranges(hipStream_t s, const FillRange* r, int n);                        // FILL_MAX ranges a launch
 // strided row copy: dst[b, r, :] = src[b, r0 + r, :]; rows of d elements of type T; the same for `layers` buffers that lie
 // dst_lstride / src_lstride elements apart
 hipError_t launch_copy_rows(hipStream_t s, int dtype, void* dst, size_t dst_bstride, size_t dst_off,
@@ -270,5 +276,12 @@ struct UpdateDesc {
   float lr, beta1, beta2, eps, bc1, bc2;
 };
 hipError_t launch_update(hipStream_t s, const UpdateDesc& u);
+// The same for n parameter groups (UPD_GROUP_MAX a launch, equal step sizes, betas and t), with the transposed bf16 copies.  A group's table
+// covers its n elements: the matrices (as in launch_transpose_table; ld_out > 0) and, with ld_out = 0 and rows = 1, what lies
+// between them; tile0 counts update_tiles().
+constexpr int UPD_GROUP_MAX = 16;
+struct UpdateTable { const TransposeEntry* dev; int entries, tiles; void* shadowT; };
+int update_tiles(int rows, int cols, int ld_out);
+hipError_t launch_update_groups(hipStream_t s, const UpdateDesc* u, const UpdateTable* tab, int n);
 
 }  // namespace ouro

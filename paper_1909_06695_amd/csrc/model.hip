@@ -161,6 +161,7 @@ struct BwdCtx {
   char *ds2[2], *dz[2], *ds1[2], *dqkv[2];
   char *ds2m[2], *ds1m[2];         // ds2 / ds1 times the dropout masks (the same buffers without dropout)
   float *attn_scratch, *dr_f32[2];
+  bool dr_clear[2];              // dr_f32 is zero: the conversion of its last gradients cleared it
   int attn_scratch_Mv;           // relative mode: memory length of the passes since the workspace was last cleared (-1: none)
   char* hscratch;                 // output of a recomputed module's last layer (never read)
 };
@@ -202,6 +203,10 @@ struct ouro_model : BwdCtx {
   std::vector<std::vector<TransposeEntry>> ttab;
   std::vector<TransposeEntry*> ttab_dev;
   std::vector<int> ttiles;
+  // what the update walks: the matrices of ttab and the pieces between them
+  std::vector<std::vector<TransposeEntry>> utab;
+  std::vector<TransposeEntry*> utab_dev;
+  std::vector<int> utiles;
   // gradient stores 0..K+1
   std::vector<int64_t> gcount, gstride, depth;   // elements per gradient (caller's), slot stride (stored, 256-byte multiple)
   std::vector<float*> ring;
@@ -233,6 +238,9 @@ struct ouro_model : BwdCtx {
   std::vector<size_t> vec_off;
   std::vector<std::vector<SumSegment>> segs;
   std::vector<SumSegment*> segs_dev;
+  // inside a step on one stream: the sums of the vector gradients are collected; the gradient slots are cleared already
+  bool batched = false, cleared = false;
+  std::vector<SumSegmentsOf> sums;
   // Stored-input schedule (cfg.schedule == 1): module k < K keeps the input of its last
   // K-k+1 forward passes (token ids for k = 1, the hidden state at the boundary otherwise),
   // tagged with the iteration; the error gradient of module k's output travels from module
@@ -481,6 +489,7 @@ static size_t lay_out(ouro_model& m, char* base) {
     for (int p2 = 0; p2 < 2; ++p2) {
       x.dr_t[p2] = c.rel_pos ? P(S * hd * es) : nullptr;
       x.dr_f32[p2] = c.rel_pos ? (float*)P(S * hd * 4) : nullptr;
+      x.dr_clear[p2] = false;
     }
     x.attn_scratch = (float*)P((c.rel_pos ? attn_bwd_scratch_floats_any(c.batch, c.n_head, c.seq_len, (int)S, m.pdh)
                                           : attn_bwd_scratch_floats(c.batch, c.n_head, c.seq_len, (int)S, m.pdh)) * 4);
@@ -524,6 +533,24 @@ static size_t lay_out(ouro_model& m, char* base) {
       tiles += (t.rows + REMAP_ROWS - 1) / REMAP_ROWS;
     }
     m.remaps_dev[k] = (RemapEntry*)P(m.remaps[k].size() * sizeof(RemapEntry));
+  }
+  m.utab.assign(K + 1, {}); m.utab_dev.assign(K + 1, nullptr); m.utiles.assign(K + 1, 0);
+  for (int k = 0; k <= K; ++k) {
+    size_t at = 0;
+    auto add = [&](size_t off, int rows, int cols, int ld_out) {
+      m.utab[k].push_back({(unsigned long long)off, rows, cols, ld_out, m.utiles[k]});
+      m.utiles[k] += update_tiles(rows, cols, ld_out);
+    };
+    auto linear = [&](size_t to) {                          // [at, to), in pieces whose length fits an int
+      for (; at < to; at += std::min<size_t>(to - at, (size_t)1 << 30)) add(at, 1, (int)std::min<size_t>(to - at, (size_t)1 << 30), 0);
+    };
+    for (const TransposeEntry& t : m.ttab[k]) {
+      linear((size_t)t.off);
+      add((size_t)t.off, t.rows, t.cols, t.ld_out);
+      at = (size_t)t.off + (size_t)t.rows * t.cols;
+    }
+    linear((size_t)m.pcount[k]);
+    m.utab_dev[k] = (TransposeEntry*)P(m.utab[k].size() * sizeof(TransposeEntry));
   }
   return bp.off;
 }
@@ -636,6 +663,9 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
   for (int k = 0; k <= K && e == hipSuccess; ++k)
     if (m->ttab_dev[k])
       e = hipMemcpyAsync(m->ttab_dev[k], m->ttab[k].data(), m->ttab[k].size() * sizeof(TransposeEntry), hipMemcpyHostToDevice, m->stream);
+  for (int k = 0; k <= K && e == hipSuccess; ++k)
+    if (!m->utab[k].empty())
+      e = hipMemcpyAsync(m->utab_dev[k], m->utab[k].data(), m->utab[k].size() * sizeof(TransposeEntry), hipMemcpyHostToDevice, m->stream);
   for (int k = 1; k <= K && e == hipSuccess; ++k)
     if (!m->segs[k].empty())
       e = hipMemcpyAsync(m->segs_dev[k], m->segs[k].data(), m->segs[k].size() * sizeof(SumSegment), hipMemcpyHostToDevice, m->stream);
@@ -1149,10 +1179,16 @@ static int layer_backward(ouro_model* m, int l, char* dh, char* dx, float* gslot
       m->attn_scratch_Mv = Mv;
     }
     a.scratch_clean = 1;
-    HIPCHK(launch_fill_zero(st, drf, (size_t)S * hd * 4));
+    // bf16: the conversion of the layer before that used this buffer left it cleared
+    if (!m->dr_clear[ps]) HIPCHK(launch_fill_zero(st, drf, (size_t)m->S * hd * 4));
+    m->dr_clear[ps] = false;
     RUN(timed_launch(m, OURO_TIMING_ATTENTION, 2.0 * attn_fwd_flops(m, Mv), st, [&] { return launch_attn_bwd(st, c.dtype, a, 0); }));
     const void* drp = drf;
-    if (c.dtype == 1) { HIPCHK(launch_convert(st, 1, m->dr_t[ps], drf, (size_t)S * hd)); drp = m->dr_t[ps]; }
+    if (c.dtype == 1) {
+      HIPCHK(launch_convert_clear(st, (bf16_t*)m->dr_t[ps], drf, (size_t)S * hd));
+      m->dr_clear[ps] = true;
+      drp = m->dr_t[ps];
+    }
     RUN(ready());
     // weight gradients: dW_r = R^T dr, dW_q = x^T dq, dW_kv = [mem ; x]^T dkv
     {
@@ -1244,7 +1280,7 @@ static int module_backward_impl(ouro_model* m, int k, bool defer_join) {
     dh_top = m->mail[pr][k];
   }
   float* gslot = m->slot_ptr(k, slot);
-  HIPCHK(launch_fill_zero(m->stream, gslot, (size_t)m->gstride[k] * 4));
+  if (!m->cleared) HIPCHK(launch_fill_zero(m->stream, gslot, (size_t)m->gstride[k] * 4));
   if (k == K) {
     // Eq. 7 (right): dV_o = G^T h_L ; error gradient dh_L = G V
     float* dvo = m->slot_ptr(K + 1, 0);
@@ -1291,7 +1327,10 @@ static int module_backward_impl(ouro_model* m, int k, bool defer_join) {
   if (stored) m->mem_valid = mem_valid_at(m, m->t);
   // the layers' vector gradients: sum of the copies into the slot.  On the stream of the
   // weight-gradient work, which has waited for every LayerNorm kernel of the module.
-  HIPCHK(launch_sum_segments(m->use_side ? m->side : m->stream, m->segs_dev[k], (int)m->segs[k].size(), m->vec_copies, m->vec_stride, gslot));
+  // Where a whole step runs on one stream, one launch behind the last module takes them all.
+  const SumSegmentsOf of{m->segs_dev[k], (int)m->segs[k].size(), gslot};
+  if (m->batched) m->sums.push_back(of);
+  else HIPCHK(launch_sum_segments(m->use_side ? m->side : m->stream, &of, 1, m->vec_copies, m->vec_stride));
   if (m->use_side) {          // the module's gradient is complete once the side work has joined
     HIPCHK(hipEventRecord(m->ev_join, m->side));
     if (!defer_join) {
@@ -1305,7 +1344,7 @@ static int module_backward_impl(ouro_model* m, int k, bool defer_join) {
     int64_t s0 = 0, t0;
     if (!stored) ouro_slot_index(K, 0, m->t, 1, &s0, &t0);
     float* dvi = m->slot_ptr(0, s0);
-    HIPCHK(launch_fill_zero(m->stream, dvi, (size_t)m->gstride[0] * 4));
+    if (!m->cleared) HIPCHK(launch_fill_zero(m->stream, dvi, (size_t)m->gstride[0] * 4));
     const DropDesc dd = drop_at(m, 0);
     HIPCHK(launch_embed_bwd(m->stream, 0, tok, m->dhb[2], dvi, N, d, V, c.emb_scale, &dd));   // dh is fp32
     m->tags[0][s0] = m->t;
@@ -1350,11 +1389,10 @@ static int close_iteration(ouro_model* m) {
   return OURO_OK;
 }
 
-// One optimizer step of a parameter group with the gradient Eq. 8 / Eq. 9 select, on stream st.
-static int update_group(ouro_model* m, int group, float lr, hipStream_t st) {
+// What one optimizer step of a parameter group takes: the gradient Eq. 8 / Eq. 9 select.
+static int prepare_update(ouro_model* m, int group, float lr, UpdateDesc& u) {
   const ouro_config& c = m->cfg;
   const int K = c.n_module;
-  UpdateDesc u;
   memset(&u, 0, sizeof u);
   u.w = m->master[group]; u.m = m->adam_m[group]; u.v = m->adam_v[group]; u.shadow = m->shadow[group];
   u.n = (size_t)m->pcount[group]; u.adam = c.optimizer; u.lr = lr;
@@ -1395,16 +1433,35 @@ static int update_group(ouro_model* m, int group, float lr, hipStream_t st) {
       u.g1 = m->slot_ptr(0, si); u.gscale1 = 0.5f;
     }
   }
-  const bool timed = m->timing && u.g0;
-  if (timed) RUN(timing_begin(m, OURO_TIMING_UPDATE, st));
-  HIPCHK(launch_update(st, u));
-  if (timed) {
+  return OURO_OK;
+}
+
+// One optimizer step of the n groups of a list, on stream st.  On a stream of its own, beside other work, a group goes out as the
+// plain streaming kernel and the one that transposes: tile by tile it gains nothing there (512- and 1024-wide decoders
+// 1.00, 512-wide fp32 0.99), alone it does (18 x 1024-wide with relative positions 2.4 -> 1.95 ms a step with its transposed
+// copies; 3 x 128-wide 33 -> 9 us).
+static int update_groups(ouro_model* m, const int* groups, int n, float lr, hipStream_t st) {
+  const int K = m->cfg.n_module;
+  std::vector<UpdateDesc> u(n);
+  std::vector<UpdateTable> tab(n);
+  double bytes = 0;
+  bool timed = m->timing != 0;
+  for (int i = 0; i < n; ++i) {
+    const int g = groups[i];
+    RUN(prepare_update(m, g, lr, u[i]));
+    tab[i] = {m->utab_dev[g], (int)m->utab[g].size(), m->utiles[g], m->cfg.dtype == 1 ? m->shadowT[g] : nullptr};
+    timed = timed && u[i].g0;
     // algorithmic bytes per element: gradient(s) 4 each, w read+write 8, Adam m,v read+write 16, bf16 copy 2
-    double per = 4.0 * ((u.g0 ? 1 : 0) + (u.g1 ? 1 : 0)) + 8.0 + (u.adam ? 16.0 : 0.0) + (u.shadow ? 2.0 : 0.0);
-    RUN(timing_end(m, OURO_TIMING_UPDATE, per * (double)u.n, st));
+    bytes += (4.0 * ((u[i].g0 ? 1 : 0) + (u[i].g1 ? 1 : 0)) + 8.0 + (u[i].adam ? 16.0 : 0.0) + (u[i].shadow ? 2.0 : 0.0)) * (double)u[i].n;
   }
-  RUN(refresh_transposed(m, group, st));
-  m->upd_mask |= 1ull << group;
+  if (timed) RUN(timing_begin(m, OURO_TIMING_UPDATE, st));
+  if (m->use_side)
+    for (int i = 0; i < n; ++i) HIPCHK(launch_update(st, u[i]));
+  else HIPCHK(launch_update_groups(st, u.data(), tab.data(), n));
+  if (timed) RUN(timing_end(m, OURO_TIMING_UPDATE, bytes, st));
+  if (m->use_side)
+    for (int i = 0; i < n; ++i) RUN(refresh_transposed(m, groups[i], st));
+  for (int i = 0; i < n; ++i) m->upd_mask |= 1ull << groups[i];
   if (m->upd_mask == (1ull << (K + 1)) - 1) {
     if (m->upd_pending) {       // the next iteration reads every weight: main waits for aux
       HIPCHK(hipEventRecord(m->ev_upd_done, m->aux));
@@ -1415,6 +1472,7 @@ static int update_group(ouro_model* m, int group, float lr, hipStream_t st) {
   }
   return OURO_OK;
 }
+static int update_group(ouro_model* m, int group, float lr, hipStream_t st) { return update_groups(m, &group, 1, lr, st); }
 
 extern "C" int ouro_delayed_update(ouro_model* m, int group, float lr) {
   if (!m) return fail(OURO_E_ARG, "model is null");
@@ -1480,6 +1538,28 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
     return OURO_OK;
   }
   const bool early = m->use_side && !m->timing;
+  // A step on one stream: the gradient slots of all modules are cleared by one launch and their vector gradients summed by
+  // one, as its small launches follow each other at 2 us each and more.
+  struct Batch {
+    ouro_model* m;
+    explicit Batch(ouro_model* x) : m(x) {}
+    ~Batch() { m->batched = m->cleared = false; m->sums.clear(); }
+  } batch(m);
+  // (beyond the 256 MB of the memory-side cache a module's slot is better cleared right before its gradients: 1.17 GB 157 us in five
+  // launches, 215 in one; 240 MB 46 and 41)
+  size_t slots = 0;
+  for (int k = 0; k <= K; ++k) slots += (size_t)m->gstride[k] * 4;
+  m->batched = !m->use_side && m->cfg.schedule == 0;
+  if (m->batched && slots <= (size_t)256 << 20) {
+    std::vector<FillRange> r;
+    int64_t slot, tau;
+    for (int k = 0; k <= K; ++k) {
+      ouro_slot_index(K, k, m->t, 1, &slot, &tau);
+      r.push_back({m->slot_ptr(k, slot), (size_t)m->gstride[k] * 4});
+    }
+    HIPCHK(launch_fill_zero_ranges(m->stream, r.data(), (int)r.size()));
+    m->cleared = true;
+  }
   for (int k = K; k >= 1; --k) {
     RUN(module_backward_impl(m, k, early && k > 1));
     if (early && k > 1) {
@@ -1493,9 +1573,11 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
       if (k == K && m->cfg.schedule == 0) RUN(update_group(m, 0, lr, m->aux));
     }
   }
-  const uint64_t done = m->upd_mask;    // the last update closes the iteration and clears the mask
+  if (m->batched) HIPCHK(launch_sum_segments(m->stream, m->sums.data(), (int)m->sums.size(), m->vec_copies, m->vec_stride));
+  std::vector<int> rest;                // the last update closes the iteration and clears the mask
   for (int k = 0; k <= K; ++k)
-    if (!(done & (1ull << k))) RUN(update_group(m, k, lr, m->stream));
+    if (!(m->upd_mask & (1ull << k))) rest.push_back(k);
+  RUN(update_groups(m, rest.data(), (int)rest.size(), lr, m->stream));
   if (host_loss) return read_loss(m, host_loss);
   return OURO_OK;
 }

@@ -490,9 +490,12 @@ hipError_t launch_layernorm_bwd_params(hipStream_t s, int dtype, const void* dy,
 }
 
 // One block per segment: sums the 8 copies, zeroes them, adds the sum to its place in dst.
-__global__ __launch_bounds__(256) void sum_segments_kernel(const SumSegment* __restrict__ table, float* __restrict__ src,
-                                                           size_t stride, float* __restrict__ dst) {
-  const SumSegment sg = table[blockIdx.x];
+struct SumSegmentsParams { int n, first[SUM_SEGMENTS_MAX]; SumSegmentsOf of[SUM_SEGMENTS_MAX]; };
+__global__ __launch_bounds__(256) void sum_segments_kernel(SumSegmentsParams q, float* __restrict__ src, size_t stride) {
+  int k = 0;
+  while (k + 1 < q.n && (int)blockIdx.x >= q.first[k + 1]) ++k;
+  float* const dst = q.of[k].dst;
+  const SumSegment sg = q.of[k].table[blockIdx.x - q.first[k]];
   if (threadIdx.x >= sg.len) return;
   float t = 0.f;
 #pragma unroll
@@ -503,10 +506,23 @@ __global__ __launch_bounds__(256) void sum_segments_kernel(const SumSegment* __r
   }
   dst[sg.dst_off + threadIdx.x] += t;
 }
-hipError_t launch_sum_segments(hipStream_t s, const SumSegment* table, int count, float* src, size_t stride, float* dst) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sum_segments_kernel, dim3(count), dim3(256), 0, s, table, src, stride, dst);
-  return hipGetLastError();
+hipError_t launch_sum_segments(hipStream_t s, const SumSegmentsOf* of, int n, float* src, size_t stride) {
+  for (int i0 = 0; i0 < n; i0 += SUM_SEGMENTS_MAX) {
+    SumSegmentsParams p;
+    memset(&p, 0, sizeof p);
+    int blocks = 0;
+    for (int i = i0; i < n && i < i0 + SUM_SEGMENTS_MAX; ++i) {
+      if (of[i].count <= 0) continue;
+      p.of[p.n] = of[i];
+      p.first[p.n++] = blocks;
+      blocks += of[i].count;
+    }
+    if (blocks == 0) continue;
+    hipLaunchKernelGGL(sum_segments_kernel, dim3(blocks), dim3(256), 0, s, p, src, stride);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_colsum(hipStream_t s, int dtype, const void* x, int ldx, float* out, int rows, int cols, size_t copy_stride) {
@@ -903,16 +919,60 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t nwords) {
   for (size_t j = i; j < n4; j += stride) p4[j] = make_uint4(0, 0, 0, 0);
   for (size_t j = n4 * 4 + i; j < nwords; j += stride) p[j] = 0;
 }
+struct FillParams { int n; unsigned first[FILL_MAX + 1]; FillRange r[FILL_MAX]; };
+__global__ __launch_bounds__(256) void fill_zero_ranges_kernel(FillParams q) {
+  int k = 0;
+  while (k + 1 < q.n && blockIdx.x >= q.first[k + 1]) ++k;
+  const size_t nwords = q.r[k].bytes / 4, stride = (size_t)(q.first[k + 1] - q.first[k]) * 256, n4 = nwords / 4;
+  const size_t i = (size_t)(blockIdx.x - q.first[k]) * 256 + threadIdx.x;
+  uint32_t* p = reinterpret_cast<uint32_t*>(q.r[k].p);
+  for (size_t j = i; j < n4; j += stride) reinterpret_cast<uint4*>(p)[j] = make_uint4(0, 0, 0, 0);
+  for (size_t j = n4 * 4 + i; j < nwords; j += stride) p[j] = 0;
+}
 static inline unsigned grid_for(size_t n, unsigned per_block = 256, unsigned cap = 8192) {
   size_t g = (n + per_block - 1) / per_block;
   if (g > cap) g = cap;
   if (g < 1) g = 1;
   return (unsigned)g;
 }
+hipError_t launch_fill_zero_ranges(hipStream_t s, const FillRange* r, int n) {
+  for (int i0 = 0; i0 < n; i0 += FILL_MAX) {
+    FillParams q;
+    memset(&q, 0, sizeof q);
+    for (int i = i0; i < n && i < i0 + FILL_MAX; ++i) {
+      if (r[i].bytes == 0) continue;
+      q.r[q.n] = r[i];
+      q.first[q.n + 1] = q.first[q.n] + grid_for(r[i].bytes / 16 + 1);
+      ++q.n;
+    }
+    if (q.n == 0) continue;
+    hipLaunchKernelGGL(fill_zero_ranges_kernel, dim3(q.first[q.n]), dim3(256), 0, s, q);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 hipError_t launch_convert(hipStream_t s, int dtype_dst, void* dst, const float* src, size_t n) {
   if (n == 0) return hipSuccess;
   if (dtype_dst == 1) hipLaunchKernelGGL(convert_kernel<bf16_t>, dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)dst, src, n);
   else hipLaunchKernelGGL(convert_kernel<float>, dim3(grid_for(n)), dim3(256), 0, s, (float*)dst, src, n);
+  return hipGetLastError();
+}
+// dst = src as bf16, src = 0
+__global__ __launch_bounds__(256) void convert_clear_kernel(bf16_t* dst, float* src, size_t n) {
+  const size_t n4 = n / 4, i = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+  for (size_t j = i; j < n4; j += stride) {
+    const float4 x = reinterpret_cast<const float4*>(src)[j];
+    reinterpret_cast<float4*>(src)[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    union { bf16_t h[4]; uint2 p; } c;
+    c.h[0] = (bf16_t)x.x; c.h[1] = (bf16_t)x.y; c.h[2] = (bf16_t)x.z; c.h[3] = (bf16_t)x.w;
+    reinterpret_cast<uint2*>(dst)[j] = c.p;
+  }
+  for (size_t j = n4 * 4 + i; j < n; j += stride) { dst[j] = (bf16_t)src[j]; src[j] = 0.f; }
+}
+hipError_t launch_convert_clear(hipStream_t s, bf16_t* dst, float* src, size_t n) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(convert_clear_kernel, dim3(grid_for(n / 4 + 1, 256, 2048)), dim3(256), 0, s, dst, src, n);
   return hipGetLastError();
 }
 hipError_t launch_to_f32(hipStream_t s, int dtype_src, float* dst, const void* src, size_t n) {
@@ -1000,11 +1060,12 @@ struct UpdParams {
 };
 template <bool ADAM>
 __device__ __forceinline__ float upd_one(float w, float g, float& m, float& v, const UpdParams& p) {
-  if (!ADAM) return w - p.lr * g;
-  m = p.b1 * m + (1.f - p.b1) * g;
-  v = p.b2 * v + (1.f - p.b2) * g * g;
-  float mh = m / p.bc1, vh = v / p.bc2;
-  return w - p.lr * (mh / (sqrtf(vh) + p.eps));
+  // the fused operations are written out: the kernels agree to the last bit
+  if (!ADAM) return fmaf(-p.lr, g, w);
+  m = fmaf(p.b1, m, (1.f - p.b1) * g);
+  v = fmaf(p.b2, v, (1.f - p.b2) * g * g);
+  const float mh = m / p.bc1, vh = v / p.bc2;
+  return fmaf(-p.lr, mh / (sqrtf(vh) + p.eps), w);
 }
 // Streaming accesses of the update: every byte is touched once per iteration, so it is kept out of
 // the caches' way (the bf16 copy, which the next forward pass reads, is stored normally).
@@ -1078,6 +1139,140 @@ hipError_t launch_update(hipStream_t s, const UpdateDesc& u) {
   if (u.adam) hipLaunchKernelGGL(update_kernel<true>, grid, block, 0, s, p);
   else hipLaunchKernelGGL(update_kernel<false>, grid, block, 0, s, p);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------ update of whole parameter groups
+// The same update over several groups in one launch, tile by tile, with both bf16 copies written on the way: a block takes 64 x
+// 128 elements of a matrix (rows of 512 bytes, 8192 elements: what 256 threads keep under way in two halves of four 16-byte
+// packs a stream), keeps their new bf16 values in LDS and writes them transposed as well.  What lies between the matrices
+// (LayerNorm, biases) goes in linear pieces of 8192.  Bound by memory: 30 bytes an element with Adam and both copies 32.
+// Measured in a step on one stream, with the transposing launches that this takes the place of before: 294 million elements
+// (18 x 1024-wide, V 65536) 2.37 -> 1.95 ms (4.8 TB/s), 3 x 128-wide with 1001 words 129 -> 37 us per four steps.
+constexpr int UPD_R = 64, UPD_C = 128, UPD_LD = 134;       // LDS row of 67 dwords: a column's two halves fall on different banks
+struct UpdGroupParams { float *w, *m, *v; bf16_t *shadow, *shadowT; const float *g0, *g1; float s0, s1; const TransposeEntry* tab; int entries, first; };
+struct UpdGroupsParams { int n; UpdParams hyper; UpdGroupParams g[UPD_GROUP_MAX]; };
+// PARTS blocks share a tile.
+template <bool ADAM, int PARTS>
+__global__ __launch_bounds__(256) void update_groups_kernel(UpdGroupsParams a) {
+  constexpr int ROWS = UPD_R / PARTS, U = ROWS / 8 < 4 ? ROWS / 8 : 4;           // rows of a block, packs of a thread under way
+  __shared__ __attribute__((aligned(16))) bf16_t tile[ROWS][UPD_LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  int gi = 0;
+  const int all = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+  while (gi + 1 < a.n && all >= a.g[gi + 1].first) ++gi;
+  const UpdGroupParams& q = a.g[gi];
+  const int block = all - q.first;
+  // the entry: the last whose first tile is not past this block
+  int e = -1;
+  for (int i0 = 0; i0 < q.entries; i0 += 64) e += __popcll(__ballot(i0 + lane < q.entries && q.tab[min(i0 + lane, q.entries - 1)].tile0 <= block));
+  const TransposeEntry t = q.tab[__builtin_amdgcn_readfirstlane(e)];
+  const bool matrix = t.ld_out != 0;
+  const int local = block - t.tile0, tiles_c = matrix ? (t.cols + UPD_C - 1) / UPD_C : 1;
+  const int r0 = local / tiles_c * UPD_R + part * ROWS, c0 = matrix ? local % tiles_c * UPD_C : 0;
+  // a linear piece is walked as rows of 128
+  const size_t pitch = matrix ? (size_t)t.cols : UPD_C, end = t.off + (matrix ? (size_t)t.rows * t.cols : (size_t)t.cols);
+  const int c = (tid & 31) * 4, rr = tid >> 5;
+  const int ncol = matrix ? t.cols - c0 : UPD_C;           // columns of the tile that exist
+  const bool vec = !(t.off & 3) && !(pitch & 3);
+#pragma unroll 1
+  for (int lr0 = 0; lr0 < ROWS; lr0 += 8 * U) {
+    float4 w[U], g[U], m[U], v[U];
+    bool on[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = r0 + lr0 + u * 8 + rr;
+      const size_t at = t.off + (size_t)row * pitch + c0 + c;
+      on[u] = vec && (!matrix || row < t.rows) && c + 4 <= ncol && at + 4 <= end;
+      g[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      m[u] = g[u]; v[u] = g[u]; w[u] = g[u];
+      if (on[u]) {
+        w[u] = nt_load4(reinterpret_cast<const float4*>(q.w + at));
+        if (q.g0) { const float4 x = nt_load4(reinterpret_cast<const float4*>(q.g0 + at)); g[u] = make_float4(q.s0 * x.x, q.s0 * x.y, q.s0 * x.z, q.s0 * x.w); }
+        if (q.g1) { const float4 x = nt_load4(reinterpret_cast<const float4*>(q.g1 + at)); g[u].x += q.s1 * x.x; g[u].y += q.s1 * x.y; g[u].z += q.s1 * x.z; g[u].w += q.s1 * x.w; }
+        if (ADAM) { m[u] = nt_load4(reinterpret_cast<const float4*>(q.m + at)); v[u] = nt_load4(reinterpret_cast<const float4*>(q.v + at)); }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int lr = lr0 + u * 8 + rr, row = r0 + lr;
+      const size_t at = t.off + (size_t)row * pitch + c0 + c;
+      union { bf16_t h[4]; uint2 p; uint32_t d[2]; } cv;
+      if (on[u]) {
+        w[u].x = upd_one<ADAM>(w[u].x, g[u].x, m[u].x, v[u].x, a.hyper);
+        w[u].y = upd_one<ADAM>(w[u].y, g[u].y, m[u].y, v[u].y, a.hyper);
+        w[u].z = upd_one<ADAM>(w[u].z, g[u].z, m[u].z, v[u].z, a.hyper);
+        w[u].w = upd_one<ADAM>(w[u].w, g[u].w, m[u].w, v[u].w, a.hyper);
+        nt_store4(reinterpret_cast<float4*>(q.w + at), w[u]);
+        if (ADAM) { nt_store4(reinterpret_cast<float4*>(q.m + at), m[u]); nt_store4(reinterpret_cast<float4*>(q.v + at), v[u]); }
+        cv.h[0] = (bf16_t)w[u].x; cv.h[1] = (bf16_t)w[u].y; cv.h[2] = (bf16_t)w[u].z; cv.h[3] = (bf16_t)w[u].w;
+        if (q.shadow) *reinterpret_cast<uint2*>(q.shadow + at) = cv.p;
+      } else {
+        cv.p = make_uint2(0, 0);
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {                      // edges and unaligned matrices, element by element
+          if ((matrix && row >= t.rows) || c + k >= ncol || at + k >= end) continue;
+          float gk = 0.f;
+          if (q.g0) gk = q.s0 * q.g0[at + k];
+          if (q.g1) gk += q.s1 * q.g1[at + k];
+          float mk = 0.f, vk = 0.f;
+          if (ADAM) { mk = q.m[at + k]; vk = q.v[at + k]; }
+          const float wk = upd_one<ADAM>(q.w[at + k], gk, mk, vk, a.hyper);
+          q.w[at + k] = wk;
+          if (ADAM) { q.m[at + k] = mk; q.v[at + k] = vk; }
+          const bf16_t hk = (bf16_t)wk;
+          if (q.shadow) q.shadow[at + k] = hk;
+          if (matrix) tile[lr][c + k] = hk;
+        }
+      }
+      if (matrix && on[u]) {
+        uint32_t* d = reinterpret_cast<uint32_t*>(&tile[lr][c]);
+        d[0] = cv.d[0]; d[1] = cv.d[1];
+      }
+    }
+  }
+  if (!matrix || !q.shadowT) return;
+  __syncthreads();
+  // output row = input column: half of its elements a thread
+  const int col = tid >> 1, h = (tid & 1) * (ROWS / 2);
+  if (col >= ncol) return;
+  bf16_t* out = q.shadowT + t.off + (size_t)(c0 + col) * t.ld_out + r0 + h;
+  const bool vout = !(t.ld_out & 7) && !(t.off & 7);
+#pragma unroll
+  for (int k = 0; k < ROWS / 16; ++k) {
+    union { bf16_t h[8]; uint4 p; } x;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x.h[i] = tile[h + 8 * k + i][col];
+    const int left = t.rows - r0 - h - 8 * k;              // rows that exist from here on
+    if (vout && left >= 8) *reinterpret_cast<uint4*>(out + 8 * k) = x.p;
+    else
+      for (int i = 0; i < min(8, left); ++i) out[8 * k + i] = tile[h + 8 * k + i][col];
+  }
+}
+
+int update_tiles(int rows, int cols, int ld_out) {
+  return ld_out ? ((rows + UPD_R - 1) / UPD_R) * ((cols + UPD_C - 1) / UPD_C) : (cols + UPD_R * UPD_C - 1) / (UPD_R * UPD_C);
+}
+hipError_t launch_update_groups(hipStream_t s, const UpdateDesc* u, const UpdateTable* tab, int n) {
+  for (int i0 = 0; i0 < n; i0 += UPD_GROUP_MAX) {
+    UpdGroupsParams a;
+    memset(&a, 0, sizeof a);
+    int blocks = 0;
+    for (int i = i0; i < n && i < i0 + UPD_GROUP_MAX; ++i) {
+      const UpdateDesc& d = u[i];
+      if (d.n == 0) continue;
+      a.hyper.lr = d.lr; a.hyper.b1 = d.beta1; a.hyper.b2 = d.beta2; a.hyper.eps = d.eps; a.hyper.bc1 = d.bc1; a.hyper.bc2 = d.bc2;
+      a.g[a.n++] = {d.w, d.m, d.v, d.shadow, (bf16_t*)tab[i].shadowT, d.g0, d.g1, d.gscale0, d.gscale1, tab[i].dev, tab[i].entries, blocks};
+      blocks += tab[i].tiles;
+    }
+    if (blocks == 0) continue;
+    // a small model's tiles leave compute units free: four blocks a tile
+    const bool parts = blocks < 512;
+    auto kern = u[i0].adam ? parts ? update_groups_kernel<true, 4> : update_groups_kernel<true, 1> : parts ? update_groups_kernel<false, 4> : update_groups_kernel<false, 1>;
+    hipLaunchKernelGGL(kern, dim3(parts ? 4 * blocks : blocks), dim3(256), 0, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace ouro

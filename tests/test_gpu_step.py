@@ -611,6 +611,60 @@ def test_checkpoint_resume(schedule, dtype, opt):
     other.close(); b.close()
 
 
+@pytest.mark.parametrize("cfg", [
+    dict(dtype=1, n_head=2, d_head=72, d_model=144, d_ff=150, vocab=77),           # not padded: rows of 150, pieces off every alignment
+    dict(dtype=1, n_head=2, d_head=64, d_model=128, d_ff=192, vocab=1001),         # tiles over the edge of V, whole tiles elsewhere
+    dict(dtype=1, n_head=2, d_head=41, d_model=82, d_ff=130, vocab=65, rel_pos=1, mem_len=8),
+    dict(dtype=0, n_head=2, d_head=17, d_model=34, d_ff=50, vocab=99),
+    dict(dtype=1, n_head=8, d_head=64, d_model=512, d_ff=2048, vocab=4096),        # more than 512 tiles in a launch
+])
+@pytest.mark.parametrize("optimizer", [0, 1])
+def test_update_of_groups_equals_update_of_one(cfg, optimizer):
+    """The tile-by-tile update of all groups (a step on one stream) and the plain update of one group: the same arithmetic on
+    the same gradients, so the same weights bit for bit, and through both bf16 copies the same loss."""
+    pkg = P()
+    c = dict(dict(n_layer=3, seq_len=16, mem_len=0, batch=2, n_module=3, rel_pos=0, optimizer=optimizer), **cfg)
+    tok = torch.randint(0, c["vocab"], (c["batch"], c["seq_len"]), dtype=torch.int32, generator=torch.Generator().manual_seed(1)).cuda()
+    out = []
+    for overlap in (False, True):
+        rng = np.random.default_rng(5)
+        m = pkg.create_model(**c)
+        m.set_overlap(overlap)
+        for g in range(c["n_module"] + 1):
+            m.set_params(g, (rng.standard_normal(m.param_count(g)) * 0.05).astype(np.float32))
+        for t in range(4):
+            for g in range(c["n_module"] + 2):
+                n = m.param_count(g if g <= c["n_module"] else 0)
+                m.inject_grad(g, rng.standard_normal(n).astype(np.float32))
+            for g in range(c["n_module"] + 1):
+                m.delayed_update(g, 0.01)
+        weights = [m.get_params(g) for g in range(c["n_module"] + 1)]
+        out.append((weights, m.eval_step(tok, tok)))
+        m.close()
+    for a, b in zip(out[0][0], out[1][0]):
+        assert np.array_equal(a, b)
+    assert out[0][1] == out[1][1] and np.isfinite(out[0][1])
+
+
+def test_step_with_more_groups_than_a_launch_takes():
+    """20 modules on one stream: clears, sums and updates go out in several launches; against the step on several streams."""
+    c = dict(n_layer=20, d_model=64, n_head=1, d_head=64, d_ff=64, vocab=64, seq_len=8, mem_len=0, batch=2, n_module=20, rel_pos=0, dtype=0, optimizer=0)
+    tok, tgt = S.token_batches(64, 2, 8, 24, 1.1, 3, False)
+    blobs = S.init_params(c, seed=1)
+    out = []
+    for overlap in (False, True):
+        m = P().create_model(**c)
+        m.set_overlap(overlap)
+        for g, blob in enumerate(blobs):
+            m.set_params(g, blob)
+        losses = [m.step(torch.from_numpy(tok[t]).cuda(), torch.from_numpy(tgt[t]).cuda(), 0.1) for t in range(24)]
+        out.append((losses, [m.get_params(g) for g in range(21)]))
+        m.close()
+    assert np.allclose(out[0][0], out[1][0], rtol=1e-5, atol=0)
+    for a, b in zip(out[0][1], out[1][1]):
+        assert rel_err(a, b) < 1e-5                        # fp32 sums in another order
+
+
 def test_timing_hooks():
     """Per-launch timing brackets and the empty-bracket cost: plausible, positive numbers."""
     c = dict(S.CONFIGS["cfg1"])
