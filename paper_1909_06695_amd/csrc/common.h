@@ -140,8 +140,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
 // n <= GEMM_GROUP_MAX accumulating products (fp32 C += alpha A^T B, plain epilogue, no batch) in one
 // launch when all of them are bf16 with transA = 1, transB = 0 and admit the direct-to-LDS MFMA
 // kernel; otherwise one launch_gemm each.  tile 0: the kernel and the length of a K range are chosen; 128, 256: that kernel,
-// also for one product, with ranges of kchunk (a multiple of 64; 0: chosen).
-hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile = 0, int kchunk = 0);
+// also for one product, with ranges of kchunk (a multiple of 64; 0: chosen).  alone: nothing else runs beside the launch.
+hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile = 0, int kchunk = 0, bool alone = false);
 // true if launch_gemm would take the MFMA path for this problem
 // What launch_gemm chooses for one product (host only): 1 the plain kernel, 20 the fp32 matrix-core
 // kernel, GEMM_TILE_*, and (bf16) the contraction ranges.

@@ -7,6 +7,8 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
+#include <vector>
 
 namespace ouro {
 
@@ -213,11 +215,16 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
     // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are four per CU (the logits: 8192 x
-    // 32768 over 512 404 us against 460 on 128x128 tiles, 4800 x 32768 over 448 212 against 241), one per CU with a long
-    // contraction (dV_o: 670 -> 592 us), or where their last round is at least three quarters full.  Alone on the chip, against
-    // 128x128 tiles, plain and with the GELU-gradient epilogue: 512 tiles over 1024 70 and 77 us, 87 and 91; 464 over 768 57
-    // and 75, 83 and 84; 496 over 1024 69 and 84, 95 and 103; 448 over 1024 68 and 74, over 512 47 and 45; 416 over 1024 63
-    // and 69 but 91 and 82; 528 over 1024 95 and 89.
+    // 32768 over 512 312 us, 4800 x 32768 over 448 190), one per CU with a long contraction (dV_o: 670 -> 592 us), or where their
+    // rounds are well filled.  Alone on the chip, 128x128 and 256x256 tiles, us (plain / GELU / GELU-gradient / fp32 result with the
+    // recomputed LayerNorm):
+    //   one round      256 tiles over 1024 38 / 46 / 45 / 62 and 32 / 41 / 42 / 52; over 512 24 / 33 / 31 / 48 and 21 / 29 / 31 / 43;
+    //                  192 over 768 27 / 33 / 32 / 40 and 24 / 32 / 33 / 39; 192 over 512 20 / 28 / 27 / 37 and 19 / 27 / 28 / 36;
+    //                  190 over 448 20 / 27 / 26 / 34 and 18 / 26 / 27 / 34; 144 over 768 26 / 32 / 31 / 35 and 22 / 30 / 32 / 35
+    //   1.1 to 1.3     288 over 1024 46 / 58 / 56 / 78 and 49 / 65 / 70 / 79; 320 over 1024 49 / 61 / 66 / 85 and 51 / 68 / 74 / 81
+    //   1.5            384 over 1024 55 / 71 / 71 / 92 and 53 / 72 / 77 / 91; over 768 45 / 60 / 58 / 85 and 45 / 67 / 70 / 82
+    //   two            512 over 1024 80 / 109 / - / 126 and 60 / 79 / - / 122; over 512 44 / 76 / 71 / 102 and 42 / 61 / 72 / 102
+    // and 416 over 1024 69 (GELU-gradient 82) and 63 (91), 464 over 768 75 and 57, 528 over 1024 89 (GELU-gradient) and 95.
     // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
     // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
@@ -226,7 +233,10 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // 1496 over 4096 32.8 us on the register-prefetch kernel, 35.9 on 64x64 tiles, over 8192 58 and 70; A B^T 57.9 and 57.1;
     // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
-    const bool big = t256 >= 1024 || (t256 >= 256 && g.K >= 4096) || (t256 >= 448 && (t256 % 256 == 0 || t256 % 256 >= 192) && g.K >= 768);
+    const bool plain = !g.out_fp32 && g.epilogue == EPI_NONE && !g.residual && !g.res32;
+    const int last = (t256 - 1) % 256 + 1;               // tiles of the last round
+    const bool big = t256 >= 1024 || (t256 >= 256 && g.K >= 4096) || (t256 >= 448 && last >= 192 && g.K >= (plain || g.epilogue == EPI_GELU ? 512 : 768)) ||
+                     (t256 >= 224 && t256 <= 256 && g.K >= 512) || (plain && g.K >= 448 && ((t256 >= 144 && t256 <= 256) || (t256 >= 384 && last >= 128)));
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
     if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
@@ -420,7 +430,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   return e;
 }
 
-hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile, int kchunk) {
+hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile, int kchunk, bool alone) {
   if (n < 1 || n > GEMM_GROUP_MAX || (tile != 0 && tile != 128 && tile != 256) || kchunk < 0 || kchunk % 64) return hipErrorInvalidValue;
   // products that do not admit the grouped kernel go by themselves
   GemmDesc in[GEMM_GROUP_MAX];
@@ -437,17 +447,22 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   }
   if (ni == 0) return hipSuccess;
   if (ni == 1 && !tile) return launch_gemm(s, dtype, in[0], 0);
+  if (alone) std::stable_sort(in, in + ni, [](const GemmDesc& x, const GemmDesc& y) { return x.K > y.K; });
   g = in; n = ni;
-  // One K-range length for all products, and one of two kernels.  128x128 tiles, two workgroups per CU, run in whole rounds
+  // One K-range length for all products, and one of two kernels.
+  // Beside the error-gradient chain a compute unit that the launch leaves free is worth as much as time: the mean of its duration
+  // and its share of the chip's is compared.  128x128 tiles, two workgroups per CU, run in whole rounds
   // of 512 and take 1.2 us per K-tile (of two side by side) plus 6 K-tiles of fixed cost (ring fill, atomic adds that the
   // neighbour's matrix work covers).  256x256 tiles, one workgroup per CU, take 1.45 us per K-tile and 6 us besides; nothing
   // covers their atomic adds, which all workgroups of a round reach together (310 adds per ns over the chip: 70 us for
-  // the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.
-  // The launch runs beside the error-gradient chain, so a compute unit it leaves free is worth as much as time: the mean
-  // of the launch's duration and its share of the chip's is compared.  Alone on the chip, 128x128 and
+  // the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.  128x128 and
   // 256x256 tiles: 1024-wide layer, 8192 rows 255 and 185 us, 6144 rows 182 and 131 (256x256 taken); 512-wide, 8192 rows 73 and
-  // 80, 448-wide, 4800 rows 47 and 58 (128x128 taken); 768-wide, 2331 rows 42 and 52 (256x256 taken: 108 compute units instead
-  // of all).
+  // 80 (128x128 taken); 768-wide, 2331 rows 42 and 52 (256x256 taken: 108 compute units instead of all).
+  // Alone on the chip the duration counts: the makespan of dealing the products, longest range first, to the slots, and the
+  // atomic adds of the split ones (400 per ns), which set the time of short ranges.  128x128 tiles take 0.65 us per K-tile
+  // where no CU has two and 0.82 side by side, and 4 us besides.  448-wide relative-position layer, 4800 rows, ranges of 1600 / 2432 /
+  // 3200 / 4800 rows: 73 / 74 / 58 / 62 us (estimated 77 / 84 / 65 / 68), on 256x256 tiles 66 at best; 512-wide, 8192 rows, 2432 / 4096 /
+  // 8192: 83 / 71 / 89; 256-wide, 2048 rows, 320 / 640 / 960: 23 / 16 / 16 (25 with the range the other rule takes).
   int kmax = 0;
   for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
   double best[2] = {1e30, 1e30};
@@ -455,17 +470,36 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   for (int kc = std::min(256, kmax); kc <= kmax; kc += 64) {
     for (int big = 0; big < 2; ++big) {
       const int bt = big ? 256 : 128;
+      const long slots = big ? 256 : 512;
+      struct Part { int range; long wgs; } part[GEMM_GROUP_MAX];
       long wgs = 0;
-      double adds = 0;
+      double adds = 0, cost;
       for (int i = 0; i < n; ++i) {
         const int splits = (g[i].K + kc - 1) / kc;
-        const long tiles = (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt);
-        wgs += tiles * splits;
-        if (splits > 1 || g[i].accumulate != ACC_STORE) adds += (double)tiles * splits * bt * bt;
+        part[i] = {((g[i].K + splits - 1) / splits + 63) / 64, (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt) * splits};
+        wgs += part[i].wgs;
+        if (splits > 1 || g[i].accumulate != ACC_STORE) adds += (double)part[i].wgs * bt * bt;
       }
-      const double slots = big ? 256 : 512;
-      const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
-      const double cost = 0.5 * one * (std::ceil(wgs / slots) + wgs / slots);
+      if (alone) {
+        const double rate = big ? 1.45 : wgs <= 256 ? 0.65 : 0.82, fixed = big ? 6 : 4;
+        std::sort(part, part + n, [](const Part& x, const Part& y) { return x.range > y.range; });
+        std::vector<std::pair<double, long>> free_at{{0.0, slots}};          // (time, slots that are free from then on)
+        double end = 0;
+        for (int i = 0; i < n; ++i)
+          for (long left = part[i].wgs; left > 0;) {
+            auto it = std::min_element(free_at.begin(), free_at.end());
+            const double t = it->first + rate * part[i].range + fixed;
+            const long take = std::min(left, it->second);
+            left -= take;
+            if ((it->second -= take) == 0) free_at.erase(it);
+            free_at.push_back({t, take});
+            end = std::max(end, t);
+          }
+        cost = end + adds / (big ? 310e3 : 400e3);
+      } else {
+        const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
+        cost = 0.5 * one * (std::ceil((double)wgs / slots) + (double)wgs / slots);
+      }
       if (cost < best[big] - 1e-9) { best[big] = cost; kchunks[big] = kc; }
     }
   }

@@ -882,7 +882,7 @@ static int run_gemm_group_on(ouro_model* m, const GemmDesc* g, int n, hipStream_
   double flops = 0;
   for (int i = 0; i < n; ++i) { timed = timed && gemm_uses_mfma(m->cfg.dtype, g[i]); flops += 2.0 * g[i].M * g[i].N * g[i].K; }
   if (timed) { int rc = timing_begin(m, OURO_TIMING_CONTRACTION, st); if (rc) return rc; }
-  HIPCHK(launch_gemm_group(st, m->cfg.dtype, g, n));
+  HIPCHK(launch_gemm_group(st, m->cfg.dtype, g, n, 0, 0, !m->use_side));
   if (timed) return timing_end(m, OURO_TIMING_CONTRACTION, flops, st);
   return OURO_OK;
 }
