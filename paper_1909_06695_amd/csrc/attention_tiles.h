@@ -29,6 +29,8 @@ struct FaParams {
   // what the relative-position dQ kernel leaves for the contractions that give dK, dV and dr
   bf16_t *pt, *dst, *qu, *qv, *dop;
   int t_ld;
+  // forward pass in parts (relative-position variant): outputs [parts, B, H, T, 64], maximum and sum [parts, B, H, T, 2]
+  int parts; float *part_o, *part_ml;
 };
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -152,6 +154,7 @@ inline FaParams fa_params(const AttnDesc& a) {
   p.u = (const bf16_t*)a.u; p.vb = (const bf16_t*)a.vb; p.r = (const bf16_t*)a.r; p.ldr = a.ldr;
   p.du = a.du; p.dvb = a.dvb; p.dr = a.dr;
   p.pt = p.dst = p.qu = p.qv = p.dop = nullptr; p.t_ld = 0;
+  p.parts = 1; p.part_o = p.part_ml = nullptr;
   return p;
 }
 

@@ -35,6 +35,7 @@ constexpr int XL_PATCHES = XL_R + 4 * TILE_BYTES;
 constexpr int XL8_LD = 68;
 constexpr int XL8_PATCH = 32 * XL8_LD * 4;           // bytes per wave
 constexpr int XL_DS_LD = 68;
+constexpr int XL_PARTS_MAX = 4;
 constexpr int XL_LDS_Q8 = XL_PATCHES + 8 * XL8_PATCH;
 static_assert(XL8_PATCH >= 5 * 1024 && 5 * 1024 >= 32 * XL_DS_LD * 2, "clearing the dS cells takes five writes");
 static_assert(XL8_PATCH >= (32 * 64 + 2 * 64) * 4, "the sums of the bias gradients use the whole patch");
@@ -117,14 +118,15 @@ __device__ __forceinline__ void xl_add_position(f32x16& s, const char* patch, in
   for (int r = 0; r < 16; ++r) s[r] += cell[8 * (r >> 2) + (r & 3)];
 }
 
-// Forward kernel: workgroup -> (query block, head, batch), longest rows first over the whole launch: the
+// Forward kernel: workgroup -> (query block, part of its keys, head, batch), longest rows first over the whole launch: the
 // dispatcher hands out workgroups in linear id order, so all workgroups of the last query block
 // (the most keys) start first and the lighter blocks fill the slots as they free up.
-__device__ __forceinline__ void xl_decode_block(int& qblk, int& head, int& b) {
+__device__ __forceinline__ void xl_decode_block(int parts, int& qblk, int& part, int& head, int& b) {
   const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   const int per = gridDim.y * gridDim.z;
-  const int rest = lin % per;
-  qblk = gridDim.x - 1 - lin / per;
+  const int rest = lin % per, x = lin / per;
+  qblk = (int)gridDim.x / parts - 1 - x / parts;
+  part = x % parts;
   head = rest % gridDim.y;
   b = rest / gridDim.y;
 }
@@ -141,12 +143,15 @@ __device__ __forceinline__ void xl_decode_block(int& qblk, int& head, int& b) {
 // ------------------------------------------------------------------------------ forward
 // The two key halves of a query group keep their own running maximum, sum and output; the
 // second half hands its state to the first through LDS at the end.
+// PARTS: the keys of a query block are dealt to p.parts workgroups (grid.x = query blocks x parts), which leave their unscaled
+// output, running maximum and sum for fa_xl_merge_kernel.
+template <bool PARTS>
 __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h32 = lane >> 5, l32 = lane & 31;
   const int qg = wave & 3, kh = wave >> 2;
-  int qblk, head, b;
-  xl_decode_block(qblk, head, b);
+  int qblk, part, head, b;
+  xl_decode_block(PARTS ? p.parts : 1, qblk, part, head, b);
   const int Q0 = qblk * 128, q0 = Q0 + qg * 32, qi = q0 + l32;
   const bf16_t* qb = p.q + (size_t)b * p.T * p.ldq + head * 64;
   const bf16_t* kb = p.k + (size_t)b * p.S * p.ldk + head * 64;
@@ -156,7 +161,8 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
   bf16x8 quf[4], qvf[4];
   const int wg_last_q = min(p.T, Q0 + 128) - 1;
   const int kend = min(p.S, p.Mv + wg_last_q + 1);
-  const int nkb = (kend + 63) / 64;
+  const int nkb_all = (kend + 63) / 64;
+  const int jb0 = PARTS ? nkb_all * part / p.parts : 0, nkb = PARTS ? nkb_all * (part + 1) / p.parts : nkb_all;
   const bool wave_on = q0 < p.T;
   const int wave_kmax = p.Mv + min(p.T - 1, q0 + 31);
   const int rrow0 = 96 - 32 * qg + 32 * kh;                 // window row of the wave's patch cell 0
@@ -173,9 +179,9 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
     const int d0 = p.Mv + Q0 - jb * 64 + 128;             // distance of window row 0
 #pragma unroll
     for (int t = 0; t < 3; ++t)
-      if (t == 2 || jb == 0) dma_tile8_down(rb, p.ldr, d0 - 64 * t, p.S, lds + XL_R + ((2 - t - jb) & 3) * TILE_BYTES, wave, lane);
+      if (t == 2 || jb == jb0) dma_tile8_down(rb, p.ldr, d0 - 64 * t, p.S, lds + XL_R + ((2 - t - jb) & 3) * TILE_BYTES, wave, lane);
   };
-  issue(0);
+  if (jb0 < nkb) issue(jb0);
   {
     uint4 q[4], ub[4], vb8[4];
     xl_load_row(qb, p.ldq, qi, p.T, h32, q);
@@ -187,7 +193,7 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
       qvf[ks] = add_bias(as_bf16x8(q[ks]), as_bf16x8(vb8[ks]));
     }
   }
-  for (int jb = 0; jb < nkb; ++jb) {
+  for (int jb = jb0; jb < nkb; ++jb) {
     fa_wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     if (jb + 1 < nkb) issue(jb + 1);
@@ -269,12 +275,53 @@ __global__ __launch_bounds__(512) void fa_xl_fwd_kernel(FaParams p) {
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[dt][r] = oacc[dt][r] * a0 + other[(16 * dt + r) * 64 + lane] * a1;
+    if (PARTS) {
+      const size_t row = (((size_t)part * p.B + b) * p.H + head) * p.T + qi;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<float4*>(p.part_o + row * 64 + 32 * dt + 8 * g + 4 * h32) = make_float4(oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]);
+      if (h32 == 0) *reinterpret_cast<float2*>(p.part_ml + row * 2) = make_float2(mm, l);
+      return;
+    }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     store_acc_row(p.o + ((size_t)b * p.T + qi) * p.ldo + head * 64, oacc, inv, h32);
     if (h32 == 0) p.lse[((size_t)b * p.H + head) * p.T + qi] = (mm + log2f(l)) * 0.6931471805599453f;
   }
 }
 
+
+// The parts' outputs, each scaled to the common maximum; 16 lanes a row.
+__global__ __launch_bounds__(256) void fa_xl_merge_kernel(FaParams p) {
+  const size_t rows = (size_t)p.B * p.H * p.T, row = (size_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (row >= rows) return;
+  const int c = (threadIdx.x & 15) * 4;
+  float2 ml[XL_PARTS_MAX];
+  float4 o[XL_PARTS_MAX];
+  float mm = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int i = 0; i < XL_PARTS_MAX; ++i) {
+    const size_t at = (size_t)min(i, p.parts - 1) * rows + row;
+    ml[i] = *reinterpret_cast<const float2*>(p.part_ml + at * 2);
+    o[i] = *reinterpret_cast<const float4*>(p.part_o + at * 64 + c);
+    if (i < p.parts) mm = fmaxf(mm, ml[i].x);
+  }
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int i = 0; i < XL_PARTS_MAX; ++i) {
+    if (i >= p.parts || ml[i].x == -INFINITY) continue;    // a part none of whose keys the row sees
+    const float a = __builtin_amdgcn_exp2f(ml[i].x - mm);
+    l += ml[i].y * a;
+    sum.x += o[i].x * a; sum.y += o[i].y * a; sum.z += o[i].z * a; sum.w += o[i].w * a;
+  }
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  const size_t i = row % p.T, bh = row / p.T, head = bh % p.H, b = bh / p.H;
+  union { bf16_t h[4]; uint2 u; } x;
+  x.h[0] = (bf16_t)(sum.x * inv); x.h[1] = (bf16_t)(sum.y * inv); x.h[2] = (bf16_t)(sum.z * inv); x.h[3] = (bf16_t)(sum.w * inv);
+  *reinterpret_cast<uint2*>(p.o + (b * p.T + i) * p.ldo + head * 64 + c) = x.u;
+  if (c == 0) p.lse[row] = (mm + log2f(l)) * 0.6931471805599453f;
+}
 
 // ---------------------------------------------------------------------------- dQ kernel
 // The two key halves of a query group add their dQ through LDS at the end.  Besides dQ the
@@ -595,16 +642,35 @@ bool attn_xl_ok(int dtype, const AttnDesc& a) {
   return true;
 }
 
+// Parts that the keys of a query block are dealt to.  One workgroup a CU, so a launch of few of them leaves compute units idle
+// for as long as the longest row takes; parts of six blocks of keys and more pay for the second launch.
+// 2 x 16 heads, T = 384 on 1152 keys of memory (96 workgroups of up to 24 blocks): 42 us; in two parts 28 and 5 for the merge.
+static int xl_parts(int B, int H, int T, int S) {
+  const long wgs = (long)((T + 127) / 128) * H * B;
+  return (int)std::max<long>(1, std::min<long>({(long)XL_PARTS_MAX, 256 / wgs, (long)(S + 63) / 64 / 6}));
+}
+size_t attn_fwd_parts_floats(int B, int H, int T, int S) {
+  const int parts = xl_parts(B, H, T, S);
+  return parts > 1 ? (size_t)parts * B * H * T * 66 : 0;
+}
 hipError_t launch_attn_fwd_xl(hipStream_t s, const AttnDesc& a) {
   FaParams p = fa_params(a);
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_xl_fwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, XL_LDS_Q8);
+  const int nq = (a.T + 127) / 128;
+  p.parts = a.parts ? xl_parts(a.B, a.H, a.T, a.S) : 1;
+  auto kern = p.parts > 1 ? fa_xl_fwd_kernel<true> : fa_xl_fwd_kernel<false>;
+  static bool attr_done[2] = {false, false};
+  if (!attr_done[p.parts > 1]) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, XL_LDS_Q8);
     if (e != hipSuccess) return e;
-    attr_done = true;
+    attr_done[p.parts > 1] = true;
   }
-  dim3 grid((a.T + 127) / 128, a.H, a.B), block(512);
-  hipLaunchKernelGGL(fa_xl_fwd_kernel, grid, block, XL_LDS_Q8, s, p);
+  const size_t rows = (size_t)a.B * a.H * a.T;
+  p.part_o = a.parts;
+  p.part_ml = a.parts ? a.parts + (size_t)p.parts * rows * 64 : nullptr;
+  hipLaunchKernelGGL(kern, dim3(nq * p.parts, a.H, a.B), dim3(512), XL_LDS_Q8, s, p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.parts == 1) return e;
+  hipLaunchKernelGGL(fa_xl_merge_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

@@ -173,6 +173,9 @@ struct AttnDesc {
   float* du; float* dvb;           // fp32 [H, dh], accumulated into (caller zeroes)
   float* dr;                       // fp32 [S, H*dh] dense, accumulated into (caller zeroes)
   float* scratch;                  // fp32 workspace, attn_bwd_scratch_floats() elements
+  // forward only, or null: attn_fwd_parts_floats() elements, 16-byte aligned, with which a launch of few workgroups may deal the keys
+  // of a query block to several
+  float* parts;
   // relative-position MFMA path: the workspace's cells that the pass does not write are known to
   // be zero (the caller cleared it and every pass since ran with the same B, H, T, Mv); else it is cleared
   int scratch_clean;
@@ -181,6 +184,7 @@ struct AttnDesc {
 size_t attn_bwd_scratch_floats(int B, int H, int T, int S, int dh);
 size_t attn_bwd_xl_scratch_floats(int B, int H, int T, int S);
 size_t attn_bwd_scratch_floats_any(int B, int H, int T, int S, int dh);
+size_t attn_fwd_parts_floats(int B, int H, int T, int S);     // relative-position MFMA path (0: it takes none)
 // records msg as the calling thread's last error (ouro_last_error) and returns code
 int set_error(int code, const char* msg);
 hipError_t launch_attn_fwd(hipStream_t s, int dtype, const AttnDesc& a, int force_generic);

@@ -161,6 +161,7 @@ struct BwdCtx {
   char *ds2[2], *dz[2], *ds1[2], *dqkv[2];
   char *ds2m[2], *ds1m[2];         // ds2 / ds1 times the dropout masks (the same buffers without dropout)
   float *attn_scratch, *dr_f32[2];
+  float* attn_parts;             // forward attention in parts: the largest workspace of all memory lengths (null: none)
   bool dr_clear[2];              // dr_f32 is zero: the conversion of its last gradients cleared it
   int attn_scratch_Mv;           // relative mode: memory length of the passes since the workspace was last cleared (-1: none)
   char* hscratch;                 // output of a recomputed module's last layer (never read)
@@ -494,6 +495,10 @@ static size_t lay_out(ouro_model& m, char* base) {
     x.attn_scratch = (float*)P((c.rel_pos ? attn_bwd_scratch_floats_any(c.batch, c.n_head, c.seq_len, (int)S, m.pdh)
                                           : attn_bwd_scratch_floats(c.batch, c.n_head, c.seq_len, (int)S, m.pdh)) * 4);
     x.attn_scratch_Mv = -1;
+    size_t parts = 0;
+    if (c.rel_pos && c.dtype == 1 && m.pdh == 64)
+      for (int mv = 0; mv <= c.mem_len; ++mv) parts = std::max(parts, attn_fwd_parts_floats(c.batch, c.n_head, c.seq_len, c.seq_len + mv));
+    x.attn_parts = parts ? (float*)P(parts * 4) : nullptr;
     x.hscratch = c.schedule == 1 ? P(N * d * es) : nullptr;
   };
   scratch(m);
@@ -930,6 +935,7 @@ static int layer_forward(ouro_model* m, int l, char* out_override = nullptr, boo
   a.B = B; a.H = c.n_head; a.T = T; a.S = S; a.dh = m->pdh; a.Mv = Mv;
   a.scale = 1.f / std::sqrt((float)c.d_head);
   a.o = b.a; a.ldo = hd; a.lse = b.lse;
+  a.parts = m->attn_parts;
   if (!c.rel_pos) {
     if (bt) RUN(run_gemm(m, gd(b.x, d, 0, m->wTt(l, o.W_qkv), d, 1, b.qkv, 3 * hd, N, 3 * hd, d)));
     else RUN(run_gemm(m, gd(b.x, d, 0, m->wT(l, o.W_qkv), 3 * hd, 0, b.qkv, 3 * hd, N, 3 * hd, d)));

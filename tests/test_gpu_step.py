@@ -567,6 +567,26 @@ def test_eval_step_with_longer_memory(dtype, tol):
     m.close(); e.close()
 
 
+@pytest.mark.parametrize("T,M,B,heads", [(150, 1300, 1, 2), (40, 800, 2, 1), (130, 700, 3, 2)])
+def test_eval_step_with_keys_dealt_to_workgroups(T, M, B, heads):
+    """Few heads and streams, a long memory that fills segment by segment: the forward attention goes from one workgroup per query
+    block to two, three and four.  Losses and rolled memories against the oracle."""
+    c = dict(n_layer=2, d_model=64 * heads, n_head=heads, d_head=64, d_ff=96, vocab=211, seq_len=T, mem_len=M, batch=B, n_module=2, rel_pos=1,
+             dtype=1, optimizer=0)
+    steps = M // T + 3
+    blobs = S.init_params(c, seed=21, std=0.1, perturb=0.1)
+    tok, tgt = S.token_batches(c["vocab"], B, T, steps, 1.1, 22, contiguous=True)
+    oe, e = O.Oracle(O.Config(**c), blobs), P().create_model(**c)
+    for g in range(3):
+        e.set_params(g, blobs[g])
+    for t in range(steps):
+        lo, lg = oe.eval_step(tok[t], tgt[t]), e.eval_step(torch.from_numpy(tok[t]).cuda(), torch.from_numpy(tgt[t]).cuda())
+        assert abs(lg - lo) / lo < 2e-3, (t, lg, lo)
+        mem = e.get_mems(1)
+        assert mem.shape == oe.mems[1].shape and rel_err(mem, oe.mems[1]) < 2e-2
+    e.close()
+
+
 @pytest.mark.parametrize("schedule,dtype,opt", [(0, 0, 1), (1, 0, 0), (1, 1, 1)])
 def test_checkpoint_resume(schedule, dtype, opt):
     """Save the whole state (weights, moments, pending stale gradients or stored inputs with their
