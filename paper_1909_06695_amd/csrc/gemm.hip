@@ -160,6 +160,8 @@ hipError_t launch_gemm_pp(hipStream_t s, GemmParams& p, int transA, int transB, 
 hipError_t launch_gemm_pp_group(hipStream_t s, const GemmParams* ps, int n);
 bool gemm_f32_ok(const GemmDesc& g);
 hipError_t launch_gemm_f32(hipStream_t s, GemmParams& p, int transA, int transB, int form);
+bool gemm_f32_group_ok(const GemmParams& p);
+hipError_t launch_gemm_f32_group(hipStream_t s, const GemmParams* ps, int n);
 hipError_t launch_gemm_dlds_group(hipStream_t s, GemmParams* ps, int n, int transA, int transB);
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
@@ -430,21 +432,35 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   return e;
 }
 
+// Parameters of one accumulating product of a grouped launch.
+static GemmParams group_params(const GemmDesc& d, size_t esz) {
+  GemmParams p;
+  memset(&p, 0, sizeof p);
+  p.A = d.A; p.B = d.B; p.C = d.C;
+  p.M = d.M; p.N = d.N; p.K = d.K; p.lda = d.lda; p.ldb = d.ldb; p.ldc = d.ldc;
+  p.bytesA = (int)operand_extent(esz, d.K, d.M, d.lda); p.bytesB = (int)operand_extent(esz, d.K, d.N, d.ldb);
+  p.out_fp32 = 1; p.epilogue = EPI_NONE; p.alpha = d.alpha; p.accumulate = d.accumulate;
+  p.by = p.bz = p.bz1 = 1;
+  return p;
+}
+
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile, int kchunk, bool alone) {
   if (n < 1 || n > GEMM_GROUP_MAX || (tile != 0 && tile != 128 && tile != 256) || kchunk < 0 || kchunk % 64) return hipErrorInvalidValue;
   // products that do not admit the grouped kernel go by themselves
   GemmDesc in[GEMM_GROUP_MAX];
-  int ni = 0;
+  GemmParams f32[GEMM_GROUP_MAX];
+  int ni = 0, nf = 0;
   for (int i = 0; i < n; ++i) {
     const GemmDesc& d = g[i];
     const size_t bA = 2 * (size_t)d.K * d.lda, bB = 2 * (size_t)d.K * d.ldb;
-    const bool ok = dtype == 1 && d.transA == 1 && d.transB == 0 && d.accumulate && d.out_fp32 && !d.bias && !d.residual &&
-                    !d.res32 && !d.colsum && d.epilogue == EPI_NONE && !d.drop.on && d.by <= 1 && d.bz <= 1 && !d.C2 && d.M > 0 && d.N > 0 &&
-                    gemm_uses_mfma(dtype, d) && bA < (1ull << 31) && bB < (1ull << 31);
-    if (ok) { in[ni++] = d; continue; }
+    const bool form = d.transA == 1 && d.transB == 0 && d.accumulate && d.out_fp32 && !d.bias && !d.residual &&
+                      !d.res32 && !d.colsum && d.epilogue == EPI_NONE && !d.drop.on && d.by <= 1 && d.bz <= 1 && !d.C2 && d.M > 0 && d.N > 0;
+    if (form && dtype == 1 && gemm_uses_mfma(dtype, d) && bA < (1ull << 31) && bB < (1ull << 31)) { in[ni++] = d; continue; }
+    if (form && dtype == 0 && f32_on_matrix_cores(d) && gemm_f32_group_ok(group_params(d, 4))) { f32[nf++] = group_params(d, 4); continue; }
     hipError_t e = launch_gemm(s, dtype, d, 0);
     if (e != hipSuccess) return e;
   }
+  if (nf) return launch_gemm_f32_group(s, f32, nf);
   if (ni == 0) return hipSuccess;
   if (ni == 1 && !tile) return launch_gemm(s, dtype, in[0], 0);
   if (alone) std::stable_sort(in, in + ni, [](const GemmDesc& x, const GemmDesc& y) { return x.K > y.K; });
@@ -509,12 +525,7 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   for (int i = 0; i < n; ++i) {
     const GemmDesc& d = g[i];
     GemmParams& p = ps[i];
-    memset(&p, 0, sizeof p);
-    p.A = d.A; p.B = d.B; p.C = d.C;
-    p.M = d.M; p.N = d.N; p.K = d.K; p.lda = d.lda; p.ldb = d.ldb; p.ldc = d.ldc;
-    p.bytesA = (int)operand_extent(2, d.K, d.M, d.lda); p.bytesB = (int)operand_extent(2, d.K, d.N, d.ldb);
-    p.out_fp32 = 1; p.epilogue = EPI_NONE; p.alpha = d.alpha;
-    p.by = p.bz = p.bz1 = 1;
+    p = group_params(d, 2);
     // every product splits into ranges of the same length, rounded so that the last is not a sliver
     const int splits = (d.K + kchunk - 1) / kchunk;
     p.kchunk = ((d.K + splits - 1) / splits + 63) / 64 * 64;

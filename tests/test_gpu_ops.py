@@ -211,6 +211,27 @@ def test_products_onto_one_output(dtype, M, N, K):
     assert np.array_equal(host(out), ref)
 
 
+@pytest.mark.parametrize("cleared", [0, 1])
+@pytest.mark.parametrize("shapes", [
+    [(64, 64, 128), (64, 256, 128), (36, 100, 97), (1, 4, 33)],           # 32x32 tiles, one range; edges and a ragged contraction
+    [(64, 64, 4096), (96, 32, 1000), (68, 40, 2050)],                      # 32x32 tiles, split contractions
+    [(1024, 1024, 70), (520, 1024, 40)],                                   # 64x64 tiles
+    [(64, 64, 128), (33, 64, 128), (64, 64, 8)],                           # beside products that go by themselves (unaligned rows)
+])
+def test_gemm_f32_group(shapes, cleared):
+    """Weight gradients of an fp32 layer in one launch: fp32 sums of K products."""
+    rng = np.random.default_rng(len(shapes) + cleared)
+    n = len(shapes)
+    A = [dev(rng.standard_normal((k, m)), 0) for m, _, k in shapes]; B = [dev(rng.standard_normal((k, w)) / math.sqrt(k), 0) for _, w, k in shapes]
+    C_ = [torch.full((m, w), float(1 - cleared), device="cuda") for m, w, _ in shapes]
+    ints = lambda i: (C.c_int * n)(*[s[i] for s in shapes])
+    ptrs = lambda t: (C.c_void_p * n)(*[x.data_ptr() for x in t])
+    ok(L().ouro_op_gemm_group_as(stream(), 0, n, ints(0), ints(1), ints(2), ptrs(A), ints(0), ptrs(B), ints(1), ptrs(C_), ints(1), 0.5, cleared, 0, 0))
+    torch.cuda.synchronize()
+    for a, b, c in zip(A, B, C_):
+        assert rel_err(host(c), 1 - cleared + 0.5 * host(a).T @ host(b)) < TOL[0]
+
+
 @pytest.mark.parametrize("tile,kchunk", [(128, 0), (256, 0), (128, 512), (256, 512)])
 @pytest.mark.parametrize("cleared", [0, 1])
 @pytest.mark.parametrize("shapes", [
