@@ -712,6 +712,7 @@ hipError_t launch_attn_bwd_xl(hipStream_t s, const AttnDesc& a) {
   g.sAy = (long long)a.S * t_ld; g.sAz = (long long)a.H * a.S * t_ld;
   g.sBy = 64; g.sBz = (long long)t_ld * HD;
   g.sCy = 64;
+  g.tri = a.Mv + 1;                // query i sees the keys up to Mv + i
   g.A = p.pt; g.B = p.dop; g.C = a.dv; g.ldc = a.lddv; g.sCz = (long long)a.S * a.lddv; g.alpha = 1.f;
   if (a.lddk == a.lddv) {          // both grids in one launch
     g.A2 = p.dst; g.B2 = p.qu; g.C2 = a.dk; g.alpha2 = a.scale;

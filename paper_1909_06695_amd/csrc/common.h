@@ -121,6 +121,7 @@ struct GemmDesc {
   // launch (C2 != null): A2, B2, C2 and alpha2 in place of A, B, C and alpha.  Two grids of short
   // products are bound by memory latency; side by side they keep twice as many loads in flight.
   const void* A2; const void* B2; void* C2; float alpha2;
+  int tri;               // not 0: A and A2 [m][k] are zero for k < m - (tri - 1), and a kernel may leave those K-tiles out
 };
 // Most products one grouped launch takes (launch_gemm_group).
 constexpr int GEMM_GROUP_MAX = 6;

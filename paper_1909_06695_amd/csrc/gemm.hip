@@ -345,6 +345,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
   if (g.C2 && (!g.A2 || !g.B2)) return hipErrorInvalidValue;
   p.by = by; p.bz = bz * grids; p.bz1 = bz;
   p.A2 = g.A2; p.B2 = g.B2; p.C2 = g.C2; p.alpha2 = g.alpha2;
+  p.tri = g.tri;
   p.bAy = g.sAy * (long long)esz; p.bAz = g.sAz * (long long)esz;
   p.bBy = g.sBy * (long long)esz; p.bBz = g.sBz * (long long)esz;
   p.bCy = g.sCy * (long long)csz; p.bCz = g.sCz * (long long)csz;

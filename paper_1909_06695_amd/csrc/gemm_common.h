@@ -24,6 +24,7 @@ struct GemmParams {
   int kind;        // EPIK_*: the straight-line epilogue that serves this product
   int by, bz, bz1;                          // bz1: blockIdx.z from here on belongs to the second grid of products
   const void* A2; const void* B2; void* C2; float alpha2;
+  int tri;         // see GemmDesc
   long long bAy, bAz, bBy, bBz, bCy, bCz;   // byte strides of a batch of products over blockIdx.y, blockIdx.z (direct-to-LDS kernels)
   DropDesc drop;
   float* colsum; size_t colsum_stride;      // see GemmDesc
