@@ -567,8 +567,18 @@ constexpr int XL_LDS_DR = 2 * DR_STAGE;
 __global__ __launch_bounds__(256) void fa_xl_dr_kernel(FaParams p, int bpw) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h32 = lane >> 5, l32 = lane & 31;
-  const int D0 = blockIdx.x * 64, head = blockIdx.y;
-  const int b0 = blockIdx.z * bpw, nb = min(p.B, b0 + bpw) - b0;
+  // Neighbouring distance blocks stage the same key rows, half of theirs, at the same step: they are kept on one XCD, whose L2
+  // then serves the second reader (the launch is bound by the bytes of dS^T; consecutive workgroups go to consecutive XCDs).
+  // 16 heads and batches of 384 queries, 768 distances 53.8 -> 41.0 us; 10 heads, 32 batches of 150 queries, 300 distances
+  // 25.4 -> 21.5 us.
+  int db = blockIdx.x, grp = blockIdx.y + gridDim.y * blockIdx.z;
+  if (((gridDim.y * gridDim.z) & 7) == 0) {
+    const int lin = blockIdx.x + gridDim.x * grp, slot = lin >> 3;
+    db = slot % gridDim.x;
+    grp = (lin & 7) + 8 * (slot / gridDim.x);
+  }
+  const int D0 = db * 64, head = grp % gridDim.y;
+  const int b0 = grp / gridDim.y * bpw, nb = min(p.B, b0 + bpw) - b0;
   const int wd = wave & 1, wf = wave >> 1;
   const int HD = p.H * 64;
   const int nib = (p.T + 63) / 64;
@@ -725,9 +735,13 @@ hipError_t launch_attn_bwd_xl(hipStream_t s, const AttnDesc& a) {
     e = launch_gemm(s, 1, g, 0);
     if (e != hipSuccess) return e;
   }
-  // dr += scale sum over (b, i) of dS at distance delta times (q + v): about 768 workgroups
-  const int ndb = (a.S + 63) / 64;
-  const int bpw = std::max(1, (int)((long long)a.B * ndb * a.H / 768));
+  // dr += scale sum over (b, i) of dS at distance delta times (q + v).  Batches per workgroup: 768 workgroups are resident at
+  // once, and one ends with 4096 atomic adds, as long as some six of its 64-query steps.  So at least 12 steps each while 384
+  // workgroups are left: 1600 units of 3 steps (10 heads, 32 batches of 150 queries, 300 distances) as 800 workgroups 21.7 us,
+  // 550 21.0, 400 19.0, 350 23.1; 3072 units of 6 steps (16 heads and batches of 384 queries, 768 distances) as 768 41.3, 576 51.
+  const int ndb = (a.S + 63) / 64, steps = (a.T + 63) / 64;
+  const long long units = (long long)a.B * ndb * a.H;
+  const int bpw = std::max(1, (int)std::max(units / 768, std::min((long long)(12 + steps - 1) / steps, units / 384)));
   hipLaunchKernelGGL(fa_xl_dr_kernel, dim3(ndb, a.H, (a.B + bpw - 1) / bpw), dim3(256), XL_LDS_DR, s, p, bpw);
   return hipGetLastError();
 }

@@ -433,7 +433,8 @@ def test_attention_mfma_kernel(B, H, T, Mv):
 
 
 @pytest.mark.parametrize("B,H,T,Mv", [(2, 2, 128, 0), (1, 3, 200, 0), (2, 1, 96, 40), (1, 2, 384, 384), (1, 1, 33, 0),
-                                      (1, 2, 300, 77), (2, 2, 150, 150), (3, 2, 20, 5), (2, 3, 64, 200)])
+                                      (1, 2, 300, 77), (2, 2, 150, 150), (3, 2, 20, 5), (2, 3, 64, 200),
+                                      (4, 2, 150, 150), (33, 8, 100, 60)])
 def test_attention_xl_mfma_kernel(B, H, T, Mv):
     """Fused matrix-core kernels with the relative-position term (bf16, head size 64): with and
     without memory, several query/key blocks, ragged tails, fewer keys than a contraction tile
