@@ -79,6 +79,13 @@ int ouro_op_attention_fwd(void* stream, int dtype, int B, int H, int T, int S, i
                           float scale, const void* q, int ldq, const void* k, int ldk,
                           const void* v, int ldv, void* o, int ldo, float* lse, int rel,
                           const void* u, const void* vb, const void* r, int ldr, int force_generic);
+/* The same for bf16, head size 64 and rel != 0, with a workspace of ouro_op_attention_fwd_parts_floats() floats (0: the keys of a
+ * query block stay with one workgroup; parts is then not used, but not NULL either), 16-byte aligned: launches of few workgroups deal the keys of a query block to
+ * several and merge their outputs, as the model's forward pass does. */
+int ouro_op_attention_fwd_parts(void* stream, int B, int H, int T, int S, int Mv, float scale, const void* q, int ldq,
+                                const void* k, int ldk, const void* v, int ldv, void* o, int ldo, float* lse,
+                                const void* u, const void* vb, const void* r, int ldr, float* parts);
+size_t ouro_op_attention_fwd_parts_floats(int B, int H, int T, int S);
 /* Backward of the above.  du, dvb (fp32 [H,dh]) and dr (fp32 [S, H*dh]) are overwritten when
  * rel != 0 (may be NULL otherwise).  scratch: fp32, ouro_op_attention_bwd_scratch() floats,
  * 16-byte aligned: enough for either form (with rel != 0, bf16 and dh == 64 the pass leaves the

@@ -95,6 +95,9 @@ def lib():
         "ouro_op_gemm_uses_mfma": (i32, [i32, i32, i32, i32, i32, i32, vp, i32, vp, i32]),
         "ouro_op_attention_fwd": (i32, [vp, i32, i32, i32, i32, i32, i32, i32, f32, vp, i32, vp, i32, vp, i32, vp,
                                         i32, vp, i32, vp, vp, vp, i32, i32]),
+        "ouro_op_attention_fwd_parts": (i32, [vp, i32, i32, i32, i32, i32, f32, vp, i32, vp, i32, vp, i32, vp, i32, vp, vp, vp, vp,
+                                              i32, vp]),
+        "ouro_op_attention_fwd_parts_floats": (sz, [i32, i32, i32, i32]),
         "ouro_op_attention_bwd": (i32, [vp, i32, i32, i32, i32, i32, i32, i32, f32, vp, i32, vp, i32, vp, i32, vp,
                                         i32, vp, vp, i32, vp, i32, vp, i32, vp, i32, i32, vp, vp, vp, i32, vp, vp,
                                         vp, vp, i32]),

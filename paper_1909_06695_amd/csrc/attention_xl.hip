@@ -310,8 +310,10 @@ __global__ __launch_bounds__(256) void fa_xl_merge_kernel(FaParams p) {
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int i = 0; i < XL_PARTS_MAX; ++i) {
-    if (i >= p.parts || ml[i].x == -INFINITY) continue;    // a part none of whose keys the row sees
-    const float a = __builtin_amdgcn_exp2f(ml[i].x - mm);
+    if (i >= p.parts) continue;
+    // a part none of whose keys the row sees has a zero sum and output; one whose scores are all NaN has the same maximum (the
+    // maximum skips NaN), and its sum and output stay NaN
+    const float a = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - mm);
     l += ml[i].y * a;
     sum.x += o[i].x * a; sum.y += o[i].y * a; sum.z += o[i].z * a; sum.w += o[i].w * a;
   }

@@ -135,6 +135,18 @@ extern "C" int ouro_op_attention_fwd(void* stream, int dtype, int B, int H, int 
   return rc_of(launch_attn_fwd((hipStream_t)stream, dtype, a, force_generic));
 }
 
+extern "C" size_t ouro_op_attention_fwd_parts_floats(int B, int H, int T, int S) {
+  return B < 1 || H < 1 || T < 1 || S < T ? 0 : attn_fwd_parts_floats(B, H, T, S);
+}
+extern "C" int ouro_op_attention_fwd_parts(void* stream, int B, int H, int T, int S, int Mv, float scale, const void* q, int ldq,
+                                           const void* k, int ldk, const void* v, int ldv, void* o, int ldo, float* lse,
+                                           const void* u, const void* vb, const void* r, int ldr, float* parts) {
+  if (!q || !k || !v || !o || !lse || !u || !vb || !r || !parts || S != Mv + T || B < 1 || H < 1 || T < 1 || Mv < 0) return OURO_E_ARG;
+  AttnDesc a = make_attn(B, H, T, S, 64, Mv, scale, q, ldq, k, ldk, v, ldv, o, ldo, lse, 1, u, vb, r, ldr);
+  a.parts = parts;
+  return rc_of(launch_attn_fwd((hipStream_t)stream, 1, a, 0));
+}
+
 extern "C" size_t ouro_op_attention_bwd_scratch(int B, int H, int T, int S, int dh) {
   return attn_bwd_scratch_floats_any(B, H, T, S, dh);
 }

@@ -442,6 +442,70 @@ def test_attention_xl_mfma_kernel(B, H, T, Mv):
     _attn_case(1, B, H, T, Mv, 64, 1, seed=200 + T + Mv, force=0)
 
 
+def _xl_fwd(q, kv, r, u, vb, B, H, T, Mv, parts):
+    """Output and log-sum-exp of the relative-position forward kernel on bf16 device tensors, and the number of parts of the keys."""
+    S, d = Mv + T, H * 64
+    n = L().ouro_op_attention_fwd_parts_floats(B, H, T, S)
+    o = torch.full((B * T, d), 3.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, H, T), 3.0, device="cuda")
+    kp, vp = C.c_void_p(kv.data_ptr()), C.c_void_p(kv.data_ptr() + 2 * d)
+    if parts:
+        ws = torch.full((max(n, 4),), float("nan"), device="cuda")
+        ok(L().ouro_op_attention_fwd_parts(stream(), B, H, T, S, Mv, 0.125, p(q), d, kp, 2 * d, vp, 2 * d, p(o), d, p(lse), p(u), p(vb), p(r), d, p(ws)))
+    else:
+        ok(L().ouro_op_attention_fwd(stream(), 1, B, H, T, S, 64, Mv, 0.125, p(q), d, kp, 2 * d, vp, 2 * d, p(o), d, p(lse), 1, p(u), p(vb), p(r), d, 0))
+    torch.cuda.synchronize()
+    return host(o), host(lse), n // (B * H * T * 66) if n else 1
+
+
+def _xl_inputs(B, H, T, Mv, seed):
+    rng = np.random.default_rng(seed)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    S, d = Mv + T, H * 64
+    return [dev(x, 1) for x in (f(B * T, d), f(B * S, 2 * d), f(S, d), 0.5 * f(H, 64), 0.5 * f(H, 64))]
+
+
+PARTS = [(1, 2, 150, 700, 2), (2, 3, 33, 900, 2), (1, 1, 200, 1000, 3), (1, 2, 70, 1500, 4), (1, 2, 1537, 0, 4), (1, 1, 1030, 1000, 4)]
+
+
+@pytest.mark.parametrize("B,H,T,Mv,n", PARTS)
+def test_attention_xl_forward_in_parts(B, H, T, Mv, n):
+    """The keys of a query block dealt to two, three and four workgroups, ragged query and key blocks, and (no memory) early query
+    blocks with fewer key blocks than parts: output and log-sum-exp against the oracle, bounds of _attn_case."""
+    ins = _xl_inputs(B, H, T, Mv, T + Mv)
+    o, lse, parts = _xl_fwd(*ins, B, H, T, Mv, True)
+    assert parts == n
+    S, d = Mv + T, H * 64
+    heads = lambda x, rows: x.reshape(B, rows, H, 64).transpose(0, 2, 1, 3)
+    q, kv, r, u, vb = (host(x) for x in ins)
+    ref, cache = O.attention_core_fwd(heads(q, T), heads(kv[:, :d], S), heads(kv[:, d:], S), Mv, 0.125, u, vb, r.reshape(S, H, 64).transpose(1, 0, 2))
+    assert rel_err(o, ref.transpose(0, 2, 1, 3).reshape(B * T, d)) < TOL[1]
+    assert np.abs(lse - cache["lse"]).max() < 2e-2
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("what", ["q", "k", "v", "keys of a part", "all keys"])
+@pytest.mark.parametrize("B,H,T,Mv,n", PARTS[:5])
+def test_attention_xl_parts_keep_what_is_not_finite(B, H, T, Mv, n, what, value):
+    """A NaN or infinity in a query, a key, a value, in all keys that one workgroup takes or in all there are reaches the same
+    outputs and log-sum-exps as in the kernel that keeps a query block's keys together; the finite ones are alike (bf16 outputs of
+    two orders of summation)."""
+    ins = _xl_inputs(B, H, T, Mv, T + Mv)
+    S, d = Mv + T, H * 64
+    if what == "q": ins[0][T // 2, 5] = value
+    elif what == "k": ins[1][S // 3, 7] = value
+    elif what == "v": ins[1][S // 3, d + 7] = value
+    elif what == "all keys": ins[1][:S, 9] = value
+    else: ins[1][:(S + 63) // 64 // n * 64, 9] = value          # the first part of the last query block
+    (o, lse, parts), (o1, lse1, _) = (_xl_fwd(*ins, B, H, T, Mv, x) for x in (True, False))
+    assert parts == n
+    assert not np.isfinite(o1).all()
+    for x, y, tol in ((o, o1, TOL[1]), (lse, lse1, 1e-5)):
+        fin = np.isfinite(y)
+        assert np.array_equal(np.isfinite(x), fin)
+        assert not fin.any() or rel_err(x[fin], y[fin]) < tol
+
+
 @pytest.mark.parametrize("B,H,T,Mv,dh", [(1, 1, 1, 0, 64), (2, 1, 10, 200, 32), (2, 2, 33, 0, 32), (1, 3, 70, 5, 41), (2, 2, 128, 0, 64), (1, 2, 150, 40, 48),
                                          (2, 1, 257, 0, 7), (1, 2, 31, 97, 36)])
 def test_attention_f32_kernel(B, H, T, Mv, dh):

@@ -439,6 +439,15 @@ def test_xl_bf16_mfma_path_memory_carry(overlap):
     run_both(c, steps=4, lr=0.05, seed=31, std=0.05, perturb=0.05, tol=2e-2, overlap=overlap)
 
 
+@pytest.mark.parametrize("schedule", [0, 1])
+def test_xl_bf16_training_with_keys_dealt_to_workgroups(schedule):
+    """One stream of few heads on a long memory: the training forward pass goes from one workgroup per query block to two, three and
+    four, and its merged log-sum-exp feeds the backward pass (under the second schedule recomputed)."""
+    c = dict(n_layer=2, d_model=128, n_head=2, d_head=64, d_ff=96, vocab=211, seq_len=300, mem_len=1300, batch=1,
+             n_module=2, rel_pos=1, dtype=1, optimizer=0, embed_warm_mode=1, schedule=schedule)
+    run_both(c, steps=7, lr=0.05, seed=33, std=0.05, perturb=0.05, tol=2e-2)
+
+
 @pytest.mark.parametrize("overlap", [False, True])
 def test_bf16_widths_off_the_tile_grid_adam(overlap):
     """bf16 mode with d_head = 41, d_model = 82, d_ff = 100: stored zero-padded to 64 / 128 / 128 so
@@ -584,6 +593,28 @@ def test_eval_step_with_keys_dealt_to_workgroups(T, M, B, heads):
         assert abs(lg - lo) / lo < 2e-3, (t, lg, lo)
         mem = e.get_mems(1)
         assert mem.shape == oe.mems[1].shape and rel_err(mem, oe.mems[1]) < 2e-2
+    e.close()
+
+
+def test_eval_step_keeps_a_diverged_model_visible():
+    """NaN in the query weights, keys dealt to several workgroups: the loss is NaN, as without memory, not a finite number."""
+    c = dict(n_layer=2, d_model=128, n_head=2, d_head=64, d_ff=96, vocab=211, seq_len=128, mem_len=1000, batch=1, n_module=2, rel_pos=1, dtype=1,
+             optimizer=0)
+    blobs = S.init_params(c, seed=23, std=0.1)
+    cfg = O.Config(**c)
+    name, shape = O.param_shapes(cfg)[0]
+    assert name == "W_qkv" and shape == (128, 384)
+    tok, tgt = S.token_batches(c["vocab"], 1, 128, 9, 1.1, 24, contiguous=True)
+    e = P().create_model(**c)
+    for t in range(9):
+        if t in (0, 8):                                       # the memories of the iterations before hold finite values
+            for g in range(3):
+                b = blobs[g].copy()
+                if g == 1 and t == 8:
+                    b[:128 * 384].reshape(128, 384)[:, :128] = np.nan
+                e.set_params(g, b)
+        loss = e.eval_step(torch.from_numpy(tok[t]).cuda(), torch.from_numpy(tgt[t]).cuda())
+        assert np.isfinite(loss) == (t < 8), (t, loss)
     e.close()
 
 
