@@ -576,7 +576,7 @@ def test_eval_step_with_longer_memory(dtype, tol):
     m.close(); e.close()
 
 
-@pytest.mark.parametrize("T,M,B,heads", [(150, 1300, 1, 2), (40, 800, 2, 1), (130, 700, 3, 2)])
+@pytest.mark.parametrize("T,M,B,heads", [(150, 1400, 1, 2), (40, 800, 2, 1), (130, 700, 3, 2)])
 def test_eval_step_with_keys_dealt_to_workgroups(T, M, B, heads):
     """Few heads and streams, a long memory that fills segment by segment: the forward attention goes from one workgroup per query
     block to two, three and four.  Losses and rolled memories against the oracle."""
