@@ -241,6 +241,7 @@ struct ouro_model : BwdCtx {
   std::vector<SumSegment*> segs_dev;
   // inside a step on one stream: the sums of the vector gradients are collected; the gradient slots are cleared already
   bool batched = false, cleared = false;
+  bool vec_dirty = false;      // a step failed between a module's vector gradients and their sum: copies that belong to no gradient may be left
   std::vector<SumSegmentsOf> sums;
   // Stored-input schedule (cfg.schedule == 1): module k < K keeps the input of its last
   // K-k+1 forward passes (token ids for k = 1, the hidden state at the boundary otherwise),
@@ -1285,6 +1286,10 @@ static int module_backward_impl(ouro_model* m, int k, bool defer_join) {
     if (m->mailtag[pr][k] != tau) return fail(OURO_E_STALE, "module %d error gradient is of mini-batch %lld, wanted %lld", k, (long long)m->mailtag[pr][k], (long long)tau);
     dh_top = m->mail[pr][k];
   }
+  if (m->vec_dirty) {
+    HIPCHK(launch_fill_zero(m->stream, m->vec_copies, 8 * m->vec_stride * 4));
+    m->vec_dirty = false;
+  }
   float* gslot = m->slot_ptr(k, slot);
   if (!m->cleared) HIPCHK(launch_fill_zero(m->stream, gslot, (size_t)m->gstride[k] * 4));
   if (k == K) {
@@ -1546,10 +1551,29 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
   const bool early = m->use_side && !m->timing;
   // A step on one stream: the gradient slots of all modules are cleared by one launch and their vector gradients summed by
   // one, as its small launches follow each other at 2 us each and more.
+  // A module's gradient is complete with its sums.  Where the step fails before they are launched, the finished modules' sums
+  // are launched on the way out; where that fails too, these modules' slots count as never written.
   struct Batch {
     ouro_model* m;
     explicit Batch(ouro_model* x) : m(x) {}
-    ~Batch() { m->batched = m->cleared = false; m->sums.clear(); }
+    hipError_t finish() {
+      m->batched = false;
+      if (m->sums.empty()) return hipSuccess;
+      const hipError_t e = launch_sum_segments(m->stream, m->sums.data(), (int)m->sums.size(), m->vec_copies, m->vec_stride);
+      const int K = m->cfg.n_module;
+      for (int k = K; e != hipSuccess && k > K - (int)m->sums.size(); --k) {
+        int64_t slot, tau;
+        ouro_slot_index(K, k, m->t, 1, &slot, &tau);
+        m->tags[k][slot] = -1;
+      }
+      m->vec_dirty |= e != hipSuccess;
+      m->sums.clear();
+      return e;
+    }
+    ~Batch() {
+      if (m->batched) { (void)finish(); m->vec_dirty = true; }       // what the module that failed had added is left too
+      m->cleared = false;
+    }
   } batch(m);
   // (beyond the 256 MB of the memory-side cache a module's slot is better cleared right before its gradients: 1.17 GB 157 us in five
   // launches, 215 in one; 240 MB 46 and 41)
@@ -1579,7 +1603,7 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
       if (k == K && m->cfg.schedule == 0) RUN(update_group(m, 0, lr, m->aux));
     }
   }
-  if (m->batched) HIPCHK(launch_sum_segments(m->stream, m->sums.data(), (int)m->sums.size(), m->vec_copies, m->vec_stride));
+  if (m->batched) HIPCHK(batch.finish());
   std::vector<int> rest;                // the last update closes the iteration and clears the mask
   for (int k = 0; k <= K; ++k)
     if (!(m->upd_mask & (1ull << k))) rest.push_back(k);

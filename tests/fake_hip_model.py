@@ -1,0 +1,108 @@
+"""A model whose host side runs on the CPU over tests/fake_hip.cpp (no torch: its own HIP runtime would be found first).  Run as
+a program: python fake_hip_model.py <stand-in library> <scenario>."""
+import ctypes as C
+import os
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+E_STALE, E_HIP = -6, -7
+
+
+class Config(C.Structure):
+    _fields_ = ([(n, C.c_int32) for n in ("n_layer", "d_model", "n_head", "d_head", "d_ff", "vocab", "seq_len", "mem_len", "batch", "n_module")]
+                + [("layers_per_module", C.POINTER(C.c_int32))] + [(n, C.c_int32) for n in ("rel_pos", "dtype", "optimizer")]
+                + [(n, C.c_float) for n in ("beta1", "beta2", "eps")] + [("embed_warm_mode", C.c_int32), ("emb_scale", C.c_float),
+                                                                         ("schedule", C.c_int32), ("dropout", C.c_float), ("seed", C.c_uint64)])
+
+
+class Model:
+    def __init__(self, fake, **kw):
+        self.F = C.CDLL(fake, C.RTLD_GLOBAL)
+        self.F.fake_name.restype = C.c_char_p
+        self.F.fake_news.restype = C.c_long
+        self.L = C.CDLL(os.path.join(ROOT, "paper_1909_06695_amd", "libouro.so"))
+        c = dict(n_layer=3, d_model=32, n_head=2, d_head=16, d_ff=64, vocab=32, seq_len=8, mem_len=0, batch=2, n_module=3, rel_pos=0, dtype=0,
+                 optimizer=0, beta1=0.9, beta2=0.999, eps=1e-8, emb_scale=1.0)
+        c.update(kw)
+        cfg, n = Config(**c), C.c_size_t()
+        assert self.L.ouro_query_arena_bytes(C.byref(cfg), C.byref(n)) == 0
+        self.buf = (C.c_char * (n.value + 256))()
+        base = (C.addressof(self.buf) + 255) // 256 * 256
+        self.h = C.c_void_p()
+        assert self.L.ouro_create_model(C.byref(cfg), C.c_void_p(base), n, None, C.byref(self.h)) == 0
+        self.K = c["n_module"]
+        self.ids = C.c_void_p(C.addressof((C.c_int32 * (c["batch"] * c["seq_len"]))()))
+        self.L.ouro_current_step.restype = C.c_int64
+
+    def step(self, loss=True):
+        x = C.c_float()
+        return self.L.ouro_step(self.h, self.ids, self.ids, C.c_float(0.1), C.byref(x) if loss else None)
+
+    def backward(self, k):
+        return self.L.ouro_module_backward(self.h, k)
+
+    def update(self, g):
+        return self.L.ouro_delayed_update(self.h, g, C.c_float(0.1))
+
+    def now(self):
+        return self.L.ouro_current_step(self.h)
+
+    def log(self, fn):
+        """(result, [(kernel, first int of its arguments), ...]) of a call."""
+        self.F.fake_reset()
+        rc = fn()
+        return rc, [(self.F.fake_name(i).decode(), self.F.fake_first_arg(i)) for i in range(self.F.fake_count())]
+
+    def fail(self, launch, times=1):
+        self.F.fake_fail(launch, times)
+
+
+def sums(log):
+    return [n for name, n in log if "sum_segments" in name]
+
+
+def fills(log):
+    return sum("fill_zero_kernel" in name for name, _ in log)
+
+
+def failed_step(fake):
+    """A step on one stream that fails at some launch: the modules whose backward pass had ended keep their whole gradient, or count
+    as without one."""
+    m = Model(fake)
+    for _ in range(4):
+        assert m.step() == 0
+    rc, clean = m.log(m.step)
+    assert rc == 0 and sums(clean) == [3]                  # the vector gradients of all three modules in one launch
+    at = [i for i, (name, _) in enumerate(clean) if "sum_segments" in name][0]
+    # in the backward pass of the last module: what the other two have added is summed on the way out
+    m.fail(at - 3)
+    rc, log = m.log(m.step)
+    assert rc == E_HIP and sums(log) == [2], (rc, sums(log))
+    rc, log = m.log(lambda: m.backward(1))
+    assert rc == 0 and sums(log) == [1]
+    extra = fills(log)
+    assert all(m.update(g) == 0 for g in range(4)) and m.now() == 6
+    # the copies that the failed module left were cleared first: one fill more than without a failure
+    assert all(m.L.ouro_module_forward(m.h, k, m.ids, m.ids) == 0 for k in (1, 2, 3)) and m.backward(3) == 0 and m.backward(2) == 0
+    rc, log = m.log(lambda: m.backward(1))
+    assert rc == 0 and fills(log) == extra - 1
+    assert all(m.update(g) == 0 for g in range(4)) and m.now() == 7
+    # nothing can be launched any more, then everything again: the top module's gradient is refused (the others' are older ones)
+    m.fail(at - 3, 1000)
+    rc, log = m.log(m.step)
+    assert rc == E_HIP and sums(log) == []
+    m.fail(-1)
+    assert m.backward(1) == 0
+    assert m.update(3) == E_STALE
+    # the launch of the sums itself
+    m = Model(fake)
+    for _ in range(4):
+        assert m.step() == 0
+    m.fail(at)
+    assert m.step() == E_HIP
+    assert m.update(3) == E_STALE
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]](sys.argv[1])
+    print("passed")

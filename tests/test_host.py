@@ -3,6 +3,8 @@ declare, and its pure-integer staleness functions follow Eq. 8-9 (brute force)."
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -170,3 +172,20 @@ def test_lr_schedule_matches_the_oracle():
     for bad in [(1.0, 10, 10, 0, 0.0), (1.0, -1, 10, 0, 0.0), (1.0, 2, 10, -1, 0.0), (1.0, 2, 10, 0, 2.0), (1.0, 2, 10, 0, -0.1)]:
         with pytest.raises(P.OuroError):
             P.lr_schedule(bad[0], bad[1], bad[2], bad[3], bad[4])
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    """The stand-in for the HIP runtime, built; returns a function that runs a scenario of fake_hip_model.py on it."""
+    here = os.path.join(ROOT, "tests")
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(here, "fake_hip.cpp")], check=True)
+
+    def run(scenario):
+        r = subprocess.run([sys.executable, os.path.join(here, "fake_hip_model.py"), so, scenario], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.endswith("passed\n"), r.stdout + r.stderr
+    return run
+
+
+def test_failed_step_leaves_no_partial_gradient(fake_hip):
+    fake_hip("failed_step")
