@@ -60,6 +60,9 @@ int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* 
 int ouro_op_gemm_group_as(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                           const void* const* A, const int* lda, const void* const* B, const int* ldb,
                           float* const* C, const int* ldc, float alpha, int cleared, int tile, int kchunk);
+/* What a grouped launch chooses for n <= 6 bf16 products (host only): *tile 128 or 256, *kchunk the length of a K range.  alone: nothing
+ * runs beside the launch (a step on one stream), so its duration alone counts. */
+int ouro_op_gemm_group_plan(int n, const int* M, const int* N, const int* K, int cleared, int alone, int* tile, int* kchunk);
 /* Bytes from the base of an operand (rows along its slow dimension, cols contiguous) to the end of its last element: what
  * the contraction kernels may read of it (host only). */
 size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld);

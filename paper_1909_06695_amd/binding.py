@@ -90,6 +90,7 @@ def lib():
                                        vp, vp, vp, f32, i32]),
         "ouro_op_gemm_group": (i32, [vp, i32, i32, P(i32), P(i32), P(i32), P(vp), P(i32), P(vp), P(i32), P(vp), P(i32), f32]),
         "ouro_op_gemm_group_as": (i32, [vp, i32, i32, P(i32), P(i32), P(i32), P(vp), P(i32), P(vp), P(i32), P(vp), P(i32), f32, i32, i32, i32]),
+        "ouro_op_gemm_group_plan": (i32, [i32, P(i32), P(i32), P(i32), i32, i32, P(i32), P(i32)]),
         "ouro_op_gemm_operand_bytes": (sz, [i32, i32, i32, i32]),
         "ouro_op_gemm_plan": (i32, [i32, i32, i32, i32, i32, i32, i32, P(i32), P(i32)]),
         "ouro_op_gemm_uses_mfma": (i32, [i32, i32, i32, i32, i32, i32, vp, i32, vp, i32]),

@@ -143,6 +143,8 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& g, int force_ge
 // kernel; otherwise one launch_gemm each.  tile 0: the kernel and the length of a K range are chosen; 128, 256: that kernel,
 // also for one product, with ranges of kchunk (a multiple of 64; 0: chosen).  alone: nothing else runs beside the launch.
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile = 0, int kchunk = 0, bool alone = false);
+// What it chooses for n products of the grouped bf16 kernels (host only): 256-wide tiles or 128-wide ones, and the K range of either.
+void gemm_group_plan(const GemmDesc* g, int n, bool alone, bool* big, int (&kchunks)[2]);
 // true if launch_gemm would take the MFMA path for this problem
 // What launch_gemm chooses for one product (host only): 1 the plain kernel, 20 the fp32 matrix-core
 // kernel, GEMM_TILE_*, and (bf16) the contraction ranges.

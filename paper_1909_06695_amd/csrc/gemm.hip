@@ -8,7 +8,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <utility>
-#include <vector>
 
 namespace ouro {
 
@@ -445,6 +444,79 @@ static GemmParams group_params(const GemmDesc& d, size_t esz) {
   return p;
 }
 
+// One K-range length for all products, and one of two kernels.
+// Beside the error-gradient chain a compute unit that the launch leaves free is worth as much as time: the mean of its duration
+// and its share of the chip's is compared.  128x128 tiles, two workgroups per CU, run in whole rounds
+// of 512 and take 1.2 us per K-tile (of two side by side) plus 6 K-tiles of fixed cost (ring fill, atomic adds that the
+// neighbour's matrix work covers).  256x256 tiles, one workgroup per CU, take 1.45 us per K-tile and 6 us besides; nothing
+// covers their atomic adds, which all workgroups of a round reach together (310 adds per ns over the chip: 70 us for
+// the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.  128x128 and
+// 256x256 tiles: 1024-wide layer, 8192 rows 255 and 185 us, 6144 rows 182 and 131 (256x256 taken); 512-wide, 8192 rows 73 and
+// 80 (128x128 taken); 768-wide, 2331 rows 42 and 52 (256x256 taken: 108 compute units instead of all).
+// Alone on the chip the duration counts: the makespan of dealing the products, longest range first, to the slots, and the
+// atomic adds of the split ones (400 per ns), which set the time of short ranges.  128x128 tiles take 0.65 us per K-tile
+// where no CU has two and 0.82 side by side, and 4 us besides.  448-wide relative-position layer, 4800 rows, ranges of 1600 / 2432 /
+// 3200 / 4800 rows: 73 / 74 / 58 / 62 us (estimated 77 / 84 / 65 / 68), on 256x256 tiles 66 at best; 512-wide, 8192 rows, 2432 / 4096 /
+// 8192: 83 / 71 / 89; 256-wide, 2048 rows, 320 / 640 / 960: 23 / 16 / 16 (25 with the range the other rule takes).
+// The search costs host time on every call, so only ranges are looked at that change some product's number of splits (of those
+// with equal numbers the shortest is the best one), and nothing is allocated: 18 x 1024-wide relative-position layers, 6144 rows,
+// 86 us a layer with every range and heap-allocated intervals, 11 now.
+void gemm_group_plan(const GemmDesc* g, int n, bool alone, bool* big_out, int (&kchunks)[2]) {
+  int kmax = 0;
+  for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
+  double best[2] = {1e30, 1e30};
+  kchunks[0] = kchunks[1] = kmax;
+  for (int kc = std::min(256, kmax), next; kc <= kmax; kc = next) {
+    int splits[GEMM_GROUP_MAX];
+    next = kmax + 64;
+    for (int i = 0; i < n; ++i) {
+      splits[i] = (g[i].K + kc - 1) / kc;
+      if (splits[i] > 1) next = std::min(next, ((g[i].K + splits[i] - 2) / (splits[i] - 1) + 63) / 64 * 64);
+    }
+    for (int big = 0; big < 2; ++big) {
+      const int bt = big ? 256 : 128;
+      const long slots = big ? 256 : 512;
+      struct Part { int range; long wgs; } part[GEMM_GROUP_MAX];       // longest range first
+      long wgs = 0;
+      double adds = 0, cost;
+      for (int i = 0; i < n; ++i) {
+        const Part x = {((g[i].K + splits[i] - 1) / splits[i] + 63) / 64, (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt) * splits[i]};
+        wgs += x.wgs;
+        if (splits[i] > 1 || g[i].accumulate != ACC_STORE) adds += (double)x.wgs * bt * bt;
+        int j = i;
+        for (; j > 0 && part[j - 1].range < x.range; --j) part[j] = part[j - 1];
+        part[j] = x;
+      }
+      if (alone) {
+        const double rate = big ? 1.45 : wgs <= 256 ? 0.65 : 0.82, fixed = big ? 6 : 4;
+        // slots by the time from which they are free: a deal takes all slots of an entry and adds one, or ends a product
+        struct Free { double at; long slots; } free_at[GEMM_GROUP_MAX + 1] = {{0.0, slots}};
+        int nf = 1;
+        double end = 0;
+        for (int i = 0; i < n; ++i)
+          for (long left = part[i].wgs; left > 0;) {
+            int first = 0;
+            for (int j = 1; j < nf; ++j)
+              if (free_at[j].at < free_at[first].at || (free_at[j].at == free_at[first].at && free_at[j].slots < free_at[first].slots)) first = j;
+            Free& f = free_at[first];
+            const double t = f.at + rate * part[i].range + fixed;
+            const long take = std::min(left, f.slots);
+            left -= take;
+            if (take == f.slots) f.at = t;
+            else { f.slots -= take; free_at[nf++] = {t, take}; }
+            end = std::max(end, t);
+          }
+        cost = end + adds / (big ? 310e3 : 400e3);
+      } else {
+        const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
+        cost = 0.5 * one * (std::ceil((double)wgs / slots) + (double)wgs / slots);
+      }
+      if (cost < best[big] - 1e-9) { best[big] = cost; kchunks[big] = kc; }
+    }
+  }
+  *big_out = best[1] < best[0];
+}
+
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n, int tile, int kchunk, bool alone) {
   if (n < 1 || n > GEMM_GROUP_MAX || (tile != 0 && tile != 128 && tile != 256) || kchunk < 0 || kchunk % 64) return hipErrorInvalidValue;
   // products that do not admit the grouped kernel go by themselves
@@ -464,63 +536,14 @@ hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* g, int n,
   if (nf) return launch_gemm_f32_group(s, f32, nf);
   if (ni == 0) return hipSuccess;
   if (ni == 1 && !tile) return launch_gemm(s, dtype, in[0], 0);
-  if (alone) std::stable_sort(in, in + ni, [](const GemmDesc& x, const GemmDesc& y) { return x.K > y.K; });
+  if (alone)                                       // longest contraction first, as planned
+    for (int i = 1; i < ni; ++i)
+      for (int j = i; j > 0 && in[j - 1].K < in[j].K; --j) std::swap(in[j - 1], in[j]);
   g = in; n = ni;
-  // One K-range length for all products, and one of two kernels.
-  // Beside the error-gradient chain a compute unit that the launch leaves free is worth as much as time: the mean of its duration
-  // and its share of the chip's is compared.  128x128 tiles, two workgroups per CU, run in whole rounds
-  // of 512 and take 1.2 us per K-tile (of two side by side) plus 6 K-tiles of fixed cost (ring fill, atomic adds that the
-  // neighbour's matrix work covers).  256x256 tiles, one workgroup per CU, take 1.45 us per K-tile and 6 us besides; nothing
-  // covers their atomic adds, which all workgroups of a round reach together (310 adds per ns over the chip: 70 us for
-  // the 22 million of a 1024-wide layer split over 256 workgroups), but a tile whose K range is not split is stored.  128x128 and
-  // 256x256 tiles: 1024-wide layer, 8192 rows 255 and 185 us, 6144 rows 182 and 131 (256x256 taken); 512-wide, 8192 rows 73 and
-  // 80 (128x128 taken); 768-wide, 2331 rows 42 and 52 (256x256 taken: 108 compute units instead of all).
-  // Alone on the chip the duration counts: the makespan of dealing the products, longest range first, to the slots, and the
-  // atomic adds of the split ones (400 per ns), which set the time of short ranges.  128x128 tiles take 0.65 us per K-tile
-  // where no CU has two and 0.82 side by side, and 4 us besides.  448-wide relative-position layer, 4800 rows, ranges of 1600 / 2432 /
-  // 3200 / 4800 rows: 73 / 74 / 58 / 62 us (estimated 77 / 84 / 65 / 68), on 256x256 tiles 66 at best; 512-wide, 8192 rows, 2432 / 4096 /
-  // 8192: 83 / 71 / 89; 256-wide, 2048 rows, 320 / 640 / 960: 23 / 16 / 16 (25 with the range the other rule takes).
-  int kmax = 0;
-  for (int i = 0; i < n; ++i) kmax = std::max(kmax, (g[i].K + 63) / 64 * 64);
-  double best[2] = {1e30, 1e30};
-  int kchunks[2] = {kmax, kmax};
-  for (int kc = std::min(256, kmax); kc <= kmax; kc += 64) {
-    for (int big = 0; big < 2; ++big) {
-      const int bt = big ? 256 : 128;
-      const long slots = big ? 256 : 512;
-      struct Part { int range; long wgs; } part[GEMM_GROUP_MAX];
-      long wgs = 0;
-      double adds = 0, cost;
-      for (int i = 0; i < n; ++i) {
-        const int splits = (g[i].K + kc - 1) / kc;
-        part[i] = {((g[i].K + splits - 1) / splits + 63) / 64, (long)((g[i].M + bt - 1) / bt) * ((g[i].N + bt - 1) / bt) * splits};
-        wgs += part[i].wgs;
-        if (splits > 1 || g[i].accumulate != ACC_STORE) adds += (double)part[i].wgs * bt * bt;
-      }
-      if (alone) {
-        const double rate = big ? 1.45 : wgs <= 256 ? 0.65 : 0.82, fixed = big ? 6 : 4;
-        std::sort(part, part + n, [](const Part& x, const Part& y) { return x.range > y.range; });
-        std::vector<std::pair<double, long>> free_at{{0.0, slots}};          // (time, slots that are free from then on)
-        double end = 0;
-        for (int i = 0; i < n; ++i)
-          for (long left = part[i].wgs; left > 0;) {
-            auto it = std::min_element(free_at.begin(), free_at.end());
-            const double t = it->first + rate * part[i].range + fixed;
-            const long take = std::min(left, it->second);
-            left -= take;
-            if ((it->second -= take) == 0) free_at.erase(it);
-            free_at.push_back({t, take});
-            end = std::max(end, t);
-          }
-        cost = end + adds / (big ? 310e3 : 400e3);
-      } else {
-        const double one = big ? 1.45 * (kc / 64) + 6 + adds / 310e3 : 1.2 * (kc / 64 + 6);
-        cost = 0.5 * one * (std::ceil((double)wgs / slots) + (double)wgs / slots);
-      }
-      if (cost < best[big] - 1e-9) { best[big] = cost; kchunks[big] = kc; }
-    }
-  }
-  const bool big = tile ? tile == 256 : best[1] < best[0];
+  bool big;
+  int kchunks[2];
+  gemm_group_plan(g, n, alone, &big, kchunks);
+  if (tile) big = tile == 256;
   if (!tile || !kchunk) kchunk = kchunks[big];
   GemmParams ps[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) {

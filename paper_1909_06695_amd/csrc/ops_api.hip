@@ -62,6 +62,21 @@ extern "C" int ouro_op_gemm_group_as(void* stream, int dtype, int n, const int* 
   }
   return rc_of(launch_gemm_group((hipStream_t)stream, dtype, g, n, tile, kchunk));
 }
+extern "C" int ouro_op_gemm_group_plan(int n, const int* M, const int* N, const int* K, int cleared, int alone, int* tile, int* kchunk) {
+  if (n < 1 || n > GEMM_GROUP_MAX || !M || !N || !K || !tile || !kchunk) return OURO_E_ARG;
+  GemmDesc g[GEMM_GROUP_MAX];
+  for (int i = 0; i < n; ++i) {
+    if (M[i] < 1 || N[i] < 1 || K[i] < 1) return OURO_E_ARG;
+    g[i] = make_gemm(1, 0, M[i], N[i], K[i], 1.f, nullptr, M[i], nullptr, N[i], nullptr, N[i], 1, 1, nullptr, nullptr, 0, EPI_NONE, nullptr, 0);
+    if (cleared) g[i].accumulate = ACC_STORE;
+  }
+  bool big;
+  int kchunks[2];
+  gemm_group_plan(g, n, alone != 0, &big, kchunks);
+  *tile = big ? 256 : 128;
+  *kchunk = kchunks[big];
+  return OURO_OK;
+}
 extern "C" int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                                   const void* const* A, const int* lda, const void* const* B, const int* ldb,
                                   float* const* C, const int* ldc, float alpha) {

@@ -2,9 +2,11 @@
 declare, and its pure-integer staleness functions follow Eq. 8-9 (brute force)."""
 import ctypes
 import os
+import random
 import re
 import subprocess
 import sys
+import time
 
 import pytest
 
@@ -159,6 +161,86 @@ def test_reads_in_inline_assembly_wait_in_their_own_block():
                 found += 1
                 assert "s_waitcnt" in block, (name, block[:80])
     assert found >= 4
+
+
+def group_plan(shapes, cleared, alone):
+    n = len(shapes)
+    ints = lambda i: (ctypes.c_int * n)(*[s[i] for s in shapes])
+    tile, kchunk = ctypes.c_int(), ctypes.c_int()
+    assert P.lib().ouro_op_gemm_group_plan(n, ints(0), ints(1), ints(2), cleared, alone, ctypes.byref(tile), ctypes.byref(kchunk)) == 0
+    return tile.value, kchunk.value
+
+
+def group_plan_over_every_range(shapes, cleared, alone):
+    """The cost model of grouped weight gradients over every range length, with list scheduling slot by slot of time."""
+    kmax = max((k + 63) // 64 * 64 for _, _, k in shapes)
+    best = {}
+    for kc in range(min(256, kmax), kmax + 1, 64):
+        for bt, slots in ((128, 512), (256, 256)):
+            part, adds = [], 0
+            for m, w, k in shapes:
+                s = -(-k // kc)
+                n = -(-m // bt) * -(-w // bt) * s
+                part.append((-(-(-(-k // s)) // 64), n))
+                if s > 1 or not cleared:
+                    adds += n * bt * bt
+            wgs = sum(n for _, n in part)
+            if alone:
+                rate, fixed = (1.45, 6) if bt == 256 else (0.65 if wgs <= 256 else 0.82, 4)
+                free, end = [(0.0, slots)], 0.0
+                for r, left in sorted(part, key=lambda x: -x[0]):
+                    while left:
+                        free.sort()
+                        at, have = free.pop(0)
+                        take = min(left, have)
+                        left -= take
+                        if have > take:
+                            free.append((at, have - take))
+                        free.append((at + rate * r + fixed, take))
+                        end = max(end, at + rate * r + fixed)
+                cost = end + adds / (310e3 if bt == 256 else 400e3)
+            else:
+                one = 1.45 * (kc // 64) + 6 + adds / 310e3 if bt == 256 else 1.2 * (kc // 64 + 6)
+                cost = 0.5 * one * (-(-wgs // slots) + wgs / slots)
+            if cost < best.get(bt, (1e30,))[0] - 1e-9:
+                best[bt] = (cost, kc)
+    bt = 256 if best[256][0] < best[128][0] else 128
+    return bt, best[bt][1]
+
+
+LAYERS = [
+    [(1024, 1024, 6144), (1024, 4096, 6144), (4096, 1024, 6144), (1024, 1024, 6144), (1024, 2048, 12288), (1024, 1024, 768)],
+    [(448, 640, 4800), (640, 448, 4800), (448, 2112, 4800), (2112, 448, 4800), (448, 1280, 9600), (448, 640, 300)],
+    [(64, 192, 8192), (64, 64, 8192), (64, 256, 8192), (256, 64, 8192)],
+    [(512, 1536, 8192), (512, 512, 8192), (512, 2048, 8192), (2048, 512, 8192)],
+    [(128, 384, 288), (128, 128, 288), (128, 256, 288), (256, 128, 288)],
+    [(72, 40, 33)],
+]
+
+
+@pytest.mark.parametrize("alone", [0, 1])
+@pytest.mark.parametrize("cleared", [0, 1])
+def test_ranges_of_grouped_weight_gradients(cleared, alone):
+    """The launcher looks at few range lengths; its choice is that of the whole search."""
+    rng = random.Random(5)
+    drawn = [[(rng.randrange(8, 2500, 8), rng.randrange(8, 2500, 8), rng.randrange(32, 9000)) for _ in range(rng.randrange(1, 7))] for _ in range(25)]
+    for shapes in LAYERS + drawn:
+        assert group_plan(shapes, cleared, alone) == group_plan_over_every_range(shapes, cleared, alone), shapes
+
+
+def test_plan_of_grouped_weight_gradients_is_cheap():
+    """Made on the host for every layer of every step: the best of many calls, as other work may run on this machine (86 and 61 us for
+    the first two layers when every range was looked at)."""
+    for shapes in LAYERS:
+        n = len(shapes)
+        args = [(ctypes.c_int * n)(*[s[i] for s in shapes]) for i in range(3)]
+        tile, kchunk, f = ctypes.c_int(), ctypes.c_int(), P.lib().ouro_op_gemm_group_plan
+        best = 1.0
+        for _ in range(200):
+            t = time.perf_counter()
+            f(n, *args, 1, 1, ctypes.byref(tile), ctypes.byref(kchunk))
+            best = min(best, time.perf_counter() - t)
+        assert best < 30e-6, (shapes, best)
 
 
 def test_lr_schedule_matches_the_oracle():
