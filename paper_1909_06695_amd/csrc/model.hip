@@ -283,6 +283,8 @@ struct ouro_model : BwdCtx {
   float* slot_ptr(int id, int64_t slot) const { return ring[id] + (size_t)slot * gstride[id]; }
 };
 
+constexpr int GROUPS_MAX = 63;      // parameter groups: V and the modules (a bit each in upd_mask)
+
 static int default_split(int L, int K, std::vector<int>& out) {
   int base = L / K, rem = L % K;
   out.assign(K, base);
@@ -302,7 +304,7 @@ static int validate(const ouro_config* c, std::vector<int>& lpm) {
   if ((int64_t)c->n_head * c->d_head != c->d_model) return fail(OURO_E_CONFIG, "n_head*d_head != d_model");
   if (c->d_model % 2) return fail(OURO_E_CONFIG, "d_model must be even");
   if (c->d_head > 256) return fail(OURO_E_CONFIG, "d_head > 256 unsupported");
-  if (c->n_module < 1 || c->n_module > c->n_layer || c->n_module > 62)
+  if (c->n_module < 1 || c->n_module > c->n_layer || c->n_module > GROUPS_MAX - 1)
     return fail(OURO_E_CONFIG, "n_module must be in [1, min(n_layer, 62)]");
   if (c->mem_len > 0 && !c->rel_pos) return fail(OURO_E_CONFIG, "mem_len > 0 needs rel_pos = 1");
   if (c->rel_pos != 0 && c->rel_pos != 1) return fail(OURO_E_CONFIG, "rel_pos must be 0 or 1");
@@ -625,6 +627,7 @@ extern "C" int ouro_create_model(const ouro_config* cfg, void* dev_arena, size_t
   m->bytes = need;
   m->stream = (hipStream_t)hip_stream;
   const int K = cfg->n_module;
+  m->sums.reserve(K);
   m->tags.resize(K + 2);
   for (int id = 0; id <= K + 1; ++id) m->tags[id].assign((size_t)m->depth[id], -1);
   m->last_slot.assign(K + 2, -1); m->last_tau.assign(K + 2, -1);
@@ -1453,8 +1456,8 @@ static int prepare_update(ouro_model* m, int group, float lr, UpdateDesc& u) {
 // copies; 3 x 128-wide 33 -> 9 us).
 static int update_groups(ouro_model* m, const int* groups, int n, float lr, hipStream_t st) {
   const int K = m->cfg.n_module;
-  std::vector<UpdateDesc> u(n);
-  std::vector<UpdateTable> tab(n);
+  UpdateDesc u[GROUPS_MAX];
+  UpdateTable tab[GROUPS_MAX];
   double bytes = 0;
   bool timed = m->timing != 0;
   for (int i = 0; i < n; ++i) {
@@ -1468,7 +1471,7 @@ static int update_groups(ouro_model* m, const int* groups, int n, float lr, hipS
   if (timed) RUN(timing_begin(m, OURO_TIMING_UPDATE, st));
   if (m->use_side)
     for (int i = 0; i < n; ++i) HIPCHK(launch_update(st, u[i]));
-  else HIPCHK(launch_update_groups(st, u.data(), tab.data(), n));
+  else HIPCHK(launch_update_groups(st, u, tab, n));
   if (timed) RUN(timing_end(m, OURO_TIMING_UPDATE, bytes, st));
   if (m->use_side)
     for (int i = 0; i < n; ++i) RUN(refresh_transposed(m, groups[i], st));
@@ -1581,13 +1584,13 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
   for (int k = 0; k <= K; ++k) slots += (size_t)m->gstride[k] * 4;
   m->batched = !m->use_side && m->cfg.schedule == 0;
   if (m->batched && slots <= (size_t)256 << 20) {
-    std::vector<FillRange> r;
+    FillRange r[GROUPS_MAX];
     int64_t slot, tau;
     for (int k = 0; k <= K; ++k) {
       ouro_slot_index(K, k, m->t, 1, &slot, &tau);
-      r.push_back({m->slot_ptr(k, slot), (size_t)m->gstride[k] * 4});
+      r[k] = {m->slot_ptr(k, slot), (size_t)m->gstride[k] * 4};
     }
-    HIPCHK(launch_fill_zero_ranges(m->stream, r.data(), (int)r.size()));
+    HIPCHK(launch_fill_zero_ranges(m->stream, r, K + 1));
     m->cleared = true;
   }
   for (int k = K; k >= 1; --k) {
@@ -1604,10 +1607,10 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
     }
   }
   if (m->batched) HIPCHK(batch.finish());
-  std::vector<int> rest;                // the last update closes the iteration and clears the mask
+  int rest[GROUPS_MAX], nrest = 0;      // the last update closes the iteration and clears the mask
   for (int k = 0; k <= K; ++k)
-    if (!(m->upd_mask & (1ull << k))) rest.push_back(k);
-  RUN(update_groups(m, rest.data(), (int)rest.size(), lr, m->stream));
+    if (!(m->upd_mask & (1ull << k))) rest[nrest++] = k;
+  RUN(update_groups(m, rest, nrest, lr, m->stream));
   if (host_loss) return read_loss(m, host_loss);
   return OURO_OK;
 }

@@ -103,6 +103,19 @@ def failed_step(fake):
     assert m.update(3) == E_STALE
 
 
+def steps_without_host_allocations(fake):
+    """Nothing throws across the C boundary: a step, which every caller makes again and again, takes no host memory."""
+    for kw in (dict(), dict(n_module=1), dict(dtype=1, d_model=128, d_head=64, d_ff=128, optimizer=1),
+               dict(dtype=1, d_model=128, d_head=64, d_ff=128, seq_len=16, mem_len=24, rel_pos=1), dict(schedule=1, dropout=0.1)):
+        m = Model(fake, **kw)
+        for on in (0, 1):
+            assert m.L.ouro_debug_set_overlap(m.h, on) == 0
+            m.F.fake_news(1)
+            for _ in range(5):
+                assert m.step() == 0
+            assert m.F.fake_news(0) == 0, (kw, on)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](sys.argv[1])
     print("passed")

@@ -271,3 +271,7 @@ def fake_hip(tmp_path_factory):
 
 def test_failed_step_leaves_no_partial_gradient(fake_hip):
     fake_hip("failed_step")
+
+
+def test_steps_take_no_host_memory(fake_hip):
+    fake_hip("steps_without_host_allocations")
