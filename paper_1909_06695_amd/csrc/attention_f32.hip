@@ -399,16 +399,17 @@ template <int DH, bool VEC>
 __global__ __launch_bounds__(256) void af_bwd_kernel(AfParams p) {
   __shared__ __attribute__((aligned(16))) float so[4][DH / 2][64];
   __shared__ __attribute__((aligned(16))) float stat[4][64];
-  const int groups = p.H * p.B, nq = (p.T + 31) / 32, nk = (p.S + 31) / 32, nmin = min(nq, nk);
-  const int i = blockIdx.x;
-  int rank = i / (2 * groups), r = i - rank * 2 * groups;
+  const unsigned groups = p.H * p.B, nq = (p.T + 31) / 32, nk = (p.S + 31) / 32, nmin = min(nq, nk);
+  // grid (nq + nk, H, B): along one axis the work items of many short streams would pass the 2^32 threads that it may have
+  const unsigned i = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  unsigned rank = i / (2 * groups), r = i - rank * 2 * groups;
   bool keys = r < groups;
   if (rank >= nmin) {                                      // the longer axis' surplus
     r = i - nmin * 2 * groups;
     rank = nmin + r / groups;
     keys = nk > nq;
   }
-  const int g = r % groups, head = g % p.H, b = g / p.H;
+  const unsigned g = r % groups, head = g % p.H, b = g / p.H;
   if (keys) af_bwd_dkv_body<DH, VEC>(p, so, stat, rank, head, b);
   else af_bwd_dq_body<DH, VEC>(p, so, rank, head, b);
 }
@@ -450,7 +451,7 @@ hipError_t launch_attn_fwd_f32(hipStream_t s, const AttnDesc& a) {
 hipError_t launch_attn_bwd_f32(hipStream_t s, const AttnDesc& a) {
   AfParams p = af_params(a);
   const bool vec = af_aligned(a, true);
-  OURO_AF(af_bwd_kernel, dim3((unsigned)((long)((a.T + 31) / 32 + (a.S + 31) / 32) * a.H * a.B)), vec);
+  OURO_AF(af_bwd_kernel, dim3((a.T + 31) / 32 + (a.S + 31) / 32, a.H, a.B), vec);
   return hipGetLastError();
 }
 #undef OURO_AF

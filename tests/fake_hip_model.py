@@ -116,6 +116,18 @@ def steps_without_host_allocations(fake):
             assert m.F.fake_news(0) == 0, (kw, on)
 
 
+def attention_of_many_short_streams(fake):
+    """fp32 attention over 65535 streams of one query and 129 heads: no axis of a grid has 2^32 threads (launches fail there)."""
+    m = Model(fake)
+    B, H, x = 65535, 129, C.c_void_p(256)
+    ldv = 2 * H
+    fwd = (None, 0, B, H, 1, 1, 2, 0, C.c_float(1.0), x, ldv, x, ldv, x, ldv, x, ldv, x)
+    rc, log = m.log(lambda: m.L.ouro_op_attention_fwd(*fwd, 0, None, None, None, 0, 0))
+    assert rc == 0 and len(log) == 1
+    rc, log = m.log(lambda: m.L.ouro_op_attention_bwd(*fwd, x, ldv, x, ldv, x, ldv, x, ldv, 0, None, None, None, 0, None, None, None, x, 0))
+    assert rc == 0 and len(log) == 1 and "af_bwd" in log[0][0], (rc, log)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](sys.argv[1])
     print("passed")

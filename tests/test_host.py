@@ -275,3 +275,7 @@ def test_failed_step_leaves_no_partial_gradient(fake_hip):
 
 def test_steps_take_no_host_memory(fake_hip):
     fake_hip("steps_without_host_allocations")
+
+
+def test_attention_of_many_short_streams_can_be_launched(fake_hip):
+    fake_hip("attention_of_many_short_streams")
