@@ -69,6 +69,10 @@ size_t ouro_op_gemm_operand_bytes(int dtype, int rows, int cols, int ld);
 /* What ouro_op_gemm chooses (force_generic 0) for dense, aligned operands: *tile as force_generic names it, *splits the
  * number of contraction ranges (bf16; host only). */
 int ouro_op_gemm_plan(int dtype, int transA, int transB, int M, int N, int K, int accumulate, int* tile, int* splits);
+/* The same for a result in fp32 (ouro_op_gemm_plan) or type T, an epilogue as ouro_op_gemm names it and a launch of several equal
+ * products. */
+int ouro_op_gemm_plan_as(int dtype, int transA, int transB, int M, int N, int K, int accumulate, int out_fp32, int epilogue, int products,
+                         int* tile, int* splits);
 /* 1 if ouro_op_gemm would run the MFMA kernel for these arguments (host only). */
 int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A,
                            int lda, const void* B, int ldb);

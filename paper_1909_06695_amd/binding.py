@@ -93,6 +93,7 @@ def lib():
         "ouro_op_gemm_group_plan": (i32, [i32, P(i32), P(i32), P(i32), i32, i32, P(i32), P(i32)]),
         "ouro_op_gemm_operand_bytes": (sz, [i32, i32, i32, i32]),
         "ouro_op_gemm_plan": (i32, [i32, i32, i32, i32, i32, i32, i32, P(i32), P(i32)]),
+        "ouro_op_gemm_plan_as": (i32, [i32, i32, i32, i32, i32, i32, i32, i32, i32, i32, P(i32), P(i32)]),
         "ouro_op_gemm_uses_mfma": (i32, [i32, i32, i32, i32, i32, i32, vp, i32, vp, i32]),
         "ouro_op_attention_fwd": (i32, [vp, i32, i32, i32, i32, i32, i32, i32, f32, vp, i32, vp, i32, vp, i32, vp,
                                         i32, vp, i32, vp, vp, vp, i32, i32]),

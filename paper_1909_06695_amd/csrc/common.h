@@ -148,7 +148,7 @@ void gemm_group_plan(const GemmDesc* g, int n, bool alone, bool* big, int (&kchu
 // true if launch_gemm would take the MFMA path for this problem
 // What launch_gemm chooses for one product (host only): 1 the plain kernel, 20 the fp32 matrix-core
 // kernel, GEMM_TILE_*, and (bf16) the contraction ranges.
-int gemm_plan(int dtype, const GemmDesc& g, int* splits);
+int gemm_plan(int dtype, const GemmDesc& g, int* splits, long products = 1);
 bool gemm_uses_mfma(int dtype, const GemmDesc& g);
 
 // ---------------------------------------------------------------------------- attention

@@ -214,7 +214,10 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // four-stage ring; otherwise, and for the split-K weight gradients, 128x64 tiles, which
     // put more workgroups on every compute unit
     const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const int t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+    // the tiles of all products, unless much of them is past the edges: results of 128 columns (98304 rows over 1024 39 us on 128-wide
+    // tiles, 49 on 256x256; 131072 over 512 with GELU 39 and 52); 192 columns, a quarter past the edge, are alike on both
+    const int t256_one = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+    const long t256 = t256_one * 65536.0 <= 1.4 * g.M * g.N ? t256_one * products : 0;
     // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are four per CU (the logits: 8192 x
     // 32768 over 512 312 us, 4800 x 32768 over 448 190), one per CU with a long contraction (dV_o: 670 -> 592 us), or where their
     // rounds are well filled.  Alone on the chip, 128x128 and 256x256 tiles, us (plain / GELU / GELU-gradient / fp32 result with the
@@ -223,9 +226,16 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     //                  192 over 768 27 / 33 / 32 / 40 and 24 / 32 / 33 / 39; 192 over 512 20 / 28 / 27 / 37 and 19 / 27 / 28 / 36;
     //                  190 over 448 20 / 27 / 26 / 34 and 18 / 26 / 27 / 34; 144 over 768 26 / 32 / 31 / 35 and 22 / 30 / 32 / 35
     //   1.1 to 1.3     288 over 1024 46 / 58 / 56 / 78 and 49 / 65 / 70 / 79; 320 over 1024 49 / 61 / 66 / 85 and 51 / 68 / 74 / 81
-    //   1.5            384 over 1024 55 / 71 / 71 / 92 and 53 / 72 / 77 / 91; over 768 45 / 60 / 58 / 85 and 45 / 67 / 70 / 82
+    //   1.5            384 over 1024 55 / 71 / 71 / 92 and 53 / 72 / 77 / 91; over 768 45 / 60 / 58 / 85 and 45 / 67 / 70 / 82;
+    //                  plain: 384 over 448 31 and 32, over 512 34 and 35 (three whole rounds of 128x128 tiles); 392 over 448 34 and 31;
+    //                  640 over 512 54 and 59 where the result is wider than high, else 56 and 54
     //   two            512 over 1024 80 / 109 / - / 126 and 60 / 79 / - / 122; over 512 44 / 76 / 71 / 102 and 42 / 61 / 72 / 102
     // and 416 over 1024 69 (GELU-gradient 82) and 63 (91), 464 over 768 75 and 57, 528 over 1024 89 (GELU-gradient) and 95.
+    // The lower end, plain (the faster of the 128-wide forms and 256x256): 128 tiles over 512 / 768 / 1024 12.7 / 16.7 / 20.3 and 16.5 /
+    // 20.5 / 23.8, 136 16.4 / 22.7 / 28.1 and 16.4 / 20.2 / 23.8, 144 17.2 / 22.8 / 27.7 and 16.9 / 20.8 / 24.6; 144 to 160 over 384 15.0 both,
+    // over 448 16.0 both, 192 17.8 and 17.1.  What counts there is whether 128x128 tiles run in one round of 512: 9288 x 832 over 640 (148
+    // tiles, 511 of 128x128) 16.9 and 19.5, 12288 x 576 over 960 19 and 24, 14872 x 576 over 704 (177 and 585) 21.8 and 21.1.
+    // Two products of 144 tiles over 512 28.0 and 32.1 (288 in all, 1.1 rounds), four of 64 24.4 and 22.5.
     // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
     // over 1024 11.7 -> 7.3 us, over 4096 30.5 -> 17.1; 2331 x 768 over 768 11.0 -> 9.1, over 3072 25.1 -> 21.7; 288 x 128
@@ -235,9 +245,10 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
     const bool plain = !g.out_fp32 && g.epilogue == EPI_NONE && !g.residual && !g.res32;
-    const int last = (t256 - 1) % 256 + 1;               // tiles of the last round
+    const int last = t256 ? (t256 - 1) % 256 + 1 : 0;    // tiles of the last round
     const bool big = t256 >= 1024 || (t256 >= 256 && g.K >= 4096) || (t256 >= 448 && last >= 192 && g.K >= (plain || g.epilogue == EPI_GELU ? 512 : 768)) ||
-                     (t256 >= 224 && t256 <= 256 && g.K >= 512) || (plain && g.K >= 448 && ((t256 >= 144 && t256 <= 256) || (t256 >= 384 && last >= 128)));
+                     (t128 * products > 512 && t256 >= (plain ? 144 : 224) && t256 <= 256 && g.K >= (plain ? 448 : 512)) ||
+                     (plain && t256 >= 384 && (g.K >= 768 ? last >= 128 : last > 128 && t128 * products > 1536 && g.K >= 448));
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
     if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
@@ -309,12 +320,12 @@ static bool f32_on_matrix_cores(const GemmDesc& g) {
   const long t32 = (long)((g.M + 31) / 32) * ((g.N + 31) / 32);
   return g.K > 16 || t32 <= 512;
 }
-int gemm_plan(int dtype, const GemmDesc& g, int* splits) {
+int gemm_plan(int dtype, const GemmDesc& g, int* splits, long products) {
   GemmPlan plan;
   *splits = 1;
   if (dtype == 0) return f32_on_matrix_cores(g) ? 20 : 1;
   if (!gemm_uses_mfma(dtype, g)) return 1;
-  if (!plan_mfma(g, 0, 1, plan)) return -1;
+  if (!plan_mfma(g, 0, products, plan)) return -1;
   *splits = plan.splits;
   return plan.cfg;
 }

@@ -123,6 +123,15 @@ extern "C" int ouro_op_gemm_plan(int dtype, int transA, int transB, int M, int N
   return OURO_OK;
 }
 
+extern "C" int ouro_op_gemm_plan_as(int dtype, int transA, int transB, int M, int N, int K, int accumulate, int out_fp32, int epilogue, int products,
+                                    int* tile, int* splits) {
+  if (!tile || !splits || M < 1 || N < 1 || K < 0 || products < 1) return OURO_E_ARG;
+  GemmDesc g = make_gemm(transA, transB, M, N, K, 1.f, nullptr, transA ? M : K, nullptr, transB ? K : N, nullptr, N, out_fp32, accumulate, nullptr, nullptr, 0,
+                         epilogue, nullptr, N);
+  *tile = gemm_plan(dtype, g, splits, products);
+  return OURO_OK;
+}
+
 extern "C" int ouro_op_gemm_uses_mfma(int dtype, int transA, int transB, int M, int N, int K, const void* A, int lda,
                                       const void* B, int ldb) {
   GemmDesc g = make_gemm(transA, transB, M, N, K, 1.f, A, lda, B, ldb, nullptr, N, 0, 0, nullptr, nullptr, 0, 0, nullptr, 0);
