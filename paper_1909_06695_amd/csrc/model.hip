@@ -208,6 +208,7 @@ struct ouro_model : BwdCtx {
   std::vector<std::vector<TransposeEntry>> utab;
   std::vector<TransposeEntry*> utab_dev;
   std::vector<int> utiles;
+  std::vector<char> uplain;      // groups that are better updated by the plain kernel also on one stream
   // gradient stores 0..K+1
   std::vector<int64_t> gcount, gstride, depth;   // elements per gradient (caller's), slot stride (stored, 256-byte multiple)
   std::vector<float*> ring;
@@ -283,6 +284,12 @@ struct ouro_model : BwdCtx {
   float* slot_ptr(int id, int64_t slot) const { return ring[id] + (size_t)slot * gstride[id]; }
 };
 
+// Elements of a group in matrices whose rows do not start on 16 bytes (bf16 models that are not stored padded: heads above 64, widths off
+// every multiple of 4).  The tile-wise update takes such matrices element by element; the plain kernel, which sees the group as
+// one array, and the transposing one are faster from here on.  Steps with Adam, plain and tile-wise: 130-wide, V of 2000 words (0.26 million)
+// 427 and 428 us, 4000 434 and 463, 32000 514 and 558; 70-wide, 8000 (0.56 million) 361 and 359, 16000 353 and 373; 350-wide, 100 (a layer
+// of 0.74 million) 793 and 821, 32000 959 and 1191.
+constexpr size_t UPD_UNALIGNED_MAX = (size_t)1 << 18;
 constexpr int GROUPS_MAX = 63;      // parameter groups: V and the modules (a bit each in upd_mask)
 
 static int default_split(int L, int K, std::vector<int>& out) {
@@ -542,7 +549,7 @@ static size_t lay_out(ouro_model& m, char* base) {
     }
     m.remaps_dev[k] = (RemapEntry*)P(m.remaps[k].size() * sizeof(RemapEntry));
   }
-  m.utab.assign(K + 1, {}); m.utab_dev.assign(K + 1, nullptr); m.utiles.assign(K + 1, 0);
+  m.utab.assign(K + 1, {}); m.utab_dev.assign(K + 1, nullptr); m.utiles.assign(K + 1, 0); m.uplain.assign(K + 1, 0);
   for (int k = 0; k <= K; ++k) {
     size_t at = 0;
     auto add = [&](size_t off, int rows, int cols, int ld_out) {
@@ -558,6 +565,10 @@ static size_t lay_out(ouro_model& m, char* base) {
       at = (size_t)t.off + (size_t)t.rows * t.cols;
     }
     linear((size_t)m.pcount[k]);
+    size_t unaligned = 0;                                   // elements of matrices that the tile-wise kernel takes one by one
+    for (const TransposeEntry& t : m.ttab[k])
+      if ((t.off | (unsigned)t.cols) & 3) unaligned += (size_t)t.rows * t.cols;
+    m.uplain[k] = unaligned > UPD_UNALIGNED_MAX;
     m.utab_dev[k] = (TransposeEntry*)P(m.utab[k].size() * sizeof(TransposeEntry));
   }
   return bp.off;
@@ -1456,25 +1467,27 @@ static int prepare_update(ouro_model* m, int group, float lr, UpdateDesc& u) {
 // copies; 3 x 128-wide 33 -> 9 us).
 static int update_groups(ouro_model* m, const int* groups, int n, float lr, hipStream_t st) {
   const int K = m->cfg.n_module;
-  UpdateDesc u[GROUPS_MAX];
+  UpdateDesc tiled[GROUPS_MAX], plain[GROUPS_MAX];
   UpdateTable tab[GROUPS_MAX];
+  int plain_group[GROUPS_MAX], nt = 0, np = 0;
   double bytes = 0;
   bool timed = m->timing != 0;
   for (int i = 0; i < n; ++i) {
     const int g = groups[i];
-    RUN(prepare_update(m, g, lr, u[i]));
-    tab[i] = {m->utab_dev[g], (int)m->utab[g].size(), m->utiles[g], m->cfg.dtype == 1 ? m->shadowT[g] : nullptr};
-    timed = timed && u[i].g0;
+    UpdateDesc u;
+    RUN(prepare_update(m, g, lr, u));
+    timed = timed && u.g0;
     // algorithmic bytes per element: gradient(s) 4 each, w read+write 8, Adam m,v read+write 16, bf16 copy 2
-    bytes += (4.0 * ((u[i].g0 ? 1 : 0) + (u[i].g1 ? 1 : 0)) + 8.0 + (u[i].adam ? 16.0 : 0.0) + (u[i].shadow ? 2.0 : 0.0)) * (double)u[i].n;
+    bytes += (4.0 * ((u.g0 ? 1 : 0) + (u.g1 ? 1 : 0)) + 8.0 + (u.adam ? 16.0 : 0.0) + (u.shadow ? 2.0 : 0.0)) * (double)u.n;
+    if (m->use_side || m->uplain[g]) { plain[np] = u; plain_group[np++] = g; continue; }
+    tiled[nt] = u;
+    tab[nt++] = {m->utab_dev[g], (int)m->utab[g].size(), m->utiles[g], m->cfg.dtype == 1 ? m->shadowT[g] : nullptr};
   }
   if (timed) RUN(timing_begin(m, OURO_TIMING_UPDATE, st));
-  if (m->use_side)
-    for (int i = 0; i < n; ++i) HIPCHK(launch_update(st, u[i]));
-  else HIPCHK(launch_update_groups(st, u, tab, n));
+  for (int i = 0; i < np; ++i) HIPCHK(launch_update(st, plain[i]));
+  HIPCHK(launch_update_groups(st, tiled, tab, nt));
   if (timed) RUN(timing_end(m, OURO_TIMING_UPDATE, bytes, st));
-  if (m->use_side)
-    for (int i = 0; i < n; ++i) RUN(refresh_transposed(m, groups[i], st));
+  for (int i = 0; i < np; ++i) RUN(refresh_transposed(m, plain_group[i], st));
   for (int i = 0; i < n; ++i) m->upd_mask |= 1ull << groups[i];
   if (m->upd_mask == (1ull << (K + 1)) - 1) {
     if (m->upd_pending) {       // the next iteration reads every weight: main waits for aux

@@ -128,6 +128,19 @@ def attention_of_many_short_streams(fake):
     assert rc == 0 and len(log) == 1 and "af_bwd" in log[0][0], (rc, log)
 
 
+def updates_of_unaligned_matrices(fake):
+    """Matrices with rows off 16 bytes go to the plain update and the transposing kernel where they are large, the rest to the tile-wise
+    one; all of it to that where the rows are aligned."""
+    for d_head, vocab, want in ((65, 2000, {"groups": 1}), (65, 3000, {"groups": 1, "plain": 1, "transpose": 1}), (66, 3000, {"groups": 1}),
+                                (127, 100, {"groups": 1, "plain": 3, "transpose": 3})):
+        m = Model(fake, dtype=1, d_head=d_head, d_model=2 * d_head, d_ff=2 * d_head, vocab=vocab, optimizer=1)
+        assert m.step() == 0
+        rc, log = m.log(m.step)
+        count = lambda what: sum(what in name for name, _ in log)
+        got = {"groups": count("update_groups_kernel"), "plain": count("13update_kernel"), "transpose": count("transpose_table")}
+        assert rc == 0 and {k: v for k, v in got.items() if v} == want, (d_head, vocab, got)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](sys.argv[1])
     print("passed")

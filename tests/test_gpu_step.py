@@ -664,6 +664,7 @@ def test_checkpoint_resume(schedule, dtype, opt):
 
 @pytest.mark.parametrize("cfg", [
     dict(dtype=1, n_head=2, d_head=72, d_model=144, d_ff=150, vocab=77),           # not padded: rows of 150, pieces off every alignment
+    dict(dtype=1, n_head=2, d_head=65, d_model=130, d_ff=130, vocab=3001),         # V too large to go tile by tile with such rows, the modules not
     dict(dtype=1, n_head=2, d_head=64, d_model=128, d_ff=192, vocab=1001),         # tiles over the edge of V, whole tiles elsewhere
     dict(dtype=1, n_head=2, d_head=41, d_model=82, d_ff=130, vocab=65, rel_pos=1, mem_len=8),
     dict(dtype=0, n_head=2, d_head=17, d_model=34, d_ff=50, vocab=99),

@@ -293,3 +293,7 @@ def test_steps_take_no_host_memory(fake_hip):
 
 def test_attention_of_many_short_streams_can_be_launched(fake_hip):
     fake_hip("attention_of_many_short_streams")
+
+
+def test_updates_of_unaligned_matrices(fake_hip):
+    fake_hip("updates_of_unaligned_matrices")
