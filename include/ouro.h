@@ -227,7 +227,8 @@ int ouro_debug_get_hidden(ouro_model* m, int layer, float* host_dst, int64_t n);
 /* Optional per-launch HIP event timing on the model's stream (slows the step while on).
  * OURO_TIMING_CONTRACTION: the MFMA contraction kernel, work = 2*M*N*K flops per launch;
  * OURO_TIMING_UPDATE: the delayed-update kernel (zero-gradient warm-up launches excluded), work =
- *         algorithmic bytes (gradient reads 4 B each, w 8 B, Adam moments 16 B, bf16 copy 2 B);
+ *         algorithmic bytes (gradient reads 4 B each, w 8 B, Adam moments 16 B, bf16 copy 2 B, and 2 B for the transposed
+ *         bf16 copy of a matrix where the update launch writes it: steps on one stream);
  * OURO_TIMING_ATTENTION: attention forward and backward launches, work = algorithmic flops
  *         (visible query-key pairs x 4 d_head forward, 6 d_head with the relative-position term;
  *         a backward launch counts twice its forward);

@@ -1480,6 +1480,8 @@ static int update_groups(ouro_model* m, const int* groups, int n, float lr, hipS
     // algorithmic bytes per element: gradient(s) 4 each, w read+write 8, Adam m,v read+write 16, bf16 copy 2
     bytes += (4.0 * ((u.g0 ? 1 : 0) + (u.g1 ? 1 : 0)) + 8.0 + (u.adam ? 16.0 : 0.0) + (u.shadow ? 2.0 : 0.0)) * (double)u.n;
     if (m->use_side || m->uplain[g]) { plain[np] = u; plain_group[np++] = g; continue; }
+    if (m->cfg.dtype == 1)                                 // this launch writes the transposed copies too
+      for (const TransposeEntry& t : m->ttab[g]) bytes += 2.0 * t.rows * t.cols;
     tiled[nt] = u;
     tab[nt++] = {m->utab_dev[g], (int)m->utab[g].size(), m->utiles[g], m->cfg.dtype == 1 ? m->shadowT[g] : nullptr};
   }

@@ -141,6 +141,25 @@ def updates_of_unaligned_matrices(fake):
         assert rc == 0 and {k: v for k, v in got.items() if v} == want, (d_head, vocab, got)
 
 
+def update_bytes(fake):
+    """The bytes that the update's timing counts: both bf16 copies where its launch writes both."""
+    for dtype, aligned in ((0, True), (1, True), (1, False)):
+        d, F, V = (128, 128, 3000) if aligned else (130, 130, 3001)
+        m = Model(fake, dtype=dtype, d_head=d // 2, d_model=d, d_ff=F, vocab=V, optimizer=1)
+        for _ in range(4):
+            assert m.step() == 0
+        m.L.ouro_debug_timing_enable(m.h, 1)
+        assert m.step() == 0
+        ms, n, work = C.c_double(), C.c_int64(), C.c_double()
+        assert m.L.ouro_debug_timing_read(m.h, 1, C.byref(ms), C.byref(n), C.byref(work)) == 0
+        mats = 4 * d * d + 2 * d * F
+        layer = mats + 5 * d + F
+        per = 4 + 8 + 16 + 2 * dtype
+        want = per * 3 * layer + (per + 4) * V * d             # V takes two gradients
+        want += dtype * 2 * (3 * mats + (V * d if aligned else 0))
+        assert n.value == 1 and work.value == want, (dtype, aligned, work.value, want)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](sys.argv[1])
     print("passed")

@@ -297,3 +297,7 @@ def test_attention_of_many_short_streams_can_be_launched(fake_hip):
 
 def test_updates_of_unaligned_matrices(fake_hip):
     fake_hip("updates_of_unaligned_matrices")
+
+
+def test_bytes_of_a_timed_update(fake_hip):
+    fake_hip("update_bytes")
