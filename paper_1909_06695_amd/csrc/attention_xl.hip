@@ -409,11 +409,8 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
       }
     }
   }
-  bool stores = false;                                      // the wave's last block left exactly 32 stores behind its loads
   for (int jb = 0; jb < nkb; ++jb) {
-    if (stores) fa_wait_vmcnt<32>();                        // the loads have landed; the stores may be under way
-    else fa_wait_vmcnt<0>();
-    stores = false;
+    fa_wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     if (jb + 1 < nkb) issue(jb + 1);
     const char* sK = lds + (jb % XL_NSTAGE) * XL_STAGE;
@@ -469,12 +466,11 @@ __global__ __launch_bounds__(512) void fa_xl_dq_kernel(FaParams p) {
         *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ptb) + at) = (uint16_t)(pw[r >> 3].w[(r & 7) >> 1] >> (16 * (r & 1)));
         *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(dstb) + at) = (uint16_t)(dw[r >> 3].w[(r & 7) >> 1] >> (16 * (r & 1)));
       };
-      if (key0 + 31 < p.S) {                                // some lane's query is in range: 32 stores
+      if (key0 + 31 < p.S) {
         if (qi < p.T) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) put(r);
         }
-        stores = true;
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r)

@@ -257,6 +257,16 @@ def test_plan_of_grouped_weight_gradients_is_cheap():
         assert best < 30e-6, (shapes, best)
 
 
+def test_waits_count_loads_by_name():
+    """A wait that leaves younger memory operations under way counts them: by a constant of the kernel that issues them, not by a number
+    that a merged or added operation would make wrong without a message."""
+    csrc = os.path.join(ROOT, "paper_1909_06695_amd", "csrc")
+    waits = [w for name in sorted(os.listdir(csrc)) if name.startswith("attention")
+             for w in re.findall(r"fa_wait_vmcnt<([^;]*)>\(\);", open(os.path.join(csrc, name)).read())]
+    assert len(waits) >= 6
+    assert all(w == "0" or "LPT" in w for w in waits), waits
+
+
 def test_lr_schedule_matches_the_oracle():
     """The library's host-side step-size function against the oracle's, over both phases and
     the boundaries (both fp64: agreement to rounding); bad arguments are refused."""
