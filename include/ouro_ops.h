@@ -135,6 +135,13 @@ int ouro_op_gemm_dropout(void* stream, int dtype, int transA, int transB, int M,
                          const void* residual, int ldr, float p, uint64_t seed, uint32_t stream_id, int drop_ld,
                          int force_generic);
 
+/* The form in which the layers of a bf16 model use it: bf16 operands, fp32 C = dropout(op(A) op(B) + bias) + R with R from either
+ * residual (bf16) or res32 (as in ouro_op_gemm_ln_residual). */
+int ouro_op_gemm_dropout_residual(void* stream, int transA, int transB, int M, int N, int K, const void* A, int lda,
+                                  const void* B, int ldb, float* C, int ldc, const float* bias, const void* residual, int ldr,
+                                  const float* res32, int ldr32, const float* mean, const float* rstd, const float* g, const float* b,
+                                  float p, uint64_t seed, uint32_t stream_id, int drop_ld, int force_generic);
+
 /* C = op(A) op(B) + bias + R, the form of the two contractions of a block that close a residual
  * connection, with the residual taken from fp32: R[m,n] = res32[m,n] when mean is NULL, else the
  * LayerNorm of res32 recomputed in place, (res32[m,n] - mean[m]) * rstd[m] * g[n] + b[n] (a block's
@@ -177,6 +184,16 @@ int ouro_op_softmax_ce(void* stream, int dtype, const void* logits, int ld, cons
 int ouro_op_update(void* stream, float* w, float* m, float* v, void* shadow, const float* g0,
                    float s0, const float* g1, float s1, size_t n, int adam, float lr, float beta1,
                    float beta2, float eps, int64_t t);
+/* The same for n <= 64 groups of parameters, tile by tile, with a second, transposed bf16 copy of the matrices (what a step on
+ * one stream runs; arrays of n, entries of shadow, shadowT, g0, g1 and without Adam m, v may be NULL).  table[i] (device memory) lists
+ * what group i consists of, in order and without gaps over its size[i] elements: struct { uint64_t off; int32_t rows, cols, ld_out,
+ * tile0; }, a matrix with ld_out > 0 (column c goes to shadowT + off + c * ld_out) or, with rows = 1 and ld_out = 0, cols elements
+ * that are not transposed; tile0 = sum of ouro_op_update_tiles() over the entries before, tiles[i] over all. */
+int ouro_op_update_groups(void* stream, int n, float* const* w, float* const* m, float* const* v, void* const* shadow, void* const* shadowT,
+                          const float* const* g0, const float* s0, const float* const* g1, const float* s1, const size_t* size,
+                          const void* const* table, const int* entries, const int* tiles, int adam, float lr, float beta1, float beta2,
+                          float eps, int64_t t);
+int ouro_op_update_tiles(int rows, int cols, int ld_out);
 /* dst (type T) = src (fp32), n elements; and back. */
 int ouro_op_from_f32(void* stream, int dtype, void* dst, const float* src, size_t n);
 int ouro_op_to_f32(void* stream, int dtype, float* dst, const void* src, size_t n);

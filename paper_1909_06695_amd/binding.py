@@ -110,6 +110,8 @@ def lib():
         "ouro_op_dropout": (i32, [vp, i32, vp, vp, i32, i32, i32, f32, C.c_uint64, C.c_uint32, i32]),
         "ouro_op_gemm_dropout": (i32, [vp, i32, i32, i32, i32, i32, i32, vp, i32, vp, i32, vp, i32, vp, vp, i32, f32,
                                        C.c_uint64, C.c_uint32, i32, i32]),
+        "ouro_op_gemm_dropout_residual": (i32, [vp, i32, i32, i32, i32, i32, vp, i32, vp, i32, vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp, f32,
+                                                C.c_uint64, C.c_uint32, i32, i32]),
         "ouro_op_gemm_ln_residual": (i32, [vp, i32, i32, i32, i32, i32, i32, vp, i32, vp, i32, vp, i32, i32, vp, vp, i32, vp,
                                            vp, vp, vp, i32]),
         "ouro_op_layernorm_fwd": (i32, [vp, i32, vp, vp, vp, vp, vp, vp, i32, i32, i32]),
@@ -119,6 +121,9 @@ def lib():
         "ouro_op_embed_bwd": (i32, [vp, i32, vp, vp, vp, i32, i32, i32, f32]),
         "ouro_op_softmax_ce": (i32, [vp, i32, vp, i32, vp, vp, i32, vp, vp, vp, i32, i32, vp]),
         "ouro_op_update": (i32, [vp, vp, vp, vp, vp, vp, f32, vp, f32, sz, i32, f32, f32, f32, f32, i64]),
+        "ouro_op_update_groups": (i32, [vp, i32, P(vp), P(vp), P(vp), P(vp), P(vp), P(vp), P(f32), P(vp), P(f32), P(sz), P(vp), P(i32), P(i32), i32,
+                                        f32, f32, f32, f32, i64]),
+        "ouro_op_update_tiles": (i32, [i32, i32, i32]),
         "ouro_op_from_f32": (i32, [vp, i32, vp, vp, sz]),
         "ouro_op_to_f32": (i32, [vp, i32, vp, vp, sz]),
     }

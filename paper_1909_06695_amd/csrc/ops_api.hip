@@ -106,6 +106,18 @@ extern "C" int ouro_op_gemm_ln_residual(void* stream, int dtype, int transA, int
   return rc_of(launch_gemm((hipStream_t)stream, dtype, gd, force_generic));
 }
 
+extern "C" int ouro_op_gemm_dropout_residual(void* stream, int transA, int transB, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
+                                             float* C, int ldc, const float* bias, const void* residual, int ldr, const float* res32, int ldr32,
+                                             const float* mean, const float* rstd, const float* g, const float* b, float p, uint64_t seed,
+                                             uint32_t stream_id, int drop_ld, int force_generic) {
+  if (!A || !B || !C || M < 0 || N < 0 || K < 0 || !(p >= 0.f && p < 1.f) || drop_ld < N || !residual == !res32) return OURO_E_ARG;
+  if (lda < (transA ? M : K) || ldb < (transB ? K : N) || ldc < N || (residual ? ldr : ldr32) < N || (mean && (!rstd || !g || !b))) return OURO_E_ARG;
+  GemmDesc d = make_gemm(transA, transB, M, N, K, 1.f, A, lda, B, ldb, C, ldc, 1, 0, bias, residual, ldr, EPI_NONE, nullptr, 0);
+  d.res32 = res32; d.ldr32 = ldr32; d.ln_mean = mean; d.ln_rstd = rstd; d.ln_g = g; d.ln_b = b;
+  d.drop = make_drop(p, seed, stream_id, drop_ld);
+  return rc_of(launch_gemm((hipStream_t)stream, 1, d, force_generic));
+}
+
 extern "C" int ouro_op_dropout(void* stream, int dtype, const void* src, void* dst, int rows, int cols, int ld,
                                float p, uint64_t seed, uint32_t stream_id, int drop_ld) {
   if (!src || !dst || rows < 0 || cols < 0 || ld < cols || !(p >= 0.f && p < 1.f) || drop_ld < cols) return OURO_E_ARG;
@@ -291,6 +303,27 @@ extern "C" int ouro_op_update(void* stream, float* w, float* m, float* v, void* 
   u.bc1 = (float)(1.0 - std::pow((double)beta1, (double)(t + 1)));
   u.bc2 = (float)(1.0 - std::pow((double)beta2, (double)(t + 1)));
   return rc_of(launch_update((hipStream_t)stream, u));
+}
+
+extern "C" int ouro_op_update_tiles(int rows, int cols, int ld_out) { return rows < 1 || cols < 1 || ld_out < 0 ? 0 : update_tiles(rows, cols, ld_out); }
+extern "C" int ouro_op_update_groups(void* stream, int n, float* const* w, float* const* m, float* const* v, void* const* shadow, void* const* shadowT,
+                                     const float* const* g0, const float* s0, const float* const* g1, const float* s1, const size_t* size,
+                                     const void* const* table, const int* entries, const int* tiles, int adam, float lr, float beta1, float beta2,
+                                     float eps, int64_t t) {
+  constexpr int MAX = 64;
+  if (n < 1 || n > MAX || !w || !m || !v || !shadow || !shadowT || !g0 || !s0 || !g1 || !s1 || !size || !table || !entries || !tiles || t < 0) return OURO_E_ARG;
+  UpdateDesc u[MAX];
+  UpdateTable tab[MAX];
+  for (int i = 0; i < n; ++i) {
+    if (!w[i] || (adam && (!m[i] || !v[i])) || !table[i] || entries[i] < 1 || tiles[i] < 1 || (shadowT[i] && !shadow[i])) return OURO_E_ARG;
+    memset(&u[i], 0, sizeof u[i]);
+    u[i].w = w[i]; u[i].m = m[i]; u[i].v = v[i]; u[i].shadow = (bf16_t*)shadow[i]; u[i].g0 = g0[i]; u[i].g1 = g1[i]; u[i].gscale0 = s0[i]; u[i].gscale1 = s1[i];
+    u[i].n = size[i]; u[i].adam = adam; u[i].lr = lr; u[i].beta1 = beta1; u[i].beta2 = beta2; u[i].eps = eps;
+    u[i].bc1 = (float)(1.0 - std::pow((double)beta1, (double)(t + 1)));
+    u[i].bc2 = (float)(1.0 - std::pow((double)beta2, (double)(t + 1)));
+    tab[i] = {(const TransposeEntry*)table[i], entries[i], tiles[i], shadowT[i]};
+  }
+  return rc_of(launch_update_groups((hipStream_t)stream, u, tab, n));
 }
 
 extern "C" int ouro_op_from_f32(void* stream, int dtype, void* dst, const float* src, size_t n) {

@@ -577,16 +577,16 @@ def test_gemm_with_fp32_layernorm_residual(dtype, force, M, N, K, ln):
 
 @pytest.mark.parametrize("force", [11, 12, 13, 14, 15, 16])
 @pytest.mark.parametrize("M,N", [(32, 40), (130, 88), (200, 100), (264, 200), (300, 530), (520, 392)])
-@pytest.mark.parametrize("kind", ["bias", "fp32", "gelu", "gelu_grad", "residual", "fp32_residual", "layernorm"])
+@pytest.mark.parametrize("kind", ["bias", "fp32", "gelu", "gelu_grad", "residual", "fp32_residual", "layernorm", "residual_dropout", "layernorm_dropout"])
 def test_gemm_fused_epilogues(kind, M, N, force):
     """Two row-form operands with each epilogue a layer uses: whole tiles, tiles over the edge, columns that do and do not
     end at a multiple of 8, results with a row pitch; nothing outside the result is written."""
     rng = np.random.default_rng(M + N + force)
     K, pitch = 128, (N + 7) // 8 * 8 + 8
     A = dev(rng.standard_normal((M, K)), 1); B = dev(rng.standard_normal((N, K)) / math.sqrt(K), 1)
-    fp32 = kind in ("fp32", "residual", "fp32_residual", "layernorm")
+    fp32 = kind == "fp32" or "residual" in kind or "layernorm" in kind
     full = torch.full((M + 2, pitch), 7.0, dtype=torch.float32 if fp32 else torch.bfloat16, device="cuda")
-    side = dev(rng.standard_normal((M, pitch)), 0 if kind in ("fp32_residual", "layernorm") else 1)      # what the epilogue reads, or Z
+    side = dev(rng.standard_normal((M, pitch)), 0 if kind == "fp32_residual" or "layernorm" in kind else 1)      # what the epilogue reads, or Z
     bias, g, b = (dev(rng.standard_normal(N), 0) for _ in range(3))
     mean, rstd = dev(rng.standard_normal(M), 0), dev(rng.random(M) + 0.5, 0)
     C_, ref, R = full[1:], host(A) @ host(B).T, host(side)[:, :N]
@@ -595,6 +595,13 @@ def test_gemm_fused_epilogues(kind, M, N, force):
         ok(L().ouro_op_gemm_ln_residual(stream(), 1, 0, 1, M, N, K, p(A), K, p(B), K, p(C_), pitch, 1, p(bias) if ln else None, p(side), pitch,
                                         p(mean) if ln else None, p(rstd) if ln else None, p(g) if ln else None, p(b) if ln else None, force))
         ref = ref + (host(bias) + (R - host(mean)[:, None]) * host(rstd)[:, None] * host(g) + host(b) if ln else R)
+    elif "dropout" in kind:
+        ln, pr, seed, sid, dld = kind == "layernorm_dropout", 0.375, 99 + M, 3, N + 5
+        mask = O.dropout_mask(O.Config(n_layer=1, d_model=2, n_head=1, d_head=2, d_ff=1, vocab=2, seq_len=1, batch=1, dropout=pr), seed, sid, (M, dld))[:, :N]
+        ok(L().ouro_op_gemm_dropout_residual(stream(), 0, 1, M, N, K, p(A), K, p(B), K, p(C_), pitch, p(bias) if ln else None, None if ln else p(side), pitch,
+                                             p(side) if ln else None, pitch, p(mean) if ln else None, p(rstd) if ln else None, p(g) if ln else None,
+                                             p(b) if ln else None, pr, seed, sid, dld, force))
+        ref = (ref + host(bias)) * mask + (R - host(mean)[:, None]) * host(rstd)[:, None] * host(g) + host(b) if ln else ref * mask + R
     else:
         epi = {"gelu": 1, "gelu_grad": 2}.get(kind, 0)
         use_bias = kind in ("bias", "gelu")
@@ -719,6 +726,58 @@ def test_gemm_with_fused_dropout(dtype, force, M, N, K):
     mask = O.dropout_mask(cfg, seed, sid, (M, N))
     ref = (host(dA) @ host(dB) + bias) * mask + host(dR)
     assert rel_err(host(Cc), ref) < TOL[dtype]
+
+
+UPDATE_GROUPS = {
+    # matrices (rows, cols) and runs of vectors (n,) of each group
+    "small tiles of several groups": [[(64, 128), (100,), (70, 36), (3,)], [(130, 260)], [(1,)], [(33, 50), (7,), (50, 33), (129, 2)]],
+    "more groups than a launch takes": [[(40 + i, 8 * i + 4), (5,)] for i in range(20)],
+    "whole tiles, one launch of more than 512": [[(16384, 512)], [(512, 2048), (4100,), (2048, 512), (1000, 130)], [(9000,)]],
+    "more than 512 tiles off every alignment": [[(17, 31), (8500, 510)], [(9001,), (515, 1026)]],
+}
+
+
+@pytest.mark.parametrize("adam", [0, 1])
+@pytest.mark.parametrize("name", list(UPDATE_GROUPS))
+def test_update_of_groups_in_one_launch(name, adam):
+    """Every group's weights, moments and bf16 copies bit for bit those of the update of one group and of a transposition: groups of
+    one launch and of several, tiles dealt to four blocks and to one, edges, pieces between the matrices, groups with two gradients, one and
+    none; the cells between the transposed rows stay as they were."""
+    rng = np.random.default_rng(adam)
+    groups, f = UPDATE_GROUPS[name], lambda n, s=1.0: torch.from_numpy((rng.standard_normal(n) * s).astype(np.float32)).cuda()
+    data, tabs = [], []
+    for i, g in enumerate(groups):
+        entries, off, tile, reach = [], 0, 0, 0
+        last = max((j for j, e in enumerate(g) if len(e) == 2), default=-1)
+        for j, e in enumerate(g):                              # the last matrix with padded transposed rows (V in a model)
+            rows, cols, ld = (1, e[0], 0) if len(e) == 1 else (e[0], e[1], (e[0] + 63) // 64 * 64 if j == last else e[0])
+            entries.append((off, rows, cols, ld, tile))
+            tile += L().ouro_op_update_tiles(rows, cols, ld)
+            reach = max(reach, off + cols * ld)
+            off += rows * cols
+        t = np.array(entries, dtype=[("off", "u8"), ("rows", "i4"), ("cols", "i4"), ("ld", "i4"), ("tile0", "i4")])
+        tabs.append((entries, torch.from_numpy(t.view(np.uint8)).cuda(), tile, off))
+        data.append(dict(w=f(off), m=f(off, 0.1), v=f(off, 0.1).abs(), g0=f(off) if i % 3 < 2 else None, g1=f(off) if i % 3 == 0 else None,
+                         sh=torch.full((off,), 5.0, dtype=torch.bfloat16, device="cuda"),
+                         st=torch.full((max(reach, 1),), 5.0, dtype=torch.bfloat16, device="cuda")))
+    ref = [dict(d, w=d["w"].clone(), m=d["m"].clone(), v=d["v"].clone(), sh=d["sh"].clone()) for d in data]
+    for d in ref:
+        ok(L().ouro_op_update(stream(), p(d["w"]), p(d["m"]), p(d["v"]), p(d["sh"]), p(d["g0"]), 0.5, p(d["g1"]), 0.25, d["w"].numel(), adam, 0.01, 0.9, 0.999, 1e-8, 7))
+    n = len(groups)
+    ptrs = lambda key: (C.c_void_p * n)(*[None if d[key] is None else d[key].data_ptr() for d in data])
+    ints = lambda xs: (C.c_int * n)(*xs)
+    ok(L().ouro_op_update_groups(stream(), n, ptrs("w"), ptrs("m"), ptrs("v"), ptrs("sh"), ptrs("st"),
+                                 ptrs("g0"), (C.c_float * n)(*[0.5] * n), ptrs("g1"), (C.c_float * n)(*[0.25] * n), (C.c_size_t * n)(*[t[3] for t in tabs]),
+                                 (C.c_void_p * n)(*[t[1].data_ptr() for t in tabs]), ints([len(t[0]) for t in tabs]), ints([t[2] for t in tabs]), adam, 0.01, 0.9, 0.999, 1e-8, 7))
+    torch.cuda.synchronize()
+    for d, r, (entries, _, _, _) in zip(data, ref, tabs):
+        for key in ("w", "m", "v", "sh"):
+            assert torch.equal(d[key], r[key]), key
+        want = torch.full_like(d["st"], 5.0)
+        for off, rows, cols, ld, _ in entries:
+            if ld:
+                torch.as_strided(want, (cols, rows), (ld, 1), off).copy_(r["sh"][off:off + rows * cols].view(rows, cols).t())
+        assert torch.equal(d["st"], want)
 
 
 @pytest.mark.parametrize("dtype", [0, 1])

@@ -668,12 +668,12 @@ def test_checkpoint_resume(schedule, dtype, opt):
     dict(dtype=1, n_head=2, d_head=64, d_model=128, d_ff=192, vocab=1001),         # tiles over the edge of V, whole tiles elsewhere
     dict(dtype=1, n_head=2, d_head=41, d_model=82, d_ff=130, vocab=65, rel_pos=1, mem_len=8),
     dict(dtype=0, n_head=2, d_head=17, d_model=34, d_ff=50, vocab=99),
-    dict(dtype=1, n_head=8, d_head=64, d_model=512, d_ff=2048, vocab=4096),        # more than 512 tiles in a launch
+    dict(dtype=1, n_head=8, d_head=64, d_model=512, d_ff=2048, vocab=16384),       # more than 512 tiles in V's launch
 ])
 @pytest.mark.parametrize("optimizer", [0, 1])
 def test_update_of_groups_equals_update_of_one(cfg, optimizer):
-    """The tile-by-tile update of all groups (a step on one stream) and the plain update of one group: the same arithmetic on
-    the same gradients, so the same weights bit for bit, and through both bf16 copies the same loss."""
+    """The tile-by-tile update (a model on one stream, here one group a launch) and the plain one: the same arithmetic on the same
+    gradients, so the same weights bit for bit, and through both bf16 copies the same loss."""
     pkg = P()
     c = dict(dict(n_layer=3, seq_len=16, mem_len=0, batch=2, n_module=3, rel_pos=0, optimizer=optimizer), **cfg)
     tok = torch.randint(0, c["vocab"], (c["batch"], c["seq_len"]), dtype=torch.int32, generator=torch.Generator().manual_seed(1)).cuda()
