@@ -607,7 +607,8 @@ static void remap_group(const ouro_model* m, int group, float* stored, float* bl
 // 128-wide on 512 tokens (0.2) 0.91, 256-wide on 1024 (1.6) 0.91, on 2048 (3.2) 0.94, 512-wide on 1024 (6.4) 0.97, on 2048 (13)
 // 1.01, on 8192 1.03, 1024-wide on 8192 1.04; fewer tokens than the model is wide: 256 1.03, 512 1.05, 1024 1.04.  fp32:
 // 64 to 256-wide (0.01 to 0.8) 0.72 to 0.91, 512-wide on 1024 (6.4) 1.03.  Relative-position layers, whose attention backward
-// fills the chip by itself: 128 to 512-wide 0.89 to 0.97, 16 x 410-wide and 18 x 1024-wide 0.99.  Under the stored-input
+// fills the chip by itself: 128 to 512-wide 0.89 to 0.97, 16 x 410-wide and 18 x 1024-wide 0.99.  (Measured before steps on one stream
+// updated, cleared and summed all groups in one launch each.)  Under the stored-input
 // schedule the modules' backward passes run side by side as well: 1.03 at 0.2, 1.05 to 1.17 from there on.
 static bool overlap_pays(const ouro_model& m) {
   const double wgrad = 2.0 * m.N * (4.0 * m.pd * m.phd + 2.0 * m.pd * m.pF);
