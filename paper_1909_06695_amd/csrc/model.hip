@@ -1605,6 +1605,7 @@ extern "C" int ouro_step(ouro_model* m, const int32_t* dev_tokens, const int32_t
     for (int k = 0; k <= K; ++k) {
       ouro_slot_index(K, k, m->t, 1, &slot, &tau);
       r[k] = {m->slot_ptr(k, slot), (size_t)m->gstride[k] * 4};
+      m->tags[k][slot] = -1;            // what it held is gone, also where the step fails before the module's turn
     }
     HIPCHK(launch_fill_zero_ranges(m->stream, r, K + 1));
     m->cleared = true;

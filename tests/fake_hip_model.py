@@ -78,6 +78,10 @@ def failed_step(fake):
     m.fail(at - 3)
     rc, log = m.log(m.step)
     assert rc == E_HIP and sums(log) == [2], (rc, sums(log))
+    tag = lambda k, depth: (m.L.ouro_debug_slot_tag(m.h, k, C.c_int64(5 % depth), C.byref(t)), t.value)[1]
+    t = C.c_int64()
+    # iteration 5: modules 3 and 2 have theirs; the cleared slots of module 1 (of iteration 2 before) and of dV_i hold nothing
+    assert (tag(3, 1), tag(2, 2), tag(1, 3), tag(0, 3)) == (5, 5, -1, -1)
     rc, log = m.log(lambda: m.backward(1))
     assert rc == 0 and sums(log) == [1]
     extra = fills(log)
