@@ -48,8 +48,9 @@ int ouro_op_gemm_batched(void* stream, int dtype, int transA, int transB, int M,
                          void* C2, float alpha2, int force_generic);
 /* n <= 6 accumulating products C_i (fp32 [M_i, N_i]) += alpha * A_i^T B_i with A_i [K_i, M_i] and
  * B_i [K_i, N_i] (the weight-gradient contractions of a layer, Eq. 6-7: contraction over all
- * tokens onto small outputs).  Products that admit it (bf16, aligned operands, any K_i >= 32) share
- * one launch in which every workgroup takes a long K range; the rest run one by one.  The adds are atomic: products may
+ * tokens onto small outputs).  Products that admit it (bf16, aligned operands, any K_i >= 32; fp32, 16-byte aligned
+ * operands with M_i, N_i and leading dimensions in whole quads) share one launch in which every workgroup takes a long K range;
+ * the rest run one by one.  The adds are atomic: products may
  * share a C. */
 int ouro_op_gemm_group(void* stream, int dtype, int n, const int* M, const int* N, const int* K,
                        const void* const* A, const int* lda, const void* const* B, const int* ldb,
