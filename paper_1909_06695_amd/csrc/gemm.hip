@@ -214,10 +214,10 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // four-stage ring; otherwise, and for the split-K weight gradients, 128x64 tiles, which
     // put more workgroups on every compute unit
     const int t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    // the tiles of all products, unless much of them is past the edges: results of 128 columns (98304 rows over 1024 39 us on 128-wide
-    // tiles, 49 on 256x256; 131072 over 512 with GELU 39 and 52); 192 columns, a quarter past the edge, are alike on both
-    const int t256_one = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-    const long t256 = t256_one * 65536.0 <= 1.4 * g.M * g.N ? t256_one * products : 0;
+    const long one = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
+    // the tiles of all products, unless they have more past the edges than 128x128 ones (90000 x 320 over 512 with GELU 63 us on 128-wide tiles,
+    // 70 on 256x256; 131072 x 128 39 and 52; 16 products of 600 x 900 over 1024 49 and 51)
+    const long t256 = 4 * one <= 1.15 * t128 ? one * products : 0;
     // 256x256 tiles (one workgroup per CU, nothing beside its epilogue) pay once there are four per CU (the logits: 8192 x
     // 32768 over 512 312 us, 4800 x 32768 over 448 190), one per CU with a long contraction (dV_o: 670 -> 592 us), or where their
     // rounds are well filled.  Alone on the chip, 128x128 and 256x256 tiles, us (plain / GELU / GELU-gradient / fp32 result with the
@@ -234,7 +234,7 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // The lower end, plain (the faster of the 128-wide forms and 256x256): 128 tiles over 512 / 768 / 1024 12.7 / 16.7 / 20.3 and 16.5 /
     // 20.5 / 23.8, 136 16.4 / 22.7 / 28.1 and 16.4 / 20.2 / 23.8, 144 17.2 / 22.8 / 27.7 and 16.9 / 20.8 / 24.6; 144 to 160 over 384 15.0 both,
     // over 448 16.0 both, 192 17.8 and 17.1.  What counts there is whether 128x128 tiles run in one round of 512: 9288 x 832 over 640 (148
-    // tiles, 511 of 128x128) 16.9 and 19.5, 12288 x 576 over 960 19 and 24, 14872 x 576 over 704 (177 and 585) 21.8 and 21.1.
+    // tiles, 511 of 128x128) 16.9 and 19.5, 12288 x 576 over 960 19 and 24.
     // Two products of 144 tiles over 512 28.0 and 32.1 (288 in all, 1.1 rounds), four of 64 24.4 and 22.5.
     // Products of few tiles are bound by what each workgroup has in flight along its contraction: 64x64 tiles with a
     // four-stage ring, two workgroups per CU, while all of them run in one round.  Against the larger tiles: 768 x 1024
@@ -245,10 +245,13 @@ static bool plan_mfma(const GemmDesc& g, int force, long products, GemmPlan& pla
     // narrower, 448 x 4096 over 8192, 60 and 50; 198 tiles, 1348 x 528 over 7552, 56 and 30).
     const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * products;
     const bool plain = !g.out_fp32 && g.epilogue == EPI_NONE && !g.residual && !g.res32;
-    const int last = t256 ? (t256 - 1) % 256 + 1 : 0;    // tiles of the last round
-    const bool big = t256 >= 1024 || (t256 >= 256 && g.K >= 4096) || (t256 >= 448 && last >= 192 && g.K >= (plain || g.epilogue == EPI_GELU ? 512 : 768)) ||
+    auto last = [](long t) { return (t + 255) % 256 + 1; };           // tiles of the last round
+    // four per CU, one per CU over a long contraction, or a last round at least three quarters full: also where much of a tile is past the edge
+    // (65536 x 160 over 4096 137 us, on 128-wide tiles 154)
+    auto many = [&](long t, int k) { return t >= 1024 || (t >= 256 && g.K >= 4096) || (t >= 448 && last(t) >= 192 && g.K >= k); };
+    const bool big = many(one, 768) || many(t256, plain || g.epilogue == EPI_GELU ? 512 : 768) ||
                      (t128 * products > 512 && t256 >= (plain ? 144 : 224) && t256 <= 256 && g.K >= (plain ? 448 : 512)) ||
-                     (plain && t256 >= 384 && (g.K >= 768 ? last >= 128 : last > 128 && t128 * products > 1536 && g.K >= 448));
+                     (plain && t256 >= 384 && (g.K >= 768 ? last(t256) >= 128 : last(t256) > 128 && t128 * products > 1536 && g.K >= 448));
     const long t128x256 = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * products;
     const bool column = g.transA || !g.transB;
     if (!g.accumulate && t64 <= 512 && !(t64 > 384 && column && g.K >= 4096 && std::min(g.M, g.N) > 512)) cfg = GEMM_TILE_64x64;
